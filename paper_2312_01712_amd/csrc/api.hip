@@ -571,7 +571,9 @@ static int scan_query_major(const ivfpq_index *ix, const float *d_queries, int64
                             int64_t *d_out_ids, float *d_out_dist, const Workspace &w, char *base, size_t ws_bytes,
                             hipStream_t s) {
   const WideWorkspace ww = plan_wide(ix, Q, k, mode);
-  ScanView view = {0, nullptr, false, nullptr, nullptr};
+  // (the flags of the filtering stage have been read when the scan starts: their place holds the
+  // bounds that the workgroups of a query share)
+  ScanView view = {0, nullptr, false, nullptr, nullptr, reinterpret_cast<uint32_t *>(base + w.coarse_flags)};
   if (ww.total > 0 && ws_bytes >= align256(w.total) + ww.total) {
     view.wide = &ww;
     view.wide_base = base + align256(w.total);

@@ -137,6 +137,7 @@ struct ScanView {
   bool bounds_ready;     // d_probe_lb already holds the list-level bounds of every row
   const WideWorkspace *wide;  // NULL: k above 128 is produced pass by pass
   char *wide_base;            // device base of the wide selection's part of the workspace
+  uint32_t *gbound;           // [Q] scratch for the bounds that the workgroups of a query share, or NULL
 };
 int launch_scan(const ivfpq_index *ix, const float *d_queries, int64_t Q, int32_t nprobe,
                 const int32_t *d_probe_ids, int32_t k, const RadiiSq &r2, int32_t nsplit,

@@ -299,6 +299,7 @@ struct ScanArgs {
   int32_t *wide_n;       // [Q] slots in use, or -1: they did not suffice
   uint32_t *wide_bound;  // [Q] the bound at the end of the scan
   int32_t wide_cap;
+  uint32_t *gbound;      // [Q] complement of a bound on the query's k-th distance, shared by the workgroups of its probe groups (0: none yet); NULL: not shared
 };
 
 // Codes of one point (the lane's) in registers.

@@ -1,0 +1,68 @@
+"""Small batches, where the probes of a query are split over several workgroups: the merge of their
+lists, the bounds they share, and the filtering stage without a matrix product.  Everything is
+compared with the oracle bit for bit (same operation order: no tolerance)."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2312_01712_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+
+def _index(rng, D, M, nlist, mean, spread=0.3, distinct=256):
+    """Random codes over clustered centroids; `distinct` < 256 makes equal distances common."""
+    sizes = rng.integers(0, 2 * mean + 1, nlist)
+    sizes[:2] = (0, 1)
+    offs = np.zeros(nlist + 1, dtype=np.int64)
+    offs[1:] = np.cumsum(sizes)
+    N = int(offs[-1])
+    cb = (rng.normal(size=(M, 256, D // M)) * spread).astype(np.float32)
+    return wl.Index(N=N, D=D, nlist=nlist, M=M, centroids=rng.normal(size=(nlist, D)).astype(np.float32), codebooks=cb,
+                    list_offsets=offs, codes=rng.integers(0, distinct, size=(N, M), dtype=np.uint8),
+                    ids=rng.permutation(N).astype(np.int64))
+
+
+def _check(idx, q, nprobe, k, radii, metric=0, mode=0, query_radii=None):
+    from paper_2312_01712_amd import binding as b
+    gi = b.IvfPqIndex.from_index(idx, metric=metric)
+    dq = torch.from_numpy(q).cuda()
+    rq = None if query_radii is None else torch.from_numpy(query_radii).cuda()
+    o_ids, o_dist = oracle.search(q, idx, nprobe, k, radii if query_radii is None else query_radii, threads=8, mode=mode,
+                                  metric=metric)
+    for _ in range(2):   # twice: the second call finds the workspace as the first one left it
+        ids, dist = gi.search(dq, nprobe, k, radii, mode=mode, query_radii=rq)
+        torch.cuda.synchronize()
+        assert np.array_equal(ids.cpu().numpy(), o_ids), "ids differ"
+        assert np.array_equal(dist.cpu().numpy().view(np.uint32), o_dist.view(np.uint32)), "distances differ"
+    gi.close()
+
+
+# probe groups per query: min(ceil(2048 / Q), nprobe, 64), so these cover 2, 4, 5, 16, 17, 33 and 64 of them
+@pytest.mark.parametrize("Q,nprobe", [(1, 2), (3, 5), (1024, 9), (511, 9), (129, 20), (123, 33), (1, 33), (5, 80)])
+@pytest.mark.parametrize("D,M", [(128, 64), (64, 16), (30, 10)])
+def test_split_probes(Q, nprobe, D, M):
+    rng = np.random.default_rng(Q * 100 + nprobe)
+    idx = _index(rng, D, M, 90, 40 if Q > 100 else 150)
+    q = (idx.centroids[rng.integers(0, idx.nlist, Q)] + 0.4 * rng.normal(size=(Q, D))).astype(np.float32)
+    radii = np.full(M, 0.5, dtype=np.float32)
+    for k in (1, 64, 65, 128):
+        _check(idx, q, nprobe, k, radii)
+
+
+@pytest.mark.parametrize("mode,metric", [(0, 0), (1, 0), (2, 0), (0, 1)])
+def test_split_probes_ties_and_more_passes(mode, metric):
+    """Two codes only (masses of equal scores across workgroups) and k above one pass."""
+    rng = np.random.default_rng(5)
+    idx = _index(rng, 128, 64, 60, 120, distinct=2)
+    q = (idx.centroids[rng.integers(0, 60, 37)] + 0.2 * rng.normal(size=(37, 128))).astype(np.float32)
+    for k in (10, 128, 200):
+        _check(idx, q, 24, k, np.full(64, 0.6, dtype=np.float32), metric=metric, mode=mode)
+
+
+def test_split_probes_per_query_radii():
+    rng = np.random.default_rng(6)
+    idx = _index(rng, 96, 48, 70, 200)
+    q = (idx.centroids[rng.integers(0, 70, 300)] + 0.3 * rng.normal(size=(300, 96))).astype(np.float32)
+    _check(idx, q, 32, 100, None, query_radii=rng.uniform(0.1, 0.9, size=(300, 48)).astype(np.float32))

@@ -17,6 +17,8 @@
 // by 0 - IP(q, centroid), reference order acc = fmaf(q_i, c_i, acc); the same
 // scheme applies with the product itself as the proposal.
 
+#include <type_traits>
+
 #include "ivfpq_internal.h"
 
 namespace {
@@ -379,6 +381,85 @@ __global__ __launch_bounds__(256) void coarse_exact_rows_kernel(const float *__r
     row[c] = exact_score(sqx, cent + (int64_t)c * D, D, ip);
 }
 
+// Small batches: reference-order distances from every query to every list, written as rows, so
+// that the selection has nothing to propose or re-rank.  A workgroup takes 64 lists and up to 16
+// queries; both tiles come to LDS with all loads in flight at once (one memory round trip per 128
+// dimensions, where the matrix product has one per 16), then a lane runs the chains of its list:
+// wavefront w serves queries w, w + 4, w + 8, w + 12 of the tile, whose values are the same in
+// every lane (LDS broadcasts).  Rows of 132 floats: the 16-byte reads of 8 consecutive lists touch
+// 32 different banks.  (Bound: the vector ALU, two instructions per element and list, at about half its
+// rate from 1000 queries on; below, one launch's latency.)  Elements past D and rows past the matrices stand as zeros (a term
+// fmaf(0, 0, acc) leaves the chain as it is).
+constexpr int XT_LISTS = 64, XT_Q = 16, XT_K = 128;
+
+template <bool VEC, bool IP>
+__global__ __launch_bounds__(256) void coarse_exact_tile_kernel(const float *__restrict__ Qm,
+                                                                const float *__restrict__ Cm,
+                                                                float *__restrict__ rows, int Qn, int nlist, int D,
+                                                                int ldo) {
+  __shared__ __align__(16) float sc[XT_LISTS][XT_K + 4];
+  __shared__ __align__(16) float sv[XT_Q][XT_K];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int c0 = blockIdx.x * XT_LISTS, q0 = blockIdx.y * XT_Q;
+  const int nq = Qn - q0 < XT_Q ? Qn - q0 : XT_Q;   // queries of this tile
+  const int mine = nq > wave ? (nq - wave + 3) / 4 : 0;
+  float acc[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+  for (int k0 = 0; k0 < D; k0 += XT_K) {
+    if (k0 > 0) __syncthreads();   // the slice before has been used
+    float va[8][4], vb[2][4];
+#pragma unroll
+    for (int r = 0; r < 8; ++r) {
+      const int f = tid + 256 * r;
+      load4_issue<VEC>(Cm, c0 + (f >> 5), nlist, k0 + (f & 31) * 4, D, va[r]);
+    }
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+      const int f = tid + 256 * r;
+      load4_issue<VEC>(Qm, q0 + (f >> 5), Qn, k0 + (f & 31) * 4, D, vb[r]);
+    }
+#pragma unroll
+    for (int r = 0; r < 8; ++r) {
+      const int f = tid + 256 * r;
+      load4_mask<VEC>(c0 + (f >> 5), nlist, k0 + (f & 31) * 4, D, va[r]);
+      *reinterpret_cast<float4 *>(&sc[f >> 5][(f & 31) * 4]) = make_float4(va[r][0], va[r][1], va[r][2], va[r][3]);
+    }
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+      const int f = tid + 256 * r;
+      load4_mask<VEC>(q0 + (f >> 5), Qn, k0 + (f & 31) * 4, D, vb[r]);
+      *reinterpret_cast<float4 *>(&sv[f >> 5][(f & 31) * 4]) = make_float4(vb[r][0], vb[r][1], vb[r][2], vb[r][3]);
+    }
+    __syncthreads();
+    const int kn = D - k0 < XT_K ? D - k0 : XT_K;
+    auto chains = [&](auto n_tag) __attribute__((always_inline)) {
+      constexpr int N = decltype(n_tag)::value;
+#pragma unroll 4
+      for (int i = 0; i < kn; i += 4) {
+        const float4 c = *reinterpret_cast<const float4 *>(&sc[lane][i]);
+#pragma unroll
+        for (int j = 0; j < N; ++j) {
+          const float4 v = *reinterpret_cast<const float4 *>(&sv[wave + 4 * j][i]);
+          const float cc[4] = {c.x, c.y, c.z, c.w}, vv[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+          for (int x = 0; x < 4; ++x) {
+            if (IP) acc[j] = fmaf(vv[x], cc[x], acc[j]);
+            else {
+              const float t = vv[x] - cc[x];
+              acc[j] = fmaf(t, t, acc[j]);
+            }
+          }
+        }
+      }
+    };
+    if (mine == 1) chains(std::integral_constant<int, 1>{});
+    else if (mine > 1) chains(std::integral_constant<int, 4>{});
+  }
+  const int c = c0 + lane;
+#pragma unroll
+  for (int j = 0; j < 4; ++j)
+    if (j < mine && c < nlist) rows[(int64_t)(q0 + wave + 4 * j) * ldo + c] = IP ? 0.0f - acc[j] : acc[j];
+}
+
 // inclusive prefix sum over the 256 threads of the workgroup (tmp: 2 x 256)
 __device__ inline uint32_t scan256(uint32_t v, uint32_t *tmp, int tid) {
   int cur = 0;
@@ -654,16 +735,22 @@ constexpr int CS_WAVES = 4;     // queries per workgroup
 
 __device__ __forceinline__ int cs_hidx(uint32_t bin) { return (int)(((bin & 15u) << 6) | (bin >> 4)); }
 
-// FUSED: `rows` holds the key rows of coarse_gemm_top_kernel (nrow keys per query) instead of
+// KIND CS_EXACT: `rows` holds the reference-order distances themselves (coarse_exact_tile_kernel):
+// the lists up to the bin of the nprobe-th are the answer once they are sorted; should they be
+// more than CS_CAND (masses of equal distances), the wavefront picks the nprobe smallest keys one
+// after the other, so that no second kernel is needed.
+// KIND CS_FUSED: `rows` holds the key rows of coarse_gemm_top_kernel (nrow keys per query) instead of
 // the product's rows (nrow = nlist values); a key gives its list and, to 64 units in the last
 // place, the proposal value, and the last key of every group of COARSE_FT bounds the lists of
 // that group that were not written.
-template <bool FUSED>
+enum { CS_ROWS = 0, CS_FUSED = 1, CS_EXACT = 2 };
+template <int KIND>
 __global__ __launch_bounds__(CS_WAVES * 64) void coarse_select_wave_kernel(
     const float *__restrict__ rows, const float *__restrict__ Qm, const float *__restrict__ cent, int qn, int nlist,
     int nrow, int D, int ldo, int nprobe, int kprop, float err_scale, float max_cnorm, int ip,
     int32_t *__restrict__ out_ids, float *__restrict__ out_dist, int32_t *__restrict__ flags,
     int32_t *__restrict__ fb) {
+  constexpr bool FUSED = KIND == CS_FUSED, EXACT = KIND == CS_EXACT;
   extern __shared__ __align__(16) unsigned char cs_smem[];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int64_t q = (int64_t)blockIdx.x * CS_WAVES + wave;
@@ -708,12 +795,13 @@ __global__ __launch_bounds__(CS_WAVES * 64) void coarse_select_wave_kernel(
   };
 
   float part = 0.0f;
-  for (int i = lane; i < D; i += 64) {
-    const float x = qv[i];
-    sq[i] = x;
-    part += x * x;
-  }
-  for (int off = 32; off > 0; off >>= 1) part += __shfl_xor(part, off);
+  if (!EXACT)
+    for (int i = lane; i < D; i += 64) {
+      const float x = qv[i];
+      sq[i] = x;
+      part += x * x;
+    }
+  for (int off = 32; off > 0 && !EXACT; off >>= 1) part += __shfl_xor(part, off);
   const float qq = part;
 
   // range of the row's proposal values
@@ -771,8 +859,8 @@ __global__ __launch_bounds__(CS_WAVES * 64) void coarse_select_wave_kernel(
   // (a key is within 64 units in the last place of its proposal value, which is at most
   // 2 (|q|^2 + max |c|^2) in magnitude: 2^-15 of that sum covers it)
   const float bound = (err_scale + (FUSED ? 3.0517578125e-05f : 0.0f)) * (qq + max_cnorm);
-  uint32_t top = bin_of_rank((uint32_t)kprop);
-  {
+  uint32_t top = bin_of_rank((uint32_t)(EXACT ? nprobe : kprop));
+  if (!EXACT) {
     const float reach = (float)(bin_of_rank((uint32_t)nprobe) + 2u) + 2.0f * bound * scale;
     const uint32_t top2 = reach >= (float)(CS_BINS - 1) ? (uint32_t)(CS_BINS - 1) : (reach > 0.0f ? (uint32_t)reach : 0u);
     top = top2 > top ? top2 : top;
@@ -790,12 +878,33 @@ __global__ __launch_bounds__(CS_WAVES * 64) void coarse_select_wave_kernel(
     const unsigned long long bal = __ballot(take);
     if (take) {
       const uint32_t slot = count + (uint32_t)__popcll(bal & ((1ull << lane) - 1ull));
-      if (slot < (uint32_t)CS_CAND) cand[slot] = (uint32_t)list;
+      if (slot < (uint32_t)CS_CAND)
+        cand[slot] = EXACT ? ((unsigned long long)orderable(v) << 32) | (uint32_t)list : (unsigned long long)(uint32_t)list;
     }
     count += (uint32_t)__popcll(bal);
   });
   for (int off = 32; off > 0; off >>= 1) rest_min = fminf(rest_min, __shfl_xor(rest_min, off));
   bool ok = count <= (uint32_t)CS_CAND;
+  if (EXACT && !ok) {   // masses of equal distances: the next smallest key, nprobe times
+    unsigned long long last = 0ull;
+    for (int p = 0; p < nprobe; ++p) {
+      unsigned long long best = ~0ull;
+      each([&](int pos, uint32_t raw) __attribute__((always_inline)) {
+        const unsigned long long k = ((unsigned long long)orderable(__uint_as_float(raw)) << 32) | (uint32_t)pos;
+        if (pos < nlist && (p == 0 || k > last) && k < best) best = k;
+      });
+      for (int off = 32; off > 0; off >>= 1) {
+        const unsigned long long o = __shfl_xor(best, off);
+        best = o < best ? o : best;
+      }
+      last = best;
+      if (lane == 0) {
+        out_ids[q * nprobe + p] = (int32_t)(uint32_t)best;
+        if (out_dist) out_dist[q * nprobe + p] = unorderable((uint32_t)(best >> 32));
+      }
+    }
+    return;
+  }
   const int n = ok ? (int)count : 0;
   __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
   // reference-order distances, one list per lane and round; keys (distance, list) back to LDS
@@ -807,17 +916,23 @@ __global__ __launch_bounds__(CS_WAVES * 64) void coarse_select_wave_kernel(
     const int i = r * 64 + lane;
     if (r * 64 < n) {   // uniform
       if (i < n) {
-        const int c = (int)(uint32_t)cand[i];
-        const float d = exact_score((const float *)sq, cent + (int64_t)c * D, D, ip);
-        key[r] = ((unsigned long long)orderable(d) << 32) | (uint32_t)c;
+        if (EXACT) {
+          key[r] = cand[i];
+        } else {
+          const int c = (int)(uint32_t)cand[i];
+          const float d = exact_score((const float *)sq, cent + (int64_t)c * D, D, ip);
+          key[r] = ((unsigned long long)orderable(d) << 32) | (uint32_t)c;
+        }
       }
     }
   }
-  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+  if (!EXACT) {
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
 #pragma unroll
-  for (int r = 0; r < ROUNDS; ++r)
-    if (r * 64 + lane < n) cand[r * 64 + lane] = key[r];
-  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    for (int r = 0; r < ROUNDS; ++r)
+      if (r * 64 + lane < n) cand[r * 64 + lane] = key[r];
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+  }
   // rank sort: position of a key = number of keys below it (keys are distinct)
   uint32_t rank[ROUNDS];
 #pragma unroll
@@ -835,7 +950,7 @@ __global__ __launch_bounds__(CS_WAVES * 64) void coarse_select_wave_kernel(
     const unsigned long long bal = __ballot(has);
     if (bal) tau = unorderable((uint32_t)(__shfl((unsigned long long)key[r], __ffsll((long long)bal) - 1) >> 32));
   }
-  if (ok && (FUSED || n < nlist)) {
+  if (!EXACT && ok && (FUSED || n < nlist)) {
     // every list that was not collected has a proposal value of at least rest_min; accept if
     // that clears the nprobe-th reference distance by more than the rounding bound of the
     // matrix product
@@ -843,7 +958,7 @@ __global__ __launch_bounds__(CS_WAVES * 64) void coarse_select_wave_kernel(
     ok = (t_prop - tau) > bound;   // false for NaN
   }
   ok = ok && n >= nprobe;
-  if (lane == 0) {
+  if (!EXACT && lane == 0) {
     int32_t f = ok ? 0 : 1;
     if (FUSED && !ok) {   // a flagged query takes a number; the first FB_SLOTS also a slot of the list
       const int32_t slot = (int32_t)atomicAdd(reinterpret_cast<unsigned int *>(fb), 1u);
@@ -873,6 +988,14 @@ int coarse_fallbacks(int reset, unsigned int *out) {
   }
   return IVFPQ_OK;
 }
+
+// Query x list x dimension products up to which a batch takes reference-order distances to every
+// list at once instead of proposing by matrix product.  Measured, both ways, in us per batch
+// (proposal / direct): 1024 lists x 128: 1 query 26 / 12.5, 300: 37 / 16.5, 2000 (2.6e8): 44 / 32,
+// 4000 (5.2e8): 56 / 52, 10 000 (1.3e9): 95 / 110; 256 x 64, 10 000 (1.6e8): 47 / 35; 2048 x 96:
+// 2000 (3.9e8): 65 / 59, 4000 (7.9e8): 77 / 84; 4000 x 100: 1000 (4e8): 93 / 86, 2000 (8e8):
+// 109 / 121.
+constexpr int64_t EXACT_TILE_WORK = 450000000;
 
 int launch_coarse(const ivfpq_index *ix, const float *d_queries, int64_t Q, int32_t nprobe,
                   int32_t *d_probe_ids, float *d_probe_dist, float *d_scratch, int64_t q_chunk,
@@ -915,7 +1038,7 @@ int launch_coarse(const ivfpq_index *ix, const float *d_queries, int64_t Q, int3
       int32_t *fb = reinterpret_cast<int32_t *>(slot_rows + (size_t)FB_SLOTS * nlist_pad);
       hipLaunchKernelGGL(vec ? coarse_gemm_top_kernel<true> : coarse_gemm_top_kernel<false>, grid, dim3(256), 0, s, qm,
                          ix->d_centroids, ix->d_cnorm, keys, qn, nlist, D, nkeys, ip, fb);
-      hipLaunchKernelGGL(coarse_select_wave_kernel<true>, dim3((qn + CS_WAVES - 1) / CS_WAVES), dim3(CS_WAVES * 64),
+      hipLaunchKernelGGL(coarse_select_wave_kernel<CS_FUSED>, dim3((qn + CS_WAVES - 1) / CS_WAVES), dim3(CS_WAVES * 64),
                          wave_lds, s, d_scratch, qm, ix->d_centroids, qn, nlist, nkeys, D, nkeys, nprobe, kprop,
                          err_scale, ix->max_cnorm, ip, ids, dist, d_flags + q0, fb);
       hipLaunchKernelGGL(coarse_exact_rows_kernel, dim3(FB_SLICES, FB_SLOTS), dim3(256), (size_t)D * sizeof(float), s, qm,
@@ -928,6 +1051,18 @@ int launch_coarse(const ivfpq_index *ix, const float *d_queries, int64_t Q, int3
                          kprop, err_scale, ix->max_cnorm, ip, ids, dist, d_flags + q0, qn, group, 1, FB_SLOTS, fb);
       continue;
     }
+    // Few queries: the matrix product is all latency (8 tiles of 8 K slices for one query of the
+    // 1M x 128 configuration), the re-ranking and the second line come on top.
+    if (kprop <= CS_CAND / 2 && nlist <= 4096 && wave_lds <= 64 * 1024 && (int64_t)qn * nlist * D <= EXACT_TILE_WORK) {
+      const dim3 tiles((nlist + XT_LISTS - 1) / XT_LISTS, (qn + XT_Q - 1) / XT_Q);
+      auto tile = ip ? (vec ? coarse_exact_tile_kernel<true, true> : coarse_exact_tile_kernel<false, true>)
+                     : (vec ? coarse_exact_tile_kernel<true, false> : coarse_exact_tile_kernel<false, false>);
+      hipLaunchKernelGGL(tile, tiles, dim3(256), 0, s, qm, ix->d_centroids, d_scratch, qn, nlist, D, nlist_pad);
+      hipLaunchKernelGGL(coarse_select_wave_kernel<CS_EXACT>, dim3((qn + CS_WAVES - 1) / CS_WAVES), dim3(CS_WAVES * 64),
+                         wave_lds, s, d_scratch, qm, ix->d_centroids, qn, nlist, nlist, D, nlist_pad, nprobe, kprop,
+                         err_scale, ix->max_cnorm, ip, ids, dist, nullptr, nullptr);
+      continue;
+    }
     hipLaunchKernelGGL(vec ? coarse_gemm_kernel<true> : coarse_gemm_kernel<false>, grid, dim3(256), 0, s, qm,
                        ix->d_centroids, ix->d_cnorm, d_scratch, qn, nlist, D, nlist_pad, ip);
     // One wavefront per query where the proposal is small enough for it; the workgroup-per-query
@@ -935,7 +1070,7 @@ int launch_coarse(const ivfpq_index *ix, const float *d_queries, int64_t Q, int3
     // so that the usual case of no flag costs a few hundred idle workgroups).
     const bool by_wave = d_flags && kprop <= CS_CAND / 2 && nlist <= 4096 && wave_lds <= 64 * 1024;
     if (by_wave) {
-      hipLaunchKernelGGL(coarse_select_wave_kernel<false>, dim3((qn + CS_WAVES - 1) / CS_WAVES), dim3(CS_WAVES * 64),
+      hipLaunchKernelGGL(coarse_select_wave_kernel<CS_ROWS>, dim3((qn + CS_WAVES - 1) / CS_WAVES), dim3(CS_WAVES * 64),
                          wave_lds, s, d_scratch, qm, ix->d_centroids, qn, nlist, nlist, D, nlist_pad, nprobe, kprop,
                          err_scale, ix->max_cnorm, ip, ids, dist, d_flags + q0, nullptr);
       const int group = 16;

@@ -66,3 +66,29 @@ def test_split_probes_per_query_radii():
     idx = _index(rng, 96, 48, 70, 200)
     q = (idx.centroids[rng.integers(0, 70, 300)] + 0.3 * rng.normal(size=(300, 96))).astype(np.float32)
     _check(idx, q, 32, 100, None, query_radii=rng.uniform(0.1, 0.9, size=(300, 48)).astype(np.float32))
+
+
+# tiles of 64 lists x 16 queries, slices of 128 dimensions, 16-byte and scalar loads
+@pytest.mark.parametrize("nlist,D,Q", [(1, 1, 1), (63, 3, 4), (64, 4, 5), (65, 127, 16), (700, 128, 17), (130, 129, 3),
+                                       (257, 260, 33), (90, 520, 2), (4096, 64, 9)])
+@pytest.mark.parametrize("metric", [0, 1])
+def test_filtering_without_matrix_product(nlist, D, Q, metric):
+    from paper_2312_01712_amd import binding as b
+    rng = np.random.default_rng(nlist + D)
+    c = rng.normal(size=(nlist, D)).astype(np.float32)
+    q = np.ascontiguousarray(np.concatenate([c[rng.integers(0, nlist, Q - 1)], np.zeros((1, D), np.float32)]))
+    cases = [c]
+    if nlist > 300:   # masses of equal distances: more lists up to the cut than the selection collects
+        few = c.copy()
+        few[nlist // 8:] = few[0]
+        cases.append(few)
+    for cent in cases:
+        gi = b.IvfPqIndex(cent, rng.normal(size=(1, 256, D)).astype(np.float32), np.arange(nlist + 1, dtype=np.int64),
+                          np.zeros((nlist, 1), dtype=np.uint8), metric=metric)
+        for nprobe in sorted({1, min(nlist, 7), min(nlist, 100)}):
+            pid, pd = gi.coarse(torch.from_numpy(q).cuda(), nprobe)
+            torch.cuda.synchronize()
+            o_pid, o_pd = oracle.coarse(q, cent, nprobe, metric=metric)
+            assert np.array_equal(pid.cpu().numpy(), o_pid)
+            assert np.array_equal(pd.cpu().numpy().view(np.uint32), o_pd.view(np.uint32))
+        gi.close()

@@ -32,6 +32,7 @@
 namespace {
 
 constexpr int LM_G = 2;        // queries per group (interleaved tables, 8-byte look-ups)
+constexpr int LMB_G = 8;       // ... with byte tables (lm_byte_kernel)
 constexpr int LM_NW = 8;       // wavefronts per workgroup: one workgroup per CU (the table fills most of its LDS), 2 per SIMD, 256 registers each
 constexpr int LM_QUEUE = 64;   // accepted candidates a wavefront holds per query before it appends them
 constexpr int LM_SEL_WORDS = 16;     // head pass: small LDS block of selection state
@@ -54,8 +55,8 @@ struct LmArgs {
   float *out_dist;              // [Q][k]
   int32_t *cnt;                 // [nlist] pairs per list
   int32_t *rank;                // [max(Q, Q*(nprobe-first))] position of a pair among its list's pairs, -1: no pair
-  int32_t *base;                // [nlist+1] first pair slot of a list (ranges padded to LM_G); [nlist] = slots in use
-  int2 *pairs;                  // [Q*(nprobe-first) + nlist] (query, list); query -1 pads a list's range
+  int32_t *base;                // [nlist+1] first pair slot of a list (ranges padded to whole groups); [nlist] = slots in use
+  int2 *pairs;                  // [Q*(nprobe-first) + (LMB_G - 1) nlist] (query, list); query -1 pads a list's range
   uint32_t *gcnt;               // [Q] candidates appended (may run past cap: the query then counts as overflowed)
   uint2 *cand;                  // [Q][cap] (distance bits, row in the index)
   int32_t *qmap;                // [Q] out: q for a query to be redone query-major, -1 otherwise
@@ -64,6 +65,7 @@ struct LmArgs {
   const float *query_radii;     // [Q][M] or NULL
   int64_t Q;
   int32_t D, M, dsub, Mp, nlist, nprobe, first, k, cap, mode;
+  int32_t group;                // queries per group of the pass the pairs are bucketed for
   int32_t head_done;            // the head pass has run: queries it left out (qmap_head) have no first-list result yet
 };
 
@@ -108,8 +110,8 @@ __global__ __launch_bounds__(256) void lm_pairs_kernel(LmArgs a, int fill, int h
   a.rank[idx] = take ? atomicAdd(&a.cnt[c], 1) : -1;
 }
 
-// Slot ranges of the lists: base[c] = sum over c' < c of cnt[c'] rounded up to LM_G.  The
-// padding slot of an odd range is marked (query -1), the counts are cleared.
+// Slot ranges of the lists: base[c] = sum over c' < c of cnt[c'] rounded up to a.group.  The
+// padding slots of a range are marked (query -1), the counts are cleared.
 // One workgroup.
 __global__ __launch_bounds__(1024) void lm_offsets_kernel(LmArgs a) {
   __shared__ int part[1024];
@@ -118,7 +120,7 @@ __global__ __launch_bounds__(1024) void lm_offsets_kernel(LmArgs a) {
   const int lo = tid * chunk < a.nlist ? tid * chunk : a.nlist;
   const int hi = lo + chunk < a.nlist ? lo + chunk : a.nlist;
   int sum = 0;
-  for (int c = lo; c < hi; ++c) sum += (a.cnt[c] + LM_G - 1) / LM_G * LM_G;
+  for (int c = lo; c < hi; ++c) sum += (a.cnt[c] + a.group - 1) / a.group * a.group;
   part[tid] = sum;
   __syncthreads();
   for (int off = 1; off < 1024; off <<= 1) {
@@ -129,7 +131,7 @@ __global__ __launch_bounds__(1024) void lm_offsets_kernel(LmArgs a) {
   }
   int run = part[tid] - sum;
   for (int c = lo; c < hi; ++c) {
-    const int n = a.cnt[c], padded = (n + LM_G - 1) / LM_G * LM_G;
+    const int n = a.cnt[c], padded = (n + a.group - 1) / a.group * a.group;
     a.base[c] = run;
     for (int j = n; j < padded; ++j) a.pairs[run + j] = make_int2(-1, c);
     run += padded;
@@ -658,6 +660,533 @@ __global__ __launch_bounds__(LM_NW * 64) __attribute__((amdgpu_waves_per_eu(LM_N
   }
 }
 
+// ---- main pass with byte tables -----------------------------------------------------------------
+// What bounds the pass over the lists is the LDS: a wavefront's gather of 8 bytes per lane costs
+// what one of 4 does (measured: 10.0 and 10.4 lanes per clock and CU), so the values that fit 8
+// bytes decide.  With fp32 tables that is two queries' values; here it is EIGHT: a table entry
+// holds one byte per query of the group.
+//
+// Distances: the byte is a LOWER BOUND on the fp32 table value in units of 1/s_q, floor(s_q v) (up
+// to a known offset per row) cut off at LMB_TOP, so the sum of a point's bytes bounds its distance
+// from below.  A point whose
+// sum, in those units, lies above the query's k-th distance so far cannot enter the result and
+// is dropped; every other point (a fraction of a percent) gets its distance in fp32 from the
+// codebook itself, with the operations and in the order of the reference, and only that distance
+// is compared, stored and ranked.  So the result is bit for bit that of the fp32 tables; the bytes
+// only decide which sums need not be formed.  LMB_TOP = 63: four bytes add up within a byte, so
+// a group of four subspaces costs two adds per four queries before the bytes are spread to
+// 16-bit sums (64 x 63 < 2^16).
+// Hit counts (Sec. 5.4): the penalties 0, 1, 2 ARE bytes, their sums (at most 2 MT <= 128) too:
+// the byte sums are the result and nothing has to be recomputed.
+//
+// 1M x 96, 64 probes, 10 000 queries (every (query, list) pair scanned): 7.1 ms with two queries
+// per fp32 table, 3.9 ms so; hit counts, 5000 queries: 3.6 -> 1.5 ms.
+constexpr int LMB_NW = 16;      // wavefronts: one workgroup per CU (the table takes 2 KiB per subspace), 4 per SIMD
+constexpr int LMB_QUEUE = 3072; // candidates a task can hold; a query that loses one is redone query-major
+constexpr int LMB_TOP = 63;
+constexpr int LMB_SETTLE = LMB_NW * 16;   // candidates settled at a time: four lanes each
+
+typedef uint16_t ushortx2 __attribute__((ext_vector_type(2)));
+typedef uint32_t uintx2 __attribute__((ext_vector_type(2)));
+
+// What is wanted of a task, kept between its request and its use.
+template <int DSUB>
+struct LmbFetch {
+  float q[DSUB], c[DSUB];   // wavefront g, lane m: subspace m of query g and of the list's centroid
+  float r2, tau;
+  int32_t qid;              // query g (-1: the group has fewer)
+};
+
+// The table; while candidates are settled, the codebook in its place.
+constexpr size_t lmb_table(int mt, int dsub) { return (size_t)mt * (dsub > 2 ? 1024 * dsub : 2048); }
+// Floats of a (subspace, query) record: the residual and r_m^2, padded to whole 16-byte reads.
+constexpr int lmb_rec(int dsub) { return dsub == 2 ? 4 : 8; }
+constexpr size_t lmb_lds(int mt, int dsub) {
+  return lmb_table(mt, dsub) + (size_t)LMB_G * mt * (8 * lmb_rec(dsub) + 4) + (size_t)mt * 4 + (size_t)LMB_QUEUE * 4 + 256;
+}
+
+template <int J>
+__device__ __forceinline__ float xor_f32(float v) { return __uint_as_float(xor_u32<J, true>(__float_as_uint(v))); }
+
+template <int MT, int DSUB, int MODE>
+__global__ __launch_bounds__(LMB_NW * 64) __attribute__((amdgpu_waves_per_eu(4))) void lm_byte_kernel(LmArgs a, RadiiSq r2) {
+  constexpr int NW = LMB_NW;
+  constexpr int ITER = (MT + NW - 1) / NW;
+  constexpr int NCH = MT / 16;
+  constexpr int PW = lmb_rec(DSUB);
+  static_assert(MT % 16 == 0 && MT <= 64, "whole chunks, one lane per subspace");
+  extern __shared__ __align__(16) unsigned char smem[];
+  LDS unsigned char *smem3 = (LDS unsigned char *)smem;
+  // LDS carve: table [MT][256][8 bytes] | records [MT][8][PW]: residual, r_m^2 | factors [MT][8][PW]:
+  // -2 s residual, s | constants [MT][8] | largest |entry|^2 of a subspace [MT] | queue | small words
+  LDS float *srec = (LDS float *)(smem3 + lmb_table(MT, DSUB));
+  LDS float *sfac = srec + MT * LMB_G * PW;
+  LDS float *scon = sfac + MT * LMB_G * PW;
+  LDS float *semax = scon + MT * LMB_G;
+  LDS uint32_t *queue = (LDS uint32_t *)(semax + MT);
+  LDS uint32_t *small = queue + LMB_QUEUE;
+  LDS uint32_t *sT = small;            // [8] sums below this are candidates
+  LDS uint32_t *stau = small + 8;      // [8] bits of the k-th distance so far
+  LDS int32_t *sq = (LDS int32_t *)(small + 16);   // [8] queries
+  LDS uint32_t *lost = small + 24;     // [8] a candidate of the query found no room
+  LDS uint32_t *qn = small + 32;       // candidates offered to the queue
+
+  int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+
+  const int ntasks = a.base[a.nlist] / LMB_G;
+  const int nwg = gridDim.x, b = blockIdx.x;
+  int t = (nwg & 7) == 0 ? (b & 7) * (nwg >> 3) + (b >> 3) : b;   // runs of tasks per XCD, as in lm_scan_kernel
+  if (t >= ntasks) return;
+
+  // This wavefront's codebook rows, resident: lane l holds entries l, 64 + l, 128 + l, 192 + l of
+  // each.
+  float ent[ITER][4][DSUB];
+#pragma unroll
+  for (int it = 0; it < ITER; ++it) {
+    const int m = wave + it * NW;   // < MT or not: MT is a multiple of NW
+    float emax = 0.0f;
+#pragma unroll
+    for (int x = 0; x < 4; ++x) {
+      const float *src = a.codebooks + ((int64_t)m * 256 + x * 64 + lane) * DSUB;
+      float n2 = 0.0f;
+#pragma unroll
+      for (int j = 0; j < DSUB; ++j) {
+        ent[it][x][j] = src[j];
+        n2 = fmaf(src[j], src[j], n2);
+      }
+      emax = fmaxf(emax, n2);
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) emax = fmaxf(emax, __shfl_xor(emax, off));
+    if (lane == 0) semax[m] = emax;
+  }
+
+  // (vector loads for what all lanes want alike: see lm_scan_kernel)
+  auto fetch_pairs = [&](int t) __attribute__((always_inline)) { return a.pairs[(int64_t)t * LMB_G + (lane & (LMB_G - 1))]; };
+  auto fetch_meta = [&](const int2 &pv) __attribute__((always_inline)) {
+    const int c = __builtin_amdgcn_readlane(pv.y, 0);
+    const int64_t *src = lane < 2 ? a.list_offsets + c + lane : a.list_blocks + c;
+    return *src;
+  };
+  auto lane64 = [&](int64_t v, int l) __attribute__((always_inline)) {
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, l);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)((uint64_t)v >> 32), l);
+    return (int64_t)(((uint64_t)hi << 32) | lo);
+  };
+  // wavefront g < 8 brings the parameters of query g: a lane per subspace
+  auto fetch_params = [&](const int2 &pv, LmbFetch<DSUB> &f) __attribute__((always_inline)) {
+    const int c = __builtin_amdgcn_readlane(pv.y, 0);
+    const int q0 = __builtin_amdgcn_readlane(pv.x, 0);   // a task's first query exists
+    f.qid = wave < LMB_G ? __builtin_amdgcn_readlane(pv.x, wave) : -1;
+    if (wave < LMB_G && lane < MT) {
+      const int64_t q = f.qid >= 0 ? f.qid : q0;
+      if constexpr (DSUB == 2) {
+        const float2 qv = *reinterpret_cast<const float2 *>(a.queries + q * a.D + 2 * lane);
+        const float2 cv = *reinterpret_cast<const float2 *>(a.centroids + (int64_t)c * a.D + 2 * lane);
+        f.q[0] = qv.x; f.q[1] = qv.y; f.c[0] = cv.x; f.c[1] = cv.y;
+      } else {
+        const float4 qv = *reinterpret_cast<const float4 *>(a.queries + q * a.D + 4 * lane);
+        const float4 cv = *reinterpret_cast<const float4 *>(a.centroids + (int64_t)c * a.D + 4 * lane);
+        f.q[0] = qv.x; f.q[1] = qv.y; f.q[2] = qv.z; f.q[3] = qv.w;
+        f.c[0] = cv.x; f.c[1] = cv.y; f.c[2] = cv.z; f.c[3] = cv.w;
+      }
+      f.r2 = r2.v[lane];
+      if (a.query_radii) {
+        const float r = a.query_radii[q * MT + lane];
+        f.r2 = r * r;
+      }
+      f.tau = a.out_dist[q * a.k + a.k - 1];
+    } else {
+#pragma unroll
+      for (int j = 0; j < DSUB; ++j) f.q[j] = f.c[j] = 0.0f;
+      f.r2 = f.tau = 0.0f;
+    }
+  };
+
+  int2 npv = make_int2(0, 0);
+  LmbFetch<DSUB> fx;
+  CodeRegs<MT / 4> nxt;
+  int64_t row0;
+  int len, nb;
+  const uint8_t *base;
+  auto take_meta = [&](int64_t mv) __attribute__((always_inline)) {
+    row0 = lane64(mv, 0);
+    len = (int)(lane64(mv, 1) - row0);
+    nb = (len + 63) >> 6;   // >= 1: only non-empty lists have tasks
+    base = a.codes + lane64(mv, 2) * ivfpq_block_bytes(MT);
+    load_chunks<MT, 0, NCH>(base, nb, wave < nb ? wave : nb - 1, lane, nxt);
+  };
+  {
+    const int2 pv = fetch_pairs(t);
+    if (t + nwg < ntasks) npv = fetch_pairs(t + nwg);
+    const int64_t mv = fetch_meta(pv);
+    fetch_params(pv, fx);
+    take_meta(mv);
+  }
+  // A task's accepted candidates: their room is reserved when they are settled, and they are
+  // written once the next task's table is built, so that nothing waits for the atomic's way.
+  uint32_t p_slot = 0, p_bits = 0, p_row = 0;
+  int32_t p_q = 0;
+  bool p_has = false;
+  uint32_t p_where = 0;   // lane that holds the first slot of the candidate's query, and the candidate's place behind it
+  auto drain = [&]() __attribute__((always_inline)) {
+    const uint32_t slot = (uint32_t)__shfl((int)p_slot, (int)(p_where & 7u)) + (p_where >> 3);
+    if (p_has && slot < (uint32_t)a.cap) a.cand[(int64_t)p_q * a.cap + slot] = make_uint2(p_bits, p_row);
+    p_has = false;
+  };
+  __syncthreads();   // semax
+  for (;;) {
+    // (the addresses of all phases are formed anew for every task: kept across tasks, they took 60
+    // registers that are not there)
+    asm volatile("" : "+v"(tid), "+v"(lane));
+    // ---- the group's parameters ----
+    if (wave < LMB_G) {
+      const bool on = lane < MT;
+      float res[DSUB];
+#pragma unroll
+      for (int j = 0; j < DSUB; ++j) res[j] = fx.q[j] - fx.c[j];
+      const float tau = __uint_as_float((uint32_t)__builtin_amdgcn_readfirstlane((int)__float_as_uint(fx.tau)));
+      uint32_t T;
+      if (on) {
+        LDS float *rec = srec + (lane * LMB_G + wave) * PW;
+#pragma unroll
+        for (int j = 0; j < DSUB; ++j) rec[j] = res[j];
+        rec[DSUB] = fx.r2;
+      }
+      if constexpr (MODE == 0) {
+        // Units: the largest r_m^2 (no table value exceeds it), or, where that is wider, four times
+        // the mean value of a point within tau, maps to LMB_TOP; values beyond are cut off, which
+        // keeps the sum a lower bound.
+        float rmax = on ? fx.r2 : 0.0f;
+#pragma unroll
+        for (int off = 32; off > 8; off >>= 1) rmax = fmaxf(rmax, __shfl_xor(rmax, off));
+        rmax = fmaxf(rmax, xor_f32<8>(rmax));
+        rmax = fmaxf(rmax, xor_f32<4>(rmax));
+        rmax = fmaxf(rmax, xor_f32<2>(rmax));
+        rmax = fmaxf(rmax, xor_f32<1>(rmax));
+        const float cap = fmaxf(fminf(rmax, tau * (4.0f / (float)MT)), 1e-30f);
+        const float s = ((float)LMB_TOP - 0.01f) / cap;   // infinite radii and no k-th distance: 0
+        // Offset of a row: up to the next integer at the row's cap, so that entries outside the
+        // radius (most of them) lose nothing to the floor; what the offsets add is known.
+        const float x = fminf(fx.r2, cap) * s, top = ceilf(x), off = top - x;
+        float rr = 0.0f;
+#pragma unroll
+        for (int j = 0; j < DSUB; ++j) rr = fmaf(res[j], res[j], rr);
+        if (on) {
+          LDS float *fac = sfac + (lane * LMB_G + wave) * PW;
+#pragma unroll
+          for (int j = 0; j < DSUB; ++j) fac[j] = -2.0f * s * res[j];
+          fac[DSUB] = s;
+          fac[DSUB + 1] = top;   // (DSUB 2: the record's last float)
+          // (-0.5 turns the round-to-nearest of the conversion to bytes into a floor, 2^-10 keeps
+          // what is at the cap above the tie)
+          scon[lane * LMB_G + wave] = fmaf(rr, s, off - 0.4990234375f);
+        }
+        // Limit on the byte sum of a point with distance <= tau: s tau, relative roundings (the fp32
+        // sum, the scaling: 2^-23 each, at most 70 of them), the offsets and their 2^-10, and the
+        // roundings of |r|^2 - 2 r.e + |e|^2 in place of |r - e|^2, each within 2^-24 of
+        // s (|r| + |e|)^2: fewer than 2 DSUB + 6 of them, counted as 32.
+        float add = 0.0f;
+        if (on) {
+          const float far = sqrtf(rr) + sqrtf(semax[lane]);
+          add = off + 0.001f + s * far * far * 1.9073486e-06f;
+        }
+#pragma unroll
+        for (int o = 32; o > 8; o >>= 1) add += __shfl_xor(add, o);
+        add += xor_f32<8>(add);
+        add += xor_f32<4>(add);
+        add += xor_f32<2>(add);
+        add += xor_f32<1>(add);
+        const float lim = fmaf(tau * s, 1.00001f, add) + 0.25f;
+        T = lim < 60000.0f ? (uint32_t)lim : 60000u;   // NaN (0 x inf): every point
+      } else {
+        T = tau < 60000.0f ? (uint32_t)tau : 60000u;
+      }
+      if (lane == 0) {
+        sT[wave] = fx.qid >= 0 ? T + 1u : 0u;
+        stau[wave] = __float_as_uint(tau);
+        sq[wave] = fx.qid;
+        lost[wave] = 0u;
+      }
+    }
+    if (tid == 0) *qn = 0u;
+    __syncthreads();
+    // ---- the table: row m holds, entry by entry, one byte per query ----
+    // Distances: s |r - e|^2 + offset as a product of depth DSUB + 1 on the matrix units, four
+    // queries (rows) by 64 entries (columns, a lane each) at a time; per value that leaves the
+    // cut-off and the conversion to the vector ALU (9.3 of a task's 35 thousand clocks went into
+    // this table with all of it there).
+    const bool five = sq[4] >= 0;   // uniform
+#pragma unroll
+    for (int it = 0; it < ITER; ++it) {
+      const int m = wave + it * NW;
+      float nrm[4];   // |entry|^2, formed anew for every task like the addresses
+#pragma unroll
+      for (int x = 0; x < 4 && MODE == 0; ++x) {
+        float e0 = ent[it][x][0];
+        asm volatile("" : "+v"(e0));
+        nrm[x] = e0 * e0;
+#pragma unroll
+        for (int j = 1; j < DSUB; ++j) nrm[x] = fmaf(ent[it][x][j], ent[it][x][j], nrm[x]);
+      }
+      uint32_t w[2][4];
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+#pragma unroll
+        for (int x = 0; x < 4; ++x) w[h][x] = 0u;
+        if (h == 1 && !five) break;
+        if constexpr (MODE == 0) {
+          const LDS float *fac = sfac + (m * LMB_G + 4 * h + (lane & 3)) * PW;   // row lane % 4 of every 4 x 4 block
+          float f[DSUB + 1], top[4];
+          const floatx4 f0 = *(const LDS floatx4 *)fac;
+#pragma unroll
+          for (int j = 0; j < DSUB; ++j) f[j] = f0[j];
+          f[DSUB] = DSUB == 2 ? f0[2] : fac[4];
+#pragma unroll
+          for (int g = 0; g < 4; ++g) top[g] = sfac[(m * LMB_G + 4 * h + g) * PW + DSUB + 1];
+          const floatx4 con = *(const LDS floatx4 *)(scon + m * LMB_G + 4 * h);
+#pragma unroll
+          for (int y = 0; y < 4; y += 2) {   // two chains of products side by side
+            floatx4 acc[2] = {con, con};
+#pragma unroll
+            for (int j = 0; j < DSUB; ++j)
+#pragma unroll
+              for (int x = 0; x < 2; ++x) acc[x] = __builtin_amdgcn_mfma_f32_4x4x1f32(f[j], ent[it][y + x][j], acc[x], 0, 0, 0);
+#pragma unroll
+            for (int x = 0; x < 2; ++x) acc[x] = __builtin_amdgcn_mfma_f32_4x4x1f32(f[DSUB], nrm[y + x], acc[x], 0, 0, 0);
+#pragma unroll
+            for (int x = 0; x < 2; ++x)
+#pragma unroll
+              for (int g = 0; g < 4; ++g)   // (the median of three is one instruction, a minimum two)
+                w[h][y + x] = __builtin_amdgcn_cvt_pk_u8_f32(__builtin_amdgcn_fmed3f(acc[x][g], 0.0f, top[g]), g, w[h][y + x]);
+          }
+        } else {
+#pragma unroll
+          for (int g = 0; g < 4; ++g) {
+            const LDS float *rec = srec + (m * LMB_G + 4 * h + g) * PW;
+            const floatx4 p0 = *(const LDS floatx4 *)rec;
+            const float rm2 = DSUB == 2 ? p0[2] : rec[4];
+#pragma unroll
+            for (int x = 0; x < 4; ++x) {
+              const float t0 = p0[0] - ent[it][x][0];
+              float d2 = t0 * t0;
+#pragma unroll
+              for (int j = 1; j < DSUB; ++j) {
+                const float tj = p0[j] - ent[it][x][j];
+                d2 = fmaf(tj, tj, d2);
+              }
+              if constexpr (MODE == 1) w[h][x] |= d2 <= rm2 ? 0u : (1u << (8 * g));
+              else w[h][x] |= d2 <= 0.25f * rm2 ? 0u : (d2 <= rm2 ? (1u << (8 * g)) : (2u << (8 * g)));
+            }
+          }
+        }
+      }
+#pragma unroll
+      for (int x = 0; x < 4; ++x) *(LDS uintx2 *)(smem3 + m * 2048 + (x * 64 + lane) * 8) = uintx2{w[0][x], w[1][x]};
+      __builtin_amdgcn_sched_barrier(0);   // a row at a time: their temporaries together do not fit the registers
+    }
+    const int tn = t + nwg;
+    const bool more = tn < ntasks;
+    int64_t nmv = 0;
+    int2 nnv = make_int2(0, 0);
+    if (more) nmv = fetch_meta(npv);
+    if (tn + nwg < ntasks) nnv = fetch_pairs(tn + nwg);
+    if (__ballot(p_has) != 0) drain();
+    __syncthreads();
+    // ---- one pass over the list's codes serves all queries of the group ----
+    // sums of queries (0, 2), (1, 3), (4, 6), (5, 7) as 16-bit halves, and the limits to compare with
+    uint32_t lim[4];
+    lim[0] = (uint32_t)__builtin_amdgcn_readfirstlane((int)(sT[0] | (sT[2] << 16)));
+    lim[1] = (uint32_t)__builtin_amdgcn_readfirstlane((int)(sT[1] | (sT[3] << 16)));
+    lim[2] = (uint32_t)__builtin_amdgcn_readfirstlane((int)(sT[4] | (sT[6] << 16)));
+    lim[3] = (uint32_t)__builtin_amdgcn_readfirstlane((int)(sT[5] | (sT[7] << 16)));
+    const int last = nb - 1;
+    for (int blk = wave; blk < nb; blk += NW) {
+      CodeRegs<MT / 4> cur = nxt;
+      load_chunks<MT, 0, NCH>(base, nb, blk + NW < last ? blk + NW : last, lane, nxt);   // past the end: the last block again
+      uint32_t s[4] = {0u, 0u, 0u, 0u}, raw0 = 0u, raw1 = 0u;
+      auto high_bytes = [](uint32_t x) __attribute__((always_inline)) {   // both halves shifted at once
+        return __builtin_bit_cast(uint32_t, (ushortx2)(__builtin_bit_cast(ushortx2, x) >> (ushortx2){8, 8}));
+      };
+#pragma unroll
+      for (int h = 0; h < MT; h += 8) {
+        uintx2 v[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+          const uint32_t off = code_offset8(cur.w[(h + j) >> 2], j & 3);   // the table starts at LDS address 0
+          v[j] = *(const LDS uintx2 *)(uintptr_t)(uint32_t)((h + j) * 2048 + off);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int j = 0; j < 8; j += 4) {   // four bytes below 64 add up within a byte
+          const uint32_t x0 = (v[j][0] + v[j + 1][0] + v[j + 2][0]) + v[j + 3][0];
+          const uint32_t x1 = (v[j][1] + v[j + 1][1] + v[j + 2][1]) + v[j + 3][1];
+          if constexpr (MODE == 0) {
+            s[0] += x0 & 0x00FF00FFu;
+            s[1] += high_bytes(x0);
+            s[2] += x1 & 0x00FF00FFu;
+            s[3] += high_bytes(x1);
+          } else {
+            raw0 += x0;
+            raw1 += x1;
+          }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      if constexpr (MODE != 0) {
+        s[0] = raw0 & 0x00FF00FFu;
+        s[1] = high_bytes(raw0);
+        s[2] = raw1 & 0x00FF00FFu;
+        s[3] = high_bytes(raw1);
+      }
+      const int i = blk * 64 + lane;
+      uint32_t z[4], any = 0u;   // limit - sum, saturated at 0: non-zero halves are candidates
+#pragma unroll
+      for (int x = 0; x < 4; ++x) {
+        z[x] = __builtin_bit_cast(uint32_t, __builtin_elementwise_sub_sat(__builtin_bit_cast(ushortx2, lim[x]), __builtin_bit_cast(ushortx2, s[x])));
+        any |= z[x];
+      }
+      if (__ballot(i < len && any != 0u) == 0) continue;
+      uint32_t mask = 0u;   // bit g: the point is a candidate of query g
+#pragma unroll
+      for (int x = 0; x < 4; ++x) {
+        const int g0 = (x >> 1) * 4 + (x & 1);
+        mask |= (z[x] & 0xFFFFu) ? 1u << g0 : 0u;
+        mask |= (z[x] >> 16) ? 4u << g0 : 0u;
+      }
+      if (i >= len) mask = 0u;
+      for (unsigned long long bal = __ballot(mask != 0u); bal != 0; bal = __ballot(mask != 0u)) {
+        uint32_t first = 0;
+        if (lane == 0) first = __hip_atomic_fetch_add(qn, (uint32_t)__popcll(bal), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        first = (uint32_t)__builtin_amdgcn_readfirstlane((int)first);
+        if (mask != 0u) {
+          const uint32_t g = (uint32_t)__ffs((int)mask) - 1u;
+          mask &= mask - 1u;
+          const uint32_t pos = first + (uint32_t)__popcll(bal & ((1ull << lane) - 1ull));
+          uint32_t word = ((uint32_t)i << 3) | g;
+          if constexpr (MODE != 0) {   // the score travels with the point (at most 2 MT <= 128)
+            const uint32_t zz = (g & 4u) ? ((g & 1u) ? s[3] : s[2]) : ((g & 1u) ? s[1] : s[0]);
+            word = ((uint32_t)i << 11) | (((g & 2u) ? zz >> 16 : zz & 0xFFFFu) << 3) | g;
+          }
+          if (pos < (uint32_t)LMB_QUEUE) queue[pos] = word;
+          else lost[g] = 1u;
+        }
+      }
+    }
+    __syncthreads();   // the list is scanned: the queue is complete, the table's place is free
+    const int n = (int)umin32(*qn, (uint32_t)LMB_QUEUE);
+    if (tid < LMB_G && lost[tid] != 0u) atomicAdd(&a.gcnt[sq[tid]], (uint32_t)a.cap + 1u);   // redone query-major
+    // ---- the candidates' distances in fp32 ----
+    // Four lanes per candidate, a chunk of 16 subspaces each; the entries come from the codebook,
+    // which the wavefronts put where the table was (random reads of it from the L2 took 8 thousand
+    // clocks of a task).
+    const int cd = tid >> 2, ch = tid & 3;
+    uint4 cw = make_uint4(0u, 0u, 0u, 0u);
+    const int64_t drow0 = row0;
+    const uint8_t *dbase = base;
+    const int dnb = nb;
+    auto codes_of = [&](int e) __attribute__((always_inline)) {   // this lane's 16 codes of candidate e
+      if (MODE == 0 && e < n && ch < NCH) {
+        const uint32_t i = queue[e] >> 3;
+        cw = *reinterpret_cast<const uint4 *>(dbase + ((int64_t)ch * dnb + (i >> 6)) * 1024 + (i & 63u) * 16);
+      }
+    };
+    codes_of(cd);
+    // the next task's inputs travel while this one's candidates are settled
+    if (more) {
+      fetch_params(npv, fx);
+      take_meta(nmv);
+      npv = nnv;
+    }
+    if (MODE == 0 && n > 0) {
+#pragma unroll
+      for (int it = 0; it < ITER; ++it)
+#pragma unroll
+        for (int x = 0; x < 4; ++x) {
+          LDS float *dst = (LDS float *)smem3 + ((wave + it * NW) * 256 + x * 64 + lane) * DSUB;
+          if constexpr (DSUB == 2) *(LDS floatx2 *)dst = floatx2{ent[it][x][0], ent[it][x][1]};
+          else *(LDS floatx4 *)dst = floatx4{ent[it][x][0], ent[it][x][1], ent[it][x][2], ent[it][x][3]};
+        }
+      __syncthreads();
+    }
+    for (int e0 = 0; e0 < n; e0 += LMB_SETTLE) {
+      const int e = e0 + cd;
+      if (e0 > 0) {
+        if (__ballot(p_has) != 0) drain();
+        codes_of(e);
+      }
+      bool pass = e < n && ch == NCH - 1;
+      uint32_t g = 0, bits = 0, i = 0;
+      if (e0 + wave * 16 < n) {   // this wavefront has candidates
+        const uint32_t word = e < n ? queue[e] : 0u;
+        g = word & 7u;
+        if constexpr (MODE == 0) {
+          i = word >> 3;
+          const uint32_t cws[4] = {cw.x, cw.y, cw.z, cw.w};
+          float v[16];
+          const int m0 = (ch < NCH ? ch : NCH - 1) * 16;
+#pragma unroll
+          for (int j = 0; j < 16; ++j) {
+            const int m = m0 + j;
+            const uint32_t code = (cws[j >> 2] >> (8 * (j & 3))) & 0xFFu;
+            const LDS float *en = (const LDS float *)smem3 + (m * 256 + (int)code) * DSUB;
+            const LDS float *rec = srec + (m * LMB_G + (int)g) * PW;
+            const floatx4 rv = *(const LDS floatx4 *)rec;
+            float d2;
+            if constexpr (DSUB == 2) {
+              const floatx2 ev = *(const LDS floatx2 *)en;
+              const float t0 = rv[0] - ev[0], t1 = rv[1] - ev[1];
+              d2 = fmaf(t1, t1, t0 * t0);
+              v[j] = table_value<0>(d2, rv[2]);
+            } else {
+              const floatx4 ev = *(const LDS floatx4 *)en;
+              const float t0 = rv[0] - ev[0], t1 = rv[1] - ev[1], t2 = rv[2] - ev[2], t3 = rv[3] - ev[3];
+              d2 = fmaf(t3, t3, fmaf(t2, t2, fmaf(t1, t1, t0 * t0)));
+              v[j] = table_value<0>(d2, rec[4]);
+            }
+            if ((j & 3) == 3) __builtin_amdgcn_sched_barrier(0);
+          }
+          float dist = 0.0f;   // subspaces ascending: the sum moves on from lane to lane
+#pragma unroll
+          for (int c = 0; c < NCH; ++c) {
+            float acc = dist;
+#pragma unroll
+            for (int j = 0; j < 16; ++j) acc += v[j];
+            dist = __shfl(acc, (lane & ~3) | c);   // lane c's sum is the one that counts in round c
+          }
+          bits = __float_as_uint(dist);
+          pass = pass && bits <= stau[g];
+        } else {
+          i = word >> 11;
+          bits = __float_as_uint((float)((word >> 3) & 255u));
+        }
+        // one atomic instruction reserves the room of all queries: lane g for query g
+        uint32_t mine = 0, before = 0;
+#pragma unroll
+        for (int x = 0; x < LMB_G; ++x) {
+          const unsigned long long bal = __ballot(pass && g == (uint32_t)x);
+          if (lane == x) mine = (uint32_t)__popcll(bal);
+          if (g == (uint32_t)x) before = (uint32_t)__popcll(bal & ((1ull << lane) - 1ull));
+        }
+        p_slot = 0;
+        if (lane < LMB_G && mine > 0) p_slot = atomicAdd(&a.gcnt[sq[lane]], mine);
+        p_where = (before << 3) | g;
+        p_bits = bits;
+        p_row = (uint32_t)(drow0 + i);
+        p_q = sq[g];
+        p_has = pass;
+      }
+    }
+    if (!more) {
+      if (__ballot(p_has) != 0) drain();
+      break;
+    }
+    t = tn;
+    __syncthreads();  // parameters, queue and table are free
+  }
+}
+
 // One wavefront per query: the candidates of the list-major scan are merged into the top-k of
 // the first lists by (distance, id).  Queries whose buffer overflowed are handed to the
 // query-major kernel through qmap.
@@ -744,6 +1273,29 @@ int launch_lm_scan_t(const LmArgs &a, const RadiiSq &r2, int grid, hipStream_t s
   return IVFPQ_OK;
 }
 
+template <int MT, int DSUB, int MODE>
+int launch_lm_byte_t(const LmArgs &a, const RadiiSq &r2, int grid, hipStream_t s) {
+  auto kern = lm_byte_kernel<MT, DSUB, MODE>;
+  static std::atomic<uint64_t> prepared;
+  if (int rc = prepare_kernel(kern, prepared)) return rc;
+  static_assert(lmb_lds(MT, DSUB) <= (size_t)LDS_PER_CU, "byte tables, records and queue fit a CU");
+  hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(LMB_NW * 64), lmb_lds(MT, DSUB), s, a, r2);
+  return IVFPQ_OK;
+}
+
+template <int MODE>
+int launch_lm_byte_m(const LmArgs &a, const RadiiSq &r2, int grid, hipStream_t s) {
+  if (a.M == 48) return launch_lm_byte_t<48, 2, MODE>(a, r2, grid, s);
+  if (a.M == 64) return launch_lm_byte_t<64, 2, MODE>(a, r2, grid, s);
+  return launch_lm_byte_t<16, 4, MODE>(a, r2, grid, s);
+}
+
+int launch_lm_byte(const LmArgs &a, const RadiiSq &r2, int grid, hipStream_t s) {
+  if (a.mode == 0) return launch_lm_byte_m<0>(a, r2, grid, s);
+  if (a.mode == 1) return launch_lm_byte_m<1>(a, r2, grid, s);
+  return launch_lm_byte_m<2>(a, r2, grid, s);
+}
+
 template <bool HEAD>
 int launch_lm_scan(const ivfpq_index *ix, const LmArgs &a, const RadiiSq &r2, int grid, hipStream_t s) {
   if (ix->M == 48) return launch_lm_scan_t<48, 2, HEAD>(a, r2, grid, s);
@@ -775,7 +1327,7 @@ LmWorkspace plan_list_major(const ivfpq_index *ix, int64_t Q, int32_t nprobe) {
   // 1M x 96 configuration (64 probes): 4096 slots 11.39 ms per batch, 8192 10.88, 16384 10.71.
   w.cap = g_lm_cap.load(std::memory_order_relaxed);
   if (w.cap == 0) w.cap = nprobe >= 64 ? 16384 : (nprobe * 256 > 4096 ? nprobe * 256 : 4096);
-  w.pairs_cap = Q * (nprobe - w.first > 1 ? nprobe - w.first : 1) + ix->nlist;   // also holds the head pass's Q pairs
+  w.pairs_cap = Q * (nprobe - w.first > 1 ? nprobe - w.first : 1) + (int64_t)(LMB_G - 1) * ix->nlist;   // also holds the head pass's Q pairs
   size_t off = 0;
   w.cnt = off;   off += lm_align((size_t)ix->nlist * 4);
   w.base = off;  off += lm_align(((size_t)ix->nlist + 1) * 4);
@@ -824,6 +1376,7 @@ int launch_scan_list_major(const ivfpq_index *ix, const float *d_queries, int64_
   a.D = ix->D; a.M = ix->M; a.dsub = ix->dsub; a.Mp = ix->Mp; a.nlist = ix->nlist;
   a.nprobe = nprobe; a.first = w.first; a.k = k; a.cap = w.cap; a.mode = mode;
   a.head_done = 0;
+  a.group = LM_G;
 
   // list-level lower bounds of every (query, probe); the same launch clears the per-list counts
   // (lm_offsets_kernel leaves them clear for the pass after it)
@@ -859,12 +1412,18 @@ int launch_scan_list_major(const ivfpq_index *ix, const float *d_queries, int64_
   }
 
   // ---- the other lists, list-major: pairs bucketed by list, scan, merge ----
+  // With byte tables unless most queries may have no k-th distance to compare with yet (lists
+  // shorter than k on average leave them without one after their first list, and then every point
+  // is a candidate), a position does not fit the queue's words, or the early exit of the sums is
+  // switched off (a plain scan forms every sum).
+  const bool bytes = ix->N >= (int64_t)2 * k * ix->nlist && ix->max_list_len < (1 << 20) && !(get_scan_ablate() & 8);
+  a.group = bytes ? LMB_G : LM_G;
   const int64_t npairs = Q * (nprobe - w.first);
   const unsigned pair_grid = (unsigned)((npairs + 255) / 256);
   hipLaunchKernelGGL(lm_pairs_kernel, dim3(pair_grid), dim3(256), 0, s, a, 0, 0);
   hipLaunchKernelGGL(lm_offsets_kernel, dim3(1), dim3(1024), 0, s, a);
   hipLaunchKernelGGL(lm_pairs_kernel, dim3(pair_grid), dim3(256), 0, s, a, 1, 0);
-  rc = launch_lm_scan<false>(ix, a, r2, cus, s);
+  rc = bytes ? launch_lm_byte(a, r2, cus, s) : launch_lm_scan<false>(ix, a, r2, cus, s);
   if (rc) return rc;
   hipLaunchKernelGGL(lm_merge_kernel, dim3((unsigned)((Q + 3) / 4)), dim3(256), 0, s, a);
   IVFPQ_HIP_TRY(hipGetLastError());

@@ -33,8 +33,13 @@ using ivfpq::GRID_G;
 
 // BYTE: the hit-count scorings with a byte table (one byte per entry, 256 bytes per row,
 // integer sums) instead of the float table; the sums are the same small integers either way.
-template <int MT, int DSUB, int NW, bool DUMP, bool BYTE = false>
+// KIND: SCAN_ALL writes every candidate's distance instead of a top-k; SCAN_SPLIT is the form in
+// which several workgroups share a query's probes (its exchange of bounds costs registers that the
+// plain form spills for: 7 % on lists of 8000 points).
+enum { SCAN_TOPK = 0, SCAN_ALL = 1, SCAN_SPLIT = 2 };
+template <int MT, int DSUB, int NW, int KIND, bool BYTE = false>
 __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(scan_wpe(BYTE ? (MT + 3) / 4 : MT, NW)))) void scan_kernel(ScanArgs a, RadiiSq r2) {
+  constexpr bool DUMP = KIND == SCAN_ALL, SPLIT = KIND == SCAN_SPLIT;
   constexpr int NT = NW * 64;
   using Acc = std::conditional_t<BYTE, uint32_t, float>;
   constexpr int MPT = (MT + 3) / 4 * 4;
@@ -73,20 +78,20 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(scan_wp
   LDS uint32_t *stat = (LDS uint32_t *)((LDS float *)(srmin + 4 * IVFPQ_MAX_M) + NW * SUF_SLOTS);  // blocks scanned / scanned to the end
   // Probe groups in the order of their lists: the workgroups with the nearest lists of all queries
   // come first, so that the bounds they publish (a.gbound) are there when most of the others start.
-  const int nq = gridDim.x / a.nsplit;
-  const int64_t q = blockIdx.x % nq;
-  const int split = blockIdx.x / nq;
-  const int p_begin = (int)((int64_t)a.nprobe * split / a.nsplit);
-  const int p_end = (int)((int64_t)a.nprobe * (split + 1) / a.nsplit);
+  const int nq = SPLIT ? gridDim.x / a.nsplit : 1;
+  const int64_t q = SPLIT ? blockIdx.x % nq : blockIdx.x;
+  const int split = SPLIT ? blockIdx.x / nq : 0;
+  const int p_begin = SPLIT ? (int)((int64_t)a.nprobe * split / a.nsplit) : 0;
+  const int p_end = SPLIT ? (int)((int64_t)a.nprobe * (split + 1) / a.nsplit) : a.nprobe;
   const int32_t *probes = a.probe_ids + q * a.probe_stride;
   // with a query map only the queries it names are served (uniform over the workgroup)
   if (a.qmap && a.qmap[q] < 0) return;
   // Bound on the query's k-th distance from the workgroups that serve its other probe groups, as
   // its complement (0: none yet).  Any workgroup's own bound is an upper bound on the final k-th
   // distance, so the smallest of them is one too, and a late value is only looser.
-  uint32_t *const gb = DUMP ? nullptr : (a.gbound ? a.gbound + q : nullptr);
+  uint32_t *const gb = SPLIT && a.gbound ? a.gbound + q : nullptr;
   uint32_t gseen = gb ? __hip_atomic_load(gb, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
-  if (!DUMP && gb && a.probe_lb) {
+  if (SPLIT && gb && a.probe_lb) {
     // a group whose lists are all ruled out needs neither codebook nor metadata: its list is empty
     // (one wavefront decides for all: the bound may change between two reads of it)
     LDS uint32_t *alive = (LDS uint32_t *)lut;   // free until the first table is built, two barriers on
@@ -172,10 +177,10 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(scan_wp
     for (int it = 0; it < RES; ++it) {
       const int m = wave + it * NW;
       const int mc = m < MT ? m : MT - 1;
-      const uint8_t *cb = uniform_ptr(reinterpret_cast<const uint8_t *>(a.codebooks + (int64_t)mc * 256 * DSUB));
+      const GLOBAL uint8_t *cb = uniform_ptr(a.codebooks + (int64_t)mc * 256 * DSUB);
 #pragma unroll
       for (int x = 0; x < DSUB; ++x)
-        cbr[it][x] = *reinterpret_cast<const float4 *>(cb + (uint32_t)(lane * 16 * DSUB + 16 * x));
+        cbr[it][x] = load_f4(cb, (uint32_t)(lane * 16 * DSUB + 16 * x));
     }
   }
   // Code chunks per point (16-byte chunks, then 4-byte chunks) and how many of them
@@ -258,18 +263,16 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(scan_wp
       if (!sres_ready)
         for (int i = tid; i < D; i += NT) sres[i] = sq[i] - cen[i];
       if (next_known && tid < D)
-        cen_next = *reinterpret_cast<const float *>(
-            uniform_ptr(reinterpret_cast<const uint8_t *>(
-                a.centroids + (int64_t)__builtin_amdgcn_readfirstlane(meta_c[pm + 1]) * D)) +
-            (uint32_t)(tid * 4));
+        cen_next = *reinterpret_cast<const GLOBAL float *>(
+            uniform_ptr(a.centroids + (int64_t)__builtin_amdgcn_readfirstlane(meta_c[pm + 1]) * D) + (uint32_t)(tid * 4));
 #pragma unroll
       for (int it = 0; it < STR; ++it) {
         const int m = wave + (RES + it) * NW;
         const int mc = m < MT ? m : MT - 1;
-        const uint8_t *cb = uniform_ptr(reinterpret_cast<const uint8_t *>(a.codebooks + (int64_t)mc * 256 * DSUB));
+        const GLOBAL uint8_t *cb = uniform_ptr(a.codebooks + (int64_t)mc * 256 * DSUB);
 #pragma unroll
         for (int x = 0; x < DSUB; ++x)
-          cbs[it][x] = *reinterpret_cast<const float4 *>(cb + (uint32_t)(lane * 16 * DSUB + 16 * x));
+          cbs[it][x] = load_f4(cb, (uint32_t)(lane * 16 * DSUB + 16 * x));
       }
     }
     if constexpr (MT > 0) {
@@ -379,7 +382,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(scan_wp
       if (next_known && tid < D) sres[tid] = sq[tid] - cen_next;  // this list's table is complete
       sres_ready = next_known;
     }
-    if (!DUMP && gb) gseen = __hip_atomic_load(gb, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // arrives during the scan
+    if (SPLIT && gb) gseen = __hip_atomic_load(gb, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // arrives during the scan
     // ---- distance calculation over list c ----
     if (MT > 0) {
       // Two register sets: `nxt` receives the loads of the next block while `cur` is
@@ -392,7 +395,6 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(scan_wp
       float suf0 = 0.0f;
       if (VEC && !DUMP && prune) {
         constexpr int NG = (MT + 7) / 8;
-        typedef uint32_t uintx4 __attribute__((ext_vector_type(4)));
         auto row_min = [&](int m) {
           const uintx4 p = *(const LDS uintx4 *)(srmin + 4 * m);
           return __uint_as_float(umin32(umin32(p[0], p[1]), umin32(p[2], p[3])));
@@ -479,14 +481,14 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(scan_wp
       }
     }
     if (DUMP) dump_pos += len;
-    if (!DUMP && gb && tid == 0) {   // exchange bounds with the query's other workgroups
+    if (SPLIT && gb && tid == 0) {   // exchange bounds with the query's other workgroups
       const uint32_t own = *(volatile LDS uint32_t *)sh.bound;
       if (own < ~gseen) __hip_atomic_fetch_max(gb, ~own, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       else __hip_atomic_fetch_min(sh.bound, ~gseen, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     }
   }
   if (DUMP) return;
-  if (gb) {   // the keys still queued tighten the bound once more: the groups yet to come profit
+  if (SPLIT && gb) {   // the keys still queued tighten the bound once more: the groups yet to come profit
     if (st.qcount > 0) wave_flush<true>(st, qd, qid, lane, a.k, sh);
     __syncthreads();
     if (tid == 0) __hip_atomic_fetch_max(gb, ~*(volatile LDS uint32_t *)sh.bound, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -1324,9 +1326,11 @@ int launch_scan_t(const ScanArgs &a, const RadiiSq &r2, int64_t grid, bool dump,
     ivfpq::set_error("scan: %zu bytes of LDS needed, 163840 available", lds);
     return IVFPQ_ERR_UNSUPPORTED;
   }
-  auto kern = dump ? scan_kernel<MT, DSUB, NW, true, BYTE> : scan_kernel<MT, DSUB, NW, false, BYTE>;
-  static std::atomic<uint64_t> prepared[2];
-  if (int rc = prepare_kernel(kern, prepared[dump ? 1 : 0])) return rc;
+  const int kind = dump ? SCAN_ALL : (a.nsplit > 1 ? SCAN_SPLIT : SCAN_TOPK);
+  auto kern = kind == SCAN_ALL ? scan_kernel<MT, DSUB, NW, SCAN_ALL, BYTE>
+                               : (kind == SCAN_SPLIT ? scan_kernel<MT, DSUB, NW, SCAN_SPLIT, BYTE> : scan_kernel<MT, DSUB, NW, SCAN_TOPK, BYTE>);
+  static std::atomic<uint64_t> prepared[3];
+  if (int rc = prepare_kernel(kern, prepared[kind])) return rc;
   hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(NW * 64), lds, s, a, r2);
   return IVFPQ_OK;
 }

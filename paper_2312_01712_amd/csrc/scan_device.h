@@ -18,6 +18,12 @@ namespace {
 // is a DS instruction and no generic-pointer dispatch is ever generated.
 #define LDS __attribute__((address_space(3)))
 typedef float floatx4 __attribute__((ext_vector_type(4)));
+typedef uint32_t uintx4 __attribute__((ext_vector_type(4)));
+// The same for global memory, where the compiler cannot see it by itself: a pointer that has been
+// through integer registers (uniform_ptr) is otherwise a generic one, its loads are FLAT, and those
+// count on the LDS counter too and return out of order: every wait for an LDS look-up then waits
+// for the code block requested ahead.
+#define GLOBAL __attribute__((address_space(1)))
 
 // Wavefronts per SIMD the scan kernel is compiled for: 4 (two 8-wave workgroups per CU, 128
 // vector registers each).  Tables of more than 72 KiB allow one workgroup per CU anyway;
@@ -310,11 +316,16 @@ struct CodeRegs {
 
 // A pointer that is the same in every lane, moved to scalar registers so that loads
 // through it use the scalar-base + 32-bit lane-offset addressing form.
-__device__ inline const uint8_t *uniform_ptr(const uint8_t *p) {
+__device__ inline const GLOBAL uint8_t *uniform_ptr(const void *p) {
   const uint64_t v = reinterpret_cast<uint64_t>(p);
   const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
   const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
-  return reinterpret_cast<const uint8_t *>(((uint64_t)hi << 32) | lo);
+  return reinterpret_cast<const GLOBAL uint8_t *>(((uint64_t)hi << 32) | lo);
+}
+// 16 bytes at a lane's offset from such a pointer, as floats
+__device__ inline float4 load_f4(const GLOBAL uint8_t *p, uint32_t off) {
+  const floatx4 v = *reinterpret_cast<const GLOBAL floatx4 *>(p + off);
+  return make_float4(v[0], v[1], v[2], v[3]);
 }
 
 // Chunks [J0, J1) of block b of a list with nb blocks (J counts the 16-byte chunks
@@ -328,16 +339,16 @@ __device__ inline void load_chunks(const uint8_t *__restrict__ list_base, int nb
 #pragma unroll
   for (int j = J0; j < J1; ++j) {
     if (j < N16) {
-      const uint8_t *sp = uniform_ptr(list_base + ((int64_t)j * nb + b) * 1024);
-      const uint4 v = *reinterpret_cast<const uint4 *>(sp + (uint32_t)(lane * 16));
-      r.w[4 * j + 0] = v.x;
-      r.w[4 * j + 1] = v.y;
-      r.w[4 * j + 2] = v.z;
-      r.w[4 * j + 3] = v.w;
+      const GLOBAL uint8_t *sp = uniform_ptr(list_base + ((int64_t)j * nb + b) * 1024);
+      const uintx4 v = *reinterpret_cast<const GLOBAL uintx4 *>(sp + (uint32_t)(lane * 16));
+      r.w[4 * j + 0] = v[0];
+      r.w[4 * j + 1] = v[1];
+      r.w[4 * j + 2] = v[2];
+      r.w[4 * j + 3] = v[3];
     } else {
       const int t = j - N16;
-      const uint8_t *sp = uniform_ptr(list_base + (int64_t)N16 * nb * 1024 + ((int64_t)t * nb + b) * 256);
-      r.w[4 * N16 + t] = *reinterpret_cast<const uint32_t *>(sp + (uint32_t)(lane * 4));
+      const GLOBAL uint8_t *sp = uniform_ptr(list_base + (int64_t)N16 * nb * 1024 + ((int64_t)t * nb + b) * 256);
+      r.w[4 * N16 + t] = *reinterpret_cast<const GLOBAL uint32_t *>(sp + (uint32_t)(lane * 4));
     }
   }
 }

@@ -321,10 +321,10 @@ __global__ __launch_bounds__(LM_NW * 64) __attribute__((amdgpu_waves_per_eu(LM_N
   auto load_row = [&](int it, float4 (&row)[DSUB]) __attribute__((always_inline)) {
     const int m = wave + it * NW;
     const int mc = m < MT ? m : MT - 1;
-    const uint8_t *cb = uniform_ptr(reinterpret_cast<const uint8_t *>(a.codebooks + (int64_t)mc * 256 * DSUB));
+    const GLOBAL uint8_t *cb = uniform_ptr(a.codebooks + (int64_t)mc * 256 * DSUB);
 #pragma unroll
     for (int x = 0; x < DSUB; ++x)
-      row[x] = *reinterpret_cast<const float4 *>(cb + (uint32_t)(lane * 16 * DSUB + 16 * x));
+      row[x] = load_f4(cb, (uint32_t)(lane * 16 * DSUB + 16 * x));
   };
 #pragma unroll
   for (int it = 0; it < RES; ++it) load_row(it, cbr[it]);
@@ -594,7 +594,6 @@ __global__ __launch_bounds__(LM_NW * 64) __attribute__((amdgpu_waves_per_eu(LM_N
       // a key is requested before the count and only needed after it; where distances tie (rare)
       // the ids of the tying keys are fetched on the spot.
       {
-        typedef uint32_t uintx4 __attribute__((ext_vector_type(4)));
         const int g = tid >> 8, i = tid & (LM_COLLECT - 1), h = (tid >> 7) & 1;
         const uint32_t n = ssel[g];
         const bool live = g < ng && n <= (uint32_t)LM_COLLECT && (uint32_t)i < n;
@@ -1082,14 +1081,14 @@ __global__ __launch_bounds__(LMB_NW * 64) __attribute__((amdgpu_waves_per_eu(4))
     // which the wavefronts put where the table was (random reads of it from the L2 took 8 thousand
     // clocks of a task).
     const int cd = tid >> 2, ch = tid & 3;
-    uint4 cw = make_uint4(0u, 0u, 0u, 0u);
+    uintx4 cw = {0u, 0u, 0u, 0u};
     const int64_t drow0 = row0;
     const uint8_t *dbase = base;
     const int dnb = nb;
     auto codes_of = [&](int e) __attribute__((always_inline)) {   // this lane's 16 codes of candidate e
       if (MODE == 0 && e < n && ch < NCH) {
         const uint32_t i = queue[e] >> 3;
-        cw = *reinterpret_cast<const uint4 *>(dbase + ((int64_t)ch * dnb + (i >> 6)) * 1024 + (i & 63u) * 16);
+        cw = *(const GLOBAL uintx4 *)(dbase + ((int64_t)ch * dnb + (i >> 6)) * 1024 + (i & 63u) * 16);
       }
     };
     codes_of(cd);
@@ -1123,7 +1122,7 @@ __global__ __launch_bounds__(LMB_NW * 64) __attribute__((amdgpu_waves_per_eu(4))
         g = word & 7u;
         if constexpr (MODE == 0) {
           i = word >> 3;
-          const uint32_t cws[4] = {cw.x, cw.y, cw.z, cw.w};
+          const uint32_t cws[4] = {cw[0], cw[1], cw[2], cw[3]};
           float v[16];
           const int m0 = (ch < NCH ? ch : NCH - 1) * 16;
 #pragma unroll

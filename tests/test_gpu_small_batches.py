@@ -92,3 +92,41 @@ def test_filtering_without_matrix_product(nlist, D, Q, metric):
             assert np.array_equal(pid.cpu().numpy(), o_pid)
             assert np.array_equal(pd.cpu().numpy().view(np.uint32), o_pd.view(np.uint32))
         gi.close()
+
+
+# List-major main pass with byte tables: groups of eight queries (lists probed by 1, 7, 8, 9 and many
+# queries), lists around a block and around sixteen blocks, ties at the k-th distance, radii that
+# are infinite, zero in one subspace and small against the residuals, queries whose nearest list
+# is shorter than k, more candidates than a task can hold.
+@pytest.mark.parametrize("D,M", [(96, 48), (128, 64), (64, 16)])
+@pytest.mark.parametrize("radius", ["mixed", "inf", "small"])
+def test_byte_tables(D, M, radius):
+    from paper_2312_01712_amd import binding as b
+    rng = np.random.default_rng(M)
+    sizes = np.array([1, 63, 64, 65, 1023, 1024, 1025, 2100, 0, 700, 40, 130, 900, 5000, 300, 1100])
+    nlist, N = len(sizes), int(sizes.sum())
+    offs = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+    idx = wl.Index(N=N, D=D, nlist=nlist, M=M, centroids=(0.2 * rng.normal(size=(nlist, D))).astype(np.float32),
+                   codebooks=(0.3 * rng.normal(size=(M, 256, D // M))).astype(np.float32), list_offsets=offs,
+                   codes=rng.integers(0, 256, size=(N, M), dtype=np.uint8), ids=rng.permutation(N).astype(np.int64))
+    idx.codes[offs[13]:offs[13] + 4000] = idx.codes[offs[13]]      # 4000 equal points
+    r = np.full(M, {"mixed": 0.45, "inf": np.inf, "small": 0.02}[radius], dtype=np.float32)
+    if radius == "mixed":
+        r *= rng.uniform(0.5, 1.5, M).astype(np.float32)
+        r[3] = 0.0
+    for Q, k in ((61, 10), (1, 128), (9, 100)):
+        q = (idx.centroids[rng.integers(0, nlist, Q)] + 0.3 * rng.normal(size=(Q, D))).astype(np.float32)
+        q[0] = idx.centroids[13]
+        rq = (r[None, :] * rng.uniform(0.5, 1.5, (Q, M))).astype(np.float32) if radius == "mixed" else None
+        for mode, radii in ((0, r), (1, r), (2, r)) + (((0, rq),) if rq is not None else ()):
+            gi = b.IvfPqIndex.from_index(idx)
+            kw = dict(mode=mode, strategy=b.SCAN_LIST_MAJOR)
+            if radii is rq:
+                ids, dist = gi.search(torch.from_numpy(q).cuda(), 12, k, None, query_radii=torch.from_numpy(rq).cuda(), **kw)
+            else:
+                ids, dist = gi.search(torch.from_numpy(q).cuda(), 12, k, radii, **kw)
+            torch.cuda.synchronize()
+            o_ids, o_dist = oracle.search(q, idx, 12, k, radii, threads=8, mode=mode)
+            assert np.array_equal(ids.cpu().numpy(), o_ids), (Q, k, mode)
+            assert np.array_equal(dist.cpu().numpy().view(np.uint32), o_dist.view(np.uint32)), (Q, k, mode)
+            gi.close()

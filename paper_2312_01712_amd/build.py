@@ -15,7 +15,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(os.path.dirname(HERE), "include")
 LIB = os.path.join(HERE, "libivfpq_hip.so")
-SOURCES = ["api.hip", "coarse.hip", "scan.hip", "scan_lm.hip", "radius.hip"]
+SOURCES = ["api.hip", "coarse.hip", "scan.hip", "scan_rt.hip", "scan_lm.hip", "radius.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-ffp-contract=off",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",

@@ -214,6 +214,20 @@ __device__ inline float table_value(float d2, float r2, int mode) {
   return mode == 0 ? table_value<0>(d2, r2) : (mode == 1 ? table_value<1>(d2, r2) : table_value<2>(d2, r2));
 }
 
+// A pointer that is the same in every lane, moved to scalar registers so that loads
+// through it use the scalar-base + 32-bit lane-offset addressing form.
+__device__ inline const GLOBAL uint8_t *uniform_ptr(const void *p) {
+  const uint64_t v = reinterpret_cast<uint64_t>(p);
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
+  const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
+  return reinterpret_cast<const GLOBAL uint8_t *>(((uint64_t)hi << 32) | lo);
+}
+// 16 bytes at a lane's offset from such a pointer, as floats
+__device__ inline float4 load_f4(const GLOBAL uint8_t *p, uint32_t off) {
+  const floatx4 v = *reinterpret_cast<const GLOBAL floatx4 *>(p + off);
+  return make_float4(v[0], v[1], v[2], v[3]);
+}
+
 // One table entry (paper Sec. 4.1; Algorithm 2): squared distance between the
 // residual projection and a codebook entry, thresholded at r2.
 template <int DSUB, typename SP>
@@ -268,6 +282,54 @@ __device__ inline float4 lut_entry4(const float (&res)[DSUB > 0 ? DSUB : 1], con
   return make_float4(d2[0], d2[1], d2[2], d2[3]);
 }
 
+// The same for any dimension dsub of the subspaces, for rows m0, m0 + step, ... of the codebook, read
+// from global memory: emit(m, four entries of this lane).  With dsub 1, 2, 4 or 8 a lane's entries are
+// whole 16-byte pieces.  (Requesting the next row before a row is worked on gains nothing: the other
+// wavefronts cover the latency, and the registers spill.)
+template <int MODE, typename SP, typename F>
+__device__ __forceinline__ void lut_rows_rt(SP sres, SP sr2, const float *__restrict__ codebooks, int m0, int M, int step,
+                                            int dsub, int lane, F emit) {
+  auto wide = [&](auto ds) __attribute__((always_inline)) {
+    constexpr int DS = decltype(ds)::value;
+#pragma unroll 1
+    for (int m = m0; m < M; m += step) {
+      const GLOBAL uint8_t *row = uniform_ptr(codebooks + (int64_t)m * 256 * DS);
+      float4 ev[DS];
+      float res[DS];
+#pragma unroll
+      for (int x = 0; x < DS; ++x) ev[x] = load_f4(row, (uint32_t)((lane * DS + x) * 16));
+#pragma unroll
+      for (int j = 0; j < DS; ++j) res[j] = sres[m * DS + j];
+      emit(m, lut_entry4<DS, MODE>(res, ev, sr2[m]));
+    }
+  };
+  if (dsub == 4) return wide(std::integral_constant<int, 4>{});
+  if (dsub == 2) return wide(std::integral_constant<int, 2>{});
+  if (dsub == 1) return wide(std::integral_constant<int, 1>{});
+  if (dsub == 8) return wide(std::integral_constant<int, 8>{});
+#pragma unroll 1
+  for (int m = m0; m < M; m += step) {
+    const GLOBAL uint8_t *row = uniform_ptr(codebooks + (int64_t)m * 256 * dsub);
+    float d2[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll 4
+    for (int j = 0; j < dsub; ++j) {
+      const float res = sres[m * dsub + j];
+#pragma unroll
+      for (int x = 0; x < 4; ++x) {
+        const float t = res - *reinterpret_cast<const GLOBAL float *>(row + (uint32_t)(((4 * lane + x) * dsub + j) * 4));
+        d2[x] = fmaf(t, t, d2[x]);   // (from 0: the first term is t * t rounded once either way)
+      }
+    }
+    const float r2 = sr2[m];
+    emit(m, make_float4(table_value<MODE>(d2[0], r2), table_value<MODE>(d2[1], r2), table_value<MODE>(d2[2], r2),
+                        table_value<MODE>(d2[3], r2)));
+  }
+}
+
+}  // namespace
+
+namespace ivfpq {
+
 struct ScanArgs {
   const float *queries;         // [Q][D]
   const int32_t *probe_ids;     // [Q][probe_stride]; the first nprobe of a row are scanned
@@ -308,25 +370,20 @@ struct ScanArgs {
   uint32_t *gbound;      // [Q] complement of a bound on the query's k-th distance, shared by the workgroups of its probe groups (0: none yet); NULL: not shared
 };
 
+// Launches the query-major kernel of a shape without a specialised one (scan_rt.hip).
+int launch_scan_rt(const ScanArgs &a, const RadiiSq &r2, int64_t grid, bool dump, hipStream_t s);
+
+}  // namespace ivfpq
+
+namespace {
+
+using ivfpq::ScanArgs;
+
 // Codes of one point (the lane's) in registers.
 template <int NDW>
 struct CodeRegs {
   uint32_t w[NDW > 0 ? NDW : 1];
 };
-
-// A pointer that is the same in every lane, moved to scalar registers so that loads
-// through it use the scalar-base + 32-bit lane-offset addressing form.
-__device__ inline const GLOBAL uint8_t *uniform_ptr(const void *p) {
-  const uint64_t v = reinterpret_cast<uint64_t>(p);
-  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
-  const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
-  return reinterpret_cast<const GLOBAL uint8_t *>(((uint64_t)hi << 32) | lo);
-}
-// 16 bytes at a lane's offset from such a pointer, as floats
-__device__ inline float4 load_f4(const GLOBAL uint8_t *p, uint32_t off) {
-  const floatx4 v = *reinterpret_cast<const GLOBAL floatx4 *>(p + off);
-  return make_float4(v[0], v[1], v[2], v[3]);
-}
 
 // Chunks [J0, J1) of block b of a list with nb blocks (J counts the 16-byte chunks
 // first, then the 4-byte chunks).  Within a list the layout is chunk-major: chunk j of
@@ -349,6 +406,34 @@ __device__ inline void load_chunks(const uint8_t *__restrict__ list_base, int nb
       const int t = j - N16;
       const GLOBAL uint8_t *sp = uniform_ptr(list_base + (int64_t)N16 * nb * 1024 + ((int64_t)t * nb + b) * 256);
       r.w[4 * N16 + t] = *reinterpret_cast<const GLOBAL uint32_t *>(sp + (uint32_t)(lane * 4));
+    }
+  }
+}
+
+// The same where only the number of 16-byte pieces a point's Mp bytes reach into (MPT / 16) is known
+// at compile time: whole chunks first, then up to three 4-byte chunks, which stand in the words they
+// would have in a 16-byte one.
+template <int MPT, int J0, int J1>
+__device__ inline void load_chunks_rt(const uint8_t *__restrict__ list_base, int nb, int b, int lane, int Mp,
+                                      CodeRegs<MPT / 4> &r) {
+  const int n16 = Mp >> 4;
+#pragma unroll
+  for (int j = J0; j < J1; ++j) {
+    if (j < MPT / 16 - 1 || j < n16) {
+      const GLOBAL uint8_t *sp = uniform_ptr(list_base + ((int64_t)j * nb + b) * 1024);
+      const uintx4 v = *reinterpret_cast<const GLOBAL uintx4 *>(sp + (uint32_t)(lane * 16));
+#pragma unroll
+      for (int t = 0; t < 4; ++t) r.w[4 * j + t] = v[t];
+    } else {
+#pragma unroll
+      for (int t = 0; t < 3; ++t) {
+        r.w[4 * j + t] = 0u;
+        if (t < ((Mp >> 2) & 3)) {
+          const GLOBAL uint8_t *sp = uniform_ptr(list_base + (int64_t)n16 * nb * 1024 + ((int64_t)t * nb + b) * 256);
+          r.w[4 * j + t] = *reinterpret_cast<const GLOBAL uint32_t *>(sp + (uint32_t)(lane * 4));
+        }
+      }
+      r.w[4 * j + 3] = 0u;
     }
   }
 }
@@ -426,12 +511,17 @@ __device__ __forceinline__ void lookup_group(const LDS float *, const CodeRegs<(
 __device__ __forceinline__ float acc_value(float a) { return a; }
 __device__ __forceinline__ float acc_value(uint32_t a) { return (float)a; }   // exact: sums of at most 2 M
 
+// (Mp: the subspaces in use, a multiple of 4, where MT only says how many 16-byte chunks there are; the
+// up to three rows between M and Mp are zero and add nothing.)
 template <int MT>
 __device__ inline float adc_sum(const LDS float *lut, const CodeRegs<((MT + 3) / 4 * 4) / 4> &r,
-                                float start = 0.0f) {
+                                float start = 0.0f, int Mp = MT) {
   float dist = start;
 #pragma unroll
-  for (int h = 0; h < MT; h += LOOKUP_GROUP) lookup_group<MT>(lut, r, h, cmin(h + LOOKUP_GROUP, MT), dist);
+  for (int h = 0; h < MT; h += LOOKUP_GROUP) {
+    if (h + LOOKUP_GROUP <= Mp || Mp == MT) lookup_group<MT>(lut, r, h, cmin(h + LOOKUP_GROUP, MT), dist);
+    else if (h < Mp) lookup_group<MT>(lut, r, h, h + 4, dist);
+  }
   return dist;
 }
 template <int MT>
@@ -455,9 +545,13 @@ __device__ inline float adc_sum_bytes(const LDS float *lut, const CodeRegs<((MT 
 // (ACC: float for a table of distances, uint32_t for a byte table of penalties.)
 template <int MT, int M0, int M1, typename ACC>
 __device__ inline bool adc_part_exit(const LDS float *lut, const CodeRegs<((MT + 3) / 4 * 4) / 4> &r,
-                                     const LDS float *suf, float tauf, bool checks, bool valid, ACC &dist) {
+                                     const LDS float *suf, float tauf, bool checks, bool valid, ACC &dist, int Mp = MT) {
 #pragma unroll
   for (int g = M0; g < M1; g += 8) {
+    if (Mp != MT && g + 8 > Mp) {   // the last, short group (see adc_sum)
+      if (g < Mp) lookup_group<MT>(lut, r, g, g + 4, dist);
+      return true;
+    }
     // requested ahead of the look-ups, so that it has arrived when they have
     float rest = 0.0f;
     if (checks && cmin(g + 8, M1) < MT) rest = suf[cmin(g + 8, M1) >> 3];

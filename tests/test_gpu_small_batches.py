@@ -130,3 +130,31 @@ def test_byte_tables(D, M, radius):
             assert np.array_equal(ids.cpu().numpy(), o_ids), (Q, k, mode)
             assert np.array_equal(dist.cpu().numpy().view(np.uint32), o_dist.view(np.uint32)), (Q, k, mode)
             gi.close()
+
+
+# Shapes without a specialised kernel: every number of code chunks, tails of 1 to 3 four-byte chunks,
+# padding rows, each way of reading a codebook row (dsub 1, 2, 4, 8 and any other).
+@pytest.mark.parametrize("M,dsub", [(1, 3), (3, 2), (4, 8), (5, 1), (15, 4), (16, 2), (17, 4), (20, 6), (31, 1), (33, 8),
+                                    (47, 2), (64, 1), (65, 3), (80, 4), (81, 2), (97, 1), (112, 2), (113, 5), (128, 4)])
+def test_shapes_without_a_specialised_kernel(M, dsub):
+    from paper_2312_01712_amd import binding as b
+    rng = np.random.default_rng(M * 10 + dsub)
+    D = M * dsub
+    idx = _index(rng, D, M, 30, 300, spread=0.3)
+    q = (idx.centroids[rng.integers(0, 30, 21)] + 0.3 * rng.normal(size=(21, D))).astype(np.float32)
+    radii = np.full(M, 0.5 * np.sqrt(dsub), dtype=np.float32)
+    for Q, nprobe, k, mode in ((21, 12, 10, 0), (21, 3, 100, 0), (1, 1, 128, 0), (21, 12, 300, 0), (21, 12, 20, 1), (5, 12, 20, 2)):
+        _check(idx, q[:Q], nprobe, k, radii, mode=mode)
+    # more queries than probe groups are made for: one workgroup walks all of a query's lists
+    big = np.ascontiguousarray(np.repeat(q, 100, axis=0)[:2050])
+    gi = b.IvfPqIndex.from_index(idx)
+    ids, dist = gi.search(torch.from_numpy(big).cuda(), 6, 10, radii)
+    o_ids, o_dist = oracle.search(q, idx, 6, 10, radii)
+    assert np.array_equal(ids.cpu().numpy(), np.repeat(o_ids, 100, axis=0)[:2050])
+    assert np.array_equal(dist.cpu().numpy().view(np.uint32), np.repeat(o_dist, 100, axis=0)[:2050].view(np.uint32))
+    pid, _ = gi.coarse(torch.from_numpy(q).cuda(), 4)
+    o_offs, o_cd, o_ci = oracle.scan_all(q, idx, pid.cpu().numpy(), radii)
+    cd, ci, err = gi.scan_all(torch.from_numpy(q).cuda(), pid, radii, torch.from_numpy(o_offs).cuda())
+    assert int(err.item()) == 0 and np.array_equal(ci.cpu().numpy(), o_ci)
+    assert np.array_equal(cd.cpu().numpy().view(np.uint32), o_cd.view(np.uint32))
+    gi.close()

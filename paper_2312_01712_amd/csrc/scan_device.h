@@ -82,8 +82,9 @@ __device__ __forceinline__ float dpp_f32(float v) {
 
 // The value of lane ^ J.  With DPP, J = 1, 2, 8 are one register-to-register move (8: a
 // rotation by half a row of 16), J = 4 is two (reverse the group of 8, then reverse the quad:
-// 7 ^ 3 = 4) and only J = 16 and 32 go through the LDS crossbar; a 64-key bitonic sort has 18
-// of its 21 stages at J <= 8.  Measured: 2-3 % faster in the L2 kernels (C2, C3), 10 % slower in
+// 7 ^ 3 = 4), and J = 16 and 32 are a swap of rows or halves between two copies of the value
+// (the LDS crossbar takes a round trip of 100 clocks for each, and a sort is one chain of them).
+// Measured, J <= 8 alone: 2-3 % faster in the L2 kernels (C2, C3), 10 % slower in
 // the 16-wavefront inner-product kernel (C4: 11.3 -> 12.4 ms), which therefore keeps the
 // crossbar shuffles (DPP = false).
 template <int J, bool DPP>
@@ -92,6 +93,13 @@ __device__ __forceinline__ uint32_t xor_u32(uint32_t v) {
   else if constexpr (DPP && J == 2) return dpp_u32<DPP_XOR2>(v);
   else if constexpr (DPP && J == 4) return dpp_u32<DPP_QUAD_MIRROR>(dpp_u32<DPP_HALF_MIRROR>(v));
   else if constexpr (DPP && J == 8) return dpp_u32<DPP_ROR8>(v);
+  else if constexpr (DPP && J == 16) {   // copies with even rows doubled and with odd rows doubled
+    const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+    return (threadIdx.x & 16) ? r[0] : r[1];
+  } else if constexpr (DPP && J == 32) {
+    const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    return (threadIdx.x & 32) ? r[0] : r[1];
+  }
   else return (uint32_t)__shfl_xor((int)v, J);
 }
 
@@ -148,11 +156,11 @@ __device__ inline void wave_merge(Key &L0, Key &L1, const Key &qd, int lane) {
   cx_cascade<32, DPP>(L1, lane, false);
 }
 
-__device__ inline Key bcast_key(const Key &a, int src) {
+__device__ inline Key bcast_key(const Key &a, int src) {   // src: the same in every lane
   Key o;
-  o.d = (uint32_t)__shfl((int)a.d, src);
-  const int lo = __shfl((int)(uint32_t)a.id, src);
-  const int hi = __shfl((int)(uint32_t)((uint64_t)a.id >> 32), src);
+  o.d = (uint32_t)__builtin_amdgcn_readlane((int)a.d, src);
+  const int lo = __builtin_amdgcn_readlane((int)(uint32_t)a.id, src);
+  const int hi = __builtin_amdgcn_readlane((int)(uint32_t)((uint64_t)a.id >> 32), src);
   o.id = (int64_t)(((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo);
   return o;
 }
@@ -624,7 +632,7 @@ __device__ __forceinline__ void wave_flush(WaveTop &st, LDS uint32_t *qd, LDS in
   const Key t0 = bcast_key(st.L0, (k - 1) & 63), t1 = bcast_key(st.L1, (k - 1) & 63);
   st.tau = (k - 1) < 64 ? t0 : t1;
   const int jr = sh.jrank - 1;
-  const uint32_t j0 = (uint32_t)__shfl((int)st.L0.d, jr & 63), j1 = (uint32_t)__shfl((int)st.L1.d, jr & 63);
+  const uint32_t j0 = (uint32_t)__builtin_amdgcn_readlane((int)st.L0.d, jr & 63), j1 = (uint32_t)__builtin_amdgcn_readlane((int)st.L1.d, jr & 63);
   volatile LDS uint32_t *rank = sh.rank;
   if (lane == 0) {
     // (rule (i) needs a list that can hold k keys: not so in the wide selection)
@@ -632,11 +640,11 @@ __device__ __forceinline__ void wave_flush(WaveTop &st, LDS uint32_t *qd, LDS in
     rank[sh.wave] = jr < 64 ? j0 : j1;
   }
   uint32_t mx = lane < sh.nw ? rank[lane] : 0u;
-#pragma unroll
-  for (int off = 8; off > 0; off >>= 1) {
-    const uint32_t o = (uint32_t)__shfl_xor((int)mx, off);
-    mx = o > mx ? o : mx;
-  }
+  auto up = [&](uint32_t o) __attribute__((always_inline)) { mx = o > mx ? o : mx; };
+  up(xor_u32<8, true>(mx));
+  up(xor_u32<4, true>(mx));
+  up(xor_u32<2, true>(mx));
+  up(xor_u32<1, true>(mx));
   if (lane == 0 && mx != SENT_D) __hip_atomic_fetch_min(sh.bound, mx, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
@@ -714,15 +722,100 @@ __device__ inline void init_wave_top(WaveTop &st, const ScanArgs &a, int64_t q) 
   }
 }
 
-// End of a workgroup's work: fold the queues, merge the wavefronts' sorted lists
-// through LDS (the table region is free by then) and write the first k keys, or
-// the whole list when the probes of the query were split over several workgroups.
+// End of a workgroup's work: fold the queues, then the first k keys of the wavefronts' lists, or a
+// list of KP when the probes of the query were split over several workgroups.  The keys within the
+// shared bound on the k-th distance (k and some, of the 128 per wavefront) are collected in the
+// table's LDS and every one of them counts the keys before it: its place in the output.  Merging the
+// lists pairwise is a chain of bitonic merges, 2 log2 NW of them (30 of the 105 thousand clocks a query
+// of the 1M x 200 configuration took, now 9); that is left for bounds that leave more than CAP
+// keys and for the hit counts (long runs of equal scores).
+// `gb` (or NULL): where the k-th distance is published for the query's other workgroups.
 template <int NW, bool SGN = false>
 __device__ __forceinline__ void finish_topk(WaveTop &st, LDS uint32_t *qd, LDS int64_t *qid, int lane,
                                             int wave, const SharedTau &sh, LDS unsigned char *smem3,
-                                            const ScanArgs &a, int64_t q, int split) {
+                                            const ScanArgs &a, int64_t q, int split, uint32_t *gb = nullptr) {
+  constexpr int CAP = NW * 64 < 320 ? NW * 64 : 320, NT = NW * 64;   // within the NW KP 12 bytes of the merge
   if (st.qcount > 0) wave_flush<!SGN>(st, qd, qid, lane, a.k, sh);
-  __syncthreads();  // tables no longer needed: their LDS becomes the staging area
+  LDS int64_t *ci = (LDS int64_t *)smem3;
+  LDS uint32_t *cd = (LDS uint32_t *)(smem3 + CAP * 8);
+  LDS uint32_t *cn = (LDS uint32_t *)(smem3 + CAP * 12);
+  const int tid = wave * 64 + lane;
+  __syncthreads();  // tables no longer needed; the bound stands
+  if (tid == 0) *cn = a.mode == 0 ? 0u : (uint32_t)CAP;
+  __syncthreads();
+  if (a.mode == 0) {
+    const uint32_t bnd = *(volatile LDS uint32_t *)sh.bound;
+    // (the lists are sorted: what is within the bound is a run of the first lanes)
+    const uint32_t n0 = (uint32_t)__popcll(__ballot(st.L0.d != SENT_D && st.L0.d <= bnd));
+    const uint32_t n1 = (uint32_t)__popcll(__ballot(st.L1.d != SENT_D && st.L1.d <= bnd));
+    uint32_t pos = 0;
+    if (lane == 0 && n0 > 0) pos = __hip_atomic_fetch_add(cn, n0 + n1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    pos = (uint32_t)__builtin_amdgcn_readfirstlane((int)pos) + (uint32_t)lane;
+    if ((uint32_t)lane < n0 && pos < (uint32_t)CAP) {
+      cd[pos] = st.L0.d;
+      ci[pos] = st.L0.id;
+    }
+    if ((uint32_t)lane < n1 && pos + n0 < (uint32_t)CAP) {
+      cd[pos + n0] = st.L1.d;
+      ci[pos + n0] = st.L1.id;
+    }
+  }
+  __syncthreads();
+  const int n = (int)*cn;
+  if (n <= CAP - 4) {   // uniform
+    if (tid < 4) cd[n + tid] = SENT_D;   // read with the last keys, precede nothing
+    __syncthreads();
+    const bool part = a.nsplit > 1;
+    const int64_t o = part ? (q * a.nsplit + split) * KP : q * a.k_out + a.k_off;
+    const int want = part ? KP : a.k;
+    // four lanes per key count a quarter of the keys each
+    for (int i0 = 0; i0 < n; i0 += NT / 4) {
+      const int i = i0 + (tid >> 2);
+      if (i0 + wave * 16 >= n) break;   // nor has a later round anything for this wavefront
+      const int ic = i < n ? i : n - 1;
+      const uint32_t d = cd[ic];
+      const int64_t id = ci[ic];
+      uint32_t before = 0, same = 0;
+#pragma unroll 4
+      for (int j = (lane & 3) * 4; j < n; j += 16) {
+        const uintx4 v = *(const LDS uintx4 *)(cd + j);
+#pragma unroll
+        for (int x = 0; x < 4; ++x) {
+          before += v[x] < d ? 1u : 0u;
+          same += v[x] == d ? 1u : 0u;
+        }
+      }
+      same += xor_u32<1, true>(same);
+      same += xor_u32<2, true>(same);
+      if (__ballot(same > 1u) != 0ull)   // equal distances: by id, equal ids by position
+        for (int j = (lane & 3); j < n; j += 4)
+          if (cd[j] == d && (ci[j] < id || (ci[j] == id && j < ic))) ++before;
+      before += xor_u32<1, true>(before);
+      before += xor_u32<2, true>(before);
+      if (i < n && (lane & 3) == 0 && (int)before < want) {
+        if (part) {
+          a.part_d[o + before] = d;
+          a.part_id[o + before] = id;
+        } else {
+          a.out_ids[o + before] = id;
+          a.out_dist[o + before] = key_dist<SGN>(d);
+        }
+        if (gb && before == (uint32_t)(a.k - 1)) __hip_atomic_fetch_max(gb, ~d, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+    }
+    for (int i = n + tid; i < want; i += NT) {
+      if (part) {
+        a.part_d[o + i] = SENT_D;
+        a.part_id[o + i] = SENT_ID;
+      } else {
+        a.out_ids[o + i] = -1;
+        a.out_dist[o + i] = __builtin_inff();
+      }
+    }
+    return;
+  }
+  // ---- more keys within the bound than the table's LDS takes: pairwise merges ----
+  __syncthreads();  // the collected keys are dropped: their LDS becomes the staging area
   LDS uint32_t *stage_d = (LDS uint32_t *)smem3;
   LDS int64_t *stage_id = (LDS int64_t *)(smem3 + NW * KP * 4);
   auto put = [&]() __attribute__((always_inline)) {

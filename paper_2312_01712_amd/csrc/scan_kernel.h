@@ -128,6 +128,38 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(scan_wp
     dump_pos = a.cand_offsets[q];
   }
 
+  // What a chunk of probes needs of its lists, a thread per probe: two trips to memory, one behind the
+  // other.  The first chunk's first trip goes out before anything else, its second behind the
+  // codebook's.
+  struct ProbeMeta {
+    int32_t c;
+    int64_t r0, r1, blk;
+    float lb;
+  };
+  auto fetch_probe = [&](int p0) __attribute__((always_inline)) { return tid < META && p0 + tid < p_end ? probes[p0 + tid] : -1; };
+  auto fetch_meta = [&](int p0, int32_t cc) __attribute__((always_inline)) {
+    ProbeMeta f = {0, 0, 0, 0, 0.0f};
+    {
+      if ((uint32_t)cc < (uint32_t)a.nlist) {   // a probe id outside [0, nlist) becomes an empty list
+        f.c = cc;
+        f.r0 = a.list_offsets[cc];
+        f.r1 = a.list_offsets[cc + 1];
+        f.blk = a.list_blocks[cc];
+        if (a.probe_lb) f.lb = a.probe_lb[q * a.probe_stride + p0 + tid];
+      }
+    }
+    return f;
+  };
+  auto put_meta = [&](const ProbeMeta &f, int p0) __attribute__((always_inline)) {
+    if (tid < META && p0 + tid < p_end) {
+      meta_c[tid] = f.c;
+      meta_row0[tid] = f.r0;
+      meta_len[tid] = (int)(f.r1 - f.r0);
+      meta_blk[tid] = f.blk;
+      meta_lb[tid] = f.lb;
+    }
+  };
+  const int32_t first_probe = fetch_probe(p_begin);
   for (int i = tid; i < D; i += NT) sq[i] = a.queries[q * D + i];
   for (int m = tid; m < MT; m += NT) {
     float v = r2.v[m];
@@ -191,6 +223,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(scan_wp
         cbr[it][x] = load_f4(cb, (uint32_t)(lane * 16 * DSUB + 16 * x));
     }
   }
+  const ProbeMeta first_meta = fetch_meta(p_begin, first_probe);
   // Code chunks per point (16-byte chunks, then 4-byte chunks) and how many of them
   // the "first half" loading mode fetches ahead; that mode exists when it splits the
   // chunks in two non-empty parts.
@@ -242,22 +275,17 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(scan_wp
       }
     }
   };
+  put_meta(first_meta, p_begin);
+  __syncthreads();
   for (int p = p_begin; p < p_end; ++p) {
     const int pm = (p - p_begin) & (META - 1);
     if (pm == 0) {
-      // every wavefront has passed the second barrier of the previous probe, so nobody
-      // still reads the old entries
-      if (tid < META && p + tid < p_end) {
-        const int32_t cc = probes[p + tid];
-        const bool ok = (uint32_t)cc < (uint32_t)a.nlist;
-        const int64_t r0 = ok ? a.list_offsets[cc] : 0;
-        meta_c[tid] = ok ? cc : 0;  // a probe id outside [0, nlist) becomes an empty list
-        meta_row0[tid] = r0;
-        meta_len[tid] = ok ? (int)(a.list_offsets[cc + 1] - r0) : 0;
-        meta_blk[tid] = ok ? a.list_blocks[cc] : 0;
-        meta_lb[tid] = (ok && a.probe_lb) ? a.probe_lb[q * a.probe_stride + p + tid] : 0.0f;
+      // (every wavefront has passed the second barrier of the previous probe, so nobody still
+      // reads the old entries; the first chunk is there already)
+      if (p > p_begin) {
+        put_meta(fetch_meta(p, fetch_probe(p)), p);
+        __syncthreads();
       }
-      __syncthreads();
     }
     const int32_t c = __builtin_amdgcn_readfirstlane(meta_c[pm]);
     const int64_t row0 = meta_row0[pm];
@@ -322,14 +350,26 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(scan_wp
       // Ruled out.  The bound cannot change while nobody scans, so the following probes of
       // this metadata chunk are checked right here and the workgroup goes on with the first
       // one that is not ruled out: a run of skipped lists costs one barrier.
+      // A lane per probe of the chunk finds its end at once (probe by probe, each with its own trip
+      // to the LDS, 60 ruled-out lists took 20 of the 100 thousand clocks of a query of the
+      // 1M x 200 configuration).
       const float bound_f = __uint_as_float(*(volatile LDS uint32_t *)sh.bound);
-      int pn = p;
-      do {
-        const int pmn = (pn - p_begin) & (META - 1);
-        const int nbn = (meta_len[pmn] + 63) >> 6;
-        if (wave < nbn) tot_blocks += (nbn - 1 - wave) / NW + 1;  // all pruned: counts for the switch
-        ++pn;
-      } while (pn < p_end && ((pn - p_begin) & (META - 1)) != 0 && meta_lb[(pn - p_begin) & (META - 1)] > bound_f);
+      const int left = p_end - (p - pm) < META ? p_end - (p - pm) : META;   // probes of this chunk
+      const bool mine = lane >= pm && lane < left;
+      const unsigned long long dead = __ballot(mine && meta_lb[mine ? lane : pm] > bound_f) >> pm;
+      const int run = ~dead == 0ull ? 64 : __ffsll((long long)~dead) - 1;   // >= 1: this probe is ruled out
+      const int pn = p + run;
+      if (!pushed) {   // all pruned: counts for the switch
+        const int nbn = mine && lane < pm + run ? (meta_len[lane] + 63) >> 6 : 0;
+        uint32_t c = wave < nbn ? (uint32_t)((nbn - 1 - wave) / NW + 1) : 0u;
+        c += xor_u32<1, true>(c);
+        c += xor_u32<2, true>(c);
+        c += xor_u32<4, true>(c);
+        c += xor_u32<8, true>(c);
+        c += xor_u32<16, true>(c);
+        c += xor_u32<32, true>(c);
+        tot_blocks += (uint32_t)__builtin_amdgcn_readfirstlane((int)c);
+      }
       push_counts(pn - 1);
       __syncthreads();  // nobody still reads the metadata when the next chunk is staged
       sres_ready = false;
@@ -502,14 +542,8 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(scan_wp
     }
   }
   if (DUMP) return;
-  if (SPLIT && gb) {   // the keys still queued tighten the bound once more: the groups yet to come profit
-    if (st.qcount > 0) wave_flush<true>(st, qd, qid, lane, a.k, sh);
-    __syncthreads();
-    if (tid == 0) __hip_atomic_fetch_max(gb, ~*(volatile LDS uint32_t *)sh.bound, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  }
-
   if (wide) finish_wide(st, qd, qid, lane, tid, sh, a, q);
-  else finish_topk<NW>(st, qd, qid, lane, wave, sh, smem3, a, q, split);
+  else finish_topk<NW>(st, qd, qid, lane, wave, sh, smem3, a, q, split, gb);
 }
 
 template <int MT, int DSUB, int NW, bool BYTE = false>

@@ -48,12 +48,27 @@ __device__ inline void ip_thresholds(SP qm, int dsub, float r2, float &thr, floa
   thr_in = 0.5f * (qq - 0.25f * r2);
 }
 
-// 0 - q.c with acc = fmaf(q_i, c_i, acc), i ascending (the list term of a score)
+// 0 - q.c with acc = fmaf(q_i, c_i, acc), i ascending (the list term of a score).  The chain is
+// sequential; its loads are not: eight 16-byte ones are in flight at a time (one per step left a trip to
+// memory between every four products, 35 thousand clocks of a 200-dimensional query).
 template <typename SP>
 __device__ inline float neg_ip_chain(SP sq, const float *__restrict__ cen, int D) {
   float acc = 0.0f;
   int i = 0;
   if ((D & 3) == 0 && (reinterpret_cast<uintptr_t>(cen) & 15) == 0) {
+    constexpr int BATCH = 8;
+    for (; i + 4 * BATCH <= D; i += 4 * BATCH) {
+      float4 c[BATCH];
+#pragma unroll
+      for (int b = 0; b < BATCH; ++b) c[b] = *reinterpret_cast<const float4 *>(cen + i + 4 * b);
+#pragma unroll
+      for (int b = 0; b < BATCH; ++b) {
+        acc = fmaf(sq[i + 4 * b], c[b].x, acc);
+        acc = fmaf(sq[i + 4 * b + 1], c[b].y, acc);
+        acc = fmaf(sq[i + 4 * b + 2], c[b].z, acc);
+        acc = fmaf(sq[i + 4 * b + 3], c[b].w, acc);
+      }
+    }
     for (; i < D; i += 4) {
       const float4 c4 = *reinterpret_cast<const float4 *>(cen + i);
       acc = fmaf(sq[i], c4.x, acc);
@@ -206,14 +221,21 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4))) vo
       }
     }
     __syncthreads();
-    if (tid == 0) {
-      float acc = 0.0f, mag = 0.0f;
-      for (int m = M - 1; m >= 0; --m) {
-        acc += srmin[m];
-        mag += srabs[m];
-        if ((m & 7) == 0) ssuf[m >> 3] = acc;
+    if (wave == 0) {   // rows l and 64 + l in lane l: groups of 8 summed in place, then accumulated from the last one down
+      float v0 = lane < M ? srmin[lane] : 0.0f, v1 = lane + 64 < M ? srmin[lane + 64 < M ? lane + 64 : 0] : 0.0f;
+      float mag = (lane < M ? srabs[lane] : 0.0f) + (lane + 64 < M ? srabs[lane + 64 < M ? lane + 64 : 0] : 0.0f);
+      v0 = group8_sum(v0);
+      v1 = group8_sum(v1);
+#pragma unroll
+      for (int off = 32; off > 0; off >>= 1) mag += __shfl_xor(mag, off);
+      constexpr int NG = (MT + 7) / 8;
+      float acc = 0.0f;
+#pragma unroll
+      for (int j = NG - 1; j >= 0; --j) {
+        acc += __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(j < 8 ? v0 : v1), (j & 7) * 8));
+        if (lane == 0) ssuf[j] = acc;
       }
-      ssuf[(M + 7) / 8] = mag;
+      if (lane == 0) ssuf[NG] = mag;
     }
   }
   // ---- the probed lists, META at a time ----
@@ -271,16 +293,22 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4))) vo
       __syncthreads();
     }
     for (int pm = 0; pm < pn; ++pm) {
+      if constexpr (MT > 0 && !DUMP) {
+        // The next list that the list-level bound does not rule out, found for all of the chunk's probes
+        // at once (a lane each; the bound only tightens, so a list ruled out stays so).  Nothing of
+        // the lists passed over is requested.
+        const uint32_t shared0 = *(volatile LDS uint32_t *)sh.bound;
+        const uint32_t pref0 = shared0 < st.tau.d ? shared0 : st.tau.d;
+        const bool mine = lane >= pm && lane < pn;
+        const unsigned long long alive = __ballot(mine && dist_key<true>(meta_lb[mine ? lane : pm]) <= pref0);
+        if (alive == 0ull) break;
+        pm = __ffsll((long long)alive) - 1;
+      }
       const int64_t row0 = meta_row0[pm];
       const int len = __builtin_amdgcn_readfirstlane(meta_len[pm]);
       const int nb = (len + 63) >> 6;
       const uint8_t *base = a.codes + meta_blk[pm] * ivfpq_block_bytes(Mp);
       const float start = meta_start[pm];
-      if constexpr (MT > 0 && !DUMP) {  // ruled out by the list-level bound: nothing of the list is requested
-        const uint32_t shared0 = *(volatile LDS uint32_t *)sh.bound;
-        const uint32_t pref0 = shared0 < st.tau.d ? shared0 : st.tau.d;
-        if (dist_key<true>(meta_lb[pm]) > pref0) continue;
-      }
       if constexpr (MT > 0) {
         if (wave < nb) {
           const int last = nb - 1;

@@ -127,6 +127,14 @@ static int check_common(const ivfpq_index *ix, const void *q, int64_t Q, int32_t
   return IVFPQ_OK;
 }
 
+// nearest bf16, ties to even; infinities and NaN keep their upper half (a NaN its payload's top bit)
+static uint16_t bf16_bits(float x) {
+  uint32_t u;
+  memcpy(&u, &x, 4);
+  if ((u & 0x7F800000u) == 0x7F800000u) return (uint16_t)((u >> 16) | ((u & 0x7FFFFFu) ? 0x40u : 0u));
+  return (uint16_t)((u + 0x7FFFu + ((u >> 16) & 1u)) >> 16);
+}
+
 static int check_k(int32_t k, const char *fn) {
   if (k < 1) { set_error("%s: k = %d must be positive", fn, k); return IVFPQ_ERR_INVALID_ARGUMENT; }
   if (k > IVFPQ_MAX_K) { set_error("%s: k = %d above the limit %d", fn, k, IVFPQ_MAX_K); return IVFPQ_ERR_UNSUPPORTED; }
@@ -234,6 +242,7 @@ void ivfpq_index_destroy(ivfpq_index *ix) {
   if (!ix) return;
   (void)hipFree(ix->d_centroids);
   (void)hipFree(ix->d_cnorm);
+  (void)hipFree(ix->d_csplit);
   (void)hipFree(ix->d_box);
   (void)hipFree(ix->d_grid);
   (void)hipFree(ix->d_grid_par);
@@ -347,6 +356,25 @@ int ivfpq_index_create(const ivfpq_index_desc *d, ivfpq_index **out) {
     }
     ix->max_cnorm = mx;
     TRY_OR_FAIL(hipMemcpy(ix->d_cnorm, cnorm.data(), (size_t)d->nlist * 4, hipMemcpyHostToDevice));
+    // many lists (for some nprobe): the product that proposes lists takes the centroids as two bf16
+    // parts each (coarse_gemm_top_kernel)
+    ix->ksplit = (d->D + 31) & ~31;
+    if (coarse_fused_keys(d->nlist, 1, d->D) > 0) {
+      const size_t part = (size_t)d->nlist * ix->ksplit;
+      std::vector<uint16_t> split(2 * part, 0);
+      for (int c = 0; c < d->nlist; ++c)
+        for (int i = 0; i < d->D; ++i) {
+          const float x = cent_h[(size_t)c * d->D + i];
+          const uint16_t hi = bf16_bits(x);
+          const uint32_t hb = (uint32_t)hi << 16;
+          float hf;
+          memcpy(&hf, &hb, 4);
+          split[(size_t)c * ix->ksplit + i] = hi;
+          split[part + (size_t)c * ix->ksplit + i] = bf16_bits(x - hf);
+        }
+      TRY_OR_FAIL(hipMalloc(&ix->d_csplit, split.size() * 2));
+      TRY_OR_FAIL(hipMemcpy(ix->d_csplit, split.data(), split.size() * 2, hipMemcpyHostToDevice));
+    }
     // per list and subspace, the bounding box of the entries the list's points use (filled
     // below from the codes; an empty list keeps the all-zero box)
     TRY_OR_FAIL(hipMalloc(&ix->d_box, (size_t)d->nlist * d->D * 2 * 4));

@@ -134,8 +134,7 @@ __global__ __launch_bounds__(256) void coarse_gemm_kernel(const float *__restric
 // -- the proposal value mapped to an int32 that orders like the float, its low 6 bits replaced
 // by the position (block, v) of the list -- and writes those.  What a lane leaves out is no
 // smaller than its last key: the selection kernel works on the keys and uses that bound for
-// the lists it never sees.  K slices are double-buffered in LDS, the next slice's global
-// loads in flight while the current one is multiplied.
+// the lists it never sees.
 
 constexpr int32_t KEY_PAD = 0x7F000000;   // key of a list that does not exist: above every real key
 constexpr float PAD_VALUE = 1.7e38f;      // its proposal value
@@ -153,18 +152,27 @@ __device__ __forceinline__ int32_t med3i(int32_t a, int32_t b, int32_t c) {
   return lo > m ? lo : m;
 }
 
+// The product runs in bf16: q = qh + ql and c = ch + cl, each part the nearest bf16 to what is left,
+// and qh.ch + qh.cl + ql.ch is accumulated in fp32.  What is dropped is at most 3 x 2^-18 of
+// sum |q_i c_i| (the parts' rests and ql.cl), which the selection's bound counts (SPLIT_ERR): a
+// proposal only has to be certain to contain the nearest lists, their distances are then formed in
+// fp32 from the fp32 vectors in the reference order, so the results stay bit for bit.  Three
+// products at 16 times the fp32 rate.  10 000 x 16 384 x 128: 421 us with fp32 products (68 % of
+// their peak), 190 us so; the selection of 6 keys per lane (about 10 vector instructions per value)
+// is now as long as the product.  Centroids are split when the index is made, queries when a tile
+// is loaded.
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef uint32_t uint32x4 __attribute__((ext_vector_type(4)));
+constexpr float SPLIT_ERR = 1.2e-5f;   // above 3 x 2^-18, in units of |q|^2 + max |c|^2 >= 2 sum |q_i c_i|
+constexpr int SK = 32;             // depth per LDS stage
+constexpr int SLD = SK + 8;        // row stride in bf16: 80 bytes, so that 8 lanes' 16-byte reads of consecutive rows touch 32 banks
+
 template <bool VEC>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void coarse_gemm_top_kernel(
-    const float *__restrict__ Qm, const float *__restrict__ Cm, const float *__restrict__ cnorm,
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void coarse_gemm_top_kernel(
+    const float *__restrict__ Qm, const uint16_t *__restrict__ Cs, int64_t part, int ldc, const float *__restrict__ cnorm,
     int32_t *__restrict__ keys, int Qn, int nlist, int D, int ldk, int ip, int32_t *__restrict__ fb_count) {
-  // Tiles stay [row][k] in LDS, as they come from memory (one 16-byte store per 16-byte load),
-  // rows LDK floats apart: 16-byte aligned, and eight lanes reading 16 bytes of eight consecutive
-  // rows touch 32 different banks.  The MFMA step (2 along k) lets each half of the wavefront
-  // bring its own k: half h takes k = 8 h .. 8 h + 7 of the slice, two 16-byte reads per row.
-  // (The order of the sum over k differs from a plain loop's; the product only proposes.)
-  constexpr int LDK = BK + 4;
-  __shared__ __align__(16) float sA[2][BN][LDK];  // [stage][list of the tile][k]
-  __shared__ __align__(16) float sB[2][BM][LDK];  // [stage][query of the tile][k]
+  __shared__ __align__(16) uint16_t sA[2][BN][SLD];  // [high, rest][list of the tile][k]
+  __shared__ __align__(16) uint16_t sB[2][BM][SLD];  // [high, rest][query of the tile][k]
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int l31 = lane & 31, half = lane >> 5;
   const int c0 = blockIdx.x * BN, q0 = blockIdx.y * BM;
@@ -174,67 +182,72 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void c
 #pragma unroll
     for (int v = 0; v < 16; ++v) acc[i][v] = 0.0f;
   if (blockIdx.x == 0 && blockIdx.y == 0 && tid == 0) *fb_count = 0;  // flagged queries of this chunk: none yet
-  float va[2][4], vb[2][4];
+  // thread = (row of both tiles, half of the slice's 32 k); rows past the matrices read row 0 and stand
+  // as zeros
+  const int row = tid >> 1, kh = (tid & 1) * 16;
+  const uint16_t *crow = Cs + (int64_t)(c0 + row < nlist ? c0 + row : 0) * ldc + kh;
+  uint32x4 va[4];
+  float vb[4][4];
   auto fetch = [&](int k0) __attribute__((always_inline)) {
 #pragma unroll
-    for (int r = 0; r < 2; ++r) {
-      const int f = tid + 256 * r;
-      const int row = f >> 2, kq = (f & 3) * 4;
-      load4_issue<VEC>(Cm, c0 + row, nlist, k0 + kq, D, va[r]);
-      load4_issue<VEC>(Qm, q0 + row, Qn, k0 + kq, D, vb[r]);
+    for (int x = 0; x < 2; ++x) {
+      va[x] = *reinterpret_cast<const uint32x4 *>(crow + k0 + 8 * x);
+      va[2 + x] = *reinterpret_cast<const uint32x4 *>(crow + part + k0 + 8 * x);
     }
-  };
-  auto stash = [&](int st, int k0) __attribute__((always_inline)) {
 #pragma unroll
-    for (int r = 0; r < 2; ++r) {
-      const int f = tid + 256 * r;
-      const int row = f >> 2, kq = (f & 3) * 4;
-      load4_mask<VEC>(c0 + row, nlist, k0 + kq, D, va[r]);
-      load4_mask<VEC>(q0 + row, Qn, k0 + kq, D, vb[r]);
-      *reinterpret_cast<float4 *>(&sA[st][row][kq]) = make_float4(va[r][0], va[r][1], va[r][2], va[r][3]);
-      *reinterpret_cast<float4 *>(&sB[st][row][kq]) = make_float4(vb[r][0], vb[r][1], vb[r][2], vb[r][3]);
+    for (int x = 0; x < 4; ++x) load4_issue<VEC>(Qm, q0 + row, Qn, k0 + kh + 4 * x, D, vb[x]);
+  };
+  auto stash = [&](int k0) __attribute__((always_inline)) {
+#pragma unroll
+    for (int x = 0; x < 2; ++x) {
+      if (c0 + row >= nlist) va[x] = va[2 + x] = uint32x4{0u, 0u, 0u, 0u};
+      *reinterpret_cast<uint32x4 *>(&sA[0][row][kh + 8 * x]) = va[x];
+      *reinterpret_cast<uint32x4 *>(&sA[1][row][kh + 8 * x]) = va[2 + x];
+      bf16x8 hi, lo;
+#pragma unroll
+      for (int y = 0; y < 2; ++y) {
+        load4_mask<VEC>(q0 + row, Qn, k0 + kh + 4 * (2 * x + y), D, vb[2 * x + y]);
+#pragma unroll
+        for (int z = 0; z < 4; ++z) {
+          const float v = vb[2 * x + y][z];
+          hi[4 * y + z] = (__bf16)v;
+          lo[4 * y + z] = (__bf16)(v - (float)hi[4 * y + z]);
+        }
+      }
+      *reinterpret_cast<bf16x8 *>(&sB[0][row][kh + 8 * x]) = hi;
+      *reinterpret_cast<bf16x8 *>(&sB[1][row][kh + 8 * x]) = lo;
     }
   };
   fetch(0);
-  stash(0, 0);
-  __syncthreads();
-  int st = 0;
-  for (int k0 = 0; k0 < D; k0 += BK) {
-    const bool more = k0 + BK < D;
-    if (more) fetch(k0 + BK);
-    const int kh = 8 * half;
-    const float4 b0 = *reinterpret_cast<const float4 *>(&sB[st][wave * 32 + l31][kh]);
-    const float4 b1 = *reinterpret_cast<const float4 *>(&sB[st][wave * 32 + l31][kh + 4]);
-    // two accumulators at a time, alternating, so that a product never waits for the one before it
+  for (int k0 = 0; k0 < D; k0 += SK) {
+    if (k0 > 0) __syncthreads();   // the slice before has been multiplied
+    stash(k0);
+    __syncthreads();
+    if (k0 + SK < D) fetch(k0 + SK);   // in flight during the products
 #pragma unroll
-    for (int i = 0; i < 4; i += 2) {
-      const float4 a0 = *reinterpret_cast<const float4 *>(&sA[st][i * 32 + l31][kh]);
-      const float4 a1 = *reinterpret_cast<const float4 *>(&sA[st][i * 32 + l31][kh + 4]);
-      const float4 c0v = *reinterpret_cast<const float4 *>(&sA[st][i * 32 + 32 + l31][kh]);
-      const float4 c1v = *reinterpret_cast<const float4 *>(&sA[st][i * 32 + 32 + l31][kh + 4]);
-      acc[i] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0.x, b0.x, acc[i], 0, 0, 0);
-      acc[i + 1] = __builtin_amdgcn_mfma_f32_32x32x2f32(c0v.x, b0.x, acc[i + 1], 0, 0, 0);
-      acc[i] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0.y, b0.y, acc[i], 0, 0, 0);
-      acc[i + 1] = __builtin_amdgcn_mfma_f32_32x32x2f32(c0v.y, b0.y, acc[i + 1], 0, 0, 0);
-      acc[i] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0.z, b0.z, acc[i], 0, 0, 0);
-      acc[i + 1] = __builtin_amdgcn_mfma_f32_32x32x2f32(c0v.z, b0.z, acc[i + 1], 0, 0, 0);
-      acc[i] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0.w, b0.w, acc[i], 0, 0, 0);
-      acc[i + 1] = __builtin_amdgcn_mfma_f32_32x32x2f32(c0v.w, b0.w, acc[i + 1], 0, 0, 0);
-      acc[i] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1.x, b1.x, acc[i], 0, 0, 0);
-      acc[i + 1] = __builtin_amdgcn_mfma_f32_32x32x2f32(c1v.x, b1.x, acc[i + 1], 0, 0, 0);
-      acc[i] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1.y, b1.y, acc[i], 0, 0, 0);
-      acc[i + 1] = __builtin_amdgcn_mfma_f32_32x32x2f32(c1v.y, b1.y, acc[i + 1], 0, 0, 0);
-      acc[i] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1.z, b1.z, acc[i], 0, 0, 0);
-      acc[i + 1] = __builtin_amdgcn_mfma_f32_32x32x2f32(c1v.z, b1.z, acc[i + 1], 0, 0, 0);
-      acc[i] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1.w, b1.w, acc[i], 0, 0, 0);
-      acc[i + 1] = __builtin_amdgcn_mfma_f32_32x32x2f32(c1v.w, b1.w, acc[i + 1], 0, 0, 0);
+    for (int kk = 0; kk < SK; kk += 16) {   // half h of the wavefront brings k = 8 h .. 8 h + 7 of a step's 16
+      const bf16x8 bh = *reinterpret_cast<const bf16x8 *>(&sB[0][wave * 32 + l31][kk + 8 * half]);
+      const bf16x8 bl = *reinterpret_cast<const bf16x8 *>(&sB[1][wave * 32 + l31][kk + 8 * half]);
+#pragma unroll
+      for (int i = 0; i < 4; i += 2) {   // two accumulators in turn
+        bf16x8 ah[2], al[2];
+#pragma unroll
+        for (int x = 0; x < 2; ++x) {
+          ah[x] = *reinterpret_cast<const bf16x8 *>(&sA[0][(i + x) * 32 + l31][kk + 8 * half]);
+          al[x] = *reinterpret_cast<const bf16x8 *>(&sA[1][(i + x) * 32 + l31][kk + 8 * half]);
+        }
+#pragma unroll
+        for (int x = 0; x < 2; ++x) acc[i + x] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah[x], bh, acc[i + x], 0, 0, 0);
+#pragma unroll
+        for (int x = 0; x < 2; ++x) acc[i + x] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah[x], bl, acc[i + x], 0, 0, 0);
+#pragma unroll
+        for (int x = 0; x < 2; ++x) acc[i + x] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al[x], bh, acc[i + x], 0, 0, 0);
+      }
     }
-    if (more) stash(st ^ 1, k0 + BK);
-    __syncthreads();  // the other stage is complete, and nobody still reads this one
-    st ^= 1;
   }
+  __syncthreads();
   // the tiles are done with: their LDS now holds the lists' squared norms
-  float *scn = &sA[0][0][0];
+  float *scn = reinterpret_cast<float *>(&sA[0][0][0]);
   if (tid < BN) {
     const int c = c0 + tid;
     scn[tid] = c < nlist ? (ip ? 0.0f : cnorm[c]) : PAD_VALUE;
@@ -858,7 +871,9 @@ __global__ __launch_bounds__(CS_WAVES * 64) void coarse_select_wave_kernel(
   // upper edge), whichever is later.
   // (a key is within 64 units in the last place of its proposal value, which is at most
   // 2 (|q|^2 + max |c|^2) in magnitude: 2^-15 of that sum covers it)
-  const float bound = (err_scale + (FUSED ? 3.0517578125e-05f : 0.0f)) * (qq + max_cnorm);
+  // (FUSED also counts what the split product drops, SPLIT_ERR, and what falls below its smallest
+  // numbers: at most 2^-126 per term)
+  const float bound = (err_scale + (FUSED ? 3.0517578125e-05f + SPLIT_ERR : 0.0f)) * (qq + max_cnorm) + (FUSED ? 2.0e-34f : 0.0f);
   uint32_t top = bin_of_rank((uint32_t)(EXACT ? nprobe : kprop));
   if (!EXACT) {
     const float reach = (float)(bin_of_rank((uint32_t)nprobe) + 2u) + 2.0f * bound * scale;
@@ -1037,7 +1052,7 @@ int launch_coarse(const ivfpq_index *ix, const float *d_queries, int64_t Q, int3
       float *slot_rows = group_rows + (size_t)((q_chunk + group - 1) / group) * nlist_pad;
       int32_t *fb = reinterpret_cast<int32_t *>(slot_rows + (size_t)FB_SLOTS * nlist_pad);
       hipLaunchKernelGGL(vec ? coarse_gemm_top_kernel<true> : coarse_gemm_top_kernel<false>, grid, dim3(256), 0, s, qm,
-                         ix->d_centroids, ix->d_cnorm, keys, qn, nlist, D, nkeys, ip, fb);
+                         ix->d_csplit, (int64_t)nlist * ix->ksplit, ix->ksplit, ix->d_cnorm, keys, qn, nlist, D, nkeys, ip, fb);
       hipLaunchKernelGGL(coarse_select_wave_kernel<CS_FUSED>, dim3((qn + CS_WAVES - 1) / CS_WAVES), dim3(CS_WAVES * 64),
                          wave_lds, s, d_scratch, qm, ix->d_centroids, qn, nlist, nkeys, D, nkeys, nprobe, kprop,
                          err_scale, ix->max_cnorm, ip, ids, dist, d_flags + q0, fb);

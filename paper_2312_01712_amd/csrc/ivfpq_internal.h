@@ -16,6 +16,8 @@ struct ivfpq_index {
   int device;
   float *d_centroids;       // [nlist][D]
   float *d_cnorm;           // [nlist] squared norms (only used to propose probe lists)
+  uint16_t *d_csplit;       // [2][nlist][ksplit] centroids as pairs of bf16 (high part, rest), zero-padded, where the filtering stage proposes from keys; else NULL
+  int32_t ksplit;           // D rounded up to 32
   float *d_box;             // [nlist][M][2][dsub] per list and subspace: bounding box (low corner, high corner) of the entries its points use
   float *d_grid;            // dsub == 2, L2 metric: [M][GRID_G * GRID_G] lower bound on the squared distance from any point of a grid cell to the subspace's nearest entry; else NULL
   float *d_grid_par;        // [M][8]: low corner (x, y), high corner (x, y), cells per unit (x, y), 0, 0

@@ -158,3 +158,29 @@ def test_shapes_without_a_specialised_kernel(M, dsub):
     assert int(err.item()) == 0 and np.array_equal(ci.cpu().numpy(), o_ci)
     assert np.array_equal(cd.cpu().numpy().view(np.uint32), o_cd.view(np.uint32))
     gi.close()
+
+
+# The split (bf16 pair) product behind the keys: depths around its slices of 32 with 16-byte and scalar
+# loads, a ragged last tile of lists and of queries, values that cancel (a large common offset), tiny
+# and huge magnitudes (the reference-order path must take over, not a wrong list).
+@pytest.mark.parametrize("nlist,D,Q", [(5000, 31, 130), (4000, 32, 257), (8193, 33, 1000), (6000, 100, 700), (3400, 260, 900)])
+@pytest.mark.parametrize("what", ["plain", "offset", "tiny", "huge"])
+@pytest.mark.parametrize("metric", [0, 1])
+def test_split_product_proposals(nlist, D, Q, what, metric):
+    from paper_2312_01712_amd import binding as b
+    rng = np.random.default_rng(nlist + D)
+    scale, offset = {"plain": (1.0, 0.0), "offset": (1.0, 300.0), "tiny": (1e-19, 0.0), "huge": (3e17, 0.0)}[what]
+    c = (scale * rng.normal(size=(nlist, D)) + offset).astype(np.float32)
+    q = (c[rng.integers(0, nlist, Q)] + 0.5 * scale * rng.normal(size=(Q, D))).astype(np.float32)
+    gi = b.IvfPqIndex(c, rng.normal(size=(1, 256, D)).astype(np.float32), np.arange(nlist + 1, dtype=np.int64),
+                      np.zeros((nlist, 1), dtype=np.uint8), metric=metric)
+    b.coarse_fallbacks(reset=True)
+    pid, pd = gi.coarse(torch.from_numpy(q).cuda(), 8)
+    torch.cuda.synchronize()
+    fb = b.coarse_fallbacks()
+    o_pid, o_pd = oracle.coarse(q, c, 8, metric=metric)
+    assert np.array_equal(pid.cpu().numpy(), o_pid)
+    assert np.array_equal(pd.cpu().numpy().view(np.uint32), o_pd.view(np.uint32))
+    if what == "plain" and metric == 0:
+        assert fb <= Q // 20, f"{fb} of {Q} queries were not accepted from the proposal"
+    gi.close()

@@ -918,6 +918,7 @@ int launch_scan(const ivfpq_index *ix, const float *d_queries, int64_t Q, int32_
   a.codebooks = ix->d_codebooks;
   a.probe_lb = nullptr;
   a.qmap = view ? view->qmap : nullptr;
+  a.nq = Q;
   a.probe_stride = (view && view->probe_stride > 0) ? view->probe_stride : nprobe;
   a.list_box = ix->d_box;
   a.list_offsets = ix->d_list_offsets;
@@ -996,6 +997,7 @@ int launch_scan(const ivfpq_index *ix, const float *d_queries, int64_t Q, int32_
     for (int64_t q0 = 0; q0 < Q; q0 += ww->q_chunk) {
       const int64_t qc = Q - q0 < ww->q_chunk ? Q - q0 : ww->q_chunk;
       ScanArgs c = a;
+      c.nq = qc;
       c.queries = d_queries + q0 * ix->D;
       c.probe_ids = d_probe_ids + q0 * a.probe_stride;
       if (a.probe_lb) c.probe_lb = a.probe_lb + q0 * a.probe_stride;

@@ -344,7 +344,8 @@ struct ScanArgs {
   const float *centroids;       // [nlist][D]
   const float *codebooks;       // [M][256][dsub]
   const float *probe_lb;        // [Q][probe_stride] lower bound on the distance of any point of the probed list, or NULL
-  const int32_t *qmap;          // [Q] or NULL: a query with a negative entry is left out (its workgroups exit at once)
+  const int32_t *qmap;          // [nq] or NULL: a query with a negative entry is left out
+  int64_t nq;                   // queries of this launch
   const float *list_box;        // [nlist][M][2][dsub] per list and subspace the bounding box of the entries in use
   const int64_t *list_offsets;  // [nlist+1]
   const int64_t *list_blocks;   // [nlist+1]

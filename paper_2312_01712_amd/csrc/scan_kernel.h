@@ -41,9 +41,13 @@ namespace {
 // KIND: SCAN_ALL writes every candidate's distance instead of a top-k; SCAN_SPLIT is the form in
 // which several workgroups share a query's probes (its exchange of bounds costs registers that the
 // plain form spills for: 7 % on lists of 8000 points).
-enum { SCAN_TOPK = 0, SCAN_ALL = 1, SCAN_SPLIT = 2 };
-template <int MT, int DSUB, int NW, int KIND, bool BYTE = false>
-__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(scan_wpe(BYTE ? (MT + 3) / 4 : MT, NW)))) void scan_kernel(ScanArgs a, RadiiSq r2) {
+// SCAN_MAPPED serves the queries that a query map names (usually none): few workgroups, each of which
+// looks up to 64 of the map's entries over at a time.  One workgroup per query that looks at its entry and
+// leaves takes 16 us per 10 000 queries, a trip to memory for every 512 of them, this form 9 us for any
+// number; below about 4000 queries the plain form is as fast.
+enum { SCAN_TOPK = 0, SCAN_ALL = 1, SCAN_SPLIT = 2, SCAN_MAPPED = 3 };
+template <int MT, int DSUB, int NW, int KIND, bool BYTE>
+__device__ __forceinline__ void scan_query(const ScanArgs &a, const RadiiSq &r2, int64_t q, int split) {
   constexpr bool DUMP = KIND == SCAN_ALL, SPLIT = KIND == SCAN_SPLIT;
   constexpr int NT = NW * 64;
   using Acc = std::conditional_t<BYTE, uint32_t, float>;
@@ -77,20 +81,15 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(scan_wp
   LDS float *sr2 = meta_lb + META;  // [M] r_m^2 of this query
   LDS uint32_t *srmin = (LDS uint32_t *)(sr2 + IVFPQ_MAX_M);  // [M][4] partial minima (bit patterns) of each row of the current table
 
-  const int tid = threadIdx.x, lane = tid & 63;
+  int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform, kept in a scalar register
   LDS float *ssuf = (LDS float *)(srmin + 4 * IVFPQ_MAX_M) + wave * SUF_SLOTS;  // this wavefront's suffix sums of srmin, per 8 subspaces
   LDS uint32_t *stat = (LDS uint32_t *)((LDS float *)(srmin + 4 * IVFPQ_MAX_M) + NW * SUF_SLOTS);  // blocks scanned / scanned to the end
-  // Probe groups in the order of their lists: the workgroups with the nearest lists of all queries
-  // come first, so that the bounds they publish (a.gbound) are there when most of the others start.
-  const int nq = SPLIT ? gridDim.x / a.nsplit : 1;
-  const int64_t q = SPLIT ? blockIdx.x % nq : blockIdx.x;
-  const int split = SPLIT ? blockIdx.x / nq : 0;
   const int p_begin = SPLIT ? (int)((int64_t)a.nprobe * split / a.nsplit) : 0;
   const int p_end = SPLIT ? (int)((int64_t)a.nprobe * (split + 1) / a.nsplit) : a.nprobe;
   const int32_t *probes = a.probe_ids + q * a.probe_stride;
   // with a query map only the queries it names are served (uniform over the workgroup)
-  if (a.qmap && a.qmap[q] < 0) return;
+  if (KIND != SCAN_MAPPED && a.qmap && a.qmap[q] < 0) return;
   // Bound on the query's k-th distance from the workgroups that serve its other probe groups, as
   // its complement (0: none yet).  Any workgroup's own bound is an upper bound on the final k-th
   // distance, so the smallest of them is one too, and a late value is only looser.
@@ -278,6 +277,8 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(scan_wp
   put_meta(first_meta, p_begin);
   __syncthreads();
   for (int p = p_begin; p < p_end; ++p) {
+    // (addresses formed anew for every list: kept across lists, they spill)
+    asm volatile("" : "+v"(tid), "+v"(lane));
     const int pm = (p - p_begin) & (META - 1);
     if (pm == 0) {
       // (every wavefront has passed the second barrier of the previous probe, so nobody still
@@ -546,6 +547,28 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(scan_wp
   else finish_topk<NW>(st, qd, qid, lane, wave, sh, smem3, a, q, split, gb);
 }
 
+template <int MT, int DSUB, int NW, int KIND, bool BYTE = false>
+__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(scan_wpe(BYTE ? (MT + 3) / 4 : MT, NW)))) void scan_kernel(ScanArgs a, RadiiSq r2) {
+  if constexpr (KIND == SCAN_SPLIT) {
+    // Probe groups in the order of their lists: the workgroups with the nearest lists of all queries
+    // come first, so that the bounds they publish (a.gbound) are there when most of the others start.
+    const int nq = gridDim.x / a.nsplit;
+    scan_query<MT, DSUB, NW, KIND, BYTE>(a, r2, blockIdx.x % nq, blockIdx.x / nq);
+  } else if constexpr (KIND == SCAN_MAPPED) {
+    const int lane = threadIdx.x & 63;
+    for (int64_t q0 = blockIdx.x; q0 < a.nq; q0 += (int64_t)gridDim.x * 64) {
+      const int64_t mine = q0 + (int64_t)lane * gridDim.x;
+      unsigned long long named = __ballot(mine < a.nq && a.qmap[mine < a.nq ? mine : 0] >= 0);   // the same in every wavefront
+      for (; named != 0ull; named &= named - 1ull) {
+        scan_query<MT, DSUB, NW, KIND, BYTE>(a, r2, q0 + (int64_t)(__ffsll((long long)named) - 1) * gridDim.x, 0);
+        __syncthreads();   // the LDS is free for the next query
+      }
+    }
+  } else {
+    scan_query<MT, DSUB, NW, KIND, BYTE>(a, r2, blockIdx.x, 0);
+  }
+}
+
 template <int MT, int DSUB, int NW, bool BYTE = false>
 int launch_scan_t(const ScanArgs &a, const RadiiSq &r2, int64_t grid, bool dump, hipStream_t s) {
   const int lut_bytes = (DSUB == 0 ? a.Mp : a.M) * (BYTE ? 256 : 1024), stage = NW * KP * 12;
@@ -556,10 +579,15 @@ int launch_scan_t(const ScanArgs &a, const RadiiSq &r2, int64_t grid, bool dump,
     ivfpq::set_error("scan: %zu bytes of LDS needed, 163840 available", lds);
     return IVFPQ_ERR_UNSUPPORTED;
   }
-  const int kind = dump ? SCAN_ALL : (a.nsplit > 1 ? SCAN_SPLIT : SCAN_TOPK);
+  const int kind = dump ? SCAN_ALL : (a.nsplit > 1 ? SCAN_SPLIT : (a.qmap && DSUB != 0 && grid > 4096 ? SCAN_MAPPED : SCAN_TOPK));
   auto kern = kind == SCAN_ALL ? scan_kernel<MT, DSUB, NW, SCAN_ALL, BYTE>
                                : (kind == SCAN_SPLIT ? scan_kernel<MT, DSUB, NW, SCAN_SPLIT, BYTE> : scan_kernel<MT, DSUB, NW, SCAN_TOPK, BYTE>);
-  static std::atomic<uint64_t> prepared[3];
+  if constexpr (DSUB != 0)   // (the shapes the list-major scan hands queries over for)
+    if (kind == SCAN_MAPPED) {
+      kern = scan_kernel<MT, DSUB, NW, SCAN_MAPPED, BYTE>;
+      if (grid > 512) grid = 512;   // two per CU
+    }
+  static std::atomic<uint64_t> prepared[4];
   if (int rc = prepare_kernel(kern, prepared[kind])) return rc;
   hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(NW * 64), lds, s, a, r2);
   return IVFPQ_OK;

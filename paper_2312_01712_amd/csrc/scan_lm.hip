@@ -311,16 +311,15 @@ __global__ __launch_bounds__(LM_NW * 64) __attribute__((amdgpu_waves_per_eu(LM_N
   LDS uint32_t *coll_pos = coll_d + LM_G * LM_COLLECT;    // ... their positions in the list ...
   LDS uint32_t *coll_rank = coll_pos + LM_G * LM_COLLECT;  // ... and in sorted order
 
-  const int tid = threadIdx.x, lane = tid & 63;
+  int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   LDS uint32_t *qd0 = queue + (wave * LM_G + 0) * 2 * LM_QUEUE, *qrow0 = qd0 + LM_QUEUE;
   LDS uint32_t *qd1 = queue + (wave * LM_G + 1) * 2 * LM_QUEUE, *qrow1 = qd1 + LM_QUEUE;
 
   // this wavefront's codebook rows (rows wave, wave + NW, ...) stay in registers for the whole
-  // kernel; the head pass at 64 subspaces has registers for three of its eight rows and fetches
-  // the others (from the L2) when a task's table is built (four and five resident rows spill 2
-  // and 6 registers; the batch takes the same time with 3 and 4)
-  constexpr int RES = (HEAD && ITER > 6) ? 3 : ITER;
+  // kernel; the head pass at 64 subspaces has registers for six of its eight rows and fetches
+  // the others (from the L2) when a task's table is built
+  constexpr int RES = (HEAD && ITER > 6) ? 6 : ITER;
   float4 cbr[RES][DSUB];
   auto load_row = [&](int it, float4 (&row)[DSUB]) __attribute__((always_inline)) {
     const int m = wave + it * NW;
@@ -414,6 +413,7 @@ __global__ __launch_bounds__(LM_NW * 64) __attribute__((amdgpu_waves_per_eu(LM_N
     pend_c0 = pend_c1 = 0;
   };
   for (;;) {
+    asm volatile("" : "+v"(tid), "+v"(lane));   // (addresses formed anew for every task: kept across tasks they spill)
     if (r_on) sres[rg * dpad + rd] = qv - cv;
     if (m_on) sr2[mg * IVFPQ_MAX_M + mm] = rv;
     if (HEAD && tid < LM_SEL_WORDS)   // [0..1] keys collected, [2..3] bin of the k-th key, [4..5] smallest key, [6..7] largest key

@@ -194,8 +194,56 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4))) vo
   LDS uint32_t *qd = queue_d + wave * 64;
   LDS int64_t *qid = queue_id + wave * 64;
   __syncthreads();
-  // ---- the query's table, built once ----
-  {
+  // ---- the query's table, built once, with the row minima and magnitudes for the early exit ----
+  // Two-dimensional subspaces: a wavefront per row, four entries per lane, every row's loads in flight
+  // before the first is used, minima from the registers.  (Entry by entry with run-time loops and the
+  // rows read again for their minima, this took 44 thousand clocks of a query of the 1M x 200
+  // configuration.)
+  const bool pairs = MT > 0 && !DUMP && dsub == 2;   // uniform
+  if constexpr (MT > 0 && !DUMP) {
+    if (pairs) {
+      constexpr int ITER = (MT + NW - 1) / NW;
+      float4 ev[ITER][2];
+#pragma unroll
+      for (int it = 0; it < ITER; ++it) {
+        const int m = wave + it * NW;
+        const GLOBAL uint8_t *cb = uniform_ptr(a.codebooks + (int64_t)(m < MT ? m : MT - 1) * 512);
+        ev[it][0] = load_f4(cb, (uint32_t)(lane * 32));
+        ev[it][1] = load_f4(cb, (uint32_t)(lane * 32 + 16));
+      }
+#pragma unroll
+      for (int it = 0; it < ITER; ++it) {
+        const int m = wave + it * NW;
+        if (m < MT) {
+          const float q0 = sq[2 * m], q1 = sq[2 * m + 1], thr = sthr[m], thr_in = sthr_in[m];
+          const float ex[4] = {ev[it][0].x, ev[it][0].z, ev[it][1].x, ev[it][1].z};
+          const float ey[4] = {ev[it][0].y, ev[it][0].w, ev[it][1].y, ev[it][1].w};
+          float v[4];
+#pragma unroll
+          for (int x = 0; x < 4; ++x) v[x] = table_value_ip(fmaf(q1, ey[x], q0 * ex[x]), thr, thr_in, mode);
+          *(LDS floatx4 *)(lut + m * 256 + 4 * lane) = floatx4{v[0], v[1], v[2], v[3]};
+          float lo = fminf(fminf(v[0], v[1]), fminf(v[2], v[3]));
+          float hi = fmaxf(fmaxf(fabsf(v[0]), fabsf(v[1])), fmaxf(fabsf(v[2]), fabsf(v[3])));
+          auto both = [&](auto off) __attribute__((always_inline)) {
+            constexpr int J = decltype(off)::value;
+            lo = fminf(lo, __uint_as_float(xor_u32<J, true>(__float_as_uint(lo))));
+            hi = fmaxf(hi, __uint_as_float(xor_u32<J, true>(__float_as_uint(hi))));
+          };
+          both(std::integral_constant<int, 1>{});
+          both(std::integral_constant<int, 2>{});
+          both(std::integral_constant<int, 4>{});
+          both(std::integral_constant<int, 8>{});
+          both(std::integral_constant<int, 16>{});
+          both(std::integral_constant<int, 32>{});
+          if (lane == 0) {
+            srmin[m] = lo;
+            srabs[m] = hi;
+          }
+        }
+      }
+    }
+  }
+  if (!pairs) {
     const int e = tid & 255;
     for (int m = tid >> 8; m < M; m += NT >> 8) {
       const int mu = __builtin_amdgcn_readfirstlane(m);
@@ -203,21 +251,22 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4))) vo
       lut[mu * 256 + e] = table_value_ip(ip, sthr[mu], sthr_in[mu], mode);
     }
   }
-  // ---- row minima and magnitudes for the early exit (one row per wavefront and pass) ----
   if constexpr (MT > 0 && !DUMP) {
-    __syncthreads();
-    for (int m = wave; m < M; m += NW) {
-      const floatx4 v = *(const LDS floatx4 *)(lut + m * 256 + 4 * lane);
-      float lo = fminf(fminf(v[0], v[1]), fminf(v[2], v[3]));
-      float hi = fmaxf(fmaxf(fabsf(v[0]), fabsf(v[1])), fmaxf(fabsf(v[2]), fabsf(v[3])));
+    if (!pairs) {   // one row per wavefront and pass
+      __syncthreads();
+      for (int m = wave; m < M; m += NW) {
+        const floatx4 v = *(const LDS floatx4 *)(lut + m * 256 + 4 * lane);
+        float lo = fminf(fminf(v[0], v[1]), fminf(v[2], v[3]));
+        float hi = fmaxf(fmaxf(fabsf(v[0]), fabsf(v[1])), fmaxf(fabsf(v[2]), fabsf(v[3])));
 #pragma unroll
-      for (int off = 32; off > 0; off >>= 1) {
-        lo = fminf(lo, __shfl_xor(lo, off));
-        hi = fmaxf(hi, __shfl_xor(hi, off));
-      }
-      if (lane == 0) {
-        srmin[m] = lo;
-        srabs[m] = hi;
+        for (int off = 32; off > 0; off >>= 1) {
+          lo = fminf(lo, __shfl_xor(lo, off));
+          hi = fmaxf(hi, __shfl_xor(hi, off));
+        }
+        if (lane == 0) {
+          srmin[m] = lo;
+          srabs[m] = hi;
+        }
       }
     }
     __syncthreads();
@@ -267,12 +316,28 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4))) vo
           const float *bx = a.list_box + (int64_t)cc * D * 2;
           const float eps_m = (float)(2 * dsub + 4) * 5.9604645e-08f;
           float acc = 0.0f, amag = 0.0f;
-          for (int m = lane; m < M; m += 64) {
+          float4 b2[(MT + 63) / 64];   // two-dimensional subspaces: a box is one 16-byte load
+          if (pairs) {
+#pragma unroll
+            for (int x = 0; x < (MT + 63) / 64; ++x) b2[x] = reinterpret_cast<const float4 *>(bx)[lane + 64 * x < MT ? lane + 64 * x : 0];
+          }
+#pragma unroll
+          for (int x = 0; x < (MT + 63) / 64; ++x) {
+            const int m = lane + 64 * x;
+            if (m >= M) break;
             float u = 0.0f, mag = 0.0f;
-            for (int j = 0; j < dsub; ++j) {
-              const float qj = sq[m * dsub + j], lo = bx[m * 2 * dsub + j], hi = bx[m * 2 * dsub + dsub + j];
-              u += fmaxf(qj * lo, qj * hi);
-              mag += fabsf(qj) * fmaxf(fabsf(lo), fabsf(hi));
+            if (pairs) {
+              const float q0 = sq[2 * m], q1 = sq[2 * m + 1];
+              u += fmaxf(q0 * b2[x].x, q0 * b2[x].z);
+              mag += fabsf(q0) * fmaxf(fabsf(b2[x].x), fabsf(b2[x].z));
+              u += fmaxf(q1 * b2[x].y, q1 * b2[x].w);
+              mag += fabsf(q1) * fmaxf(fabsf(b2[x].y), fabsf(b2[x].w));
+            } else {
+              for (int j = 0; j < dsub; ++j) {
+                const float qj = sq[m * dsub + j], lo = bx[m * 2 * dsub + j], hi = bx[m * 2 * dsub + dsub + j];
+                u += fmaxf(qj * lo, qj * hi);
+                mag += fabsf(qj) * fmaxf(fabsf(lo), fabsf(hi));
+              }
             }
             const float thr = sthr[m];
             const float t = fmaxf(u, thr) + eps_m * (mag + fabsf(thr));
@@ -292,7 +357,10 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4))) vo
       }
       __syncthreads();
     }
+    [[maybe_unused]] CodeRegs<MPT / 4> ahead;   // first chunk of the wavefront's first block of list `ahead_of`
+    [[maybe_unused]] int ahead_of = -1;
     for (int pm = 0; pm < pn; ++pm) {
+      [[maybe_unused]] int after = -1;   // the list that is up after this one, as things stand
       if constexpr (MT > 0 && !DUMP) {
         // The next list that the list-level bound does not rule out, found for all of the chunk's probes
         // at once (a lane each; the bound only tightens, so a list ruled out stays so).  Nothing of
@@ -303,6 +371,8 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4))) vo
         const unsigned long long alive = __ballot(mine && dist_key<true>(meta_lb[mine ? lane : pm]) <= pref0);
         if (alive == 0ull) break;
         pm = __ffsll((long long)alive) - 1;
+        const unsigned long long others = alive & (alive - 1ull);
+        after = others ? __ffsll((long long)others) - 1 : -1;
       }
       const int64_t row0 = meta_row0[pm];
       const int len = __builtin_amdgcn_readfirstlane(meta_len[pm]);
@@ -326,7 +396,20 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4))) vo
               if (!ahead1) load_chunks<MPT, 1, NCH>(base, nb, blk, lane, r);
           };
           CodeRegs<MPT / 4> nxt;
-          load_ahead(wave, nxt);
+          if (PARTS && ahead1 && ahead_of == pm) nxt = ahead;   // requested during the list before
+          else load_ahead(wave, nxt);
+          // a list has about one block per wavefront, which mostly ends within its first chunk: without
+          // this every list waits a trip to memory
+          ahead_of = -1;
+          if constexpr (PARTS) {
+            if (ahead1 && after >= 0) {
+              const int nb2 = (__builtin_amdgcn_readfirstlane(meta_len[after]) + 63) >> 6;
+              if (wave < nb2) {
+                load_chunks<MPT, 0, 1>(a.codes + meta_blk[after] * ivfpq_block_bytes(Mp), nb2, wave, lane, ahead);
+                ahead_of = after;
+              }
+            }
+          }
           for (int b = wave; b < nb; b += NW) {
             CodeRegs<MPT / 4> cur = nxt;
             const int bn = b + NW < last ? b + NW : last;

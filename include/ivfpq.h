@@ -328,7 +328,7 @@ int64_t ivfpq_coarse_fallbacks(int reset);
  * calls that start after it returns and may be set from any thread.  Unknown names and values
  * outside the stated sets give IVFPQ_ERR_INVALID_ARGUMENT.
  *   "scan_waves"   wavefronts per workgroup of the fused scan kernel: 0 (default: chosen from
- *                  the shape), 4, 8 or 16.
+ *                  the shape), 4, 8 or 16 (shapes without a specialised kernel: always the default).
  *   "scan_loads"   how the scan kernel fetches code blocks: 0 (default) the first chunk (16
  *                  subspaces) of a block ahead and the rest only when the block needs it, whole
  *                  blocks once pruning has been switched off for a query; 1 always whole blocks;

@@ -520,16 +520,16 @@ __device__ __forceinline__ void lookup_group(const LDS float *, const CodeRegs<(
 __device__ __forceinline__ float acc_value(float a) { return a; }
 __device__ __forceinline__ float acc_value(uint32_t a) { return (float)a; }   // exact: sums of at most 2 M
 
-// (Mp: the subspaces in use, a multiple of 4, where MT only says how many 16-byte chunks there are; the
-// up to three rows between M and Mp are zero and add nothing.)
+// (M: the subspaces in use, where MT only says how many 16-byte chunks there are; the last, short group
+// decides look-up by look-up, which is uniform over the wavefront.)
 template <int MT>
 __device__ inline float adc_sum(const LDS float *lut, const CodeRegs<((MT + 3) / 4 * 4) / 4> &r,
-                                float start = 0.0f, int Mp = MT) {
+                                float start = 0.0f, int M = MT) {
   float dist = start;
 #pragma unroll
   for (int h = 0; h < MT; h += LOOKUP_GROUP) {
-    if (h + LOOKUP_GROUP <= Mp || Mp == MT) lookup_group<MT>(lut, r, h, cmin(h + LOOKUP_GROUP, MT), dist);
-    else if (h < Mp) lookup_group<MT>(lut, r, h, h + 4, dist);
+    if (h + LOOKUP_GROUP <= M || M == MT) lookup_group<MT>(lut, r, h, cmin(h + LOOKUP_GROUP, MT), dist);
+    else if (h < M) lookup_group<MT>(lut, r, h, M, dist);
   }
   return dist;
 }
@@ -554,11 +554,11 @@ __device__ inline float adc_sum_bytes(const LDS float *lut, const CodeRegs<((MT 
 // (ACC: float for a table of distances, uint32_t for a byte table of penalties.)
 template <int MT, int M0, int M1, typename ACC>
 __device__ inline bool adc_part_exit(const LDS float *lut, const CodeRegs<((MT + 3) / 4 * 4) / 4> &r,
-                                     const LDS float *suf, float tauf, bool checks, bool valid, ACC &dist, int Mp = MT) {
+                                     const LDS float *suf, float tauf, bool checks, bool valid, ACC &dist, int M = MT) {
 #pragma unroll
   for (int g = M0; g < M1; g += 8) {
-    if (Mp != MT && g + 8 > Mp) {   // the last, short group (see adc_sum)
-      if (g < Mp) lookup_group<MT>(lut, r, g, g + 4, dist);
+    if (M != MT && g + 8 > M) {   // the last, short group (see adc_sum)
+      if (g < M) lookup_group<MT>(lut, r, g, M, dist);
       return true;
     }
     // requested ahead of the look-ups, so that it has arrived when they have

@@ -58,7 +58,7 @@ __device__ __forceinline__ void scan_query(const ScanArgs &a, const RadiiSq &r2,
   const int Mp = RT ? a.Mp : MPT;
   const int D = a.D;
   // LDS carve: table | merge staging (aliases the table) | query | queues | tau
-  const int lut_bytes = (RT ? Mp : M) * (BYTE ? 256 : 1024);
+  const int lut_bytes = M * (BYTE ? 256 : 1024);
   const int stage_bytes = NW * KP * 12;
   const int region0 = lut_bytes > stage_bytes ? lut_bytes : stage_bytes;
   LDS unsigned char *smem3 = (LDS unsigned char *)smem;
@@ -185,9 +185,6 @@ __device__ __forceinline__ void scan_query(const ScanArgs &a, const RadiiSq &r2,
   sh.wide_d = wide ? a.wide_d + q * a.wide_cap : nullptr;
   sh.wide_id = wide ? a.wide_id + q * a.wide_cap : nullptr;
   sh.wide_cap = a.wide_cap;
-
-  if constexpr (RT)   // the rows that stand for the codes' padding add nothing, and no table writes them
-    for (int i = M * 256 + tid; i < Mp * 256; i += NT) lut[i] = 0.0f;
 
   WaveTop st;
   init_wave_top<false, DUMP>(st, a, q);
@@ -491,7 +488,7 @@ __device__ __forceinline__ void scan_query(const ScanArgs &a, const RadiiSq &r2,
           const int i = b * 64 + lane;
           const bool valid = i < len;
           if (DUMP) {
-            const float dist = BYTE ? adc_sum_bytes<MT>(lut, cur) : adc_sum<MT>(lut, cur, 0.0f, RT ? Mp : MT);
+            const float dist = BYTE ? adc_sum_bytes<MT>(lut, cur) : adc_sum<MT>(lut, cur, 0.0f, RT ? M : MT);
             if (valid) {
               a.all_dist[dump_pos + i] = dist;
               a.all_ids[dump_pos + i] = a.ids[row0 + i];
@@ -513,16 +510,16 @@ __device__ __forceinline__ void scan_query(const ScanArgs &a, const RadiiSq &r2,
             // half); most blocks end in an early part, and a part that was not fetched ahead
             // is fetched when a block turns out to need it.
             if constexpr (QUARTER_OK) {
-              if (!adc_part_exit<MT, 0, 16>(lut, cur, ssuf, tauf, prune, valid, dist, RT ? Mp : MT)) continue;
+              if (!adc_part_exit<MT, 0, 16>(lut, cur, ssuf, tauf, prune, valid, dist, RT ? M : MT)) continue;
               if (depth == 2) load_part(c1, cH, base, nb, b, cur);
-              if (!adc_part_exit<MT, 16, MH>(lut, cur, ssuf, tauf, prune, valid, dist, RT ? Mp : MT)) continue;
+              if (!adc_part_exit<MT, 16, MH>(lut, cur, ssuf, tauf, prune, valid, dist, RT ? M : MT)) continue;
             } else if constexpr (HALF_OK) {
-              if (!adc_part_exit<MT, 0, MH>(lut, cur, ssuf, tauf, prune, valid, dist, RT ? Mp : MT)) continue;
+              if (!adc_part_exit<MT, 0, MH>(lut, cur, ssuf, tauf, prune, valid, dist, RT ? M : MT)) continue;
             }
             if constexpr (HALF_OK) {
               if (depth >= 1) load_part(cH, cE, base, nb, b, cur);
             }
-            if (!adc_part_exit<MT, HALF_OK ? MH : 0, MT>(lut, cur, ssuf, tauf, prune, valid, dist, RT ? Mp : MT)) continue;
+            if (!adc_part_exit<MT, HALF_OK ? MH : 0, MT>(lut, cur, ssuf, tauf, prune, valid, dist, RT ? M : MT)) continue;
             ++full;
             wave_offer(st, acc_value(dist), valid, row0 + i, a.ids, qd, qid, lane, a.k, sh);
           }
@@ -571,7 +568,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(scan_wp
 
 template <int MT, int DSUB, int NW, bool BYTE = false>
 int launch_scan_t(const ScanArgs &a, const RadiiSq &r2, int64_t grid, bool dump, hipStream_t s) {
-  const int lut_bytes = (DSUB == 0 ? a.Mp : a.M) * (BYTE ? 256 : 1024), stage = NW * KP * 12;
+  const int lut_bytes = a.M * (BYTE ? 256 : 1024), stage = NW * KP * 12;
   const size_t lds = (size_t)(lut_bytes > stage ? lut_bytes : stage) + 2 * ((a.D * 4 + 15) & ~15) +
                      (size_t)NW * 64 * 12 + ((4 * (2 * NW + 4) + 15) & ~15) + 64 * 28 + 5 * IVFPQ_MAX_M * 4 +
                      (size_t)NW * SUF_SLOTS * 4 + 16;

@@ -37,7 +37,7 @@ namespace {
 // It shares everything with the others -- chunked loads, eight look-ups in flight, row minima, early
 // exits, the list-level bound -- but streams its codebook rows per list.  (500k x 120, 30 subspaces of 4:
 // the form it replaces built its table entry by entry from scalar loads, pruned nothing and had one
-// look-up in flight: 1205 us for 999 queries, 425 us so.)
+// look-up in flight: 1205 us for 999 queries, 382 us so.)
 // KIND: SCAN_ALL writes every candidate's distance instead of a top-k; SCAN_SPLIT is the form in
 // which several workgroups share a query's probes (its exchange of bounds costs registers that the
 // plain form spills for: 7 % on lists of 8000 points).

@@ -1,5 +1,5 @@
 // List-major batched scan: the queries that probe the same inverted list are served
-// together, two at a time, from ONE pass over the list's codes.
+// together, eight at a time (two where fp32 tables serve), from ONE pass over the list's codes.
 //
 // Paper Sec. 5.2 / Algorithm 1 builds an inverted entry -> points map per list so that the
 // distance calculation (Sec. 5.3) touches a list's points once per hit entry.  On CDNA4 the
@@ -10,8 +10,8 @@
 // interleaved entry by entry, so a single 8-byte LDS read returns both queries' values for a
 // point's code.  The LDS gather rate, which bounds the query-major scan on data where
 // nothing can be pruned, is per lane-address and not per byte, so two queries cost what one
-// did.  Sums keep the subspace order of the plain loop: results are bit for bit those of the
-// query-major scan.
+// did (lm_scan_kernel); with a byte per query the same read serves eight (lm_byte_kernel).  Sums keep the
+// subspace order of the plain loop: results are bit for bit those of the query-major scan.
 //
 // A query's lists are now scanned by different workgroups at different times, so the running
 // k-th distance is not at hand.  Instead:

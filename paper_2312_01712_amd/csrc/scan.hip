@@ -1,7 +1,10 @@
 // Query-major scan: the inner-product kernel, the list-level bounds, the selections behind the scan
 // kernels, index-build helpers, and the launchers.  The L2 kernel itself is in scan_kernel.h.
 
+#include "scan_ip_carve.h"
 #include "scan_kernel.h"
+
+static_assert(IP_TOP == KP, "the inner-product scan stages whole lists");
 
 namespace {
 
@@ -114,33 +117,28 @@ template <int MT, int NW, bool DUMP>
 __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4))) void scan_ip_kernel(ScanArgs a, RadiiSq r2) {
   constexpr int NT = NW * 64;
   constexpr int MPT = (MT + 3) / 4 * 4;
-  constexpr int META = 64;
+  constexpr int META = IP_META;
   extern __shared__ __align__(16) unsigned char smem[];
   const int M = MT > 0 ? MT : a.M;
   const int Mp = MT > 0 ? MPT : a.Mp;
   const int D = a.D, dsub = a.dsub;
-  // LDS carve: table | merge staging (aliases the table) | query | queues | bounds | list metadata | thresholds
-  const int lut_bytes = M * 1024;
-  const int stage_bytes = NW * KP * 12;
-  const int region0 = lut_bytes > stage_bytes ? lut_bytes : stage_bytes;
+  const IpCarve at = ip_carve(M, D, NW);
   LDS unsigned char *smem3 = (LDS unsigned char *)smem;
   LDS float *lut = (LDS float *)smem3;
-  LDS float *sq = (LDS float *)(smem3 + region0);
-  const int sq_bytes = (D * 4 + 15) & ~15;
-  LDS int64_t *queue_id = (LDS int64_t *)(smem3 + region0 + sq_bytes);
-  LDS uint32_t *queue_d = (LDS uint32_t *)(smem3 + region0 + sq_bytes + NW * 64 * 8);
-  LDS uint32_t *tau_words = (LDS uint32_t *)(smem3 + region0 + sq_bytes + NW * 64 * 12);
-  const int tau_bytes = (4 * (2 * NW + 4) + 15) & ~15;  // bound | ranks [NW] | wide: slots taken, overflow | wide: counts [NW]
-  LDS int64_t *meta_row0 = (LDS int64_t *)(smem3 + region0 + sq_bytes + NW * 64 * 12 + tau_bytes);
-  LDS int64_t *meta_blk = meta_row0 + META;
-  LDS int32_t *meta_len = (LDS int32_t *)(meta_blk + META);
-  LDS float *meta_start = (LDS float *)(meta_len + META);
-  LDS float *meta_lb = meta_start + META;  // lower bound on the score of any point of the list
-  LDS float *sthr = meta_lb + META;  // [M]
-  LDS float *sthr_in = sthr + IVFPQ_MAX_M;
-  LDS float *srmin = sthr_in + IVFPQ_MAX_M;    // [M] smallest value of each table row
-  LDS float *srabs = srmin + IVFPQ_MAX_M;      // [M] largest magnitude of each table row
-  LDS float *ssuf = srabs + IVFPQ_MAX_M;       // [M/8 + 2] suffix sums of srmin at the check points, then sum srabs
+  LDS float *sq = (LDS float *)(smem3 + at.query);
+  LDS int64_t *queue_id = (LDS int64_t *)(smem3 + at.queue_id);
+  LDS uint32_t *queue_d = (LDS uint32_t *)(smem3 + at.queue_d);
+  LDS uint32_t *tau_words = (LDS uint32_t *)(smem3 + at.bounds);
+  LDS int64_t *meta_row0 = (LDS int64_t *)(smem3 + at.row0);
+  LDS int64_t *meta_blk = (LDS int64_t *)(smem3 + at.block0);
+  LDS int32_t *meta_len = (LDS int32_t *)(smem3 + at.len);
+  LDS float *meta_start = (LDS float *)(smem3 + at.start);
+  LDS float *meta_lb = (LDS float *)(smem3 + at.lower);
+  LDS float *sthr = (LDS float *)(smem3 + at.thr);
+  LDS float *sthr_in = (LDS float *)(smem3 + at.thr_in);
+  LDS float *srmin = (LDS float *)(smem3 + at.row_min);
+  LDS float *srabs = (LDS float *)(smem3 + at.row_abs);
+  LDS float *ssuf = (LDS float *)(smem3 + at.suffix);
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -951,11 +949,7 @@ int launch_scan_nw(const ScanArgs &a, const RadiiSq &r2, int64_t grid, bool dump
   return launch_scan_t<MT, DSUB, 4>(a, r2, grid, dump, s);
 }
 
-size_t scan_ip_lds(const ScanArgs &a, int nw) {
-  const int lut_bytes = a.M * 1024, stage = nw * KP * 12;
-  return (size_t)(lut_bytes > stage ? lut_bytes : stage) + ((a.D * 4 + 15) & ~15) + (size_t)nw * 64 * 12 +
-         ((4 * (nw + 1) + 15) & ~15) + 64 * 28 + 4 * IVFPQ_MAX_M * 4 + (IVFPQ_MAX_M / 8 + 2) * 4;
-}
+size_t scan_ip_lds(const ScanArgs &a, int nw) { return (size_t)ip_carve(a.M, a.D, nw).end; }
 
 template <int MT, int NW>
 int launch_scan_ip_t(const ScanArgs &a, const RadiiSq &r2, int64_t grid, bool dump, hipStream_t s) {

@@ -1,0 +1,45 @@
+"""Edges of what the kernels accept: the last bytes of their LDS, values that overflow, grid limits,
+batches and candidate buffers at which another route takes over.  Everything is compared with the
+oracle bit for bit (same operation order: no tolerance)."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2312_01712_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+
+def _binding():
+    from paper_2312_01712_amd import binding
+    return binding
+
+
+def _index(rng, D, M, sizes, spread=0.3, centre=1.0):
+    offs = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+    N, nlist = int(offs[-1]), len(sizes)
+    return wl.Index(N=N, D=D, nlist=nlist, M=M, centroids=(centre * rng.normal(size=(nlist, D))).astype(np.float32),
+                    codebooks=(spread * rng.normal(size=(M, 256, D // M))).astype(np.float32), list_offsets=offs,
+                    codes=rng.integers(0, 256, size=(N, M), dtype=np.uint8), ids=rng.permutation(N).astype(np.int64))
+
+
+def _same(got, want, what):
+    torch.cuda.synchronize()
+    assert np.array_equal(got[0].cpu().numpy(), want[0]), f"{what}: ids differ"
+    assert np.array_equal(got[1].cpu().numpy().view(np.uint32), want[1].view(np.uint32)), f"{what}: distances differ"
+
+
+@pytest.mark.parametrize("M,D", [(100, 100), (100, 300), (100, 400), (64, 256)])
+def test_inner_product_last_suffix_sums(M, D):
+    """Inner products where the suffix sums of the row minima lie at the very end of the LDS: with
+    100 subspaces of 4 the allocation's rounding leaves 40 bytes behind what is asked for."""
+    b = _binding()
+    rng = np.random.default_rng(D)
+    idx = _index(rng, D, M, rng.integers(100, 900, size=40))
+    q = rng.normal(size=(40, D)).astype(np.float32)
+    gi = b.IvfPqIndex.from_index(idx, metric=b.METRIC_IP)
+    for radii in (np.full(M, np.inf, np.float32), np.full(M, 0.8 * np.sqrt(D / M), np.float32)):
+        for k in (1, 10, 100):
+            _same(gi.search(torch.from_numpy(q).cuda(), 12, k, radii), oracle.search(q, idx, 12, k, radii, threads=8, metric=1), (M, D, k))
+    gi.close()

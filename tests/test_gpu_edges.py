@@ -43,3 +43,29 @@ def test_inner_product_last_suffix_sums(M, D):
         for k in (1, 10, 100):
             _same(gi.search(torch.from_numpy(q).cuda(), 12, k, radii), oracle.search(q, idx, 12, k, radii, threads=8, metric=1), (M, D, k))
     gi.close()
+
+
+@pytest.mark.parametrize("nlist", [200, 700])
+@pytest.mark.parametrize("Q", [1, 9])
+def test_filtering_with_infinite_centroids(nlist, Q):
+    """Inner products with centroids that are infinite where the query is zero are NaN: the other lists
+    come first, in order, as where every distance is formed and sorted."""
+    b = _binding()
+    rng = np.random.default_rng(nlist)
+    cent = np.zeros((nlist, 2), np.float32)
+    cent[:, 1] = rng.permutation(nlist) - nlist // 2
+    bad = rng.permutation(nlist)[:nlist // 3]
+    cent[bad, 0] = np.inf
+    q = np.tile(np.array([[0.0, 1.0]], np.float32), (Q, 1))
+    real = np.setdiff1d(np.arange(nlist), bad)
+    score = np.float32(0) - cent[real, 1]
+    order = real[np.lexsort((real, score))]
+    gi = b.IvfPqIndex(cent, rng.normal(size=(1, 256, 2)).astype(np.float32), np.arange(nlist + 1, dtype=np.int64),
+                      np.zeros((nlist, 1), dtype=np.uint8), metric=b.METRIC_IP)
+    for nprobe in (1, 60, 90, 101):
+        pid, pd = gi.coarse(torch.from_numpy(q).cuda(), nprobe)
+        torch.cuda.synchronize()
+        for row, dist in zip(pid.cpu().numpy(), pd.cpu().numpy()):
+            assert np.array_equal(row, order[:nprobe]), nprobe
+            assert np.array_equal(dist, np.sort(score)[:nprobe]), nprobe
+    gi.close()

@@ -153,8 +153,9 @@ __device__ __forceinline__ int32_t med3i(int32_t a, int32_t b, int32_t c) {
 }
 
 // The product runs in bf16: q = qh + ql and c = ch + cl, each part the nearest bf16 to what is left,
-// and qh.ch + qh.cl + ql.ch is accumulated in fp32.  What is dropped is at most 3 x 2^-18 of
-// sum |q_i c_i| (the parts' rests and ql.cl), which the selection's bound counts (SPLIT_ERR): a
+// and qh.ch + qh.cl + ql.ch is accumulated in fp32.  With 8 significant bits, |ql| <= 2^-8 |q| and the rest
+// behind ql is at most 2^-17 |q|: what is dropped (ql.cl and the rests) is at most 2^-15 + 2^-34 of
+// sum |q_i c_i|, which the selection's bound counts (SPLIT_ERR): a
 // proposal only has to be certain to contain the nearest lists, their distances are then formed in
 // fp32 from the fp32 vectors in the reference order, so the results stay bit for bit.  Three
 // products at 16 times the fp32 rate.  10 000 x 16 384 x 128: 421 us with fp32 products (68 % of
@@ -163,7 +164,8 @@ __device__ __forceinline__ int32_t med3i(int32_t a, int32_t b, int32_t c) {
 // is loaded.
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef uint32_t uint32x4 __attribute__((ext_vector_type(4)));
-constexpr float SPLIT_ERR = 1.2e-5f;   // above 3 x 2^-18, in units of |q|^2 + max |c|^2 >= 2 sum |q_i c_i|
+constexpr float SPLIT_ERR = 3.06e-5f;  // above 2^-15 + 2^-34, in units of |q|^2 + max |c|^2 >= 2 sum |q_i c_i|
+constexpr float KEY_ERR = 1.53e-5f;    // above 2^-16: 63 units in the last place of a value of at most 2 (|q|^2 + max |c|^2)
 constexpr int SK = 32;             // depth per LDS stage
 constexpr int SLD = SK + 8;        // row stride in bf16: 80 bytes, so that 8 lanes' 16-byte reads of consecutive rows touch 32 banks
 
@@ -871,11 +873,12 @@ __global__ __launch_bounds__(CS_WAVES * 64) void coarse_select_wave_kernel(
   // The cut: the bin of the kprop-th smallest proposal, and far enough beyond the bin of the
   // nprobe-th for the acceptance test below to hold (twice the rounding bound past that bin's
   // upper edge), whichever is later.
-  // (a key is within 64 units in the last place of its proposal value, which is at most
-  // 2 (|q|^2 + max |c|^2) in magnitude: 2^-15 of that sum covers it)
-  // (FUSED also counts what the split product drops, SPLIT_ERR, and what falls below its smallest
-  // numbers: at most 2^-126 per term)
-  const float bound = (err_scale + (FUSED ? 3.0517578125e-05f + SPLIT_ERR : 0.0f)) * (qq + max_cnorm) + (FUSED ? 2.0e-34f : 0.0f);
+  // FUSED counts, in units of 2^-23 (|q|^2 + max |c|^2), D + 2 for the reference distance's own roundings, 3 D
+  // additions of the split product's terms (one unit each, as if they were cut off and not rounded, their
+  // magnitudes 1.012 times those of q_i c_i) and ten single ones (norms, sums, differences); besides
+  // SPLIT_ERR and KEY_ERR, and what falls below the smallest numbers: 2^-126 per factor or sum.
+  const float bound = FUSED ? ((5.0f * (float)D + 16.0f) * 1.1920929e-07f + SPLIT_ERR + KEY_ERR) * (qq + max_cnorm) + 4.0e-34f
+                            : err_scale * (qq + max_cnorm);
   uint32_t top = bin_of_rank((uint32_t)(EXACT ? nprobe : kprop));
   if (!EXACT) {
     const float reach = (float)(bin_of_rank((uint32_t)nprobe) + 2u) + 2.0f * bound * scale;

@@ -69,3 +69,31 @@ def test_filtering_with_infinite_centroids(nlist, Q):
             assert np.array_equal(row, order[:nprobe]), nprobe
             assert np.array_equal(dist, np.sort(score)[:nprobe]), nprobe
     gi.close()
+
+
+# (at 8 probes the proposals come from keys from 4481 lists on)
+@pytest.mark.parametrize("nlist,D,Q", [(4481, 32, 257), (5000, 64, 100), (4737, 260, 90)])
+@pytest.mark.parametrize("what", ["plain", "worst"])
+@pytest.mark.parametrize("metric", [0, 1])
+def test_split_product_bound(nlist, D, Q, what, metric):
+    """Depths of whole slices and with 16-byte loads, and values whose split product drops most: all
+    of one sign and near 1 + 2^-8, so that the dropped parts add up instead of averaging out."""
+    b = _binding()
+    rng = np.random.default_rng(nlist + D)
+    if what == "plain":
+        c = rng.normal(size=(nlist, D)).astype(np.float32)
+        q = (c[rng.integers(0, nlist, Q)] + 0.5 * rng.normal(size=(Q, D))).astype(np.float32)
+    else:   # two populations: mantissas that drop 3e-5 and ones that drop nothing, norms alike
+        c = np.where(rng.random((nlist, 1)) < 0.5, 1.0039136, 1.0).astype(np.float32) * np.ones((1, D), np.float32)
+        c += (2e-5 * rng.normal(size=c.shape)).astype(np.float32)
+        q = np.full((Q, D), 1.0039136, np.float32) + (2e-5 * rng.normal(size=(Q, D))).astype(np.float32)
+    gi = b.IvfPqIndex(c, rng.normal(size=(1, 256, D)).astype(np.float32), np.arange(nlist + 1, dtype=np.int64),
+                      np.zeros((nlist, 1), dtype=np.uint8), metric=metric)
+    b.coarse_fallbacks(reset=True)
+    got = gi.coarse(torch.from_numpy(q).cuda(), 8)
+    torch.cuda.synchronize()
+    fb = b.coarse_fallbacks()
+    _same(got, oracle.coarse(q, c, 8, metric=metric), (nlist, D, what))
+    if what == "plain" and metric == 0:
+        assert fb <= Q // 20, f"{fb} of {Q} queries were not accepted from the proposal"
+    gi.close()

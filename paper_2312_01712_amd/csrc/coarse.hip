@@ -752,7 +752,7 @@ __device__ __forceinline__ int cs_hidx(uint32_t bin) { return (int)(((bin & 15u)
 
 // KIND CS_EXACT: `rows` holds the reference-order distances themselves (coarse_exact_tile_kernel):
 // the lists up to the bin of the nprobe-th are the answer once they are sorted; should they be
-// more than CS_CAND (masses of equal distances) or some of the row's values NaN, the wavefront picks the
+// more than CS_CAND (masses of equal distances) or not all finite, the wavefront picks the
 // nprobe smallest keys one after the other, so that no second kernel is needed.
 // KIND CS_FUSED: `rows` holds the key rows of coarse_gemm_top_kernel (nrow keys per query) instead of
 // the product's rows (nrow = nlist values); a key gives its list and, to 64 units in the last
@@ -821,11 +821,11 @@ __global__ __launch_bounds__(CS_WAVES * 64) void coarse_select_wave_kernel(
 
   // range of the row's proposal values
   float vmin = __builtin_inff(), vmax = -__builtin_inff();
-  bool nan = false;
+  float nonfinite = 0.0f;   // stays 0 unless a value is NaN or infinite (one instruction per value, where a comparison takes two)
   each([&](int p, uint32_t raw) __attribute__((always_inline)) {
     if (list_of(p, raw) < nlist) {
       const float v = value_of(raw);
-      if (EXACT) nan = nan || v != v;
+      if (EXACT) nonfinite = fmaf(v, 0.0f, nonfinite);
       vmin = fminf(vmin, v);
       vmax = fmaxf(vmax, v);
     }
@@ -906,8 +906,8 @@ __global__ __launch_bounds__(CS_WAVES * 64) void coarse_select_wave_kernel(
   for (int off = 32; off > 0; off >>= 1) rest_min = fminf(rest_min, __shfl_xor(rest_min, off));
   // (the inner product of an infinite centroid may be NaN: it stands in the first bin and is last in order,
   // so the cut may be short of the nprobe-th list; the proposals' acceptance test is never met then)
-  bool ok = count <= (uint32_t)CS_CAND && !(EXACT && __ballot(nan) != 0ull);
-  if (EXACT && !ok) {   // masses of equal distances, or NaN: the next smallest key, nprobe times
+  bool ok = count <= (uint32_t)CS_CAND && !(EXACT && __ballot(nonfinite != 0.0f) != 0ull);
+  if (EXACT && !ok) {   // masses of equal distances, or not all finite: the next smallest key, nprobe times
     unsigned long long last = 0ull;
     for (int p = 0; p < nprobe; ++p) {
       unsigned long long best = ~0ull;

@@ -415,7 +415,7 @@ __global__ __launch_bounds__(256) void coarse_exact_tile_kernel(const float *__r
   __shared__ __align__(16) float sc[XT_LISTS][XT_K + 4];
   __shared__ __align__(16) float sv[XT_Q][XT_K];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int c0 = blockIdx.x * XT_LISTS, q0 = blockIdx.y * XT_Q;
+  const int c0 = blockIdx.y * XT_LISTS, q0 = blockIdx.x * XT_Q;   // (few lists of few dimensions allow millions of queries: theirs is the long side of the grid)
   const int nq = Qn - q0 < XT_Q ? Qn - q0 : XT_Q;   // queries of this tile
   const int mine = nq > wave ? (nq - wave + 3) / 4 : 0;
   float acc[4] = {0.0f, 0.0f, 0.0f, 0.0f};
@@ -1076,7 +1076,7 @@ int launch_coarse(const ivfpq_index *ix, const float *d_queries, int64_t Q, int3
     // Few queries: the matrix product is all latency (8 tiles of 8 K slices for one query of the
     // 1M x 128 configuration), the re-ranking and the second line come on top.
     if (kprop <= CS_CAND / 2 && nlist <= 4096 && wave_lds <= 64 * 1024 && (int64_t)qn * nlist * D <= EXACT_TILE_WORK) {
-      const dim3 tiles((nlist + XT_LISTS - 1) / XT_LISTS, (qn + XT_Q - 1) / XT_Q);
+      const dim3 tiles((qn + XT_Q - 1) / XT_Q, (nlist + XT_LISTS - 1) / XT_LISTS);
       auto tile = ip ? (vec ? coarse_exact_tile_kernel<true, true> : coarse_exact_tile_kernel<false, true>)
                      : (vec ? coarse_exact_tile_kernel<true, false> : coarse_exact_tile_kernel<false, false>);
       hipLaunchKernelGGL(tile, tiles, dim3(256), 0, s, qm, ix->d_centroids, d_scratch, qn, nlist, D, nlist_pad);

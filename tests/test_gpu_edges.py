@@ -97,3 +97,23 @@ def test_split_product_bound(nlist, D, Q, what, metric):
     if what == "plain" and metric == 0:
         assert fb <= Q // 20, f"{fb} of {Q} queries were not accepted from the proposal"
     gi.close()
+
+
+@pytest.mark.parametrize("metric", [0, 1])
+def test_filtering_of_more_than_a_million_queries(metric):
+    """Few lists and dimensions leave a batch of millions within what is done without a matrix product:
+    65 536 tiles of 16 queries and one more."""
+    b = _binding()
+    rng = np.random.default_rng(3)
+    nlist, D, Q = 40, 3, 65_536 * 16 + 1
+    c = rng.normal(size=(nlist, D)).astype(np.float32)
+    some = rng.normal(size=(4096, D)).astype(np.float32)
+    q = torch.from_numpy(some).cuda().repeat(257, 1)[:Q].contiguous()
+    gi = b.IvfPqIndex(c, rng.normal(size=(1, 256, D)).astype(np.float32), np.arange(nlist + 1, dtype=np.int64),
+                      np.zeros((nlist, 1), dtype=np.uint8), metric=metric)
+    pid, pd = gi.coarse(q, 5)
+    o_pid, o_pd = oracle.coarse(some, c, 5, metric=metric)
+    _same((pid[:4096], pd[:4096]), (o_pid, o_pd), "first queries")
+    for got in (pid, pd.view(torch.int32)):
+        assert torch.equal(got, got[:4096].repeat(257, 1)[:Q])
+    gi.close()

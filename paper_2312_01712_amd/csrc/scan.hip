@@ -1034,14 +1034,17 @@ int launch_scan(const ivfpq_index *ix, const float *d_queries, int64_t Q, int32_
   }
   const int M = ix->M, ds = ix->dsub;
   const bool ip = ix->metric == IVFPQ_METRIC_IP;
+  const WideWorkspace *ww = view ? view->wide : nullptr;
+  const bool wide = ww && ww->total > 0 && k > KP && k <= 8 * KP && !dump && !ip && mode == 0 && !a.qmap;
   a.gbound = nullptr;
   if (d_probe_lb && !dump && !ip && !(a.ablate & 64)) {
     // Probes split over workgroups: with one list per workgroup and all workgroups resident at
     // once (two per CU) nobody ever has a bound before its list is scanned, and the list-level
     // bounds would be computed for nothing.  Otherwise the workgroups of a query share their
     // bounds (300 queries of 32 probes on the 1M x 128 configuration: 390 -> 88 us of scan, 76 with
-    // the kernel's later changes).
-    const bool split_once = nsplit > 1 && nsplit == nprobe && grid <= 512;
+    // the kernel's later changes).  The wide selection splits nothing: one workgroup walks a query's
+    // lists and needs the bounds (16 subspaces, 11 queries of 42 probes, k = 500: 87 us, 177 without).
+    const bool split_once = nsplit > 1 && nsplit == nprobe && grid <= 512 && !wide;
     if (view && view->gbound && nsplit > 1 && !split_once && k <= KP) a.gbound = view->gbound;
     if (!split_once) {
       if (!(view && view->bounds_ready))
@@ -1069,8 +1072,7 @@ int launch_scan(const ivfpq_index *ix, const float *d_queries, int64_t Q, int32_
   // k above KP in one pass (wide selection): chunks of queries share the slot arrays; each
   // chunk is scanned once with every key within the bound kept, sorted by wide_select_kernel,
   // and the queries that kernel could not finish go through the passes below.
-  const WideWorkspace *ww = view ? view->wide : nullptr;
-  if (ww && ww->total > 0 && k > KP && k <= 8 * KP && !dump && !ip && mode == 0 && !a.qmap) {
+  if (wide) {
     char *wb = view->wide_base;
     for (int64_t q0 = 0; q0 < Q; q0 += ww->q_chunk) {
       const int64_t qc = Q - q0 < ww->q_chunk ? Q - q0 : ww->q_chunk;

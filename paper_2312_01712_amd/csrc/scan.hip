@@ -52,15 +52,17 @@ __device__ inline void ip_thresholds(SP qm, int dsub, float r2, float &thr, floa
 }
 
 // 0 - q.c with acc = fmaf(q_i, c_i, acc), i ascending (the list term of a score).  The chain is
-// sequential; its loads are not: eight 16-byte ones are in flight at a time (one per step left a trip to
-// memory between every four products, 35 thousand clocks of a 200-dimensional query).
-template <typename SP>
+// sequential; its loads are not: BATCH 16-byte ones are in flight at a time (one per step left a trip to
+// memory between every four products, 35 thousand clocks of a 200-dimensional query).  Eight in the
+// specialised kernels; four in the run-time one, which has one look-up in flight and lives on its occupancy:
+// eight take 86 registers instead of 70 and leave two workgroups per CU where three fit (4000 queries of 24
+// probes, 30 subspaces of 4: 1540 us with eight, 1210 with four).
+template <int BATCH, typename SP>
 __device__ inline float neg_ip_chain(SP sq, const float *__restrict__ cen, int D) {
   float acc = 0.0f;
   int i = 0;
   if ((D & 3) == 0 && (reinterpret_cast<uintptr_t>(cen) & 15) == 0) {
-    constexpr int BATCH = 8;
-    for (; i + 4 * BATCH <= D; i += 4 * BATCH) {
+    for (; BATCH > 1 && i + 4 * BATCH <= D; i += 4 * BATCH) {
       float4 c[BATCH];
 #pragma unroll
       for (int b = 0; b < BATCH; ++b) c[b] = *reinterpret_cast<const float4 *>(cen + i + 4 * b);
@@ -295,7 +297,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4))) vo
       meta_row0[tid] = r0;
       meta_len[tid] = ok ? (int)(a.list_offsets[cc + 1] - r0) : 0;  // outside [0, nlist): an empty list
       meta_blk[tid] = ok ? a.list_blocks[cc] : 0;
-      meta_start[tid] = (ok && mode == 0) ? neg_ip_chain(sq, a.centroids + (int64_t)cc * D, D) : 0.0f;
+      meta_start[tid] = (ok && mode == 0) ? neg_ip_chain<(MT > 0 ? 8 : 4)>(sq, a.centroids + (int64_t)cc * D, D) : 0.0f;
     }
     __syncthreads();
     const int pn = p_end - p0 < META ? p_end - p0 : META;

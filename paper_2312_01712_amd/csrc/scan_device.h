@@ -520,16 +520,48 @@ __device__ __forceinline__ void lookup_group(const LDS float *, const CodeRegs<(
 __device__ __forceinline__ float acc_value(float a) { return a; }
 __device__ __forceinline__ float acc_value(uint32_t a) { return (float)a; }   // exact: sums of at most 2 M
 
-// (M: the subspaces in use, where MT only says how many 16-byte chunks there are; the last, short group
-// decides look-up by look-up, which is uniform over the wavefront.)
-template <int MT>
+// The last group where M, the subspaces in use, ends within it (MT only says how many 16-byte chunks of
+// codes there are): subspaces [G, M).  All eight look-ups go out together as in a whole group; those from M
+// on do not count.  Their codes are the zeros that pad a point, so a wavefront reads one word for all lanes,
+// from rows that do not exist: at most 6 KiB behind the table, where the kernels hold their other LDS.
+// A group's number is a constant: were it not, the codes would be indexed at run time and so live in scratch
+// memory, which every block would write and every short group read back, waiting for all loads in flight
+// (the empty asm, different for every group, keeps the compiler from making one of several).
+// (400k points, 6 subspaces of 1, 3000 queries of 24 probes: 535 us with the codes in scratch, 391 so.)
+template <int MT, int G>
+__device__ __forceinline__ void lookup_tail(const CodeRegs<((MT + 3) / 4 * 4) / 4> &r, int M, float &dist) {
+  float t[LOOKUP_GROUP];
+#pragma unroll
+  for (int j = 0; j < LOOKUP_GROUP; ++j) {
+    const uint32_t off = code_offset(r.w[(G + j) >> 2], (G + j) & 3);
+    t[j] = *(const LDS float *)(uintptr_t)(uint32_t)((G + j) * 1024 + off);
+  }
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int j = 0; j < LOOKUP_GROUP; ++j) dist += G + j < M ? t[j] : 0.0f;   // (no sum is below zero: + 0 leaves it)
+  asm volatile("" : "+v"(dist) : "n"(G));
+}
+// M lies in the last chunk, (MT - 16, MT], so only that chunk's two groups can end early.  True if the sum ends
+// with group G.
+template <int MT, int G>
+__device__ __forceinline__ bool last_group(const CodeRegs<((MT + 3) / 4 * 4) / 4> &r, int M, float &dist) {
+  if (G + 8 <= M) return false;
+  if (G < M) lookup_tail<MT, G>(r, M, dist);
+  return true;
+}
+
+// RT: M is a run-time value in (MT - 16, MT], otherwise it is MT.
+template <int MT, bool RT = false>
 __device__ inline float adc_sum(const LDS float *lut, const CodeRegs<((MT + 3) / 4 * 4) / 4> &r,
                                 float start = 0.0f, int M = MT) {
   float dist = start;
 #pragma unroll
   for (int h = 0; h < MT; h += LOOKUP_GROUP) {
-    if (h + LOOKUP_GROUP <= M || M == MT) lookup_group<MT>(lut, r, h, cmin(h + LOOKUP_GROUP, MT), dist);
-    else if (h < M) lookup_group<MT>(lut, r, h, M, dist);
+    if constexpr (RT) {
+      if (h == MT - 16 && last_group<MT, MT - 16>(r, M, dist)) return dist;
+      if (h == MT - 8 && last_group<MT, MT - 8>(r, M, dist)) return dist;
+    }
+    lookup_group<MT>(lut, r, h, cmin(h + LOOKUP_GROUP, MT), dist);
   }
   return dist;
 }
@@ -552,14 +584,15 @@ __device__ inline float adc_sum_bytes(const LDS float *lut, const CodeRegs<((MT 
 // bound; if none can, the rest of the block is skipped and false returned.  Points that
 // survive get exactly the sum adc_sum computes.  With `checks` off it is the plain sum.
 // (ACC: float for a table of distances, uint32_t for a byte table of penalties.)
-template <int MT, int M0, int M1, typename ACC>
+// (RT as in adc_sum.)
+template <int MT, int M0, int M1, bool RT, typename ACC>
 __device__ inline bool adc_part_exit(const LDS float *lut, const CodeRegs<((MT + 3) / 4 * 4) / 4> &r,
                                      const LDS float *suf, float tauf, bool checks, bool valid, ACC &dist, int M = MT) {
 #pragma unroll
   for (int g = M0; g < M1; g += 8) {
-    if (M != MT && g + 8 > M) {   // the last, short group (see adc_sum)
-      if (g < M) lookup_group<MT>(lut, r, g, M, dist);
-      return true;
+    if constexpr (RT) {
+      if (g == MT - 16 && last_group<MT, MT - 16>(r, M, dist)) return true;
+      if (g == MT - 8 && last_group<MT, MT - 8>(r, M, dist)) return true;
     }
     // requested ahead of the look-ups, so that it has arrived when they have
     float rest = 0.0f;

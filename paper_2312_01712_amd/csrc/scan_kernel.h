@@ -488,7 +488,7 @@ __device__ __forceinline__ void scan_query(const ScanArgs &a, const RadiiSq &r2,
           const int i = b * 64 + lane;
           const bool valid = i < len;
           if (DUMP) {
-            const float dist = BYTE ? adc_sum_bytes<MT>(lut, cur) : adc_sum<MT>(lut, cur, 0.0f, RT ? M : MT);
+            const float dist = BYTE ? adc_sum_bytes<MT>(lut, cur) : adc_sum<MT, RT>(lut, cur, 0.0f, M);
             if (valid) {
               a.all_dist[dump_pos + i] = dist;
               a.all_ids[dump_pos + i] = a.ids[row0 + i];
@@ -510,16 +510,16 @@ __device__ __forceinline__ void scan_query(const ScanArgs &a, const RadiiSq &r2,
             // half); most blocks end in an early part, and a part that was not fetched ahead
             // is fetched when a block turns out to need it.
             if constexpr (QUARTER_OK) {
-              if (!adc_part_exit<MT, 0, 16>(lut, cur, ssuf, tauf, prune, valid, dist, RT ? M : MT)) continue;
+              if (!adc_part_exit<MT, 0, 16, RT>(lut, cur, ssuf, tauf, prune, valid, dist, M)) continue;
               if (depth == 2) load_part(c1, cH, base, nb, b, cur);
-              if (!adc_part_exit<MT, 16, MH>(lut, cur, ssuf, tauf, prune, valid, dist, RT ? M : MT)) continue;
+              if (!adc_part_exit<MT, 16, MH, RT>(lut, cur, ssuf, tauf, prune, valid, dist, M)) continue;
             } else if constexpr (HALF_OK) {
-              if (!adc_part_exit<MT, 0, MH>(lut, cur, ssuf, tauf, prune, valid, dist, RT ? M : MT)) continue;
+              if (!adc_part_exit<MT, 0, MH, RT>(lut, cur, ssuf, tauf, prune, valid, dist, M)) continue;
             }
             if constexpr (HALF_OK) {
               if (depth >= 1) load_part(cH, cE, base, nb, b, cur);
             }
-            if (!adc_part_exit<MT, HALF_OK ? MH : 0, MT>(lut, cur, ssuf, tauf, prune, valid, dist, RT ? M : MT)) continue;
+            if (!adc_part_exit<MT, HALF_OK ? MH : 0, MT, RT>(lut, cur, ssuf, tauf, prune, valid, dist, M)) continue;
             ++full;
             wave_offer(st, acc_value(dist), valid, row0 + i, a.ids, qd, qid, lane, a.k, sh);
           }
@@ -572,6 +572,7 @@ int launch_scan_t(const ScanArgs &a, const RadiiSq &r2, int64_t grid, bool dump,
   const size_t lds = (size_t)(lut_bytes > stage ? lut_bytes : stage) + 2 * ((a.D * 4 + 15) & ~15) +
                      (size_t)NW * 64 * 12 + ((4 * (2 * NW + 4) + 15) & ~15) + 64 * 28 + 5 * IVFPQ_MAX_M * 4 +
                      (size_t)NW * SUF_SLOTS * 4 + 16;
+  static_assert(NW * 64 * 12 + 64 * 28 + 5 * IVFPQ_MAX_M * 4 >= 7 * 1024, "lookup_tail reads at most seven rows behind the table");
   if (lds > (size_t)LDS_PER_CU) {
     ivfpq::set_error("scan: %zu bytes of LDS needed, 163840 available", lds);
     return IVFPQ_ERR_UNSUPPORTED;

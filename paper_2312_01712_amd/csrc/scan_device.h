@@ -291,9 +291,14 @@ __device__ inline float4 lut_entry4(const float (&res)[DSUB > 0 ? DSUB : 1], con
 }
 
 // The same for any dimension dsub of the subspaces, for rows m0, m0 + step, ... of the codebook, read
-// from global memory: emit(m, four entries of this lane).  With dsub 1, 2, 4 or 8 a lane's entries are
-// whole 16-byte pieces.  (Requesting the next row before a row is worked on gains nothing: the other
-// wavefronts cover the latency, and the registers spill.)
+// from global memory: emit(m, four entries of this lane, whether they are strided).  With dsub 1, 2, 4 or 8
+// a lane's entries 4 lane .. 4 lane + 3 are whole 16-byte pieces.  (Requesting the next row before a row is
+// worked on gains nothing: the other wavefronts cover the latency, and the registers spill.)
+// Any other dsub: entries lane, 64 + lane, 128 + lane and 192 + lane, one after the other, in loads of 16 or
+// 8 bytes where dsub is a multiple of 4 or 2, so that a wavefront reads a quarter row at a time from end
+// to end.  Four consecutive entries per lane in 4-byte loads touched the whole row with every load, and a
+// CU's rows together are far beyond its cache: 3000 queries of 24 probes, 10 subspaces of 6 1610 us,
+// 637 so; of 12 3592 and 709; of 9 1929 and 1387; of 3 678 and 611.
 template <int MODE, typename SP, typename F>
 __device__ __forceinline__ void lut_rows_rt(SP sres, SP sr2, const float *__restrict__ codebooks, int m0, int M, int step,
                                             int dsub, int lane, F emit) {
@@ -308,30 +313,44 @@ __device__ __forceinline__ void lut_rows_rt(SP sres, SP sr2, const float *__rest
       for (int x = 0; x < DS; ++x) ev[x] = load_f4(row, (uint32_t)((lane * DS + x) * 16));
 #pragma unroll
       for (int j = 0; j < DS; ++j) res[j] = sres[m * DS + j];
-      emit(m, lut_entry4<DS, MODE>(res, ev, sr2[m]));
+      emit(m, lut_entry4<DS, MODE>(res, ev, sr2[m]), std::false_type{});
     }
   };
   if (dsub == 4) return wide(std::integral_constant<int, 4>{});
   if (dsub == 2) return wide(std::integral_constant<int, 2>{});
   if (dsub == 1) return wide(std::integral_constant<int, 1>{});
   if (dsub == 8) return wide(std::integral_constant<int, 8>{});
+  auto strided = [&](auto ws) __attribute__((always_inline)) {
+    constexpr int W = decltype(ws)::value;   // floats per load: what dsub keeps every entry aligned to
+    typedef float vecW __attribute__((ext_vector_type(W)));
 #pragma unroll 1
-  for (int m = m0; m < M; m += step) {
-    const GLOBAL uint8_t *row = uniform_ptr(codebooks + (int64_t)m * 256 * dsub);
-    float d2[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll 4
-    for (int j = 0; j < dsub; ++j) {
-      const float res = sres[m * dsub + j];
+    for (int m = m0; m < M; m += step) {
+      const GLOBAL uint8_t *row = uniform_ptr(codebooks + (int64_t)m * 256 * dsub);
+      const float r2 = sr2[m];
+      float v[4];
 #pragma unroll
       for (int x = 0; x < 4; ++x) {
-        const float t = res - *reinterpret_cast<const GLOBAL float *>(row + (uint32_t)(((4 * lane + x) * dsub + j) * 4));
-        d2[x] = fmaf(t, t, d2[x]);   // (from 0: the first term is t * t rounded once either way)
+        const GLOBAL uint8_t *src = row + (int64_t)x * 64 * dsub * 4;
+        float d2 = 0.0f;
+#pragma unroll 4
+        for (int j = 0; j < dsub; j += W) {
+          const vecW e = *reinterpret_cast<const GLOBAL vecW *>(src + (uint32_t)((lane * dsub + j) * 4));
+#pragma unroll
+          for (int w = 0; w < W; ++w) {
+            float ew;
+            if constexpr (W == 1) ew = e[0]; else ew = e[w];
+            const float t = sres[m * dsub + j + w] - ew;
+            d2 = fmaf(t, t, d2);   // (from 0: the first term is t * t rounded once either way)
+          }
+        }
+        v[x] = table_value<MODE>(d2, r2);
       }
+      emit(m, make_float4(v[0], v[1], v[2], v[3]), std::true_type{});
     }
-    const float r2 = sr2[m];
-    emit(m, make_float4(table_value<MODE>(d2[0], r2), table_value<MODE>(d2[1], r2), table_value<MODE>(d2[2], r2),
-                        table_value<MODE>(d2[3], r2)));
-  }
+  };
+  if ((dsub & 3) == 0) strided(std::integral_constant<int, 4>{});
+  else if ((dsub & 1) == 0) strided(std::integral_constant<int, 2>{});
+  else strided(std::integral_constant<int, 1>{});
 }
 
 }  // namespace

@@ -420,8 +420,15 @@ __device__ __forceinline__ void scan_query(const ScanArgs &a, const RadiiSq &r2,
       };
       // run-time shapes: a row at a time, its minima over 16 lanes straight to LDS
       [[maybe_unused]] auto build_rows_rt = [&](auto mode_tag) __attribute__((always_inline)) {
-        lut_rows_rt<decltype(mode_tag)::value>(sres, sr2, a.codebooks, wave, M, NW, a.dsub, lane, [&](int m, float4 v) __attribute__((always_inline)) {
-          *(LDS floatx4 *)(lut + m * 256 + 4 * lane) = floatx4{v.x, v.y, v.z, v.w};
+        lut_rows_rt<decltype(mode_tag)::value>(sres, sr2, a.codebooks, wave, M, NW, a.dsub, lane, [&](int m, float4 v, auto strided) __attribute__((always_inline)) {
+          if constexpr (decltype(strided)::value) {
+            lut[m * 256 + lane] = v.x;
+            lut[m * 256 + 64 + lane] = v.y;
+            lut[m * 256 + 128 + lane] = v.z;
+            lut[m * 256 + 192 + lane] = v.w;
+          } else {
+            *(LDS floatx4 *)(lut + m * 256 + 4 * lane) = floatx4{v.x, v.y, v.z, v.w};
+          }
           if (!DUMP && prune) {
             uint32_t lo = umin32(umin32(__float_as_uint(v.x), __float_as_uint(v.y)), umin32(__float_as_uint(v.z), __float_as_uint(v.w)));
             lo = umin32(lo, xor_u32<1, true>(lo));

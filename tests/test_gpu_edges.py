@@ -117,3 +117,21 @@ def test_filtering_of_more_than_a_million_queries(metric):
     for got in (pid, pd.view(torch.int32)):
         assert torch.equal(got, got[:4096].repeat(257, 1)[:Q])
     gi.close()
+
+
+@pytest.mark.parametrize("M,dsub", [(2, 10), (3, 12), (5, 7), (7, 9), (9, 16), (17, 14), (33, 20), (65, 11), (1, 40)])
+@pytest.mark.parametrize("mode", [0, 1, 2])
+def test_run_time_dimension_of_the_subspaces(M, dsub, mode):
+    """Codebook rows in loads of 4, 8 and 16 bytes: dsub odd, even and a multiple of 4, beyond the ones
+    whose entries are whole 16-byte pieces; short last groups of every kind of length."""
+    b = _binding()
+    rng = np.random.default_rng(M * 100 + dsub)
+    D = M * dsub
+    idx = _index(rng, D, M, np.array([0, 1, 64, 65, 700, 300, 129, 1000, 63, 400]))
+    q = (idx.centroids[rng.integers(0, 10, 40)] + 0.3 * rng.normal(size=(40, D))).astype(np.float32)
+    radii = np.full(M, 0.45 * np.sqrt(dsub), dtype=np.float32)
+    gi = b.IvfPqIndex.from_index(idx)
+    for Q, nprobe, k in ((40, 6, 10), (2, 9, 128), (40, 9, 300)):
+        _same(gi.search(torch.from_numpy(q[:Q]).cuda(), nprobe, k, radii, mode=mode),
+              oracle.search(q[:Q], idx, nprobe, k, radii, threads=8, mode=mode), (M, dsub, k))
+    gi.close()

@@ -320,6 +320,7 @@ __device__ __forceinline__ void lut_rows_rt(SP sres, SP sr2, const float *__rest
   if (dsub == 2) return wide(std::integral_constant<int, 2>{});
   if (dsub == 1) return wide(std::integral_constant<int, 1>{});
   if (dsub == 8) return wide(std::integral_constant<int, 8>{});
+  if (dsub == 3) return wide(std::integral_constant<int, 3>{});
   auto strided = [&](auto ws) __attribute__((always_inline)) {
     constexpr int W = decltype(ws)::value;   // floats per load: what dsub keeps every entry aligned to
     typedef float vecW __attribute__((ext_vector_type(W)));

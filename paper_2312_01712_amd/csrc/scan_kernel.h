@@ -590,7 +590,11 @@ int launch_scan_t(const ScanArgs &a, const RadiiSq &r2, int64_t grid, bool dump,
   if constexpr (DSUB != 0)   // (the shapes the list-major scan hands queries over for)
     if (kind == SCAN_MAPPED) {
       kern = scan_kernel<MT, DSUB, NW, SCAN_MAPPED, BYTE>;
-      if (grid > 512) grid = 512;   // two per CU
+      // as many as the chip holds at once: what a CU's LDS and its SIMDs' registers allow (four of the
+      // 16-subspace kernel: MAPPED16)
+      const int64_t waves = 4 * scan_wpe(BYTE ? (MT + 3) / 4 : MT, NW) / NW, fit = LDS_PER_CU / (int64_t)lds;
+      const int64_t room = 256 * (waves < 1 ? 1 : (waves < fit ? waves : fit));
+      if (grid > room) grid = room;
     }
   static std::atomic<uint64_t> prepared[4];
   if (int rc = prepare_kernel(kern, prepared[kind])) return rc;

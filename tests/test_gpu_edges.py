@@ -135,3 +135,51 @@ def test_run_time_dimension_of_the_subspaces(M, dsub, mode):
         _same(gi.search(torch.from_numpy(q[:Q]).cuda(), nprobe, k, radii, mode=mode),
               oracle.search(q[:Q], idx, nprobe, k, radii, threads=8, mode=mode), (M, dsub, k))
     gi.close()
+
+
+def _rounds(q, idx, pid, k, radii, mode, first_probes, cap):
+    """How the list-major scan sees each query: overflows in the first round of its main pass (probes 1 to
+    first_probes, filtered by the k-th distance of the nearest list), only in the second (the other
+    probes, filtered by the k-th distance so far), or never."""
+    offs, dist, _ = oracle.scan_all(q, idx, pid, radii, mode=mode)
+    lens = np.diff(idx.list_offsets)[pid]
+    out = []
+    for i in range(q.shape[0]):
+        d, ends = dist[offs[i]:offs[i + 1]], np.concatenate([[0], np.cumsum(lens[i])])
+        head, near = d[:ends[1]], d[:ends[1 + first_probes]]
+        tau = np.sort(head)[k - 1] if head.size >= k else np.inf
+        if (near[ends[1]:] <= tau).sum() > cap:
+            out.append("first")
+            continue
+        tau = np.sort(near)[k - 1] if near.size >= k else np.inf
+        out.append("second" if (d[ends[1 + first_probes]:] <= tau).sum() > cap else "never")
+    return out
+
+
+@pytest.mark.parametrize("D,M", [(96, 48), (128, 64), (64, 16)])
+@pytest.mark.parametrize("mode", [0, 1, 2])
+def test_candidates_that_overflow_in_either_round(D, M, mode):
+    """Enough probes for two rounds of the list-major main pass and candidate buffers of 64 slots: queries
+    that overflow in the first round stay out of the second and are still redone, like those that overflow
+    in the second; over 4096 queries, so that the redoing workgroups serve several queries each."""
+    b = _binding()
+    rng = np.random.default_rng(M + mode)
+    nlist, k, cap, nprobe, distinct = 70, 10, 64, 52, 200
+    idx = _index(rng, D, M, rng.integers(40, 260, size=nlist), centre=0.04)
+    q = (idx.centroids[rng.integers(0, nlist, distinct)] + 0.25 * rng.normal(size=(distinct, D))).astype(np.float32)
+    q[::3] = idx.centroids[rng.integers(0, nlist, len(q[::3]))]
+    radii = np.full(M, (0.6 if mode == 0 else 0.45) * np.sqrt(D / M), dtype=np.float32)
+    want = oracle.search(q, idx, nprobe, k, radii, threads=8, mode=mode)
+    pid, _ = oracle.coarse(q, idx.centroids, nprobe)
+    kinds = _rounds(q, idx, pid, k, radii, mode, 7, cap)
+    assert min(kinds.count(x) for x in ("first", "second", "never")) >= 3, {x: kinds.count(x) for x in set(kinds)}
+    gi = b.IvfPqIndex.from_index(idx)
+    try:
+        b.set_option("lm_cap", cap)
+        for reps in (1, 22):
+            Q = distinct * reps
+            got = gi.search(torch.from_numpy(q).cuda().repeat(reps, 1), nprobe, k, radii, mode=mode, strategy=b.SCAN_LIST_MAJOR)
+            _same(got, (np.tile(want[0], (reps, 1)), np.tile(want[1], (reps, 1))), (D, M, mode, Q))
+    finally:
+        b.set_option("lm_cap", 0)
+        gi.close()

@@ -140,6 +140,8 @@ struct ScanView {
   const WideWorkspace *wide;  // NULL: k above 128 is produced pass by pass
   char *wide_base;            // device base of the wide selection's part of the workspace
   uint32_t *gbound;           // [Q] scratch for the bounds that the workgroups of a query share, or NULL
+  const int32_t *qlist;       // device: only these queries are served, or NULL (shapes of the list-major scan) ...
+  int32_t *qlist_n;           // ... [2] how many they are, and 0: how many have been taken up
 };
 int launch_scan(const ivfpq_index *ix, const float *d_queries, int64_t Q, int32_t nprobe,
                 const int32_t *d_probe_ids, int32_t k, const RadiiSq &r2, int32_t nsplit,
@@ -152,9 +154,9 @@ int launch_probe_bounds(const ivfpq_index *ix, const float *d_queries, int64_t Q
                         float *d_probe_lb, hipStream_t s, int32_t *d_zero = nullptr, int64_t zero_n = 0);
 // ---- list-major batched scan (scan_lm.hip) --------------------------------------------------
 struct LmWorkspace {      // offsets into the list-major part of the workspace, 256-byte aligned
-  size_t cnt, base;       // [nlist], [nlist+1] int32
+  size_t cnt, base;       // [nlist+2], [nlist+1] int32
   size_t pairs;           // [pairs_cap] (query, list) int32 pairs bucketed by list
-  size_t rank;            // [pairs_cap] int32: a pair's position among the pairs of its list
+  size_t rank;            // [pairs_cap] int32: a pair's position among the pairs of its list; behind the main pass the queries to redo
   size_t gcnt, qmap;      // [Q] uint32 / int32
   size_t qmap_head;       // [Q] int32
   size_t cand;            // [Q][cap] (distance bits, row) candidates of the list-major scan

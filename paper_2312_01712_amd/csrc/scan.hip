@@ -997,7 +997,8 @@ int launch_scan(const ivfpq_index *ix, const float *d_queries, int64_t Q, int32_
   a.codebooks = ix->d_codebooks;
   a.probe_lb = nullptr;
   a.qmap = view ? view->qmap : nullptr;
-  a.nq = Q;
+  a.qlist = view ? view->qlist : nullptr;
+  a.qlist_n = view ? view->qlist_n : nullptr;
   a.probe_stride = (view && view->probe_stride > 0) ? view->probe_stride : nprobe;
   a.list_box = ix->d_box;
   a.list_offsets = ix->d_list_offsets;
@@ -1079,7 +1080,6 @@ int launch_scan(const ivfpq_index *ix, const float *d_queries, int64_t Q, int32_
     for (int64_t q0 = 0; q0 < Q; q0 += ww->q_chunk) {
       const int64_t qc = Q - q0 < ww->q_chunk ? Q - q0 : ww->q_chunk;
       ScanArgs c = a;
-      c.nq = qc;
       c.queries = d_queries + q0 * ix->D;
       c.probe_ids = d_probe_ids + q0 * a.probe_stride;
       if (a.probe_lb) c.probe_lb = a.probe_lb + q0 * a.probe_stride;
@@ -1105,6 +1105,8 @@ int launch_scan(const ivfpq_index *ix, const float *d_queries, int64_t Q, int32_
       rest.wide = nullptr;
       rest.wide_base = nullptr;
       rest.gbound = nullptr;
+      rest.qlist = nullptr;
+      rest.qlist_n = nullptr;
       if (int rc = launch_scan(ix, c.queries, qc, nprobe, c.probe_ids, k, r2, 1, nullptr, nullptr, c.out_ids, c.out_dist,
                                nullptr, nullptr, nullptr, nullptr, mode, c.query_radii,
                                a.probe_lb ? d_probe_lb + q0 * a.probe_stride : nullptr, s, &rest))

@@ -364,8 +364,9 @@ struct ScanArgs {
   const float *centroids;       // [nlist][D]
   const float *codebooks;       // [M][256][dsub]
   const float *probe_lb;        // [Q][probe_stride] lower bound on the distance of any point of the probed list, or NULL
-  const int32_t *qmap;          // [nq] or NULL: a query with a negative entry is left out
-  int64_t nq;                   // queries of this launch
+  const int32_t *qmap;          // [Q] or NULL: a query with a negative entry is left out
+  const int32_t *qlist;         // the queries to serve, or NULL: all
+  int32_t *qlist_n;             // [2] how many they are; 0 at first: how many have been taken up beyond one per workgroup
   const float *list_box;        // [nlist][M][2][dsub] per list and subspace the bounding box of the entries in use
   const int64_t *list_offsets;  // [nlist+1]
   const int64_t *list_blocks;   // [nlist+1]

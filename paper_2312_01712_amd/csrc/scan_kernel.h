@@ -41,11 +41,12 @@ namespace {
 // KIND: SCAN_ALL writes every candidate's distance instead of a top-k; SCAN_SPLIT is the form in
 // which several workgroups share a query's probes (its exchange of bounds costs registers that the
 // plain form spills for: 7 % on lists of 8000 points).
-// SCAN_MAPPED serves the queries that a query map names (usually none): few workgroups, each of which
-// looks up to 64 of the map's entries over at a time.  One workgroup per query that looks at its entry and
-// leaves takes 16 us per 10 000 queries, a trip to memory for every 512 of them, this form 9 us for any
-// number; below about 4000 queries the plain form is as fast.
-enum { SCAN_TOPK = 0, SCAN_ALL = 1, SCAN_SPLIT = 2, SCAN_MAPPED = 3 };
+// SCAN_LISTED serves the queries of a list that a kernel before it made (usually none): as many workgroups as
+// the chip holds at once, each of which takes the next entry when it is done with one.  10 000 queries of 16
+// subspaces, nearly all of them named: 4820 us a batch; 5118 where every workgroup serves the named ones among
+// a fixed share of the batch, 6590 with half as many workgroups.  None named: a workgroup per query of the batch
+// that looks whether it is takes 16 us, this form and the kernel that makes the list 6.
+enum { SCAN_TOPK = 0, SCAN_ALL = 1, SCAN_SPLIT = 2, SCAN_LISTED = 3 };
 template <int MT, int DSUB, int NW, int KIND, bool BYTE>
 __device__ __forceinline__ void scan_query(const ScanArgs &a, const RadiiSq &r2, int64_t q, int split) {
   constexpr bool DUMP = KIND == SCAN_ALL, SPLIT = KIND == SCAN_SPLIT;
@@ -81,7 +82,9 @@ __device__ __forceinline__ void scan_query(const ScanArgs &a, const RadiiSq &r2,
   LDS float *sr2 = meta_lb + META;  // [M] r_m^2 of this query
   LDS uint32_t *srmin = (LDS uint32_t *)(sr2 + IVFPQ_MAX_M);  // [M][4] partial minima (bit patterns) of each row of the current table
 
-  int tid = threadIdx.x, lane = tid & 63;
+  int tid = threadIdx.x;
+  if (KIND == SCAN_LISTED) asm volatile("" : "+v"(tid));   // (addresses formed anew for every query: kept across queries, they spill)
+  int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform, kept in a scalar register
   LDS float *ssuf = (LDS float *)(srmin + 4 * IVFPQ_MAX_M) + wave * SUF_SLOTS;  // this wavefront's suffix sums of srmin, per 8 subspaces
   LDS uint32_t *stat = (LDS uint32_t *)((LDS float *)(srmin + 4 * IVFPQ_MAX_M) + NW * SUF_SLOTS);  // blocks scanned / scanned to the end
@@ -89,7 +92,7 @@ __device__ __forceinline__ void scan_query(const ScanArgs &a, const RadiiSq &r2,
   const int p_end = SPLIT ? (int)((int64_t)a.nprobe * (split + 1) / a.nsplit) : a.nprobe;
   const int32_t *probes = a.probe_ids + q * a.probe_stride;
   // with a query map only the queries it names are served (uniform over the workgroup)
-  if (KIND != SCAN_MAPPED && a.qmap && a.qmap[q] < 0) return;
+  if (a.qmap && a.qmap[q] < 0) return;
   // Bound on the query's k-th distance from the workgroups that serve its other probe groups, as
   // its complement (0: none yet).  Any workgroup's own bound is an upper bound on the final k-th
   // distance, so the smallest of them is one too, and a late value is only looser.
@@ -558,15 +561,18 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(scan_wp
     // come first, so that the bounds they publish (a.gbound) are there when most of the others start.
     const int nq = gridDim.x / a.nsplit;
     scan_query<MT, DSUB, NW, KIND, BYTE>(a, r2, blockIdx.x % nq, blockIdx.x / nq);
-  } else if constexpr (KIND == SCAN_MAPPED) {
-    const int lane = threadIdx.x & 63;
-    for (int64_t q0 = blockIdx.x; q0 < a.nq; q0 += (int64_t)gridDim.x * 64) {
-      const int64_t mine = q0 + (int64_t)lane * gridDim.x;
-      unsigned long long named = __ballot(mine < a.nq && a.qmap[mine < a.nq ? mine : 0] >= 0);   // the same in every wavefront
-      for (; named != 0ull; named &= named - 1ull) {
-        scan_query<MT, DSUB, NW, KIND, BYTE>(a, r2, q0 + (int64_t)(__ffsll((long long)named) - 1) * gridDim.x, 0);
-        __syncthreads();   // the LDS is free for the next query
-      }
+  } else if constexpr (KIND == SCAN_LISTED) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    LDS int *shared_next = (LDS int *)smem;   // the table's first word: free between two queries
+    const int n = a.qlist_n[0];
+    for (int i = blockIdx.x; i < n;) {
+      int next = n;
+      if (threadIdx.x == 0 && n > (int)gridDim.x) next = (int)gridDim.x + atomicAdd(a.qlist_n + 1, 1);   // arrives during the query
+      scan_query<MT, DSUB, NW, KIND, BYTE>(a, r2, a.qlist[i], 0);
+      __syncthreads();
+      if (threadIdx.x == 0) *shared_next = next;
+      __syncthreads();
+      i = __builtin_amdgcn_readfirstlane(*shared_next);
     }
   } else {
     scan_query<MT, DSUB, NW, KIND, BYTE>(a, r2, blockIdx.x, 0);
@@ -584,14 +590,13 @@ int launch_scan_t(const ScanArgs &a, const RadiiSq &r2, int64_t grid, bool dump,
     ivfpq::set_error("scan: %zu bytes of LDS needed, 163840 available", lds);
     return IVFPQ_ERR_UNSUPPORTED;
   }
-  const int kind = dump ? SCAN_ALL : (a.nsplit > 1 ? SCAN_SPLIT : (a.qmap && DSUB != 0 && grid > 4096 ? SCAN_MAPPED : SCAN_TOPK));
+  const int kind = dump ? SCAN_ALL : (a.nsplit > 1 ? SCAN_SPLIT : (a.qlist ? SCAN_LISTED : SCAN_TOPK));
   auto kern = kind == SCAN_ALL ? scan_kernel<MT, DSUB, NW, SCAN_ALL, BYTE>
                                : (kind == SCAN_SPLIT ? scan_kernel<MT, DSUB, NW, SCAN_SPLIT, BYTE> : scan_kernel<MT, DSUB, NW, SCAN_TOPK, BYTE>);
-  if constexpr (DSUB != 0)   // (the shapes the list-major scan hands queries over for)
-    if (kind == SCAN_MAPPED) {
-      kern = scan_kernel<MT, DSUB, NW, SCAN_MAPPED, BYTE>;
-      // as many as the chip holds at once: what a CU's LDS and its SIMDs' registers allow (four of the
-      // 16-subspace kernel: MAPPED16)
+  if constexpr (DSUB != 0 && MT <= 64)   // (the shapes the list-major scan hands queries over for)
+    if (kind == SCAN_LISTED) {
+      kern = scan_kernel<MT, DSUB, NW, SCAN_LISTED, BYTE>;
+      // as many as the chip holds at once: what a CU's LDS and its SIMDs' registers allow
       const int64_t waves = 4 * scan_wpe(BYTE ? (MT + 3) / 4 : MT, NW) / NW, fit = LDS_PER_CU / (int64_t)lds;
       const int64_t room = 256 * (waves < 1 ? 1 : (waves < fit ? waves : fit));
       if (grid > room) grid = room;

@@ -54,13 +54,14 @@ struct LmArgs {
   const int64_t *ids;           // [N]
   int64_t *out_ids;             // [Q][k]: phase A's top-k on entry to the merge, the result after it
   float *out_dist;              // [Q][k]
-  int32_t *cnt;                 // [nlist] pairs per list
+  int32_t *cnt;                 // [nlist] pairs per list; then [2]: queries to be redone, and those of them taken up
   int32_t *rank;                // [max(Q, Q*(nprobe-first))] position of a pair among its list's pairs, -1: no pair
   int32_t *base;                // [nlist+1] first pair slot of a list (ranges padded to whole groups); [nlist] = slots in use
   int2 *pairs;                  // [Q*(nprobe-first) + (LMB_G - 1) nlist] (query, list); query -1 pads a list's range
   uint32_t *gcnt;               // [Q] candidates appended (may run past cap: the query then counts as overflowed)
   uint2 *cand;                  // [Q][cap] (distance bits, row in the index)
-  int32_t *qmap;                // [Q] out: q for a query to be redone query-major, -1 otherwise
+  int32_t *qmap;                // [Q] q for a query to be redone query-major, -1 otherwise
+  int32_t *redo;                // [Q] those queries, in any order (the place of rank)
   int32_t *qmap_head;           // [Q] head pass: q for a query whose nearest list is left to the query-major kernel, else -1
   int32_t head_max;             // head pass: longest list (points) whose distances fit the workgroup's LDS
   const float *query_radii;     // [Q][M] or NULL
@@ -1266,6 +1267,20 @@ int lm_head_max(int M, int D) {
 }
 size_t lm_head_lds(int M, int D) { return lm_fixed_lds(M, D) + (size_t)LM_G * lm_head_max(M, D) * 4 + LM_SEL_WORDS * 4 + LM_G * LM_BINS * 4; }
 
+// The queries that qmap names, as a list.  (One atomic per wavefront of 64 queries: one per query, from
+// lm_merge_kernel, took 110 us where all of 10 000 are named.)
+__global__ __launch_bounds__(256) void lm_redo_kernel(LmArgs a) {
+  const int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  const int lane = threadIdx.x & 63;
+  const bool named = q < a.Q && a.qmap[q] >= 0;
+  const unsigned long long bal = __ballot(named);
+  if (bal == 0ull) return;
+  int first = 0;
+  if (lane == 0) first = atomicAdd(&a.cnt[a.nlist], __popcll(bal));
+  first = __builtin_amdgcn_readfirstlane(first);
+  if (named) a.redo[first + __popcll(bal & ((1ull << lane) - 1ull))] = (int32_t)q;
+}
+
 template <int MT, int DSUB, bool HEAD>
 int launch_lm_scan_t(const LmArgs &a, const RadiiSq &r2, int grid, hipStream_t s) {
   auto kern = lm_scan_kernel<MT, DSUB, HEAD>;
@@ -1332,7 +1347,7 @@ LmWorkspace plan_list_major(const ivfpq_index *ix, int64_t Q, int32_t nprobe) {
   if (w.cap == 0) w.cap = nprobe >= 64 ? 16384 : (nprobe * 256 > 4096 ? nprobe * 256 : 4096);
   w.pairs_cap = Q * (nprobe - w.first > 1 ? nprobe - w.first : 1) + (int64_t)(LMB_G - 1) * ix->nlist;   // also holds the head pass's Q pairs
   size_t off = 0;
-  w.cnt = off;   off += lm_align((size_t)ix->nlist * 4);
+  w.cnt = off;   off += lm_align(((size_t)ix->nlist + 2) * 4);
   w.base = off;  off += lm_align(((size_t)ix->nlist + 1) * 4);
   w.pairs = off; off += lm_align((size_t)w.pairs_cap * 8);
   w.rank = off;  off += lm_align((size_t)w.pairs_cap * 4);
@@ -1367,6 +1382,7 @@ int launch_scan_list_major(const ivfpq_index *ix, const float *d_queries, int64_
   a.out_dist = d_out_dist;
   a.cnt = reinterpret_cast<int32_t *>(lm_base + w.cnt);
   a.rank = reinterpret_cast<int32_t *>(lm_base + w.rank);
+  a.redo = a.rank;
   a.base = reinterpret_cast<int32_t *>(lm_base + w.base);
   a.pairs = reinterpret_cast<int2 *>(lm_base + w.pairs);
   a.gcnt = reinterpret_cast<uint32_t *>(lm_base + w.gcnt);
@@ -1387,7 +1403,7 @@ int launch_scan_list_major(const ivfpq_index *ix, const float *d_queries, int64_
   // list-level lower bounds of every (query, probe); the same launch clears the per-list counts
   // (lm_offsets_kernel leaves them clear for the pass after it)
   int rc = launch_probe_bounds(ix, d_queries, Q, nprobe, d_probe_ids, r2, mode, d_query_radii, d_probe_lb, s, a.cnt,
-                               ix->nlist);
+                               (int64_t)ix->nlist + 2);
   if (rc) return rc;
 
   int dev = 0, cus = 0;
@@ -1445,7 +1461,8 @@ int launch_scan_list_major(const ivfpq_index *ix, const float *d_queries, int64_
   }
   IVFPQ_HIP_TRY(hipGetLastError());
   // queries whose candidate buffer overflowed: the query-major kernel over all of their probes
-  ScanView redo = {0, a.qmap, true};
+  ScanView redo = {0, nullptr, true, nullptr, nullptr, nullptr, a.redo, a.cnt + ix->nlist};
+  hipLaunchKernelGGL(lm_redo_kernel, dim3((unsigned)((Q + 255) / 256)), dim3(256), 0, s, a);
   return launch_scan(ix, d_queries, Q, nprobe, d_probe_ids, k, r2, 1, nullptr, nullptr, d_out_ids, d_out_dist,
                      nullptr, nullptr, nullptr, nullptr, mode, d_query_radii, d_probe_lb, s, &redo);
 }

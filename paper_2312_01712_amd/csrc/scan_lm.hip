@@ -688,7 +688,9 @@ __global__ __launch_bounds__(LM_NW * 64) __attribute__((amdgpu_waves_per_eu(LM_N
 constexpr int LMB_NW = 16;      // wavefronts: one workgroup per CU (the table takes 2 KiB per subspace), 4 per SIMD
 constexpr int LMB_QUEUE = 3072; // candidates a task can hold; a query that loses one is redone query-major
 constexpr int LMB_TOP = 63;
-constexpr int LMB_SETTLE = LMB_NW * 16;   // candidates settled at a time: four lanes each
+// Lanes that settle a candidate together, 16 subspaces each; candidates settled at a time.
+constexpr int lmb_lanes(int mt) { return mt > 16 ? 4 : 1; }
+constexpr int lmb_settle(int mt) { return LMB_NW * 64 / lmb_lanes(mt); }
 
 typedef uint16_t ushortx2 __attribute__((ext_vector_type(2)));
 typedef uint32_t uintx2 __attribute__((ext_vector_type(2)));
@@ -718,6 +720,7 @@ __global__ __launch_bounds__(LMB_NW * 64) __attribute__((amdgpu_waves_per_eu(4))
   constexpr int ITER = (MT + NW - 1) / NW;
   constexpr int NCH = MT / 16;
   constexpr int PW = lmb_rec(DSUB);
+  constexpr int LPC = lmb_lanes(MT), SETTLE = lmb_settle(MT);
   static_assert(MT % 16 == 0 && MT <= 64, "whole chunks, one lane per subspace");
   extern __shared__ __align__(16) unsigned char smem[];
   LDS unsigned char *smem3 = (LDS unsigned char *)smem;
@@ -1082,10 +1085,10 @@ __global__ __launch_bounds__(LMB_NW * 64) __attribute__((amdgpu_waves_per_eu(4))
     const int n = (int)umin32(*qn, (uint32_t)LMB_QUEUE);
     if (tid < LMB_G && lost[tid] != 0u) atomicAdd(&a.gcnt[sq[tid]], (uint32_t)a.cap + 1u);   // redone query-major
     // ---- the candidates' distances in fp32 ----
-    // Four lanes per candidate, a chunk of 16 subspaces each; the entries come from the codebook,
+    // A lane per chunk of 16 subspaces of a candidate; the entries come from the codebook,
     // which the wavefronts put where the table was (random reads of it from the L2 took 8 thousand
     // clocks of a task).
-    const int cd = tid >> 2, ch = tid & 3;
+    const int cd = tid / LPC, ch = tid % LPC;
     uintx4 cw = {0u, 0u, 0u, 0u};
     const int64_t drow0 = row0;
     const uint8_t *dbase = base;
@@ -1114,7 +1117,7 @@ __global__ __launch_bounds__(LMB_NW * 64) __attribute__((amdgpu_waves_per_eu(4))
         }
       __syncthreads();
     }
-    for (int e0 = 0; e0 < n; e0 += LMB_SETTLE) {
+    for (int e0 = 0; e0 < n; e0 += SETTLE) {
       const int e = e0 + cd;
       if (e0 > 0) {
         if (__ballot(p_has) != 0) drain();
@@ -1122,7 +1125,7 @@ __global__ __launch_bounds__(LMB_NW * 64) __attribute__((amdgpu_waves_per_eu(4))
       }
       bool pass = e < n && ch == NCH - 1;
       uint32_t g = 0, bits = 0, i = 0;
-      if (e0 + wave * 16 < n) {   // this wavefront has candidates
+      if (e0 + wave * (64 / LPC) < n) {   // this wavefront has candidates
         const uint32_t word = e < n ? queue[e] : 0u;
         g = word & 7u;
         if constexpr (MODE == 0) {
@@ -1157,7 +1160,7 @@ __global__ __launch_bounds__(LMB_NW * 64) __attribute__((amdgpu_waves_per_eu(4))
             float acc = dist;
 #pragma unroll
             for (int j = 0; j < 16; ++j) acc += v[j];
-            dist = __shfl(acc, (lane & ~3) | c);   // lane c's sum is the one that counts in round c
+            dist = LPC > 1 ? __shfl(acc, (lane & ~(LPC - 1)) | c) : acc;   // lane c's sum is the one that counts in round c
           }
           bits = __float_as_uint(dist);
           pass = pass && bits <= stau[g];

@@ -1440,14 +1440,26 @@ int launch_scan_list_major(const ivfpq_index *ix, const float *d_queries, int64_
   // With byte tables unless most queries may have no k-th distance to compare with yet (lists
   // shorter than k on average leave them without one after their first list, and then every point
   // is a candidate), a position does not fit the queue's words, or the early exit of the sums is
-  // switched off (a plain scan forms every sum).
-  const bool bytes = ix->N >= (int64_t)2 * k * ix->nlist && ix->max_list_len < (1 << 20) && !(get_scan_ablate() & 8);
+  // switched off (a plain scan forms every sum).  A candidate costs about what 16 byte sums do, and the shorter
+  // the lists against k, the more of their points are candidates.  10 000 queries, 32 probes, us with fp32 pairs
+  // / with byte tables at a mean list of so many k: data with cluster structure, 48 subspaces 2.9 2363 / 1887,
+  // 6.8 2929 / 1992, 9.8 3275 / 2064; data without, 48 subspaces 2.9 3008 / 3809, 4.9 3405 / 3819, 6.8 3666 /
+  // 3903, 8.9 2581 / 2460, 9.8 4057 / 3984, 64 subspaces 2.9 3436 / 3962, 4.9 3902 / 3903, 6.8 4248 / 3936;
+  // 16 subspaces 2.9 2343 / 2276, 9.8 2742 / 2302.  So from 6 on, with 16 subspaces from 2 on, and with the
+  // hit counts, whose byte sums are the result.
+  const bool bytes = ix->N >= (int64_t)(mode == 0 && ix->M > 16 ? 6 : 2) * k * ix->nlist && ix->max_list_len < (1 << 20) && !(get_scan_ablate() & 8);
   a.group = bytes ? LMB_G : LM_G;
   // Many probes: the nearest few lists first, merged, so that the rest is filtered by a k-th distance
-  // over eight lists instead of one.  On data without cluster structure that leaves a third of the
-  // candidates (1M x 96, 64 probes, 10 000 queries: 5500 -> 4440 us; the overflowing queries, 476 us of
-  // query-major scan, are gone); where the bounds rule everything out the second round is five small
-  // launches (about 20 us), too much for fewer probes, which gain less.
+  // over eight lists instead of one.  That costs five launches (14 us of 10 000 queries) where the bounds rule
+  // everything out, and pays where they do not.  10 000 queries, k = 100, lists of 976, us in one round / two:
+  //   probes                          16           32           47           64          128
+  //   48 subspaces, clustered    1177 / 1222  2070 / 2091  2885 / 2899  3810 / 3810  7302 / 7256
+  //   48, without structure      2172 / 1772  4001 / 2734  5630 / 3638  7387 / 4650  14618 / 8511
+  //   64, clustered               381 / 395    416 / 431    453 / 467    496 / 510    730 / 745
+  //   64, without structure      2239 / 1930  3994 / 3062  5584 / 4126  7298 / 5318  13494 / 9868
+  //   16, clustered               315 / 330    389 / 403    460 / 474    541 / 555    965 / 980
+  // (2000 queries, 64 clustered: 131 / 143 at 32 probes, 143 / 156 at 64).  The line is where the two rounds cost
+  // clustered data 3 % or less of a large batch.
   const int split = bytes && nprobe - w.first >= 2 * LM_STAGE1 + 32 ? w.first + LM_STAGE1 : nprobe;
   for (int p0 = w.first, p1 = split; p0 < nprobe; p0 = p1, p1 = nprobe) {
     a.p0 = p0;

@@ -183,3 +183,33 @@ def test_candidates_that_overflow_in_either_round(D, M, mode):
     finally:
         b.set_option("lm_cap", 0)
         gi.close()
+
+
+@pytest.mark.parametrize("metric", [0, 1])
+@pytest.mark.parametrize("name", ["all equal", "two values", "tiny jitter", "duplicates", "zero"])
+def test_row_proposals_that_are_not_accepted(name, metric):
+    """Few lists (up to 4096), and a batch too large for the path without a matrix product (more than 4.5e8
+    query x list x dimension products): degenerate centroids, where the proposal's window cannot separate the
+    lists, its collection overflows, and the flagged queries go to the second line."""
+    b = _binding()
+    rng = np.random.default_rng(len(name))
+    D, distinct, reps = 16, 40, 235
+    cent = {
+        "all equal": lambda: np.tile(rng.normal(size=(1, D)), (4000, 1)),
+        "two values": lambda: np.repeat(rng.normal(size=(2, D)), 1800, axis=0),
+        "tiny jitter": lambda: rng.normal(size=(1, D)) + 1e-7 * rng.normal(size=(3000, D)),
+        "duplicates": lambda: np.concatenate([rng.normal(size=(300, D)), rng.normal(size=(300, D))[rng.integers(0, 300, 3300)]]),
+        "zero": lambda: np.zeros((3100, D)),
+    }[name]().astype(np.float32)
+    nlist = len(cent)
+    assert distinct * reps * nlist * D > 450_000_000
+    q = rng.normal(size=(distinct, D)).astype(np.float32)
+    dq = torch.from_numpy(q).cuda().repeat(reps, 1)
+    gi = b.IvfPqIndex(cent, rng.normal(size=(1, 256, D)).astype(np.float32), np.arange(nlist + 1, dtype=np.int64),
+                      np.zeros((nlist, 1), dtype=np.uint8), metric=metric)
+    b.coarse_fallbacks(reset=True)
+    for nprobe in (1, 10, 100, 200):
+        o_pid, o_pd = oracle.coarse(q, cent, nprobe, metric=metric)
+        _same(gi.coarse(dq, nprobe), (np.tile(o_pid, (reps, 1)), np.tile(o_pd, (reps, 1))), (name, nprobe))
+    assert name == "duplicates" or b.coarse_fallbacks() > 0
+    gi.close()

@@ -752,8 +752,8 @@ __device__ __forceinline__ int cs_hidx(uint32_t bin) { return (int)(((bin & 15u)
 
 // KIND CS_EXACT: `rows` holds the reference-order distances themselves (coarse_exact_tile_kernel):
 // the lists up to the bin of the nprobe-th are the answer once they are sorted; should they be
-// more than CS_CAND (masses of equal distances) or not all finite, the wavefront picks the
-// nprobe smallest keys one after the other, so that no second kernel is needed.
+// more than CS_CAND (masses of equal distances), the wavefront picks the nprobe smallest keys one
+// after the other, so that no second kernel is needed.
 // KIND CS_FUSED: `rows` holds the key rows of coarse_gemm_top_kernel (nrow keys per query) instead of
 // the product's rows (nrow = nlist values); a key gives its list and, to 64 units in the last
 // place, the proposal value, and the last key of every group of COARSE_FT bounds the lists of
@@ -821,11 +821,9 @@ __global__ __launch_bounds__(CS_WAVES * 64) void coarse_select_wave_kernel(
 
   // range of the row's proposal values
   float vmin = __builtin_inff(), vmax = -__builtin_inff();
-  float nonfinite = 0.0f;   // stays 0 unless a value is NaN or infinite (one instruction per value, where a comparison takes two)
   each([&](int p, uint32_t raw) __attribute__((always_inline)) {
     if (list_of(p, raw) < nlist) {
       const float v = value_of(raw);
-      if (EXACT) nonfinite = fmaf(v, 0.0f, nonfinite);
       vmin = fminf(vmin, v);
       vmax = fmaxf(vmax, v);
     }
@@ -835,10 +833,13 @@ __global__ __launch_bounds__(CS_WAVES * 64) void coarse_select_wave_kernel(
     vmax = fmaxf(vmax, __shfl_xor(vmax, off));
   }
   // bins of equal width in value: bin(v) is monotone in v whatever the roundings, which is all
-  // the selection needs (NaN and a degenerate range go to bin 0 / the last bin)
+  // the selection needs (NaN and a degenerate range go to bin 0 / the last bin; EXACT, which has no
+  // acceptance test behind it, puts what is NaN last, where it stands in order: the inner product of an
+  // infinite centroid may be NaN, and in the first bin it pushes real lists out of the collection)
   const float scale = (float)CS_BINS / (vmax - vmin);
   auto bin_of = [&](float v) __attribute__((always_inline)) {
     const float x = (v - vmin) * scale;
+    if (EXACT) return x < (float)(CS_BINS - 1) ? (x > 0.0f ? (uint32_t)x : 0u) : (uint32_t)(CS_BINS - 1);
     return x >= (float)(CS_BINS - 1) ? (uint32_t)(CS_BINS - 1) : (x > 0.0f ? (uint32_t)x : 0u);
   };
   for (int i = lane; i < CS_BINS; i += 64) hist[i] = 0u;
@@ -904,10 +905,8 @@ __global__ __launch_bounds__(CS_WAVES * 64) void coarse_select_wave_kernel(
     count += (uint32_t)__popcll(bal);
   });
   for (int off = 32; off > 0; off >>= 1) rest_min = fminf(rest_min, __shfl_xor(rest_min, off));
-  // (the inner product of an infinite centroid may be NaN: it stands in the first bin and is last in order,
-  // so the cut may be short of the nprobe-th list; the proposals' acceptance test is never met then)
-  bool ok = count <= (uint32_t)CS_CAND && !(EXACT && __ballot(nonfinite != 0.0f) != 0ull);
-  if (EXACT && !ok) {   // masses of equal distances, or not all finite: the next smallest key, nprobe times
+  bool ok = count <= (uint32_t)CS_CAND;
+  if (EXACT && !ok) {   // masses of equal distances: the next smallest key, nprobe times
     unsigned long long last = 0ull;
     for (int p = 0; p < nprobe; ++p) {
       unsigned long long best = ~0ull;

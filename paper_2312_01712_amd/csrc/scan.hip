@@ -124,23 +124,31 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4))) vo
   const int M = MT > 0 ? MT : a.M;
   const int Mp = MT > 0 ? MPT : a.Mp;
   const int D = a.D, dsub = a.dsub;
-  const IpCarve at = ip_carve(M, D, NW);
+  // (the distances between the regions behind the query are constants: written as constants added to one
+  // pointer they become offsets of the instructions; an address of its own for each spilled 23 more scalar
+  // registers and cost 5 %)
+  // (Regions as ip_carve lays them out; behind the query their distances are constants.  Written as constants added to
+  // one pointer they become offsets of the instructions; the fields of one run-time IpCarve, an address each, spilled
+  // 23 more scalar registers and cost the 1M x 200 configuration 5 %.)
+  constexpr IpCarve rel = ip_carve(0, 0, NW);
+  const int region0 = ip_query_at(M, NW), sq_bytes = ip_query_bytes(D);
   LDS unsigned char *smem3 = (LDS unsigned char *)smem;
   LDS float *lut = (LDS float *)smem3;
-  LDS float *sq = (LDS float *)(smem3 + at.query);
-  LDS int64_t *queue_id = (LDS int64_t *)(smem3 + at.queue_id);
-  LDS uint32_t *queue_d = (LDS uint32_t *)(smem3 + at.queue_d);
-  LDS uint32_t *tau_words = (LDS uint32_t *)(smem3 + at.bounds);
-  LDS int64_t *meta_row0 = (LDS int64_t *)(smem3 + at.row0);
-  LDS int64_t *meta_blk = (LDS int64_t *)(smem3 + at.block0);
-  LDS int32_t *meta_len = (LDS int32_t *)(smem3 + at.len);
-  LDS float *meta_start = (LDS float *)(smem3 + at.start);
-  LDS float *meta_lb = (LDS float *)(smem3 + at.lower);
-  LDS float *sthr = (LDS float *)(smem3 + at.thr);
-  LDS float *sthr_in = (LDS float *)(smem3 + at.thr_in);
-  LDS float *srmin = (LDS float *)(smem3 + at.row_min);
-  LDS float *srabs = (LDS float *)(smem3 + at.row_abs);
-  LDS float *ssuf = (LDS float *)(smem3 + at.suffix);
+  LDS float *sq = (LDS float *)(smem3 + region0);
+  LDS unsigned char *behind = smem3 + region0 + sq_bytes;
+  LDS int64_t *queue_id = (LDS int64_t *)behind;
+  LDS uint32_t *queue_d = (LDS uint32_t *)(behind + (rel.queue_d - rel.queue_id));
+  LDS uint32_t *tau_words = (LDS uint32_t *)(behind + (rel.bounds - rel.queue_id));
+  LDS int64_t *meta_row0 = (LDS int64_t *)(behind + (rel.row0 - rel.queue_id));
+  LDS int64_t *meta_blk = (LDS int64_t *)(behind + (rel.block0 - rel.queue_id));
+  LDS int32_t *meta_len = (LDS int32_t *)(behind + (rel.len - rel.queue_id));
+  LDS float *meta_start = (LDS float *)(behind + (rel.start - rel.queue_id));
+  LDS float *meta_lb = (LDS float *)(behind + (rel.lower - rel.queue_id));
+  LDS float *sthr = (LDS float *)(behind + (rel.thr - rel.queue_id));
+  LDS float *sthr_in = (LDS float *)(behind + (rel.thr_in - rel.queue_id));
+  LDS float *srmin = (LDS float *)(behind + (rel.row_min - rel.queue_id));
+  LDS float *srabs = (LDS float *)(behind + (rel.row_abs - rel.queue_id));
+  LDS float *ssuf = (LDS float *)(behind + (rel.suffix - rel.queue_id));
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);

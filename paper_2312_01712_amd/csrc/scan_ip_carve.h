@@ -33,11 +33,13 @@ struct IpCarve {   // byte offsets; the table starts at 0 and shares its place w
   int end;
 };
 
+IVFPQ_HD constexpr int ip_query_at(int M, int nw) { return M * 1024 > nw * IP_TOP * 12 ? M * 1024 : nw * IP_TOP * 12; }
+IVFPQ_HD constexpr int ip_query_bytes(int D) { return (D * 4 + 15) & ~15; }
+
 IVFPQ_HD constexpr IpCarve ip_carve(int M, int D, int nw) {
   IpCarve c = {};
-  const int table = M * 1024, stage = nw * IP_TOP * 12;
-  c.query = table > stage ? table : stage;
-  c.queue_id = c.query + ((D * 4 + 15) & ~15);
+  c.query = ip_query_at(M, nw);
+  c.queue_id = c.query + ip_query_bytes(D);
   c.queue_d = c.queue_id + nw * 64 * 8;
   c.bounds = c.queue_d + nw * 64 * 4;
   c.row0 = c.bounds + ((4 * (nw + 1) + 15) & ~15);

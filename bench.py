@@ -206,12 +206,13 @@ def run_workload(args, name: str, steps: int, warmup: int, cpu_seconds: float, p
     resolved = gi_strategy
     pruned = {"strategy": "list-major" if resolved == binding.SCAN_LIST_MAJOR else "query-major",
               "kernel": ("probe_bound_kernel + lm_pairs / lm_offsets + lm_scan_kernel (head pass: every query's nearest list, "
-                         "ranked list-major; main pass: the other lists that the list-level bound does not rule out, two "
-                         "queries per table pass) + lm_merge_kernel, as shipped") if resolved == binding.SCAN_LIST_MAJOR else
+                         "ranked list-major, two queries per fp32 table) + lm_byte_kernel (main pass: the other lists that the "
+                         "list-level bound does not rule out, eight queries per byte table, fp32 distances for what passes; "
+                         "lm_scan_kernel where lists are short against k) + lm_merge_kernel, as shipped") if resolved == binding.SCAN_LIST_MAJOR else
                         "probe_bound_kernel + scan_kernel as shipped (list-level bound, early exit of the sums, chunked loads: "
                         "bytes that cannot change the result are not read)",
-              "bound": ("lds + per-task phases: one workgroup per CU alternates between building the interleaved table "
-                        "(vector ALU) and 8-byte LDS gathers") if resolved == binding.SCAN_LIST_MAJOR else
+              "bound": ("lds + per-task phases: one workgroup per CU alternates between building the table of a group of "
+                        "queries (vector ALU, matrix units), 8-byte LDS gathers and the settling of candidates") if resolved == binding.SCAN_LIST_MAJOR else
                        "alu where most lists are ruled out (the tables of the lists that remain), lds gathers where nothing is",
               "avg_launch_ms": launch_ms, "algorithmic_rate": algo_bytes / (launch_ms * 1e-3) / 1e9, "unit": "GB/s",
               "note": "algorithmic bytes over time: exceeds the HBM peak when exact pruning skips bytes; not an efficiency",

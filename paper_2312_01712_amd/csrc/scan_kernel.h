@@ -37,7 +37,7 @@ namespace {
 // It shares everything with the others -- chunked loads, eight look-ups in flight, row minima, early
 // exits, the list-level bound -- but streams its codebook rows per list.  (500k x 120, 30 subspaces of 4:
 // the form it replaces built its table entry by entry from scalar loads, pruned nothing and had one
-// look-up in flight: 1205 us for 999 queries, 382 us so.)
+// look-up in flight: 1205 us of scan for 999 queries, 335 us so.)
 // KIND: SCAN_ALL writes every candidate's distance instead of a top-k; SCAN_SPLIT is the form in
 // which several workgroups share a query's probes (its exchange of bounds costs registers that the
 // plain form spills for: 7 % on lists of 8000 points).
@@ -45,7 +45,7 @@ namespace {
 // the chip holds at once, each of which takes the next entry when it is done with one.  10 000 queries of 16
 // subspaces, nearly all of them named: 4820 us a batch; 5118 where every workgroup serves the named ones among
 // a fixed share of the batch, 6590 with half as many workgroups.  None named: a workgroup per query of the batch
-// that looks whether it is takes 16 us, this form and the kernel that makes the list 6.
+// that looks whether it is takes 16 us, this form and the kernel that makes the list 10.
 enum { SCAN_TOPK = 0, SCAN_ALL = 1, SCAN_SPLIT = 2, SCAN_LISTED = 3 };
 template <int MT, int DSUB, int NW, int KIND, bool BYTE>
 __device__ __forceinline__ void scan_query(const ScanArgs &a, const RadiiSq &r2, int64_t q, int split) {

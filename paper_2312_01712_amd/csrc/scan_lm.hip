@@ -23,7 +23,8 @@
 //   C  the list-major scan appends every point with distance <= tau_q to the query's
 //      candidate buffer (a few hundred per query: anything above tau_q cannot be in the
 //      result);
-//   D  one wavefront per query merges its buffer into the top-k of phase A by (distance, id).
+//   D  one wavefront per query merges its buffer into the top-k of phase A by (distance, id);
+//      behind byte tables (lm_byte_kernel) it forms the candidates' distances first.
 // A query whose buffer overflows is redone by the query-major kernel, so the result is
 // always that of the plain loop.
 
@@ -54,12 +55,12 @@ struct LmArgs {
   const int64_t *ids;           // [N]
   int64_t *out_ids;             // [Q][k]: phase A's top-k on entry to the merge, the result after it
   float *out_dist;              // [Q][k]
-  int32_t *cnt;                 // [nlist] pairs per list; then [2]: queries to be redone, and those of them taken up
+  int32_t *cnt;                 // [nlist] pairs per list; then [2]: queries to be redone, and those of them taken up; then [2]: queries with candidates in each main pass, and [2]: those of them taken up by lm_settle_kernel
   int32_t *rank;                // [max(Q, Q*(nprobe-first))] position of a pair among its list's pairs, -1: no pair
   int32_t *base;                // [nlist+1] first pair slot of a list (ranges padded to whole groups); [nlist] = slots in use
   int2 *pairs;                  // [Q*(nprobe-first) + (LMB_G - 1) nlist] (query, list); query -1 pads a list's range
   uint32_t *gcnt;               // [Q] candidates appended (may run past cap: the query then counts as overflowed)
-  uint2 *cand;                  // [Q][cap] (distance bits, row in the index)
+  uint2 *cand;                  // [Q][cap] (distance bits, row in the index); from byte tables of distances (list, row)
   int32_t *qmap;                // [Q] q for a query to be redone query-major, -1 otherwise
   int32_t *redo;                // [Q] those queries, in any order (the place of rank)
   int32_t *qmap_head;           // [Q] head pass: q for a query whose nearest list is left to the query-major kernel, else -1
@@ -675,7 +676,7 @@ __global__ __launch_bounds__(LM_NW * 64) __attribute__((amdgpu_waves_per_eu(LM_N
 // from below.  A point whose
 // sum, in those units, lies above the query's k-th distance so far cannot enter the result and
 // is dropped; every other point (a fraction of a percent) gets its distance in fp32 from the
-// codebook itself, with the operations and in the order of the reference, and only that distance
+// codebook itself (lm_settle_kernel), with the operations and in the order of the reference, and only that distance
 // is compared, stored and ranked.  So the result is bit for bit that of the fp32 tables; the bytes
 // only decide which sums need not be formed.  LMB_TOP = 63: four bytes add up within a byte, so
 // a group of four subspaces costs two adds per four queries before the bytes are spread to
@@ -684,13 +685,11 @@ __global__ __launch_bounds__(LM_NW * 64) __attribute__((amdgpu_waves_per_eu(LM_N
 // the byte sums are the result and nothing has to be recomputed.
 //
 // 1M x 96, 64 probes, 10 000 queries (every (query, list) pair scanned): 7.1 ms with two queries
-// per fp32 table, 3.9 ms so; hit counts, 5000 queries: 3.6 -> 1.5 ms.
+// per fp32 table, 3.6 ms with byte tables and every task settling its candidates, 2.6 and 0.45 ms with
+// lm_settle_kernel behind (0.2 of which the merge took before); hit counts, 5000 queries: 3.6, 1.4, 1.2 ms.
 constexpr int LMB_NW = 16;      // wavefronts: one workgroup per CU (the table takes 2 KiB per subspace), 4 per SIMD
 constexpr int LMB_QUEUE = 3072; // candidates a task can hold; a query that loses one is redone query-major
 constexpr int LMB_TOP = 63;
-// Lanes that settle a candidate together, 16 subspaces each; candidates settled at a time.
-constexpr int lmb_lanes(int mt) { return mt > 16 ? 4 : 1; }
-constexpr int lmb_settle(int mt) { return LMB_NW * 64 / lmb_lanes(mt); }
 
 typedef uint16_t ushortx2 __attribute__((ext_vector_type(2)));
 typedef uint32_t uintx2 __attribute__((ext_vector_type(2)));
@@ -698,45 +697,51 @@ typedef uint32_t uintx2 __attribute__((ext_vector_type(2)));
 // What is wanted of a task, kept between its request and its use.
 template <int DSUB>
 struct LmbFetch {
-  float q[DSUB], c[DSUB];   // wavefront g, lane m: subspace m of query g and of the list's centroid
+  float q[DSUB], c[DSUB];   // lane m: subspace m of the query and of the list's centroid
   float r2, tau;
-  int32_t qid;              // query g (-1: the group has fewer)
+  int32_t qid;              // the query (-1: the group has fewer)
 };
 
-// The table; while candidates are settled, the codebook in its place.
-constexpr size_t lmb_table(int mt, int dsub) { return (size_t)mt * (dsub > 2 ? 1024 * dsub : 2048); }
-// Floats of a (subspace, query) record: the residual and r_m^2, padded to whole 16-byte reads.
+// Floats of a (subspace, query) record, padded to whole 16-byte reads.
 constexpr int lmb_rec(int dsub) { return dsub == 2 ? 4 : 8; }
+constexpr int LMB_SMALL = 96;   // words: two sets of a task's limits, queries and losses, and the two queue counters
 constexpr size_t lmb_lds(int mt, int dsub) {
-  return lmb_table(mt, dsub) + (size_t)LMB_G * mt * (8 * lmb_rec(dsub) + 4) + (size_t)mt * 4 + (size_t)LMB_QUEUE * 4 + 256;
+  return (size_t)mt * 2048 + (size_t)LMB_G * mt * (4 * lmb_rec(dsub) + 4 + 2) + (size_t)mt * 4 + (size_t)LMB_QUEUE * 4 + LMB_SMALL * 4;
 }
 
 template <int J>
 __device__ __forceinline__ float xor_f32(float v) { return __uint_as_float(xor_u32<J, true>(__float_as_uint(v))); }
 
+// A task has two phases and a barrier behind each: the table (vector ALU and matrix units) and the pass
+// over the codes (LDS).  What else a task needs is out of their way.  The next task's parameters are
+// formed by wavefronts 8 to 15 behind their share of the blocks, while the others, which have one block
+// more, still scan.  The candidates leave the LDS for the queries' slots in the shadow of the next
+// table, and their fp32 distances are formed by lm_settle_kernel, query by query: settled here they cost
+// 8.5 of a task's 30 thousand clocks, since every task had to put the codebook where the table was and had
+// candidates (125) for half of the lanes.
 template <int MT, int DSUB, int MODE>
 __global__ __launch_bounds__(LMB_NW * 64) __attribute__((amdgpu_waves_per_eu(4))) void lm_byte_kernel(LmArgs a, RadiiSq r2) {
   constexpr int NW = LMB_NW;
   constexpr int ITER = (MT + NW - 1) / NW;
   constexpr int NCH = MT / 16;
   constexpr int PW = lmb_rec(DSUB);
-  constexpr int LPC = lmb_lanes(MT), SETTLE = lmb_settle(MT);
   static_assert(MT % 16 == 0 && MT <= 64, "whole chunks, one lane per subspace");
   extern __shared__ __align__(16) unsigned char smem[];
   LDS unsigned char *smem3 = (LDS unsigned char *)smem;
-  // LDS carve: table [MT][256][8 bytes] | records [MT][8][PW]: residual, r_m^2 | factors [MT][8][PW]:
-  // -2 s residual, s | constants [MT][8] | largest |entry|^2 of a subspace [MT] | queue | small words
-  LDS float *srec = (LDS float *)(smem3 + lmb_table(MT, DSUB));
-  LDS float *sfac = srec + MT * LMB_G * PW;
-  LDS float *scon = sfac + MT * LMB_G * PW;
-  LDS float *semax = scon + MT * LMB_G;
+  // LDS carve: table [MT][256][8 bytes] | records [MT][8][PW]: distances -2 s residual, s; hit counts
+  // residual, r_m^2 | constants [MT][8] | highest bytes [MT][8], 16 bits each | largest |entry|^2 of a subspace [MT] |
+  // queue | small words
+  LDS float *srec = (LDS float *)(smem3 + (size_t)MT * 2048);
+  LDS float *scon = srec + MT * LMB_G * PW;
+  LDS uint16_t *stop = (LDS uint16_t *)(scon + MT * LMB_G);
+  LDS float *semax = (LDS float *)(stop + MT * LMB_G);
   LDS uint32_t *queue = (LDS uint32_t *)(semax + MT);
   LDS uint32_t *small = queue + LMB_QUEUE;
-  LDS uint32_t *sT = small;            // [8] sums below this are candidates
-  LDS uint32_t *stau = small + 8;      // [8] bits of the k-th distance so far
-  LDS int32_t *sq = (LDS int32_t *)(small + 16);   // [8] queries
-  LDS uint32_t *lost = small + 24;     // [8] a candidate of the query found no room
-  LDS uint32_t *qn = small + 32;       // candidates offered to the queue
+  // two sets: a task's are read until its candidates have left, when the next one's are already there
+  LDS uint32_t *sT = small;                        // [2][8] sums below this are candidates
+  LDS int32_t *sq = (LDS int32_t *)(small + 16);   // [2][8] queries
+  LDS uint32_t *lost = small + 32;                 // [2][8] a candidate of the query found no room
+  LDS uint32_t *qn = small + 48;                   // [2] candidates offered to the queue
 
   int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -781,12 +786,18 @@ __global__ __launch_bounds__(LMB_NW * 64) __attribute__((amdgpu_waves_per_eu(4))
     const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)((uint64_t)v >> 32), l);
     return (int64_t)(((uint64_t)hi << 32) | lo);
   };
-  // wavefront g < 8 brings the parameters of query g: a lane per subspace
+  // wavefront 8 + g brings the parameters of query g: a lane per subspace
+  constexpr int W0 = NW - LMB_G;
   auto fetch_params = [&](const int2 &pv, LmbFetch<DSUB> &f) __attribute__((always_inline)) {
+    f.qid = -1;
+    f.r2 = f.tau = 0.0f;
+#pragma unroll
+    for (int j = 0; j < DSUB; ++j) f.q[j] = f.c[j] = 0.0f;
+    if (wave < W0) return;
     const int c = __builtin_amdgcn_readlane(pv.y, 0);
     const int q0 = __builtin_amdgcn_readlane(pv.x, 0);   // a task's first query exists
-    f.qid = wave < LMB_G ? __builtin_amdgcn_readlane(pv.x, wave) : -1;
-    if (wave < LMB_G && lane < MT) {
+    f.qid = __builtin_amdgcn_readlane(pv.x, wave - W0);
+    if (lane < MT) {
       const int64_t q = f.qid >= 0 ? f.qid : q0;
       if constexpr (DSUB == 2) {
         const float2 qv = *reinterpret_cast<const float2 *>(a.queries + q * a.D + 2 * lane);
@@ -804,127 +815,127 @@ __global__ __launch_bounds__(LMB_NW * 64) __attribute__((amdgpu_waves_per_eu(4))
         f.r2 = r * r;
       }
       f.tau = a.out_dist[q * a.k + a.k - 1];
-    } else {
+    }
+  };
+  // ... and writes them to the records and to set `par` of the small words
+  auto put_params = [&](const LmbFetch<DSUB> &f, int par) __attribute__((always_inline)) {
+    if (wave < W0) return;
+    const int g = wave - W0;
+    const bool on = lane < MT;
+    float res[DSUB];
 #pragma unroll
-      for (int j = 0; j < DSUB; ++j) f.q[j] = f.c[j] = 0.0f;
-      f.r2 = f.tau = 0.0f;
+    for (int j = 0; j < DSUB; ++j) res[j] = f.q[j] - f.c[j];
+    const float tau = __uint_as_float((uint32_t)__builtin_amdgcn_readfirstlane((int)__float_as_uint(f.tau)));
+    LDS float *rec = srec + (lane * LMB_G + g) * PW;
+    uint32_t T;
+    if constexpr (MODE == 0) {
+      // Units: the largest r_m^2 (no table value exceeds it), or, where that is wider, four times
+      // the mean value of a point within tau, maps to LMB_TOP; values beyond are cut off, which
+      // keeps the sum a lower bound.
+      float rmax = on ? f.r2 : 0.0f;
+#pragma unroll
+      for (int off = 32; off > 8; off >>= 1) rmax = fmaxf(rmax, __shfl_xor(rmax, off));
+      rmax = fmaxf(rmax, xor_f32<8>(rmax));
+      rmax = fmaxf(rmax, xor_f32<4>(rmax));
+      rmax = fmaxf(rmax, xor_f32<2>(rmax));
+      rmax = fmaxf(rmax, xor_f32<1>(rmax));
+      const float cap = fmaxf(fminf(rmax, tau * (4.0f / (float)MT)), 1e-30f);
+      const float s = ((float)LMB_TOP - 0.01f) / cap;   // infinite radii and no k-th distance: 0
+      // Offset of a row: up to the next integer at the row's cap, so that entries outside the
+      // radius (most of them) lose nothing to the floor; what the offsets add is known.
+      const float x = fminf(f.r2, cap) * s, top = ceilf(x), off = top - x;
+      float rr = 0.0f;
+#pragma unroll
+      for (int j = 0; j < DSUB; ++j) rr = fmaf(res[j], res[j], rr);
+      // A byte is taken from the bits of 2^15 + value, whose last place is 2^-8: the four roundings at
+      // that magnitude move a value by 2^-9 each, together below 0.01, those of |r|^2 - 2 r.e + |e|^2 in place
+      // of |r - e|^2 by 2^-24 of s (|r| + |e|)^2 each: fewer than 2 DSUB + 10 of them, counted as 32.
+      // The values are raised by that much, so that none is below 0.
+      float add = 0.0f;
+      if (on) {
+        const float far = sqrtf(rr) + sqrtf(semax[lane]);
+        const float err = fmaf(s * far, far * 1.9073486e-06f, 0.01f);
+#pragma unroll
+        for (int j = 0; j < DSUB; ++j) rec[j] = -2.0f * s * res[j];
+        rec[DSUB] = s;
+        scon[lane * LMB_G + g] = fmaf(rr, s, off + err) + 32768.0f;
+        stop[lane * LMB_G + g] = (uint16_t)top;   // NaN (0 x inf): 0
+        add = off + 2.0f * err;
+      }
+      // Limit on the byte sum of a point with distance <= tau: s tau, relative roundings (the fp32
+      // sum, the scaling: 2^-23 each, at most 70 of them), the offsets, the raise and the roundings again.
+#pragma unroll
+      for (int o = 32; o > 8; o >>= 1) add += __shfl_xor(add, o);
+      add += xor_f32<8>(add);
+      add += xor_f32<4>(add);
+      add += xor_f32<2>(add);
+      add += xor_f32<1>(add);
+      const float lim = fmaf(tau * s, 1.00001f, add) + 0.25f;
+      T = lim < 60000.0f ? (uint32_t)lim : 60000u;   // NaN (0 x inf): every point
+    } else {
+      if (on) {
+#pragma unroll
+        for (int j = 0; j < DSUB; ++j) rec[j] = res[j];
+        rec[DSUB] = f.r2;
+      }
+      T = tau < 60000.0f ? (uint32_t)tau : 60000u;
+    }
+    if (lane == 0) {
+      sT[par * 8 + g] = f.qid >= 0 ? T + 1u : 0u;
+      sq[par * 8 + g] = f.qid;
+      lost[par * 8 + g] = 0u;
+      if (g == 0) qn[par] = 0u;
     }
   };
 
-  int2 npv = make_int2(0, 0);
+  int2 npv = make_int2(0, 0);   // pair entries of the next task
   LmbFetch<DSUB> fx;
   CodeRegs<MT / 4> nxt;
   int64_t row0;
-  int len, nb;
+  int list, len, nb;
   const uint8_t *base;
-  auto take_meta = [&](int64_t mv) __attribute__((always_inline)) {
+  auto take_meta = [&](const int2 &pv, int64_t mv) __attribute__((always_inline)) {
+    list = __builtin_amdgcn_readlane(pv.y, 0);
     row0 = lane64(mv, 0);
     len = (int)(lane64(mv, 1) - row0);
     nb = (len + 63) >> 6;   // >= 1: only non-empty lists have tasks
     base = a.codes + lane64(mv, 2) * ivfpq_block_bytes(MT);
     load_chunks<MT, 0, NCH>(base, nb, wave < nb ? wave : nb - 1, lane, nxt);
   };
-  {
-    const int2 pv = fetch_pairs(t);
-    if (t + nwg < ntasks) npv = fetch_pairs(t + nwg);
-    const int64_t mv = fetch_meta(pv);
-    fetch_params(pv, fx);
-    take_meta(mv);
-  }
-  // A task's accepted candidates: their room is reserved when they are settled, and they are
+  // A task's candidates: their room is reserved when the list has been scanned, and they are
   // written once the next task's table is built, so that nothing waits for the atomic's way.
-  uint32_t p_slot = 0, p_bits = 0, p_row = 0;
+  uint32_t p_slot = 0, p_x = 0, p_row = 0;
   int32_t p_q = 0;
   bool p_has = false;
   uint32_t p_where = 0;   // lane that holds the first slot of the candidate's query, and the candidate's place behind it
   auto drain = [&]() __attribute__((always_inline)) {
     const uint32_t slot = (uint32_t)__shfl((int)p_slot, (int)(p_where & 7u)) + (p_where >> 3);
-    if (p_has && slot < (uint32_t)a.cap) a.cand[(int64_t)p_q * a.cap + slot] = make_uint2(p_bits, p_row);
+    if (p_has && slot < (uint32_t)a.cap) a.cand[(int64_t)p_q * a.cap + slot] = make_uint2(p_x, p_row);
     p_has = false;
   };
   __syncthreads();   // semax
-  for (;;) {
+  {
+    const int2 pv = fetch_pairs(t);
+    if (t + nwg < ntasks) npv = fetch_pairs(t + nwg);
+    const int64_t mv = fetch_meta(pv);
+    fetch_params(pv, fx);
+    take_meta(pv, mv);
+    put_params(fx, 0);
+  }
+  __syncthreads();
+  for (int par = 0;; par ^= 1) {
     // (the addresses of all phases are formed anew for every task: kept across tasks, they took 60
     // registers that are not there)
     asm volatile("" : "+v"(tid), "+v"(lane));
-    // ---- the group's parameters ----
-    if (wave < LMB_G) {
-      const bool on = lane < MT;
-      float res[DSUB];
-#pragma unroll
-      for (int j = 0; j < DSUB; ++j) res[j] = fx.q[j] - fx.c[j];
-      const float tau = __uint_as_float((uint32_t)__builtin_amdgcn_readfirstlane((int)__float_as_uint(fx.tau)));
-      uint32_t T;
-      if (on) {
-        LDS float *rec = srec + (lane * LMB_G + wave) * PW;
-#pragma unroll
-        for (int j = 0; j < DSUB; ++j) rec[j] = res[j];
-        rec[DSUB] = fx.r2;
-      }
-      if constexpr (MODE == 0) {
-        // Units: the largest r_m^2 (no table value exceeds it), or, where that is wider, four times
-        // the mean value of a point within tau, maps to LMB_TOP; values beyond are cut off, which
-        // keeps the sum a lower bound.
-        float rmax = on ? fx.r2 : 0.0f;
-#pragma unroll
-        for (int off = 32; off > 8; off >>= 1) rmax = fmaxf(rmax, __shfl_xor(rmax, off));
-        rmax = fmaxf(rmax, xor_f32<8>(rmax));
-        rmax = fmaxf(rmax, xor_f32<4>(rmax));
-        rmax = fmaxf(rmax, xor_f32<2>(rmax));
-        rmax = fmaxf(rmax, xor_f32<1>(rmax));
-        const float cap = fmaxf(fminf(rmax, tau * (4.0f / (float)MT)), 1e-30f);
-        const float s = ((float)LMB_TOP - 0.01f) / cap;   // infinite radii and no k-th distance: 0
-        // Offset of a row: up to the next integer at the row's cap, so that entries outside the
-        // radius (most of them) lose nothing to the floor; what the offsets add is known.
-        const float x = fminf(fx.r2, cap) * s, top = ceilf(x), off = top - x;
-        float rr = 0.0f;
-#pragma unroll
-        for (int j = 0; j < DSUB; ++j) rr = fmaf(res[j], res[j], rr);
-        if (on) {
-          LDS float *fac = sfac + (lane * LMB_G + wave) * PW;
-#pragma unroll
-          for (int j = 0; j < DSUB; ++j) fac[j] = -2.0f * s * res[j];
-          fac[DSUB] = s;
-          fac[DSUB + 1] = top;   // (DSUB 2: the record's last float)
-          // (-0.5 turns the round-to-nearest of the conversion to bytes into a floor, 2^-10 keeps
-          // what is at the cap above the tie)
-          scon[lane * LMB_G + wave] = fmaf(rr, s, off - 0.4990234375f);
-        }
-        // Limit on the byte sum of a point with distance <= tau: s tau, relative roundings (the fp32
-        // sum, the scaling: 2^-23 each, at most 70 of them), the offsets and their 2^-10, and the
-        // roundings of |r|^2 - 2 r.e + |e|^2 in place of |r - e|^2, each within 2^-24 of
-        // s (|r| + |e|)^2: fewer than 2 DSUB + 6 of them, counted as 32.
-        float add = 0.0f;
-        if (on) {
-          const float far = sqrtf(rr) + sqrtf(semax[lane]);
-          add = off + 0.001f + s * far * far * 1.9073486e-06f;
-        }
-#pragma unroll
-        for (int o = 32; o > 8; o >>= 1) add += __shfl_xor(add, o);
-        add += xor_f32<8>(add);
-        add += xor_f32<4>(add);
-        add += xor_f32<2>(add);
-        add += xor_f32<1>(add);
-        const float lim = fmaf(tau * s, 1.00001f, add) + 0.25f;
-        T = lim < 60000.0f ? (uint32_t)lim : 60000u;   // NaN (0 x inf): every point
-      } else {
-        T = tau < 60000.0f ? (uint32_t)tau : 60000u;
-      }
-      if (lane == 0) {
-        sT[wave] = fx.qid >= 0 ? T + 1u : 0u;
-        stau[wave] = __float_as_uint(tau);
-        sq[wave] = fx.qid;
-        lost[wave] = 0u;
-      }
-    }
-    if (tid == 0) *qn = 0u;
-    __syncthreads();
     // ---- the table: row m holds, entry by entry, one byte per query ----
     // Distances: s |r - e|^2 + offset as a product of depth DSUB + 1 on the matrix units, four
-    // queries (rows) by 64 entries (columns, a lane each) at a time; per value that leaves the
-    // cut-off and the conversion to the vector ALU (9.3 of a task's 35 thousand clocks went into
-    // this table with all of it there).
-    const bool five = sq[4] >= 0;   // uniform
+    // queries (rows) by 64 entries (columns, a lane each) at a time.  The sums carry 2^15, so bits 8
+    // to 23 are a value's whole part, or 2^15 and more where it does not fit (from 3 x 2^15 on any number, a lower bound
+    // all the same): per four values two permutations that pair those bits, two minima with the rows' highest bytes and
+    // one permutation that collects the bytes.  This phase is bound by what a SIMD's four wavefronts issue (9.2
+    // thousand clocks for 48 subspaces): a median and a conversion to a byte per value, conversions to normalised
+    // 16 bits, or half of the products on the vector ALU all took as long to 3 %.
+    const bool five = sq[par * 8 + 4] >= 0;   // uniform
 #pragma unroll
     for (int it = 0; it < ITER; ++it) {
       const int m = wave + it * NW;
@@ -944,15 +955,22 @@ __global__ __launch_bounds__(LMB_NW * 64) __attribute__((amdgpu_waves_per_eu(4))
         for (int x = 0; x < 4; ++x) w[h][x] = 0u;
         if (h == 1 && !five) break;
         if constexpr (MODE == 0) {
-          const LDS float *fac = sfac + (m * LMB_G + 4 * h + (lane & 3)) * PW;   // row lane % 4 of every 4 x 4 block
-          float f[DSUB + 1], top[4];
+          const floatx4 con = *(const LDS floatx4 *)(scon + m * LMB_G + 4 * h);
+          const LDS ushortx2 *top = (const LDS ushortx2 *)(stop + m * LMB_G + 4 * h);
+          const ushortx2 top01 = top[0], top23 = top[1];
+          auto bytes_of = [&](const floatx4 &acc) __attribute__((always_inline)) {
+            const uint32_t v01 = __builtin_amdgcn_perm(__float_as_uint(acc[1]), __float_as_uint(acc[0]), 0x06050201u);
+            const uint32_t v23 = __builtin_amdgcn_perm(__float_as_uint(acc[3]), __float_as_uint(acc[2]), 0x06050201u);
+            const ushortx2 lo = __builtin_elementwise_min(__builtin_bit_cast(ushortx2, v01), top01);
+            const ushortx2 hi = __builtin_elementwise_min(__builtin_bit_cast(ushortx2, v23), top23);
+            return __builtin_amdgcn_perm(__builtin_bit_cast(uint32_t, hi), __builtin_bit_cast(uint32_t, lo), 0x06040200u);
+          };
+          const LDS float *fac = srec + (m * LMB_G + 4 * h + (lane & 3)) * PW;   // row lane % 4 of every 4 x 4 block
+          float f[DSUB + 1];
           const floatx4 f0 = *(const LDS floatx4 *)fac;
 #pragma unroll
           for (int j = 0; j < DSUB; ++j) f[j] = f0[j];
           f[DSUB] = DSUB == 2 ? f0[2] : fac[4];
-#pragma unroll
-          for (int g = 0; g < 4; ++g) top[g] = sfac[(m * LMB_G + 4 * h + g) * PW + DSUB + 1];
-          const floatx4 con = *(const LDS floatx4 *)(scon + m * LMB_G + 4 * h);
 #pragma unroll
           for (int y = 0; y < 4; y += 2) {   // two chains of products side by side
             floatx4 acc[2] = {con, con};
@@ -963,10 +981,7 @@ __global__ __launch_bounds__(LMB_NW * 64) __attribute__((amdgpu_waves_per_eu(4))
 #pragma unroll
             for (int x = 0; x < 2; ++x) acc[x] = __builtin_amdgcn_mfma_f32_4x4x1f32(f[DSUB], nrm[y + x], acc[x], 0, 0, 0);
 #pragma unroll
-            for (int x = 0; x < 2; ++x)
-#pragma unroll
-              for (int g = 0; g < 4; ++g)   // (the median of three is one instruction, a minimum two)
-                w[h][y + x] = __builtin_amdgcn_cvt_pk_u8_f32(__builtin_amdgcn_fmed3f(acc[x][g], 0.0f, top[g]), g, w[h][y + x]);
+            for (int x = 0; x < 2; ++x) w[h][y + x] = bytes_of(acc[x]);
           }
         } else {
 #pragma unroll
@@ -997,17 +1012,23 @@ __global__ __launch_bounds__(LMB_NW * 64) __attribute__((amdgpu_waves_per_eu(4))
     const bool more = tn < ntasks;
     int64_t nmv = 0;
     int2 nnv = make_int2(0, 0);
-    if (more) nmv = fetch_meta(npv);
+    if (more) {
+      nmv = fetch_meta(npv);
+      fetch_params(npv, fx);
+    }
     if (tn + nwg < ntasks) nnv = fetch_pairs(tn + nwg);
     if (__ballot(p_has) != 0) drain();
-    __syncthreads();
+    __syncthreads();   // the table is complete; the queue has been read
     // ---- one pass over the list's codes serves all queries of the group ----
     // sums of queries (0, 2), (1, 3), (4, 6), (5, 7) as 16-bit halves, and the limits to compare with
     uint32_t lim[4];
-    lim[0] = (uint32_t)__builtin_amdgcn_readfirstlane((int)(sT[0] | (sT[2] << 16)));
-    lim[1] = (uint32_t)__builtin_amdgcn_readfirstlane((int)(sT[1] | (sT[3] << 16)));
-    lim[2] = (uint32_t)__builtin_amdgcn_readfirstlane((int)(sT[4] | (sT[6] << 16)));
-    lim[3] = (uint32_t)__builtin_amdgcn_readfirstlane((int)(sT[5] | (sT[7] << 16)));
+    {
+      const LDS uint32_t *T = sT + par * 8;
+      lim[0] = (uint32_t)__builtin_amdgcn_readfirstlane((int)(T[0] | (T[2] << 16)));
+      lim[1] = (uint32_t)__builtin_amdgcn_readfirstlane((int)(T[1] | (T[3] << 16)));
+      lim[2] = (uint32_t)__builtin_amdgcn_readfirstlane((int)(T[4] | (T[6] << 16)));
+      lim[3] = (uint32_t)__builtin_amdgcn_readfirstlane((int)(T[5] | (T[7] << 16)));
+    }
     const int last = nb - 1;
     for (int blk = wave; blk < nb; blk += NW) {
       CodeRegs<MT / 4> cur = nxt;
@@ -1065,7 +1086,7 @@ __global__ __launch_bounds__(LMB_NW * 64) __attribute__((amdgpu_waves_per_eu(4))
       if (i >= len) mask = 0u;
       for (unsigned long long bal = __ballot(mask != 0u); bal != 0; bal = __ballot(mask != 0u)) {
         uint32_t first = 0;
-        if (lane == 0) first = __hip_atomic_fetch_add(qn, (uint32_t)__popcll(bal), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        if (lane == 0) first = __hip_atomic_fetch_add(&qn[par], (uint32_t)__popcll(bal), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         first = (uint32_t)__builtin_amdgcn_readfirstlane((int)first);
         if (mask != 0u) {
           const uint32_t g = (uint32_t)__ffs((int)mask) - 1u;
@@ -1077,120 +1098,252 @@ __global__ __launch_bounds__(LMB_NW * 64) __attribute__((amdgpu_waves_per_eu(4))
             word = ((uint32_t)i << 11) | (((g & 2u) ? zz >> 16 : zz & 0xFFFFu) << 3) | g;
           }
           if (pos < (uint32_t)LMB_QUEUE) queue[pos] = word;
-          else lost[g] = 1u;
+          else lost[par * 8 + g] = 1u;
         }
       }
     }
-    __syncthreads();   // the list is scanned: the queue is complete, the table's place is free
-    const int n = (int)umin32(*qn, (uint32_t)LMB_QUEUE);
-    if (tid < LMB_G && lost[tid] != 0u) atomicAdd(&a.gcnt[sq[tid]], (uint32_t)a.cap + 1u);   // redone query-major
-    // ---- the candidates' distances in fp32 ----
-    // A lane per chunk of 16 subspaces of a candidate; the entries come from the codebook,
-    // which the wavefronts put where the table was (random reads of it from the L2 took 8 thousand
-    // clocks of a task).
-    const int cd = tid / LPC, ch = tid % LPC;
-    uintx4 cw = {0u, 0u, 0u, 0u};
+    if (more) put_params(fx, par ^ 1);
+    __syncthreads();   // the list is scanned: the queue is complete, the next task's records are there
+    const int n = (int)umin32(qn[par], (uint32_t)LMB_QUEUE);
+    if (tid < LMB_G && lost[par * 8 + tid] != 0u) atomicAdd(&a.gcnt[sq[par * 8 + tid]], (uint32_t)a.cap + 1u);   // redone query-major
     const int64_t drow0 = row0;
-    const uint8_t *dbase = base;
-    const int dnb = nb;
-    auto codes_of = [&](int e) __attribute__((always_inline)) {   // this lane's 16 codes of candidate e
-      if (MODE == 0 && e < n && ch < NCH) {
-        const uint32_t i = queue[e] >> 3;
-        cw = *(const GLOBAL uintx4 *)(dbase + ((int64_t)ch * dnb + (i >> 6)) * 1024 + (i & 63u) * 16);
-      }
-    };
-    codes_of(cd);
-    // the next task's inputs travel while this one's candidates are settled
+    const int dlist = list;
     if (more) {
-      fetch_params(npv, fx);
-      take_meta(nmv);
+      take_meta(npv, nmv);
       npv = nnv;
     }
-    if (MODE == 0 && n > 0) {
+    for (int e0 = wave * 64; e0 < n; e0 += NW * 64) {
+      if (__ballot(p_has) != 0) drain();
+      const bool live = e0 + lane < n;
+      const uint32_t word = live ? queue[e0 + lane] : 0u;
+      const uint32_t g = word & 7u, i = word >> (MODE == 0 ? 3 : 11);
+      // one atomic instruction reserves the room of all queries: lane g for query g
+      uint32_t mine = 0, before = 0;
 #pragma unroll
-      for (int it = 0; it < ITER; ++it)
-#pragma unroll
-        for (int x = 0; x < 4; ++x) {
-          LDS float *dst = (LDS float *)smem3 + ((wave + it * NW) * 256 + x * 64 + lane) * DSUB;
-          if constexpr (DSUB == 2) *(LDS floatx2 *)dst = floatx2{ent[it][x][0], ent[it][x][1]};
-          else *(LDS floatx4 *)dst = floatx4{ent[it][x][0], ent[it][x][1], ent[it][x][2], ent[it][x][3]};
-        }
-      __syncthreads();
-    }
-    for (int e0 = 0; e0 < n; e0 += SETTLE) {
-      const int e = e0 + cd;
-      if (e0 > 0) {
-        if (__ballot(p_has) != 0) drain();
-        codes_of(e);
+      for (int x = 0; x < LMB_G; ++x) {
+        const unsigned long long bal = __ballot(live && g == (uint32_t)x);
+        if (lane == x) mine = (uint32_t)__popcll(bal);
+        if (g == (uint32_t)x) before = (uint32_t)__popcll(bal & ((1ull << lane) - 1ull));
       }
-      bool pass = e < n && ch == NCH - 1;
-      uint32_t g = 0, bits = 0, i = 0;
-      if (e0 + wave * (64 / LPC) < n) {   // this wavefront has candidates
-        const uint32_t word = e < n ? queue[e] : 0u;
-        g = word & 7u;
-        if constexpr (MODE == 0) {
-          i = word >> 3;
-          const uint32_t cws[4] = {cw[0], cw[1], cw[2], cw[3]};
-          float v[16];
-          const int m0 = (ch < NCH ? ch : NCH - 1) * 16;
-#pragma unroll
-          for (int j = 0; j < 16; ++j) {
-            const int m = m0 + j;
-            const uint32_t code = (cws[j >> 2] >> (8 * (j & 3))) & 0xFFu;
-            const LDS float *en = (const LDS float *)smem3 + (m * 256 + (int)code) * DSUB;
-            const LDS float *rec = srec + (m * LMB_G + (int)g) * PW;
-            const floatx4 rv = *(const LDS floatx4 *)rec;
-            float d2;
-            if constexpr (DSUB == 2) {
-              const floatx2 ev = *(const LDS floatx2 *)en;
-              const float t0 = rv[0] - ev[0], t1 = rv[1] - ev[1];
-              d2 = fmaf(t1, t1, t0 * t0);
-              v[j] = table_value<0>(d2, rv[2]);
-            } else {
-              const floatx4 ev = *(const LDS floatx4 *)en;
-              const float t0 = rv[0] - ev[0], t1 = rv[1] - ev[1], t2 = rv[2] - ev[2], t3 = rv[3] - ev[3];
-              d2 = fmaf(t3, t3, fmaf(t2, t2, fmaf(t1, t1, t0 * t0)));
-              v[j] = table_value<0>(d2, rec[4]);
-            }
-            if ((j & 3) == 3) __builtin_amdgcn_sched_barrier(0);
-          }
-          float dist = 0.0f;   // subspaces ascending: the sum moves on from lane to lane
-#pragma unroll
-          for (int c = 0; c < NCH; ++c) {
-            float acc = dist;
-#pragma unroll
-            for (int j = 0; j < 16; ++j) acc += v[j];
-            dist = LPC > 1 ? __shfl(acc, (lane & ~(LPC - 1)) | c) : acc;   // lane c's sum is the one that counts in round c
-          }
-          bits = __float_as_uint(dist);
-          pass = pass && bits <= stau[g];
-        } else {
-          i = word >> 11;
-          bits = __float_as_uint((float)((word >> 3) & 255u));
-        }
-        // one atomic instruction reserves the room of all queries: lane g for query g
-        uint32_t mine = 0, before = 0;
-#pragma unroll
-        for (int x = 0; x < LMB_G; ++x) {
-          const unsigned long long bal = __ballot(pass && g == (uint32_t)x);
-          if (lane == x) mine = (uint32_t)__popcll(bal);
-          if (g == (uint32_t)x) before = (uint32_t)__popcll(bal & ((1ull << lane) - 1ull));
-        }
-        p_slot = 0;
-        if (lane < LMB_G && mine > 0) p_slot = atomicAdd(&a.gcnt[sq[lane]], mine);
-        p_where = (before << 3) | g;
-        p_bits = bits;
-        p_row = (uint32_t)(drow0 + i);
-        p_q = sq[g];
-        p_has = pass;
-      }
+      p_slot = 0;
+      if (lane < LMB_G && mine > 0) p_slot = atomicAdd(&a.gcnt[sq[par * 8 + lane]], mine);
+      p_where = (before << 3) | g;
+      p_x = MODE == 0 ? (uint32_t)dlist : __float_as_uint((float)((word >> 3) & 255u));
+      p_row = (uint32_t)(drow0 + i);
+      p_q = sq[par * 8 + g];
+      p_has = live;
     }
     if (!more) {
       if (__ballot(p_has) != 0) drain();
       break;
     }
     t = tn;
-    __syncthreads();  // parameters, queue and table are free
+  }
+}
+
+// What follows a pass with byte tables of distances: the queries that have candidates are listed (in the place of
+// the pairs, whose groups have all been served), the queries to be redone marked and, behind the last pass of a
+// large batch (list_redo), listed too.  (One atomic per list and wavefront of 64 queries.)
+__global__ __launch_bounds__(256) void lm_sort_out_kernel(LmArgs a, int list_redo) {
+  const int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  const int lane = threadIdx.x & 63;
+  bool named = false, active = false;
+  if (q < a.Q) {
+    const uint32_t n = a.gcnt[q];
+    named = n > (uint32_t)a.cap || (a.head_done && a.qmap_head[q] >= 0) || (a.later && a.qmap[q] >= 0);
+    active = !named && n > 0u;
+    a.qmap[q] = named ? (int32_t)q : -1;
+  }
+  auto put = [&](bool on, int32_t *count, int32_t *list) __attribute__((always_inline)) {
+    const unsigned long long bal = __ballot(on);
+    if (bal == 0ull) return;
+    int first = 0;
+    if (lane == 0) first = atomicAdd(count, __popcll(bal));
+    first = __builtin_amdgcn_readfirstlane(first);
+    if (on) list[first + __popcll(bal & ((1ull << lane) - 1ull))] = (int32_t)q;
+  };
+  put(active, a.cnt + a.nlist + 2 + (a.later ? 1 : 0), (int32_t *)a.pairs);
+  if (list_redo) put(named, a.cnt + a.nlist, a.redo);
+}
+
+// ---- the candidates of the byte tables: distances in fp32, merged into the queries' results --------
+// One wavefront per query at a time, a lane per candidate: the entries come from the codebook, which the
+// workgroup keeps in its LDS (one workgroup of 16 wavefronts per CU; the queries that have candidates are taken up one by one), the
+// query's row and radii through scalar registers, the centroid's row from the L2 (a query's candidates
+// stand in its slots in runs of the same list, so few lines serve a wavefront).  The operations and their order are those of the reference.
+// A candidate within the k-th distance so far is queued, and 64 at a time are folded into the query's
+// sorted list.  Three requests are in flight while a group of 64 is summed: the next group's codes, its lists'
+// ranges before them, and the slots of the group after it.
+constexpr int LMS_NW = 16;
+constexpr int LMS_QUEUE = 128;   // per wavefront: fewer than 64 waiting and the 64 of a group
+constexpr size_t lms_lds(int mt, int dsub) { return (size_t)mt * 1024 * dsub + (size_t)LMS_NW * (LMS_QUEUE * 8 + mt * 4); }
+#define CONSTANT __attribute__((address_space(4)))
+
+template <int MT, int DSUB>
+__global__ __launch_bounds__(LMS_NW * 64) __attribute__((amdgpu_waves_per_eu(4))) void lm_settle_kernel(LmArgs a, RadiiSq r2) {
+  constexpr int NCH = MT / 16;
+  extern __shared__ __align__(16) unsigned char smem[];
+  LDS unsigned char *smem3 = (LDS unsigned char *)smem;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int32_t *active = (const int32_t *)a.pairs;   // queries with candidates, listed by lm_sort_out_kernel
+  const int nactive = a.cnt[a.nlist + 2 + (a.later ? 1 : 0)], nwg = gridDim.x;
+  if ((int)blockIdx.x >= nactive) return;
+  for (int i = tid; i < MT * 256 * DSUB / 4; i += LMS_NW * 64)
+    ((LDS floatx4 *)smem3)[i] = ((const floatx4 *)a.codebooks)[i];
+  LDS uint32_t *qd = (LDS uint32_t *)(smem3 + (size_t)MT * 1024 * DSUB) + wave * LMS_QUEUE * 2, *qrow = qd + LMS_QUEUE;
+  LDS float *sr2 = (LDS float *)(smem3 + (size_t)MT * 1024 * DSUB + (size_t)LMS_NW * LMS_QUEUE * 8) + wave * MT;   // r_m^2 of the wavefront's query
+  __syncthreads();   // the last one: from here on every wavefront is by itself
+  const int k = a.k;
+  int32_t *ticket = a.cnt + a.nlist + 4 + (a.later ? 1 : 0);
+  for (int x = wave * nwg + (int)blockIdx.x; x < nactive;) {
+    int32_t next = 0;
+    if (lane == 0) next = atomicAdd(ticket, 1);
+    const int64_t q = __builtin_amdgcn_readfirstlane(active[x]);
+    const int n = __builtin_amdgcn_readfirstlane((int)a.gcnt[q]);   // 1 .. cap
+    {
+      const uint2 *slots = a.cand + q * a.cap;
+      Key L0, L1, tau;
+      auto take_tau = [&]() __attribute__((always_inline)) {
+        const Key t0 = bcast_key(L0, (k - 1) & 63), t1 = bcast_key(L1, (k - 1) & 63);
+        tau = (k - 1) < 64 ? t0 : t1;
+      };
+      {
+        const int64_t o = q * k;
+        const bool in0 = lane < k, in1 = 64 + lane < k;
+        const int64_t id0 = in0 ? a.out_ids[o + lane] : -1, id1 = in1 ? a.out_ids[o + 64 + lane] : -1;
+        L0.d = id0 >= 0 ? __float_as_uint(a.out_dist[o + lane]) : SENT_D;
+        L0.id = id0 >= 0 ? id0 : SENT_ID;
+        L1.d = id1 >= 0 ? __float_as_uint(a.out_dist[o + 64 + lane]) : SENT_D;
+        L1.id = id1 >= 0 ? id1 : SENT_ID;
+      }
+      take_tau();
+      int waiting = 0;
+      bool changed = false;
+      auto fold = [&](int from, int count) __attribute__((always_inline)) {   // at most 64 of the queue
+        Key c;
+        c.d = SENT_D;
+        c.id = SENT_ID;
+        if (lane < count) {
+          c.d = qd[from + lane];
+          if (c.d <= tau.d) c.id = a.ids[qrow[from + lane]];   // (the bound may have tightened since: no id fetched)
+        }
+        const bool pass = kless(c, tau);
+        if (__ballot(pass) == 0) return;
+        if (!pass) {
+          c.d = SENT_D;
+          c.id = SENT_ID;
+        }
+        wave_sort_desc<true>(c, lane);
+        wave_merge<true>(L0, L1, c, lane);
+        take_tau();
+        changed = true;
+      };
+      // a lane past the end repeats the query's last candidate; it is not offered
+      auto slot_of = [&](int u) __attribute__((always_inline)) { return slots[u + lane < n ? u + lane : n - 1]; };
+      struct Where { int64_t o0, o1, blk; };
+      auto where_of = [&](uint32_t c) __attribute__((always_inline)) {
+        return Where{a.list_offsets[c], a.list_offsets[c + 1], a.list_blocks[c]};
+      };
+      auto codes_of = [&](const uint2 &e, const Where &w, uintx4 (&cw)[NCH]) __attribute__((always_inline)) {
+        const uint32_t i = e.y - (uint32_t)w.o0;   // (rows are below 2^32)
+        const int64_t nb = (w.o1 - w.o0 + 63) >> 6;
+        const uint8_t *src = a.codes + w.blk * ivfpq_block_bytes(MT) + (int64_t)(i >> 6) * 1024 + (i & 63u) * 16;
+#pragma unroll
+        for (int j = 0; j < NCH; ++j) cw[j] = *(const GLOBAL uintx4 *)(src + j * nb * 1024);
+      };
+      const CONSTANT float *qp = (const CONSTANT float *)(uintptr_t)(a.queries + q * a.D);
+      if (lane < MT) {
+        float r = r2.v[lane];
+        if (a.query_radii) {
+          r = a.query_radii[q * MT + lane];
+          r = r * r;
+        }
+        sr2[lane] = r;
+      }
+      uint2 e = slot_of(0), en = slot_of(64);
+      uintx4 cw[NCH];
+      codes_of(e, where_of(e.x), cw);
+      for (int u = 0; u < n; u += 64) {
+        const Where wn = where_of(en.x);
+        const uint2 enn = slot_of(u + 128);
+        const float *cp = a.centroids + (int64_t)e.x * (MT * DSUB);
+        float dist = 0.0f;
+        uintx4 cwn[NCH];
+        // (one chunk's code for all: with every chunk's loads hoisted to the front the registers spill)
+#pragma unroll 1
+        for (int j = 0; j < NCH; ++j) {
+          floatx4 cv[4 * DSUB];
+#pragma unroll
+          for (int x = 0; x < 4 * DSUB; ++x) cv[x] = *(const GLOBAL floatx4 *)(cp + (j * 4 * DSUB + x) * 4);
+          if (j == NCH - 1) codes_of(en, wn, cwn);   // behind this group's last rows, which are wanted sooner
+          const uintx4 w = cw[0];
+#pragma unroll
+          for (int x = 1; x < NCH; ++x) cw[x - 1] = cw[x];
+          const LDS unsigned char *rows = smem3 + j * 16 * 1024 * DSUB;
+          typedef float entry __attribute__((ext_vector_type(DSUB)));
+          constexpr int LK = MT == 48 ? 8 : 4;   // look-ups in flight (more spill)
+#pragma unroll
+          for (int h = 0; h < 16; h += LK) {
+            entry ev[LK];
+            floatx4 rm2[LK / 4];
+#pragma unroll
+            for (int x = 0; x < LK; ++x) {
+              const uint32_t code = (w[(h + x) >> 2] >> (8 * (x & 3))) & 0xFFu;
+              ev[x] = *(const LDS entry *)(rows + (h + x) * 1024 * DSUB + code * (4 * DSUB));
+            }
+#pragma unroll
+            for (int x = 0; x < LK / 4; ++x) rm2[x] = *(const LDS floatx4 *)(sr2 + j * 16 + h + 4 * x);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int x = 0; x < LK; ++x) {
+              float d2 = 0.0f;
+#pragma unroll
+              for (int y = 0; y < DSUB; ++y) {
+                const int z = (h + x) * DSUB + y;
+                const float t = (qp[j * 16 * DSUB + z] - cv[z >> 2][z & 3]) - ev[x][y];
+                d2 = y == 0 ? t * t : fmaf(t, t, d2);
+              }
+              dist += table_value<0>(d2, rm2[x >> 2][x & 3]);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+          }
+        }
+        const uint32_t bits = __float_as_uint(dist);
+        const bool pass = u + lane < n && bits <= tau.d;
+        const unsigned long long bal = __ballot(pass);
+        if (bal != 0ull) {
+          if (pass) {
+            const int pos = waiting + __popcll(bal & ((1ull << lane) - 1ull));
+            qd[pos] = bits;
+            qrow[pos] = e.y;
+          }
+          waiting += __popcll(bal);
+        }
+        while (waiting >= 64 || (waiting > 0 && u + 64 >= n)) {   // the last 64, at the end all
+          const int m = waiting < 64 ? waiting : 64;
+          waiting -= m;
+          fold(waiting, m);
+        }
+        e = en;
+        en = enn;
+#pragma unroll
+        for (int j = 0; j < NCH; ++j) cw[j] = cwn[j];
+      }
+      if (changed) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const Key x = h ? L1 : L0;
+          const int i = h * 64 + lane;
+          if (i < k) {
+            const bool real = x.d != SENT_D;
+            a.out_ids[q * k + i] = real ? x.id : -1;
+            a.out_dist[q * k + i] = real ? __uint_as_float(x.d) : __builtin_inff();
+          }
+        }
+      }
+    }
+    x = nwg * LMS_NW + __builtin_amdgcn_readfirstlane(next);
   }
 }
 
@@ -1304,6 +1457,24 @@ int launch_lm_byte_t(const LmArgs &a, const RadiiSq &r2, int grid, hipStream_t s
   return IVFPQ_OK;
 }
 
+template <int MT, int DSUB>
+int launch_lm_settle_t(const LmArgs &a, const RadiiSq &r2, int grid, hipStream_t s) {
+  auto kern = lm_settle_kernel<MT, DSUB>;
+  static std::atomic<uint64_t> prepared;
+  if (int rc = prepare_kernel(kern, prepared)) return rc;
+  static_assert(lms_lds(MT, DSUB) <= (size_t)LDS_PER_CU, "codebook and queues fit a CU");
+  hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(LMS_NW * 64), lms_lds(MT, DSUB), s, a, r2);
+  return IVFPQ_OK;
+}
+
+int launch_lm_settle(const LmArgs &a, const RadiiSq &r2, int cus, hipStream_t s) {
+  const int64_t need = (a.Q + LMS_NW - 1) / LMS_NW;
+  const int grid = need < cus ? (int)need : cus;
+  if (a.M == 48) return launch_lm_settle_t<48, 2>(a, r2, grid, s);
+  if (a.M == 64) return launch_lm_settle_t<64, 2>(a, r2, grid, s);
+  return launch_lm_settle_t<16, 4>(a, r2, grid, s);
+}
+
 template <int MODE>
 int launch_lm_byte_m(const LmArgs &a, const RadiiSq &r2, int grid, hipStream_t s) {
   if (a.M == 48) return launch_lm_byte_t<48, 2, MODE>(a, r2, grid, s);
@@ -1350,7 +1521,7 @@ LmWorkspace plan_list_major(const ivfpq_index *ix, int64_t Q, int32_t nprobe) {
   if (w.cap == 0) w.cap = nprobe >= 64 ? 16384 : (nprobe * 256 > 4096 ? nprobe * 256 : 4096);
   w.pairs_cap = Q * (nprobe - w.first > 1 ? nprobe - w.first : 1) + (int64_t)(LMB_G - 1) * ix->nlist;   // also holds the head pass's Q pairs
   size_t off = 0;
-  w.cnt = off;   off += lm_align(((size_t)ix->nlist + 2) * 4);
+  w.cnt = off;   off += lm_align(((size_t)ix->nlist + 6) * 4);
   w.base = off;  off += lm_align(((size_t)ix->nlist + 1) * 4);
   w.pairs = off; off += lm_align((size_t)w.pairs_cap * 8);
   w.rank = off;  off += lm_align((size_t)w.pairs_cap * 4);
@@ -1406,7 +1577,7 @@ int launch_scan_list_major(const ivfpq_index *ix, const float *d_queries, int64_
   // list-level lower bounds of every (query, probe); the same launch clears the per-list counts
   // (lm_offsets_kernel leaves them clear for the pass after it)
   int rc = launch_probe_bounds(ix, d_queries, Q, nprobe, d_probe_ids, r2, mode, d_query_radii, d_probe_lb, s, a.cnt,
-                               (int64_t)ix->nlist + 2);
+                               (int64_t)ix->nlist + 6);
   if (rc) return rc;
 
   int dev = 0, cus = 0;
@@ -1472,7 +1643,13 @@ int launch_scan_list_major(const ivfpq_index *ix, const float *d_queries, int64_
     hipLaunchKernelGGL(lm_pairs_kernel, dim3(pair_grid), dim3(256), 0, s, a, 1, 0);
     rc = bytes ? launch_lm_byte(a, r2, cus, s) : launch_lm_scan<false>(ix, a, r2, cus, s);
     if (rc) return rc;
-    hipLaunchKernelGGL(lm_merge_kernel, dim3((unsigned)((Q + 3) / 4)), dim3(256), 0, s, a);
+    if (bytes && mode == 0) {
+      hipLaunchKernelGGL(lm_sort_out_kernel, dim3((unsigned)((Q + 255) / 256)), dim3(256), 0, s, a, p1 == nprobe && Q > 4096 ? 1 : 0);
+      rc = launch_lm_settle(a, r2, cus, s);
+      if (rc) return rc;
+    } else {
+      hipLaunchKernelGGL(lm_merge_kernel, dim3((unsigned)((Q + 3) / 4)), dim3(256), 0, s, a);
+    }
   }
   IVFPQ_HIP_TRY(hipGetLastError());
   // queries whose candidate buffer overflowed: the query-major kernel over all of their probes
@@ -1484,7 +1661,7 @@ int launch_scan_list_major(const ivfpq_index *ix, const float *d_queries, int64_
     redo.qmap = nullptr;
     redo.qlist = a.redo;
     redo.qlist_n = a.cnt + ix->nlist;
-    hipLaunchKernelGGL(lm_redo_kernel, dim3((unsigned)((Q + 255) / 256)), dim3(256), 0, s, a);
+    if (!bytes || mode != 0) hipLaunchKernelGGL(lm_redo_kernel, dim3((unsigned)((Q + 255) / 256)), dim3(256), 0, s, a);   // (lm_sort_out_kernel has listed them)
   }
   return launch_scan(ix, d_queries, Q, nprobe, d_probe_ids, k, r2, 1, nullptr, nullptr, d_out_ids, d_out_dist,
                      nullptr, nullptr, nullptr, nullptr, mode, d_query_radii, d_probe_lb, s, &redo);

@@ -113,8 +113,9 @@ void ivfpq_index_destroy(ivfpq_index *index);
  * The workspace must be 256-byte aligned.  For 128 < k <= 1024 with L2 distances
  * the figure includes the per-query slots ("wide_cap" below, 12 bytes each, for
  * at most 1 GiB at a time) that let one pass over the lists produce all k
- * neighbours; a workspace sized for k = 128 is accepted too, and the call then
- * takes ceil(k / 128) passes.  Results are the same either way. */
+ * neighbours, and for large batches of shapes that have list-major kernels the tables
+ * that let this pass go list by list; a workspace sized for k = 128 is accepted too, and the
+ * call then takes ceil(k / 128) passes.  Results are the same either way. */
 size_t ivfpq_search_workspace_bytes(const ivfpq_index *index, int64_t Q, int32_t nprobe, int32_t k);
 
 /* The whole search path (stages 1-4) for a batch.
@@ -221,7 +222,9 @@ typedef enum {
  *     bound that filters the query's other lists).  Best where the per-query fixed costs or
  *     the look-up rate dominate: short lists, data without cluster structure.
  *     Needs the L2 metric, k <= 128 and an (M, dsub) of (48, 2), (64, 2) or (16, 4); any other
- *     call is served query-major.  Takes a larger workspace.
+ *     call is served query-major.  Takes a larger workspace.  (For 128 < k <= 1024 with distance
+ *     scoring, either setting but QUERY_MAJOR lets large batches of these shapes be selected list-major
+ *     in stages; ivfpq_resolve_strategy calls that query-major.)
  *   IVFPQ_SCAN_AUTO         the library chooses: list-major where it is available, when the
  *     batch has at least 16 384 (query, list) pairs and the index's mean list length is at
  *     most 4096; query-major otherwise.
@@ -344,7 +347,9 @@ int64_t ivfpq_coarse_fallbacks(int reset);
  *   "wide_cap"     128 < k <= 1024: slots per query for the keys within the running bound on the
  *                  k-th distance (1024 .. 65536, default 8192).  Between lists the bound, which
  *                  only tightens, clears the slots it has overtaken; a query that still runs
- *                  out of slots is redone pass by pass.  0: no slots, every query pass by
+ *                  out of slots is redone pass by pass (behind the list-major form of large
+ *                  batches, in stages that the slots have to hold, query-major first).
+ *                  0: no slots, every query pass by
  *                  pass (128 neighbours per pass).  Set before sizing the workspace.
  *   "scan_ablate"  bit mask that switches exact pruning off, to measure what it saves: 8 the
  *                  early exit of the distance sums, 16 all of the per-block pruning from the

@@ -83,7 +83,26 @@ static std::atomic<int> g_wide_cap{8192};  // slots per query of the wide select
 
 void set_wide_cap(int v) { g_wide_cap.store(v, std::memory_order_relaxed); }
 
-WideWorkspace plan_wide(const ivfpq_index *ix, int64_t Q, int32_t k, int32_t mode) {
+// Lists of the list-major wide selection's first stage: as many as hold 2 k points on average.  0 where it does not
+// serve: shapes without list-major kernels, few pairs or long lists (the lines of the list-major scan), slots that
+// do not hold twice the first lists (those near a query are longer than the mean) or so few that the stages crawl.
+static int32_t wide_first(const ivfpq_index *ix, const WideWorkspace &w, int32_t nprobe, int32_t k, int32_t strategy) {
+  const int64_t Q = w.q_chunk;
+  if (strategy == IVFPQ_SCAN_QUERY_MAJOR || !list_major_shape(ix)) return 0;
+  if (Q * (int64_t)nprobe < 16384 || ix->N > (int64_t)4096 * ix->nlist || ix->N < (int64_t)ix->nlist * 128) return 0;
+  if (ix->max_list_len >= (1 << 20) || Q * (int64_t)nprobe > 0x3FFFFFFFll) return 0;
+  const int64_t first = (2 * (int64_t)k * ix->nlist + ix->N - 1) / ix->N;
+  if (first * 2 > nprobe || first * 2 * ix->N > (int64_t)w.cap * ix->nlist) return 0;
+  int stages = 1;
+  for (int32_t p = (int32_t)first; p < nprobe; ++stages) {
+    const int32_t next = wide_next(w, k, p, nprobe);
+    if (next == p || stages == LM_STAGES) return 0;
+    p = next;
+  }
+  return (int32_t)first;
+}
+
+WideWorkspace plan_wide(const ivfpq_index *ix, int64_t Q, int32_t nprobe, int32_t k, int32_t mode, int32_t strategy) {
   WideWorkspace w = {};
   if (ix->metric != IVFPQ_METRIC_L2 || mode != 0 || k <= 128 || k > 8 * 128 || Q < 1) return w;
   w.cap = g_wide_cap.load(std::memory_order_relaxed);
@@ -99,6 +118,14 @@ WideWorkspace plan_wide(const ivfpq_index *ix, int64_t Q, int32_t k, int32_t mod
   w.n = off;     off += a256((size_t)w.q_chunk * 4);
   w.bound = off; off += a256((size_t)w.q_chunk * 4);
   w.qmap = off;  off += a256((size_t)w.q_chunk * 4);
+  w.first = wide_first(ix, w, nprobe, k, strategy);
+  w.lm_off = off;
+  if (w.first > 0) {
+    w.lm.first = w.first;
+    w.lm.cap = w.cap;
+    plan_list_major_tables(w.lm, ix->nlist, w.q_chunk, nprobe);
+    off += w.lm.total;
+  }
   w.total = off;
   return w;
 }
@@ -532,7 +559,7 @@ size_t ivfpq_search_workspace_bytes_ex(const ivfpq_index *ix, int64_t Q, int32_t
   size_t n = w.total;
   if (use_list_major(ix, Q, nprobe, k, sc ? sc->mode : IVFPQ_SCORE_DISTANCE, sc ? sc->strategy : IVFPQ_SCAN_AUTO))
     n = align256(w.total) + plan_list_major(ix, Q, nprobe).total;
-  else if (const size_t wide = plan_wide(ix, Q, k, sc ? sc->mode : IVFPQ_SCORE_DISTANCE).total)
+  else if (const size_t wide = plan_wide(ix, Q, nprobe, k, sc ? sc->mode : IVFPQ_SCORE_DISTANCE, sc ? sc->strategy : IVFPQ_SCAN_AUTO).total)
     n = align256(w.total) + wide;
   return n < 256 ? 256 : n;
 }
@@ -597,8 +624,12 @@ static int unpack_scoring(const ivfpq_index *ix, const ivfpq_scoring *sc, const 
 static int scan_query_major(const ivfpq_index *ix, const float *d_queries, int64_t Q, int32_t nprobe,
                             const int32_t *d_probe_ids, int32_t k, const RadiiSq &r2, int32_t mode, const float *qr,
                             int64_t *d_out_ids, float *d_out_dist, const Workspace &w, char *base, size_t ws_bytes,
-                            hipStream_t s) {
-  const WideWorkspace ww = plan_wide(ix, Q, k, mode);
+                            hipStream_t s, int32_t strategy) {
+  WideWorkspace ww = plan_wide(ix, Q, nprobe, k, mode, strategy);
+  if (ww.first > 0 && ws_bytes < align256(w.total) + ww.total) {   // room for the slots alone
+    ww.total = ww.lm_off;
+    ww.first = 0;
+  }
   // (the flags of the filtering stage have been read when the scan starts: their place holds the
   // bounds that the workgroups of a query share)
   ScanView view = {0, nullptr, false, nullptr, nullptr, reinterpret_cast<uint32_t *>(base + w.coarse_flags)};
@@ -670,7 +701,7 @@ int ivfpq_scan_topk_ex(const ivfpq_index *ix, const float *d_queries, int64_t Q,
                            ws_bytes, static_cast<hipStream_t>(stream), fn);
   if ((rc = check_workspace(w, ws, ws_bytes, fn))) return rc;
   return scan_query_major(ix, d_queries, Q, nprobe, d_probe_ids, k, r2, mode, qr, d_out_ids, d_out_dist, w, base,
-                          ws_bytes, static_cast<hipStream_t>(stream));
+                          ws_bytes, static_cast<hipStream_t>(stream), strategy);
 }
 
 int ivfpq_scan_topk(const ivfpq_index *ix, const float *d_queries, int64_t Q, int32_t nprobe,
@@ -715,14 +746,15 @@ static int scratch_address(void **out, const char *fn) {
 // Stages 1-4 with the workspace `base` carved as `w` says.
 static int search_in_workspace(const ivfpq_index *ix, const float *d_queries, int64_t Q, int32_t nprobe,
                                int32_t k, const RadiiSq &r2, int32_t mode, const float *qr, int64_t *d_out_ids,
-                               float *d_out_dist, const Workspace &w, char *base, size_t ws_bytes, hipStream_t s) {
+                               float *d_out_dist, const Workspace &w, char *base, size_t ws_bytes, hipStream_t s,
+                               int32_t strategy) {
   int32_t *probe_ids = reinterpret_cast<int32_t *>(base + w.probe_ids);
   int rc = launch_coarse(ix, d_queries, Q, nprobe, probe_ids, nullptr,
                          reinterpret_cast<float *>(base + w.coarse_dist), w.q_chunk, w.nlist_pad,
                          reinterpret_cast<int32_t *>(base + w.coarse_flags), s);
   if (rc) return rc;
   return scan_query_major(ix, d_queries, Q, nprobe, probe_ids, k, r2, mode, qr, d_out_ids, d_out_dist, w, base,
-                          ws_bytes, s);
+                          ws_bytes, s, strategy);
 }
 
 int ivfpq_search_noalloc(const ivfpq_index *ix, const float *d_queries, int64_t Q, int32_t nprobe, int32_t k,
@@ -748,7 +780,7 @@ int ivfpq_search_noalloc(const ivfpq_index *ix, const float *d_queries, int64_t 
   // rows and probes of this call) before it is read, so the previous call's contents do not matter.
   return search_in_workspace(ix, d_queries, Q, nprobe, k, r2, IVFPQ_SCORE_DISTANCE, nullptr, d_out_ids,
                              d_out_dist, w, static_cast<char *>(base), IVFPQ_NOALLOC_SCRATCH_BYTES,
-                             static_cast<hipStream_t>(stream));
+                             static_cast<hipStream_t>(stream), IVFPQ_SCAN_QUERY_MAJOR);
 }
 
 int ivfpq_search_ex(const ivfpq_index *ix, const float *d_queries, int64_t Q, int32_t nprobe, int32_t k,
@@ -780,7 +812,7 @@ int ivfpq_search_ex(const ivfpq_index *ix, const float *d_queries, int64_t Q, in
   }
   if ((rc = check_workspace(w, ws, ws_bytes, fn))) return rc;
   return search_in_workspace(ix, d_queries, Q, nprobe, k, r2, mode, qr, d_out_ids, d_out_dist, w,
-                             static_cast<char *>(ws), ws_bytes, static_cast<hipStream_t>(stream));
+                             static_cast<char *>(ws), ws_bytes, static_cast<hipStream_t>(stream), strategy);
 }
 
 int ivfpq_search(const ivfpq_index *ix, const float *d_queries, int64_t Q, int32_t nprobe, int32_t k,

@@ -118,6 +118,41 @@ int launch_coarse(const ivfpq_index *ix, const float *d_queries, int64_t Q, int3
 int launch_build_lut(const ivfpq_index *ix, const float *d_queries, int64_t Q, int32_t nprobe,
                      const int32_t *d_probe_ids, const RadiiSq &r2, float *d_lut, uint64_t *d_mask,
                      int32_t mode, const float *d_query_radii, hipStream_t s);
+// Workspace of the list-major scan (scan_lm.hip).
+struct LmWorkspace {      // offsets into the list-major part of the workspace, 256-byte aligned
+  size_t cnt, base;       // [lm_counters(nlist)], [nlist+1] int32
+  size_t pairs;           // [pairs_cap] (query, list) int32 pairs bucketed by list; behind a pass with byte tables the queries with candidates
+  size_t rank;            // [pairs_cap] int32: a pair's position among the pairs of its list; behind the main pass the queries to redo
+  size_t gcnt, qmap;      // [Q] uint32 / int32
+  size_t qmap_head;       // [Q] int32
+  size_t cand;            // [Q][cap] (distance bits, row) candidates of the list-major scan
+  size_t total;
+  int64_t pairs_cap;
+  int32_t first;          // probed lists per query that are scanned query-major first
+  int32_t cap;            // candidate slots per query
+};
+inline size_t lm_align(size_t v) { return (v + 255) & ~(size_t)255; }
+constexpr int LM_STAGES = 8;   // passes of a call with candidates to settle
+inline int64_t lm_counters(int32_t nlist) { return (int64_t)nlist + 2 + 2 * LM_STAGES; }
+// Everything but the candidates' slots, for w.first.  A group of the byte tables has 8 queries.
+inline void plan_list_major_tables(LmWorkspace &w, int32_t nlist, int64_t Q, int32_t nprobe) {
+  w.pairs_cap = Q * (nprobe - w.first > 1 ? nprobe - w.first : 1) + (int64_t)7 * nlist;   // also holds the head pass's Q pairs
+  size_t off = 0;
+  w.cnt = off;   off += lm_align((size_t)lm_counters(nlist) * 4);
+  w.base = off;  off += lm_align(((size_t)nlist + 1) * 4);
+  w.pairs = off; off += lm_align((size_t)w.pairs_cap * 8);
+  w.rank = off;  off += lm_align((size_t)w.pairs_cap * 4);
+  w.gcnt = off;  off += lm_align((size_t)Q * 4);
+  w.qmap = off;  off += lm_align((size_t)Q * 4);
+  w.qmap_head = off; off += lm_align((size_t)Q * 4);
+  w.cand = off;
+  w.total = off;
+}
+// Shapes that have list-major kernels.
+inline bool list_major_shape(const ivfpq_index *ix) {
+  return (ix->M == 48 && ix->dsub == 2) || (ix->M == 64 && ix->dsub == 2) || (ix->M == 16 && ix->dsub == 4);
+}
+
 // Workspace of the wide selection (more than 128 neighbours per query in one pass of the
 // query-major scan): offsets into its part of the workspace, 256-byte aligned.
 struct WideWorkspace {
@@ -127,9 +162,22 @@ struct WideWorkspace {
   size_t total;      // 0: the wide selection does not apply
   int64_t q_chunk;   // queries that share the slot arrays at a time
   int32_t cap;       // slots per query
+  // list-major instead: the lists every point of which is a candidate at first (0: query-major), see wide_next
+  int32_t first;
+  size_t lm_off;     // part of the list-major tables, behind the slots
+  LmWorkspace lm;
 };
+// The list-major wide selection goes through a query's probes in stages.  Behind each the k nearest so far are kept and
+// bound the next one, which on data without structure lets k points through for every p0 lists again, twice as many as
+// a byte sum is a lower bound: as many lists at a time as the free slots then hold.
+inline int32_t wide_next(const WideWorkspace &w, int32_t k, int32_t p0, int32_t nprobe) {
+  const int64_t room = (int64_t)w.cap - k - 256;
+  if (room <= 0) return p0;
+  const int64_t p1 = p0 + (int64_t)p0 * room / (2 * k);
+  return p1 < nprobe ? (int32_t)p1 : nprobe;
+}
 // total == 0 unless the wide selection serves this call (L2 distances, 128 < k <= 1024).
-WideWorkspace plan_wide(const ivfpq_index *ix, int64_t Q, int32_t k, int32_t mode);
+WideWorkspace plan_wide(const ivfpq_index *ix, int64_t Q, int32_t nprobe, int32_t k, int32_t mode, int32_t strategy);
 void set_wide_cap(int v);  // slots per query of the wide selection (1024 .. 65536)
 
 // Which part of the probe table a scan launch covers, and for which queries (NULL: all of it).
@@ -153,24 +201,16 @@ int launch_probe_bounds(const ivfpq_index *ix, const float *d_queries, int64_t Q
                         const int32_t *d_probe_ids, const RadiiSq &r2, int32_t mode, const float *d_query_radii,
                         float *d_probe_lb, hipStream_t s, int32_t *d_zero = nullptr, int64_t zero_n = 0);
 // ---- list-major batched scan (scan_lm.hip) --------------------------------------------------
-struct LmWorkspace {      // offsets into the list-major part of the workspace, 256-byte aligned
-  size_t cnt, base;       // [nlist+6], [nlist+1] int32
-  size_t pairs;           // [pairs_cap] (query, list) int32 pairs bucketed by list; behind a pass with byte tables the queries with candidates
-  size_t rank;            // [pairs_cap] int32: a pair's position among the pairs of its list; behind the main pass the queries to redo
-  size_t gcnt, qmap;      // [Q] uint32 / int32
-  size_t qmap_head;       // [Q] int32
-  size_t cand;            // [Q][cap] (distance bits, row) candidates of the list-major scan
-  size_t total;
-  int64_t pairs_cap;
-  int32_t first;          // probed lists per query that are scanned query-major first
-  int32_t cap;            // candidate slots per query
-};
 bool list_major_supported(const ivfpq_index *ix, int32_t nprobe, int32_t k);
 LmWorkspace plan_list_major(const ivfpq_index *ix, int64_t Q, int32_t nprobe);
 int launch_scan_list_major(const ivfpq_index *ix, const float *d_queries, int64_t Q, int32_t nprobe,
                            const int32_t *d_probe_ids, int32_t k, const RadiiSq &r2, int32_t mode,
                            const float *d_query_radii, float *d_probe_lb, int64_t *d_out_ids, float *d_out_dist,
                            const LmWorkspace &w, char *lm_base, hipStream_t s);
+int launch_wide_stage(const ivfpq_index *ix, const float *d_queries, int64_t Q, int32_t nprobe, const int32_t *d_probe_ids,
+                      const RadiiSq &r2, const float *d_query_radii, const float *d_probe_lb, uint32_t *wide_d, int64_t *wide_id,
+                      int32_t *wide_n, uint32_t *wide_bound, int32_t cap, const LmWorkspace &w, char *lm_base, int stage,
+                      int32_t p0, int32_t p1, hipStream_t s);
 void set_lm_first(int v);  // lists per query scanned query-major before the list-major scan (1 .. 64)
 void set_lm_cap(int v);    // candidate slots per query of the list-major scan (64 .. 65536; 0: by the number of probes)
 int get_scan_ablate();

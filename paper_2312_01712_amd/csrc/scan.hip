@@ -595,29 +595,149 @@ __global__ __launch_bounds__(256) void probe_bound_kernel(const float *__restric
 // A query whose slots overflowed, or that has more than WIDE_SORT keys within the bound
 // (long runs of equal distances), gets map[q] = 0 and is served pass by pass afterwards;
 // every other query gets map[q] = -1.
+// Where more than WIDE_EXTRA keys beyond k lie within the bound, the k-th key is looked for first, in a histogram
+// of the keys' range, and only what lies up to its bin is sorted: fewer keys than the next power of two, and the
+// slots may hold any number (a list-major pass over the later lists leaves thousands).
+// only: the other queries' entries of it are negative, or NULL (it may be map itself).
 constexpr int WIDE_SORT = 2048;
+constexpr int WIDE_EXTRA = 24;   // at most: k = 1000 is sorted among 1024
+constexpr int WIDE_BINS = 2048;
+
+// The bound, tightened to the end of the bin that holds the k-th key where more than WIDE_EXTRA keys beyond k lie
+// within it.  256 threads; bins: WIDE_BINS words.  Begins and ends with a barrier.
+__device__ inline uint32_t wide_cut(const uint32_t *d, int n, uint32_t bound, int k, uint32_t *bins, uint32_t *part, int tid) {
+  __shared__ uint32_t cnt, lo, hi, cut;
+  __syncthreads();
+  if (tid == 0) {
+    cnt = 0u;
+    lo = SENT_D;
+    hi = 0u;
+    cut = SENT_D;
+  }
+  for (int i = tid; i < WIDE_BINS; i += 256) bins[i] = 0u;
+  __syncthreads();
+  {
+    uint32_t mine = 0, mlo = SENT_D, mhi = 0;
+    for (int i = tid; i < n; i += 256) {
+      const uint32_t v = d[i];
+      if (v <= bound) {
+        ++mine;
+        mlo = v < mlo ? v : mlo;
+        mhi = v > mhi ? v : mhi;
+      }
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {
+      const uint32_t l = (uint32_t)__shfl_xor((int)mlo, off), h = (uint32_t)__shfl_xor((int)mhi, off);
+      mine += (uint32_t)__shfl_xor((int)mine, off);
+      mlo = l < mlo ? l : mlo;
+      mhi = h > mhi ? h : mhi;
+    }
+    if ((tid & 63) == 0) {
+      __hip_atomic_fetch_add(&cnt, mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      __hip_atomic_fetch_min(&lo, mlo, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      __hip_atomic_fetch_max(&hi, mhi, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+  }
+  __syncthreads();
+  if (cnt <= (uint32_t)(k + WIDE_EXTRA)) return cnt >= (uint32_t)k && hi < bound ? hi : bound;   // (cnt and hi are written no more)
+  const uint32_t first = lo;
+  const int width = 32 - __clz((int)((hi - first) | 1u));   // bits of the range
+  const int shift = width > 11 ? width - 11 : 0;            // 2^11 bins
+  for (int i = tid; i < n; i += 256) {
+    const uint32_t v = d[i];
+    if (v <= bound) __hip_atomic_fetch_add(&bins[(v - first) >> shift], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  }
+  __syncthreads();
+  uint32_t c[WIDE_BINS / 256], sum = 0;   // thread t: bins 8 t .. 8 t + 7
+#pragma unroll
+  for (int j = 0; j < WIDE_BINS / 256; ++j) sum += c[j] = bins[tid * (WIDE_BINS / 256) + j];
+  part[tid] = sum;
+  __syncthreads();
+  for (int off = 1; off < 256; off <<= 1) {
+    const uint32_t v = tid >= off ? part[tid - off] : 0u;
+    __syncthreads();
+    part[tid] += v;
+    __syncthreads();
+  }
+  uint32_t run = part[tid] - sum;
+#pragma unroll
+  for (int j = 0; j < WIDE_BINS / 256; ++j) {
+    if (run < (uint32_t)k && (uint32_t)k <= run + c[j]) {   // exactly one thread and bin
+      const uint64_t end = (uint64_t)first + ((uint64_t)(tid * (WIDE_BINS / 256) + j + 1) << shift) - 1;   // the bin's last key
+      cut = end < (uint64_t)SENT_D ? (uint32_t)end : SENT_D;
+    }
+    run += c[j];
+  }
+  __syncthreads();
+  return cut < bound ? cut : bound;
+}
+
+// Between two stages of the list-major wide selection: a query's bound is tightened and the slots it rules out are
+// dropped.  Chunks of 256 slots are read, counted and written back in order; a key never moves to a higher slot, so the
+// chunk being written never reaches the one read next.
+__global__ __launch_bounds__(256) void wide_tighten_kernel(uint32_t *wd, int64_t *wid, int32_t *__restrict__ wn,
+                                                           uint32_t *__restrict__ wbound, int cap, int k) {
+  __shared__ uint32_t bins[WIDE_BINS], part[256];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int64_t q = blockIdx.x;
+  const int n = wn[q];
+  if (n < k) return;   // a bound takes k keys (-1: the query's slots did not suffice)
+  uint32_t *d = wd + q * cap;
+  int64_t *id = wid + q * cap;
+  const uint32_t bound = wide_cut(d, n, wbound[q], k, bins, part, tid);
+  int out = 0;
+  for (int base = 0; base < n; base += 256) {
+    const int i = base + tid;
+    const uint32_t v = i < n ? d[i] : SENT_D;
+    const int64_t row = i < n ? id[i] : 0;
+    const bool keep = i < n && v <= bound;
+    const unsigned long long bal = __ballot(keep);
+    if (lane == 0) part[wave] = (uint32_t)__popcll(bal);
+    __syncthreads();   // the counts are there, and every read of this chunk has completed
+    int before = 0, total = 0;
+    for (int w = 0; w < 4; ++w) {
+      const int c = (int)part[w];
+      total += c;
+      if (w < wave) before += c;
+    }
+    if (keep) {
+      const int pos = out + before + __popcll(bal & ((1ull << lane) - 1ull));
+      d[pos] = v;
+      id[pos] = row;
+    }
+    out += total;
+    __syncthreads();   // counts free for the next chunk
+  }
+  if (tid == 0) {
+    wn[q] = out;
+    wbound[q] = bound;
+  }
+}
 
 __global__ __launch_bounds__(256) void wide_select_kernel(const uint32_t *__restrict__ wd, const int64_t *__restrict__ wid,
                                                           const int32_t *__restrict__ wn,
                                                           const uint32_t *__restrict__ wbound,
                                                           const int64_t *__restrict__ ids, int cap, int k,
                                                           int64_t *__restrict__ out_ids, float *__restrict__ out_dist,
-                                                          int32_t *__restrict__ map) {
-  __shared__ uint32_t sd[WIDE_SORT];
-  __shared__ int64_t sid[WIDE_SORT];
+                                                          int32_t *map, const int32_t *only) {
+  __shared__ uint32_t sd[WIDE_SORT];    // first the bins
+  __shared__ int64_t sid[WIDE_SORT];    // first the sums over bins
   __shared__ uint32_t cnt;
+  static_assert(WIDE_BINS <= WIDE_SORT, "bins in the keys' place");
   const int tid = threadIdx.x;
   const int64_t q = blockIdx.x;
+  if (only && only[q] < 0) return;
   const int n = wn[q];
   if (n < 0) {
     if (tid == 0) map[q] = 0;
     return;
   }
-  const uint32_t bound = wbound[q];
-  if (tid == 0) cnt = 0u;
-  __syncthreads();
   const uint32_t *d = wd + q * cap;
   const int64_t *id = wid + q * cap;
+  const uint32_t bound = wide_cut(d, n, wbound[q], k, sd, reinterpret_cast<uint32_t *>(sid), tid);
+  if (tid == 0) cnt = 0u;
+  __syncthreads();
   for (int i = tid; i < n; i += 256) {
     const uint32_t v = d[i];
     if (v <= bound) {
@@ -1047,6 +1167,8 @@ int launch_scan(const ivfpq_index *ix, const float *d_queries, int64_t Q, int32_
   const bool ip = ix->metric == IVFPQ_METRIC_IP;
   const WideWorkspace *ww = view ? view->wide : nullptr;
   const bool wide = ww && ww->total > 0 && k > KP && k <= 8 * KP && !dump && !ip && mode == 0 && !a.qmap;
+  // (a plain scan forms every sum; without list-level bounds nothing keeps the candidates few)
+  const int32_t rest_first = wide && d_probe_lb && a.probe_stride == nprobe && !(a.ablate & (8 | 64)) ? ww->first : 0;
   a.gbound = nullptr;
   if (d_probe_lb && !dump && !ip && !(a.ablate & 64)) {
     // Probes split over workgroups: with one list per workgroup and all workgroups resident at
@@ -1060,7 +1182,9 @@ int launch_scan(const ivfpq_index *ix, const float *d_queries, int64_t Q, int32_
     if (!split_once) {
       if (!(view && view->bounds_ready))
         if (int rc = launch_probe_bounds(ix, d_queries, Q, nprobe, d_probe_ids, r2, mode, d_query_radii, d_probe_lb, s,
-                                         reinterpret_cast<int32_t *>(a.gbound), Q))
+                                         rest_first > 0 ? reinterpret_cast<int32_t *>(view->wide_base + ww->lm_off + ww->lm.cnt)
+                                                        : reinterpret_cast<int32_t *>(a.gbound),
+                                         rest_first > 0 ? lm_counters(ix->nlist) : Q))
           return rc;
       a.probe_lb = d_probe_lb;
     }
@@ -1103,9 +1227,30 @@ int launch_scan(const ivfpq_index *ix, const float *d_queries, int64_t Q, int32_
       c.wide_bound = reinterpret_cast<uint32_t *>(wb + ww->bound);
       c.wide_cap = ww->cap;
       int32_t *map = reinterpret_cast<int32_t *>(wb + ww->qmap);
+      auto select = [&](const int32_t *only) {
+        hipLaunchKernelGGL(wide_select_kernel, dim3((unsigned)qc), dim3(256), 0, s, c.wide_d, c.wide_id, c.wide_n,
+                           c.wide_bound, ix->d_ids, ww->cap, k, c.out_ids, c.out_dist, map, only);
+      };
+      if (rest_first > 0) {
+        // In stages, list-major: every point of the first lists, then what byte tables find within the bound of
+        // the k nearest so far.  The queries whose slots did not suffice go through all lists query-major.
+        char *lm_base = wb + ww->lm_off;
+        if (q0 > 0)
+          if (int rc = launch_fill_i32(reinterpret_cast<int32_t *>(lm_base + ww->lm.cnt), lm_counters(ix->nlist), 0, s)) return rc;
+        int32_t p0 = 0, p1 = rest_first;
+        for (int stage = 0; p0 < nprobe; ++stage, p0 = p1, p1 = wide_next(*ww, k, p0, nprobe)) {
+          if (stage > 0)
+            hipLaunchKernelGGL(wide_tighten_kernel, dim3((unsigned)qc), dim3(256), 0, s, c.wide_d, c.wide_id, c.wide_n,
+                               c.wide_bound, ww->cap, k);
+          if (int rc = launch_wide_stage(ix, c.queries, qc, nprobe, c.probe_ids, r2, c.query_radii, c.probe_lb, c.wide_d,
+                                         c.wide_id, c.wide_n, c.wide_bound, ww->cap, ww->lm, lm_base, stage, p0, p1, s))
+            return rc;
+        }
+        select(nullptr);
+        c.qmap = map;
+      }
       if (int rc = dispatch(c, qc)) return rc;
-      hipLaunchKernelGGL(wide_select_kernel, dim3((unsigned)qc), dim3(256), 0, s, c.wide_d, c.wide_id, c.wide_n,
-                         c.wide_bound, ix->d_ids, ww->cap, k, c.out_ids, c.out_dist, map);
+      select(c.qmap);
       ScanView rest;
       rest.probe_stride = a.probe_stride;
       rest.qmap = map;

@@ -55,7 +55,7 @@ struct LmArgs {
   const int64_t *ids;           // [N]
   int64_t *out_ids;             // [Q][k]: phase A's top-k on entry to the merge, the result after it
   float *out_dist;              // [Q][k]
-  int32_t *cnt;                 // [nlist] pairs per list; then [2]: queries to be redone, and those of them taken up; then [2]: queries with candidates in each main pass, and [2]: those of them taken up by lm_settle_kernel
+  int32_t *cnt;                 // [nlist] pairs per list; then [2]: queries to be redone, and those of them taken up; then per stage [2]: queries with candidates, and those of them taken up by lm_settle_kernel
   int32_t *rank;                // [max(Q, Q*(nprobe-first))] position of a pair among its list's pairs, -1: no pair
   int32_t *base;                // [nlist+1] first pair slot of a list (ranges padded to whole groups); [nlist] = slots in use
   int2 *pairs;                  // [Q*(nprobe-first) + (LMB_G - 1) nlist] (query, list); query -1 pads a list's range
@@ -70,8 +70,15 @@ struct LmArgs {
   int32_t D, M, dsub, Mp, nlist, nprobe, first, k, cap, mode;
   int32_t p0, p1;               // the probes [p0, p1) of every query that the current main pass serves
   int32_t later;                // this is not the first main pass: qmap already names queries to be redone
+  int32_t stage;                // which of the passes of a call with candidates to settle
   int32_t group;                // queries per group of the pass the pairs are bucketed for
   int32_t head_done;            // the head pass has run: queries it left out (qmap_head) have no first-list result yet
+  const float *tau;             // [Q] x tau_stride: the k-th distance that filters the main pass (NaN: none yet)
+  int32_t tau_stride;
+  // Behind the wide selection's first lists (k above KP; NULL otherwise) the slots are its own: cand is [Q][cap] row,
+  // as 64 bits, once settled, with the distances beside; cap the slots of a query
+  int32_t *wide_n;              // [Q] slots in use, -1: a query that is left out
+  uint32_t *wide_d;             // [Q][cap] distance keys
 };
 
 // One thread per (query, probe >= first).  fill == 0: count the surviving pairs of every list
@@ -94,12 +101,13 @@ __global__ __launch_bounds__(256) void lm_pairs_kernel(LmArgs a, int fill, int h
     if (r >= 0) a.pairs[a.base[c] + r] = make_int2((int)q, c);
     return;
   }
-  if (!head && p == a.p0) a.gcnt[q] = 0u;
+  if (!head && p == a.p0) a.gcnt[q] = a.wide_n && a.wide_n[q] > 0 ? (uint32_t)a.wide_n[q] : 0u;
   bool take = true;
   // a query the head pass left out has no bound yet: it takes no part here and is redone
   // query-major over all of its lists (lm_merge_kernel puts it on that list)
   if (!head && a.head_done && a.qmap_head[q] >= 0) take = false;
   if (!head && a.later && a.qmap[q] >= 0) take = false;   // nor does one whose slots have overflowed
+  if (a.wide_n && a.wide_n[q] < 0) take = false;
   const bool exists = (uint32_t)c < (uint32_t)a.nlist;
   const int64_t len = exists ? a.list_offsets[c + 1] - a.list_offsets[c] : 0;
   if (head) {
@@ -110,8 +118,7 @@ __global__ __launch_bounds__(256) void lm_pairs_kernel(LmArgs a, int fill, int h
   if (len <= 0) take = false;
   if (take && !head && a.probe_lb) {
     // no point of the list can reach the k-th distance that phase A already guarantees
-    const float tau = a.out_dist[q * a.k + a.k - 1];
-    if (a.probe_lb[q * a.nprobe + p] > tau) take = false;
+    if (a.probe_lb[q * a.nprobe + p] > a.tau[q * a.tau_stride]) take = false;
   }
   a.rank[idx] = take ? atomicAdd(&a.cnt[c], 1) : -1;
 }
@@ -688,7 +695,7 @@ __global__ __launch_bounds__(LM_NW * 64) __attribute__((amdgpu_waves_per_eu(LM_N
 // per fp32 table, 3.6 ms with byte tables and every task settling its candidates, 2.6 and 0.45 ms with
 // lm_settle_kernel behind (0.2 of which the merge took before); hit counts, 5000 queries: 3.6, 1.4, 1.2 ms.
 constexpr int LMB_NW = 16;      // wavefronts: one workgroup per CU (the table takes 2 KiB per subspace), 4 per SIMD
-constexpr int LMB_QUEUE = 3072; // candidates a task can hold; a query that loses one is redone query-major
+constexpr int LMB_QUEUE = 3072; // candidates a task holds; more go to the queries' slots one by one
 constexpr int LMB_TOP = 63;
 
 typedef uint16_t ushortx2 __attribute__((ext_vector_type(2)));
@@ -704,7 +711,7 @@ struct LmbFetch {
 
 // Floats of a (subspace, query) record, padded to whole 16-byte reads.
 constexpr int lmb_rec(int dsub) { return dsub == 2 ? 4 : 8; }
-constexpr int LMB_SMALL = 96;   // words: two sets of a task's limits, queries and losses, and the two queue counters
+constexpr int LMB_SMALL = 64;   // words: two sets of a task's limits and queries, and the two queue counters
 constexpr size_t lmb_lds(int mt, int dsub) {
   return (size_t)mt * 2048 + (size_t)LMB_G * mt * (4 * lmb_rec(dsub) + 4 + 2) + (size_t)mt * 4 + (size_t)LMB_QUEUE * 4 + LMB_SMALL * 4;
 }
@@ -740,8 +747,7 @@ __global__ __launch_bounds__(LMB_NW * 64) __attribute__((amdgpu_waves_per_eu(4))
   // two sets: a task's are read until its candidates have left, when the next one's are already there
   LDS uint32_t *sT = small;                        // [2][8] sums below this are candidates
   LDS int32_t *sq = (LDS int32_t *)(small + 16);   // [2][8] queries
-  LDS uint32_t *lost = small + 32;                 // [2][8] a candidate of the query found no room
-  LDS uint32_t *qn = small + 48;                   // [2] candidates offered to the queue
+  LDS uint32_t *qn = small + 32;                   // [2] candidates offered to the queue
 
   int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -814,7 +820,7 @@ __global__ __launch_bounds__(LMB_NW * 64) __attribute__((amdgpu_waves_per_eu(4))
         const float r = a.query_radii[q * MT + lane];
         f.r2 = r * r;
       }
-      f.tau = a.out_dist[q * a.k + a.k - 1];
+      f.tau = a.tau[q * a.tau_stride];
     }
   };
   // ... and writes them to the records and to set `par` of the small words
@@ -871,7 +877,7 @@ __global__ __launch_bounds__(LMB_NW * 64) __attribute__((amdgpu_waves_per_eu(4))
       add += xor_f32<2>(add);
       add += xor_f32<1>(add);
       const float lim = fmaf(tau * s, 1.00001f, add) + 0.25f;
-      T = lim < 60000.0f ? (uint32_t)lim : 60000u;   // NaN (0 x inf): every point
+      T = lim < 60000.0f ? (uint32_t)lim : 60000u;   // NaN (0 x inf, or no k-th distance): every point
     } else {
       if (on) {
 #pragma unroll
@@ -883,7 +889,6 @@ __global__ __launch_bounds__(LMB_NW * 64) __attribute__((amdgpu_waves_per_eu(4))
     if (lane == 0) {
       sT[par * 8 + g] = f.qid >= 0 ? T + 1u : 0u;
       sq[par * 8 + g] = f.qid;
-      lost[par * 8 + g] = 0u;
       if (g == 0) qn[par] = 0u;
     }
   };
@@ -1098,14 +1103,18 @@ __global__ __launch_bounds__(LMB_NW * 64) __attribute__((amdgpu_waves_per_eu(4))
             word = ((uint32_t)i << 11) | (((g & 2u) ? zz >> 16 : zz & 0xFFFFu) << 3) | g;
           }
           if (pos < (uint32_t)LMB_QUEUE) queue[pos] = word;
-          else lost[par * 8 + g] = 1u;
+          else {   // no room: straight to the query's slots
+            const int64_t q = sq[par * 8 + g];
+            const uint32_t slot = atomicAdd(&a.gcnt[q], 1u);
+            if (slot < (uint32_t)a.cap)
+              a.cand[q * a.cap + slot] = make_uint2(MODE == 0 ? (uint32_t)list : __float_as_uint((float)((word >> 3) & 255u)), (uint32_t)(row0 + i));
+          }
         }
       }
     }
     if (more) put_params(fx, par ^ 1);
     __syncthreads();   // the list is scanned: the queue is complete, the next task's records are there
     const int n = (int)umin32(qn[par], (uint32_t)LMB_QUEUE);
-    if (tid < LMB_G && lost[par * 8 + tid] != 0u) atomicAdd(&a.gcnt[sq[par * 8 + tid]], (uint32_t)a.cap + 1u);   // redone query-major
     const int64_t drow0 = row0;
     const int dlist = list;
     if (more) {
@@ -1148,7 +1157,14 @@ __global__ __launch_bounds__(256) void lm_sort_out_kernel(LmArgs a, int list_red
   const int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x;
   const int lane = threadIdx.x & 63;
   bool named = false, active = false;
-  if (q < a.Q) {
+  if (q < a.Q && a.wide_n) {
+    const uint32_t n = a.gcnt[q];
+    const int32_t n0 = a.wide_n[q];
+    active = n0 >= 0 && n > (uint32_t)n0 && n <= (uint32_t)a.cap;
+    a.qmap[q] = n0;                                            // from here on lm_settle_kernel settles
+    if (n > (uint32_t)a.cap) a.wide_n[q] = -1;                 // its slots did not suffice
+    else if (active) a.wide_n[q] = (int32_t)n;
+  } else if (q < a.Q) {
     const uint32_t n = a.gcnt[q];
     named = n > (uint32_t)a.cap || (a.head_done && a.qmap_head[q] >= 0) || (a.later && a.qmap[q] >= 0);
     active = !named && n > 0u;
@@ -1162,7 +1178,7 @@ __global__ __launch_bounds__(256) void lm_sort_out_kernel(LmArgs a, int list_red
     first = __builtin_amdgcn_readfirstlane(first);
     if (on) list[first + __popcll(bal & ((1ull << lane) - 1ull))] = (int32_t)q;
   };
-  put(active, a.cnt + a.nlist + 2 + (a.later ? 1 : 0), (int32_t *)a.pairs);
+  put(active, a.cnt + a.nlist + 2 + 2 * a.stage, (int32_t *)a.pairs);
   if (list_redo) put(named, a.cnt + a.nlist, a.redo);
 }
 
@@ -1175,11 +1191,16 @@ __global__ __launch_bounds__(256) void lm_sort_out_kernel(LmArgs a, int list_red
 // sorted list.  Three requests are in flight while a group of 64 is summed: the next group's codes, its lists'
 // ranges before them, and the slots of the group after it.
 constexpr int LMS_NW = 16;
+// Slots a wavefront settles at a time for the wide selection, where a query's are independent.  1M x 128, 2000 queries
+// of 32 probes, k = 1000: 581 us with a query a wavefront, 224 so.
+constexpr int LMS_PIECE = 512;
 constexpr int LMS_QUEUE = 128;   // per wavefront: fewer than 64 waiting and the 64 of a group
-constexpr size_t lms_lds(int mt, int dsub) { return (size_t)mt * 1024 * dsub + (size_t)LMS_NW * (LMS_QUEUE * 8 + mt * 4); }
+constexpr size_t lms_lds(int mt, int dsub) { return (size_t)mt * 1024 * dsub + (size_t)LMS_NW * (LMS_QUEUE * 8 + mt * 4) + 16; }
 #define CONSTANT __attribute__((address_space(4)))
 
-template <int MT, int DSUB>
+// WIDE: behind the wide selection's first lists.  A candidate's distance and row take its slot; those beyond the bound
+// are left to wide_select_kernel, which picks the k nearest of a query's slots.
+template <int MT, int DSUB, bool WIDE>
 __global__ __launch_bounds__(LMS_NW * 64) __attribute__((amdgpu_waves_per_eu(4))) void lm_settle_kernel(LmArgs a, RadiiSq r2) {
   constexpr int NCH = MT / 16;
   extern __shared__ __align__(16) unsigned char smem[];
@@ -1187,28 +1208,48 @@ __global__ __launch_bounds__(LMS_NW * 64) __attribute__((amdgpu_waves_per_eu(4))
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int32_t *active = (const int32_t *)a.pairs;   // queries with candidates, listed by lm_sort_out_kernel
-  const int nactive = a.cnt[a.nlist + 2 + (a.later ? 1 : 0)], nwg = gridDim.x;
+  const int pieces = WIDE ? (a.cap + LMS_PIECE - 1) / LMS_PIECE : 1;   // of a query
+  const int nqueries = a.cnt[a.nlist + 2 + 2 * a.stage], nactive = nqueries * pieces, nwg = gridDim.x;
   if ((int)blockIdx.x >= nactive) return;
   for (int i = tid; i < MT * 256 * DSUB / 4; i += LMS_NW * 64)
     ((LDS floatx4 *)smem3)[i] = ((const floatx4 *)a.codebooks)[i];
   LDS uint32_t *qd = (LDS uint32_t *)(smem3 + (size_t)MT * 1024 * DSUB) + wave * LMS_QUEUE * 2, *qrow = qd + LMS_QUEUE;
   LDS float *sr2 = (LDS float *)(smem3 + (size_t)MT * 1024 * DSUB + (size_t)LMS_NW * LMS_QUEUE * 8) + wave * MT;   // r_m^2 of the wavefront's query
+  LDS uint32_t *taken = (LDS uint32_t *)(smem3 + lms_lds(MT, DSUB) - 16);
+  if (tid == 0) *taken = 0u;
   __syncthreads();   // the last one: from here on every wavefront is by itself
   const int k = a.k;
-  int32_t *ticket = a.cnt + a.nlist + 4 + (a.later ? 1 : 0);
-  for (int x = wave * nwg + (int)blockIdx.x; x < nactive;) {
-    int32_t next = 0;
-    if (lane == 0) next = atomicAdd(ticket, 1);
-    const int64_t q = __builtin_amdgcn_readfirstlane(active[x]);
-    const int n = __builtin_amdgcn_readfirstlane((int)a.gcnt[q]);   // 1 .. cap
-    {
-      const uint2 *slots = a.cand + q * a.cap;
+  int32_t *ticket = a.cnt + a.nlist + 3 + 2 * a.stage;
+  // Three quarters of the queries are dealt to the workgroups, whose wavefronts take them up by a counter in LDS; the
+  // others are taken up by whoever is free.  (All of them so, an atomic on one word of global memory for each: 454 us
+  // instead of 322 for the two passes of 10 000 queries of the 1M x 96 configuration.)  The wide selection's
+  // pieces are dealt out altogether, the first pieces of all queries first.
+  const int dealt = WIDE ? nactive : nactive - nactive / 4;
+  for (;;) {
+    uint32_t turn = 0;
+    if (lane == 0) turn = lds_add(taken);
+    int x = (int)blockIdx.x + nwg * __builtin_amdgcn_readfirstlane((int)turn);
+    if (x >= dealt) {
+      if (WIDE) break;
+      int32_t next = 0;
+      if (lane == 0) next = atomicAdd(ticket, 1);
+      x = dealt + __builtin_amdgcn_readfirstlane(next);
+      if (x >= nactive) break;
+    }
+    const int64_t q = __builtin_amdgcn_readfirstlane(active[WIDE ? x % nqueries : x]);
+    int n = __builtin_amdgcn_readfirstlane((int)a.gcnt[q]), n0 = 0;   // 1 .. cap
+    if constexpr (WIDE) {
+      n0 = __builtin_amdgcn_readfirstlane(a.qmap[q]) + x / nqueries * LMS_PIECE;
+      n = n < n0 + LMS_PIECE ? n : n0 + LMS_PIECE;
+    }
+    if (n > n0) {
+      uint2 *slots = a.cand + q * a.cap;
       Key L0, L1, tau;
       auto take_tau = [&]() __attribute__((always_inline)) {
         const Key t0 = bcast_key(L0, (k - 1) & 63), t1 = bcast_key(L1, (k - 1) & 63);
         tau = (k - 1) < 64 ? t0 : t1;
       };
-      {
+      if constexpr (!WIDE) {
         const int64_t o = q * k;
         const bool in0 = lane < k, in1 = 64 + lane < k;
         const int64_t id0 = in0 ? a.out_ids[o + lane] : -1, id1 = in1 ? a.out_ids[o + 64 + lane] : -1;
@@ -1216,8 +1257,8 @@ __global__ __launch_bounds__(LMS_NW * 64) __attribute__((amdgpu_waves_per_eu(4))
         L0.id = id0 >= 0 ? id0 : SENT_ID;
         L1.d = id1 >= 0 ? __float_as_uint(a.out_dist[o + 64 + lane]) : SENT_D;
         L1.id = id1 >= 0 ? id1 : SENT_ID;
+        take_tau();
       }
-      take_tau();
       int waiting = 0;
       bool changed = false;
       auto fold = [&](int from, int count) __attribute__((always_inline)) {   // at most 64 of the queue
@@ -1245,14 +1286,18 @@ __global__ __launch_bounds__(LMS_NW * 64) __attribute__((amdgpu_waves_per_eu(4))
       auto where_of = [&](uint32_t c) __attribute__((always_inline)) {
         return Where{a.list_offsets[c], a.list_offsets[c + 1], a.list_blocks[c]};
       };
-      auto codes_of = [&](const uint2 &e, const Where &w, uintx4 (&cw)[NCH]) __attribute__((always_inline)) {
+      auto codes_of = [&](const uint2 &e, const Where &w, uint32_t (&cw)[MT / 4]) __attribute__((always_inline)) {
         const uint32_t i = e.y - (uint32_t)w.o0;   // (rows are below 2^32)
         const int64_t nb = (w.o1 - w.o0 + 63) >> 6;
         const uint8_t *src = a.codes + w.blk * ivfpq_block_bytes(MT) + (int64_t)(i >> 6) * 1024 + (i & 63u) * 16;
 #pragma unroll
-        for (int j = 0; j < NCH; ++j) cw[j] = *(const GLOBAL uintx4 *)(src + j * nb * 1024);
+        for (int j = 0; j < NCH; ++j) {
+          const uintx4 v = *(const GLOBAL uintx4 *)(src + j * nb * 1024);
+#pragma unroll
+          for (int x = 0; x < 4; ++x) cw[4 * j + x] = v[x];
+        }
       };
-      const CONSTANT float *qp = (const CONSTANT float *)(uintptr_t)(a.queries + q * a.D);
+      uintptr_t qaddr = (uintptr_t)(a.queries + q * a.D);
       if (lane < MT) {
         float r = r2.v[lane];
         if (a.query_radii) {
@@ -1261,30 +1306,35 @@ __global__ __launch_bounds__(LMS_NW * 64) __attribute__((amdgpu_waves_per_eu(4))
         }
         sr2[lane] = r;
       }
-      uint2 e = slot_of(0), en = slot_of(64);
-      uintx4 cw[NCH];
+      uint2 e = slot_of(n0), en = slot_of(n0 + 64);
+      uint32_t cw[MT / 4];   // one word per four subspaces
       codes_of(e, where_of(e.x), cw);
-      for (int u = 0; u < n; u += 64) {
+      for (int u = n0; u < n; u += 64) {
+        asm volatile("" : "+s"(qaddr) : : "memory");   // (the query's row and radii are read anew: kept across groups they spill)
+        const CONSTANT float *qp = (const CONSTANT float *)qaddr;
         const Where wn = where_of(en.x);
         const uint2 enn = slot_of(u + 128);
         const float *cp = a.centroids + (int64_t)e.x * (MT * DSUB);
         float dist = 0.0f;
-        uintx4 cwn[NCH];
-        // (one chunk's code for all: with every chunk's loads hoisted to the front the registers spill)
+        uint32_t cwn[MT / 4];
+        // (one piece of code for all steps: with the loads of all hoisted to the front the registers spill)
+        constexpr int STEP = DSUB == 2 ? 16 : 4;   // subspaces whose part of the centroid's row is requested together
+        constexpr int LK = MT == 48 ? 8 : 4;       // look-ups in flight (more spill)
 #pragma unroll 1
-        for (int j = 0; j < NCH; ++j) {
-          floatx4 cv[4 * DSUB];
+        for (int m0 = 0; m0 < MT; m0 += STEP) {
+          floatx4 cv[STEP * DSUB / 4];
 #pragma unroll
-          for (int x = 0; x < 4 * DSUB; ++x) cv[x] = *(const GLOBAL floatx4 *)(cp + (j * 4 * DSUB + x) * 4);
-          if (j == NCH - 1) codes_of(en, wn, cwn);   // behind this group's last rows, which are wanted sooner
-          const uintx4 w = cw[0];
+          for (int x = 0; x < STEP * DSUB / 4; ++x) cv[x] = *(const GLOBAL floatx4 *)(cp + m0 * DSUB + 4 * x);
+          if (m0 + STEP == MT) codes_of(en, wn, cwn);   // behind this group's last rows, which are wanted sooner
+          uint32_t w[STEP / 4];
 #pragma unroll
-          for (int x = 1; x < NCH; ++x) cw[x - 1] = cw[x];
-          const LDS unsigned char *rows = smem3 + j * 16 * 1024 * DSUB;
+          for (int x = 0; x < STEP / 4; ++x) w[x] = cw[x];
+#pragma unroll
+          for (int x = STEP / 4; x < MT / 4; ++x) cw[x - STEP / 4] = cw[x];
+          const LDS unsigned char *rows = smem3 + m0 * 1024 * DSUB;
           typedef float entry __attribute__((ext_vector_type(DSUB)));
-          constexpr int LK = MT == 48 ? 8 : 4;   // look-ups in flight (more spill)
 #pragma unroll
-          for (int h = 0; h < 16; h += LK) {
+          for (int h = 0; h < STEP; h += LK) {
             entry ev[LK];
             floatx4 rm2[LK / 4];
 #pragma unroll
@@ -1293,7 +1343,7 @@ __global__ __launch_bounds__(LMS_NW * 64) __attribute__((amdgpu_waves_per_eu(4))
               ev[x] = *(const LDS entry *)(rows + (h + x) * 1024 * DSUB + code * (4 * DSUB));
             }
 #pragma unroll
-            for (int x = 0; x < LK / 4; ++x) rm2[x] = *(const LDS floatx4 *)(sr2 + j * 16 + h + 4 * x);
+            for (int x = 0; x < LK / 4; ++x) rm2[x] = *(const LDS floatx4 *)(sr2 + m0 + h + 4 * x);
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int x = 0; x < LK; ++x) {
@@ -1301,7 +1351,7 @@ __global__ __launch_bounds__(LMS_NW * 64) __attribute__((amdgpu_waves_per_eu(4))
 #pragma unroll
               for (int y = 0; y < DSUB; ++y) {
                 const int z = (h + x) * DSUB + y;
-                const float t = (qp[j * 16 * DSUB + z] - cv[z >> 2][z & 3]) - ev[x][y];
+                const float t = (qp[m0 * DSUB + z] - cv[z >> 2][z & 3]) - ev[x][y];
                 d2 = y == 0 ? t * t : fmaf(t, t, d2);
               }
               dist += table_value<0>(d2, rm2[x >> 2][x & 3]);
@@ -1310,27 +1360,34 @@ __global__ __launch_bounds__(LMS_NW * 64) __attribute__((amdgpu_waves_per_eu(4))
           }
         }
         const uint32_t bits = __float_as_uint(dist);
-        const bool pass = u + lane < n && bits <= tau.d;
-        const unsigned long long bal = __ballot(pass);
-        if (bal != 0ull) {
-          if (pass) {
-            const int pos = waiting + __popcll(bal & ((1ull << lane) - 1ull));
-            qd[pos] = bits;
-            qrow[pos] = e.y;
+        if constexpr (WIDE) {
+          if (u + lane < n) {
+            a.wide_d[q * a.cap + u + lane] = bits;
+            slots[u + lane] = make_uint2(e.y, 0u);
           }
-          waiting += __popcll(bal);
-        }
-        while (waiting >= 64 || (waiting > 0 && u + 64 >= n)) {   // the last 64, at the end all
-          const int m = waiting < 64 ? waiting : 64;
-          waiting -= m;
-          fold(waiting, m);
+        } else {
+          const bool pass = u + lane < n && bits <= tau.d;
+          const unsigned long long bal = __ballot(pass);
+          if (bal != 0ull) {
+            if (pass) {
+              const int pos = waiting + __popcll(bal & ((1ull << lane) - 1ull));
+              qd[pos] = bits;
+              qrow[pos] = e.y;
+            }
+            waiting += __popcll(bal);
+          }
+          while (waiting >= 64 || (waiting > 0 && u + 64 >= n)) {   // the last 64, at the end all
+            const int m = waiting < 64 ? waiting : 64;
+            waiting -= m;
+            fold(waiting, m);
+          }
         }
         e = en;
         en = enn;
 #pragma unroll
-        for (int j = 0; j < NCH; ++j) cw[j] = cwn[j];
+        for (int x = 0; x < MT / 4; ++x) cw[x] = cwn[x];
       }
-      if (changed) {
+      if (!WIDE && changed) {
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
           const Key x = h ? L1 : L0;
@@ -1343,7 +1400,6 @@ __global__ __launch_bounds__(LMS_NW * 64) __attribute__((amdgpu_waves_per_eu(4))
         }
       }
     }
-    x = nwg * LMS_NW + __builtin_amdgcn_readfirstlane(next);
   }
 }
 
@@ -1457,9 +1513,9 @@ int launch_lm_byte_t(const LmArgs &a, const RadiiSq &r2, int grid, hipStream_t s
   return IVFPQ_OK;
 }
 
-template <int MT, int DSUB>
+template <int MT, int DSUB, bool WIDE>
 int launch_lm_settle_t(const LmArgs &a, const RadiiSq &r2, int grid, hipStream_t s) {
-  auto kern = lm_settle_kernel<MT, DSUB>;
+  auto kern = lm_settle_kernel<MT, DSUB, WIDE>;
   static std::atomic<uint64_t> prepared;
   if (int rc = prepare_kernel(kern, prepared)) return rc;
   static_assert(lms_lds(MT, DSUB) <= (size_t)LDS_PER_CU, "codebook and queues fit a CU");
@@ -1467,12 +1523,12 @@ int launch_lm_settle_t(const LmArgs &a, const RadiiSq &r2, int grid, hipStream_t
   return IVFPQ_OK;
 }
 
+template <bool WIDE>
 int launch_lm_settle(const LmArgs &a, const RadiiSq &r2, int cus, hipStream_t s) {
-  const int64_t need = (a.Q + LMS_NW - 1) / LMS_NW;
-  const int grid = need < cus ? (int)need : cus;
-  if (a.M == 48) return launch_lm_settle_t<48, 2>(a, r2, grid, s);
-  if (a.M == 64) return launch_lm_settle_t<64, 2>(a, r2, grid, s);
-  return launch_lm_settle_t<16, 4>(a, r2, grid, s);
+  const int grid = a.Q < cus ? (int)a.Q : cus;   // (a workgroup without a query of its own leaves at once)
+  if (a.M == 48) return launch_lm_settle_t<48, 2, WIDE>(a, r2, grid, s);
+  if (a.M == 64) return launch_lm_settle_t<64, 2, WIDE>(a, r2, grid, s);
+  return launch_lm_settle_t<16, 4, WIDE>(a, r2, grid, s);
 }
 
 template <int MODE>
@@ -1504,12 +1560,9 @@ void set_lm_cap(int v) { g_lm_cap.store(v, std::memory_order_relaxed); }
 
 bool list_major_supported(const ivfpq_index *ix, int32_t nprobe, int32_t k) {
   if (ix->metric != IVFPQ_METRIC_L2 || k > KP) return false;
-  const bool shape = (ix->M == 48 && ix->dsub == 2) || (ix->M == 64 && ix->dsub == 2) || (ix->M == 16 && ix->dsub == 4);
-  if (!shape || lm_scan_lds(ix->M, ix->D) > (size_t)LDS_PER_CU || LM_G * ix->D > LM_NW * 64 || LM_G * ix->M > LM_NW * 64) return false;
+  if (!list_major_shape(ix) || lm_scan_lds(ix->M, ix->D) > (size_t)LDS_PER_CU || LM_G * ix->D > LM_NW * 64 || LM_G * ix->M > LM_NW * 64) return false;
   return nprobe > g_lm_first.load(std::memory_order_relaxed);
 }
-
-static size_t lm_align(size_t v) { return (v + 255) & ~(size_t)255; }
 
 LmWorkspace plan_list_major(const ivfpq_index *ix, int64_t Q, int32_t nprobe) {
   LmWorkspace w;
@@ -1519,18 +1572,97 @@ LmWorkspace plan_list_major(const ivfpq_index *ix, int64_t Q, int32_t nprobe) {
   // 1M x 96 configuration (64 probes): 4096 slots 11.39 ms per batch, 8192 10.88, 16384 10.71.
   w.cap = g_lm_cap.load(std::memory_order_relaxed);
   if (w.cap == 0) w.cap = nprobe >= 64 ? 16384 : (nprobe * 256 > 4096 ? nprobe * 256 : 4096);
-  w.pairs_cap = Q * (nprobe - w.first > 1 ? nprobe - w.first : 1) + (int64_t)(LMB_G - 1) * ix->nlist;   // also holds the head pass's Q pairs
-  size_t off = 0;
-  w.cnt = off;   off += lm_align(((size_t)ix->nlist + 6) * 4);
-  w.base = off;  off += lm_align(((size_t)ix->nlist + 1) * 4);
-  w.pairs = off; off += lm_align((size_t)w.pairs_cap * 8);
-  w.rank = off;  off += lm_align((size_t)w.pairs_cap * 4);
-  w.gcnt = off;  off += lm_align((size_t)Q * 4);
-  w.qmap = off;  off += lm_align((size_t)Q * 4);
-  w.qmap_head = off; off += lm_align((size_t)Q * 4);
-  w.cand = off;  off += lm_align((size_t)Q * w.cap * 8);
-  w.total = off;
+  plan_list_major_tables(w, ix->nlist, Q, nprobe);
+  w.cand = w.total;
+  w.total += lm_align((size_t)Q * w.cap * 8);
   return w;
+}
+
+static LmArgs lm_args(const ivfpq_index *ix, const float *d_queries, int64_t Q, int32_t nprobe, const int32_t *d_probe_ids,
+                      const float *d_query_radii, const float *d_probe_lb, const LmWorkspace &w, char *lm_base) {
+  LmArgs a = {};
+  a.queries = d_queries;
+  a.probe_ids = d_probe_ids;
+  a.probe_lb = d_probe_lb;
+  a.centroids = ix->d_centroids;
+  a.codebooks = ix->d_codebooks;
+  a.list_offsets = ix->d_list_offsets;
+  a.list_blocks = ix->d_list_blocks;
+  a.codes = ix->d_codes;
+  a.ids = ix->d_ids;
+  a.cnt = reinterpret_cast<int32_t *>(lm_base + w.cnt);
+  a.rank = reinterpret_cast<int32_t *>(lm_base + w.rank);
+  a.redo = a.rank;
+  a.base = reinterpret_cast<int32_t *>(lm_base + w.base);
+  a.pairs = reinterpret_cast<int2 *>(lm_base + w.pairs);
+  a.gcnt = reinterpret_cast<uint32_t *>(lm_base + w.gcnt);
+  a.cand = reinterpret_cast<uint2 *>(lm_base + w.cand);
+  a.qmap = reinterpret_cast<int32_t *>(lm_base + w.qmap);
+  a.qmap_head = reinterpret_cast<int32_t *>(lm_base + w.qmap_head);
+  a.query_radii = d_query_radii;
+  a.Q = Q;
+  a.D = ix->D; a.M = ix->M; a.dsub = ix->dsub; a.Mp = ix->Mp; a.nlist = ix->nlist;
+  a.nprobe = nprobe; a.first = w.first; a.cap = w.cap;
+  a.p0 = w.first;
+  a.p1 = nprobe;
+  a.group = LM_G;
+  return a;
+}
+
+// One wavefront per query: every point of its first lists becomes a candidate of the wide selection.
+__global__ __launch_bounds__(256) void wide_seed_kernel(LmArgs a, uint32_t *__restrict__ bound) {
+  const int lane = threadIdx.x & 63;
+  const int64_t q = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (q >= a.Q) return;
+  int64_t n = 0;
+  for (int p = 0; p < a.first && n <= a.cap; ++p) {
+    const int32_t c = a.probe_ids[q * a.nprobe + p];
+    if ((uint32_t)c >= (uint32_t)a.nlist) continue;
+    const int64_t o0 = a.list_offsets[c], len = a.list_offsets[c + 1] - o0;
+    if (n + len <= a.cap)
+      for (int64_t i = lane; i < len; i += 64) a.cand[q * a.cap + n + i] = make_uint2((uint32_t)c, (uint32_t)(o0 + i));
+    n += len;
+  }
+  if (lane == 0) {
+    a.gcnt[q] = n <= a.cap ? (uint32_t)n : (uint32_t)a.cap + 1u;
+    a.wide_n[q] = 0;
+    bound[q] = SENT_D;
+  }
+}
+
+// The wide selection's candidates (k above KP).  stage 0: all points of the first w.first lists.  Later ones: what lies
+// within the query's bound so far in the probes [p0, p1), from byte tables; it takes the slots behind those in use.
+// Either way the candidates' distances are formed.  (The per-list counts and the words behind them are zero at first.)
+int launch_wide_stage(const ivfpq_index *ix, const float *d_queries, int64_t Q, int32_t nprobe, const int32_t *d_probe_ids,
+                      const RadiiSq &r2, const float *d_query_radii, const float *d_probe_lb, uint32_t *wide_d, int64_t *wide_id,
+                      int32_t *wide_n, uint32_t *wide_bound, int32_t cap, const LmWorkspace &w, char *lm_base, int stage,
+                      int32_t p0, int32_t p1, hipStream_t s) {
+  LmArgs a = lm_args(ix, d_queries, Q, nprobe, d_probe_ids, d_query_radii, d_probe_lb, w, lm_base);
+  a.cand = reinterpret_cast<uint2 *>(wide_id);
+  a.cap = cap;
+  a.tau = reinterpret_cast<const float *>(wide_bound);   // (keys of distances are their bits; none yet: a NaN)
+  a.tau_stride = 1;
+  a.wide_n = wide_n;
+  a.wide_d = wide_d;
+  a.group = LMB_G;
+  a.stage = stage;
+  a.p0 = p0;
+  a.p1 = p1;
+  int dev = 0, cus = 0;
+  IVFPQ_HIP_TRY(hipGetDevice(&dev));
+  IVFPQ_HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
+  if (cus < 1) cus = 1;
+  if (stage == 0) {
+    hipLaunchKernelGGL(wide_seed_kernel, dim3((unsigned)((Q + 3) / 4)), dim3(256), 0, s, a, wide_bound);
+  } else {
+    const unsigned pair_grid = (unsigned)((Q * (p1 - p0) + 255) / 256);
+    hipLaunchKernelGGL(lm_pairs_kernel, dim3(pair_grid), dim3(256), 0, s, a, 0, 0);
+    hipLaunchKernelGGL(lm_offsets_kernel, dim3(1), dim3(1024), 0, s, a);
+    hipLaunchKernelGGL(lm_pairs_kernel, dim3(pair_grid), dim3(256), 0, s, a, 1, 0);
+    if (int rc = launch_lm_byte(a, r2, cus, s)) return rc;
+  }
+  hipLaunchKernelGGL(lm_sort_out_kernel, dim3((unsigned)((Q + 255) / 256)), dim3(256), 0, s, a, 0);
+  return launch_lm_settle<true>(a, r2, cus, s);
 }
 
 int launch_scan_list_major(const ivfpq_index *ix, const float *d_queries, int64_t Q, int32_t nprobe,
@@ -1542,42 +1674,19 @@ int launch_scan_list_major(const ivfpq_index *ix, const float *d_queries, int64_
     return IVFPQ_ERR_UNSUPPORTED;
   }
 
-  LmArgs a;
-  a.queries = d_queries;
-  a.probe_ids = d_probe_ids;
-  a.probe_lb = (get_scan_ablate() & 64) ? nullptr : d_probe_lb;
-  a.centroids = ix->d_centroids;
-  a.codebooks = ix->d_codebooks;
-  a.list_offsets = ix->d_list_offsets;
-  a.list_blocks = ix->d_list_blocks;
-  a.codes = ix->d_codes;
-  a.ids = ix->d_ids;
+  LmArgs a = lm_args(ix, d_queries, Q, nprobe, d_probe_ids, d_query_radii, (get_scan_ablate() & 64) ? nullptr : d_probe_lb, w, lm_base);
   a.out_ids = d_out_ids;
   a.out_dist = d_out_dist;
-  a.cnt = reinterpret_cast<int32_t *>(lm_base + w.cnt);
-  a.rank = reinterpret_cast<int32_t *>(lm_base + w.rank);
-  a.redo = a.rank;
-  a.base = reinterpret_cast<int32_t *>(lm_base + w.base);
-  a.pairs = reinterpret_cast<int2 *>(lm_base + w.pairs);
-  a.gcnt = reinterpret_cast<uint32_t *>(lm_base + w.gcnt);
-  a.cand = reinterpret_cast<uint2 *>(lm_base + w.cand);
-  a.qmap = reinterpret_cast<int32_t *>(lm_base + w.qmap);
-  a.qmap_head = reinterpret_cast<int32_t *>(lm_base + w.qmap_head);
+  a.tau = d_out_dist + k - 1;
+  a.tau_stride = k;
   a.head_max = lm_head_max(ix->M, ix->D);
-  a.query_radii = d_query_radii;
-  a.Q = Q;
-  a.D = ix->D; a.M = ix->M; a.dsub = ix->dsub; a.Mp = ix->Mp; a.nlist = ix->nlist;
-  a.nprobe = nprobe; a.first = w.first; a.k = k; a.cap = w.cap; a.mode = mode;
-  a.head_done = 0;
-  a.later = 0;
-  a.p0 = w.first;
-  a.p1 = nprobe;
-  a.group = LM_G;
+  a.k = k;
+  a.mode = mode;
 
   // list-level lower bounds of every (query, probe); the same launch clears the per-list counts
   // (lm_offsets_kernel leaves them clear for the pass after it)
   int rc = launch_probe_bounds(ix, d_queries, Q, nprobe, d_probe_ids, r2, mode, d_query_radii, d_probe_lb, s, a.cnt,
-                               (int64_t)ix->nlist + 6);
+                               lm_counters(ix->nlist));
   if (rc) return rc;
 
   int dev = 0, cus = 0;
@@ -1635,7 +1744,7 @@ int launch_scan_list_major(const ivfpq_index *ix, const float *d_queries, int64_
   for (int p0 = w.first, p1 = split; p0 < nprobe; p0 = p1, p1 = nprobe) {
     a.p0 = p0;
     a.p1 = p1;
-    a.later = p0 > w.first ? 1 : 0;
+    a.later = a.stage = p0 > w.first ? 1 : 0;
     const int64_t npairs = Q * (p1 - p0);
     const unsigned pair_grid = (unsigned)((npairs + 255) / 256);
     hipLaunchKernelGGL(lm_pairs_kernel, dim3(pair_grid), dim3(256), 0, s, a, 0, 0);
@@ -1645,7 +1754,7 @@ int launch_scan_list_major(const ivfpq_index *ix, const float *d_queries, int64_
     if (rc) return rc;
     if (bytes && mode == 0) {
       hipLaunchKernelGGL(lm_sort_out_kernel, dim3((unsigned)((Q + 255) / 256)), dim3(256), 0, s, a, p1 == nprobe && Q > 4096 ? 1 : 0);
-      rc = launch_lm_settle(a, r2, cus, s);
+      rc = launch_lm_settle<false>(a, r2, cus, s);
       if (rc) return rc;
     } else {
       hipLaunchKernelGGL(lm_merge_kernel, dim3((unsigned)((Q + 3) / 4)), dim3(256), 0, s, a);

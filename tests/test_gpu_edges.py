@@ -213,3 +213,37 @@ def test_row_proposals_that_are_not_accepted(name, metric):
         _same(gi.coarse(dq, nprobe), (np.tile(o_pid, (reps, 1)), np.tile(o_pd, (reps, 1))), (name, nprobe))
     assert name == "duplicates" or b.coarse_fallbacks() > 0
     gi.close()
+
+
+@pytest.mark.parametrize("D,M", [(96, 48), (128, 64), (64, 16)])
+@pytest.mark.parametrize("k,cap,radius", [(129, 8192, 0.6), (500, 8192, 0.6), (1000, 8192, 0.6), (700, 1024, 0.6), (300, 2048, np.inf)])
+def test_more_than_128_neighbours_of_large_batches(D, M, k, cap, radius):
+    """k above 128 in batches whose later probes are scanned list-major behind the first few: queries that one list
+    answers, queries between the lists (slots and queues that overflow: with 1024 slots most of them, redone by the
+    plain wide selection and then pass by pass), many equal distances, empty lists, probes that hold fewer than k
+    points at first, shared and per-query radii, and the query-major scan of the same call."""
+    b = _binding()
+    rng = np.random.default_rng(M + k)
+    nlist, nprobe, distinct, reps = 60, 40, 100, 5
+    sizes = rng.integers(100, 420, size=nlist)
+    sizes[:3] = (0, 1, 64)
+    idx = _index(rng, D, M, sizes, centre=0.15)
+    idx.codes[idx.list_offsets[5]:idx.list_offsets[8]] = idx.codes[0]   # runs of equal distances
+    q = (idx.centroids[rng.integers(0, nlist, distinct)] + 0.25 * rng.normal(size=(distinct, D))).astype(np.float32)
+    q[::3] = idx.centroids[rng.integers(0, nlist, len(q[::3]))]
+    radii = np.full(M, radius * np.sqrt(D / M), dtype=np.float32)
+    per_query = np.where(np.isinf(radius), np.inf, rng.uniform(0.3, 0.9, size=(distinct, M)) * np.sqrt(D / M)).astype(np.float32)
+    gi = b.IvfPqIndex.from_index(idx)
+    dq = torch.from_numpy(q).cuda().repeat(reps, 1)
+    try:
+        b.set_option("wide_cap", cap)
+        for own in (None, per_query):
+            want = oracle.search(q, idx, nprobe, k, radii if own is None else own, threads=8)
+            want = (np.tile(want[0], (reps, 1)), np.tile(want[1], (reps, 1)))
+            rq = None if own is None else torch.from_numpy(own).cuda().repeat(reps, 1)
+            for strategy in (b.SCAN_AUTO, b.SCAN_QUERY_MAJOR):
+                got = gi.search(dq, nprobe, k, radii if own is None else None, query_radii=rq, strategy=strategy)
+                _same(got, want, (D, M, k, cap, own is not None, strategy))
+    finally:
+        b.set_option("wide_cap", 8192)
+        gi.close()

@@ -83,6 +83,26 @@ static std::atomic<int> g_wide_cap{8192};  // slots per query of the wide select
 
 void set_wide_cap(int v) { g_wide_cap.store(v, std::memory_order_relaxed); }
 
+WideWorkspace plan_wide(const ivfpq_index *ix, int64_t Q, int32_t k, int32_t mode) {
+  WideWorkspace w = {};
+  if (ix->metric != IVFPQ_METRIC_L2 || mode != 0 || k <= 128 || k > 8 * 128 || Q < 1) return w;
+  w.cap = g_wide_cap.load(std::memory_order_relaxed);
+  if (w.cap == 0) return w;  // switched off: pass by pass
+  // the slot arrays take at most 1 GiB: larger batches go through them in chunks
+  int64_t qc = ((int64_t)1 << 30) / ((int64_t)w.cap * 12);
+  if (qc < 1024) qc = 1024;
+  w.q_chunk = qc < Q ? qc : Q;
+  auto a256 = [](size_t v) { return (v + 255) & ~(size_t)255; };
+  size_t off = 0;
+  w.d = off;     off += a256((size_t)w.q_chunk * w.cap * 4);
+  w.id = off;    off += a256((size_t)w.q_chunk * w.cap * 8);
+  w.n = off;     off += a256((size_t)w.q_chunk * 4);
+  w.bound = off; off += a256((size_t)w.q_chunk * 4);
+  w.qmap = off;  off += a256((size_t)w.q_chunk * 4);
+  w.total = off;
+  return w;
+}
+
 // Lists of the list-major wide selection's first stage: as many as hold 2 k points on average.  0 where it does not
 // serve: shapes without list-major kernels, few pairs or long lists (the lines of the list-major scan), slots that
 // do not hold twice the first lists (those near a query are longer than the mean) or so few that the stages crawl.
@@ -103,30 +123,16 @@ static int32_t wide_first(const ivfpq_index *ix, const WideWorkspace &w, int32_t
 }
 
 WideWorkspace plan_wide(const ivfpq_index *ix, int64_t Q, int32_t nprobe, int32_t k, int32_t mode, int32_t strategy) {
-  WideWorkspace w = {};
-  if (ix->metric != IVFPQ_METRIC_L2 || mode != 0 || k <= 128 || k > 8 * 128 || Q < 1) return w;
-  w.cap = g_wide_cap.load(std::memory_order_relaxed);
-  if (w.cap == 0) return w;  // switched off: pass by pass
-  // the slot arrays take at most 1 GiB: larger batches go through them in chunks
-  int64_t qc = ((int64_t)1 << 30) / ((int64_t)w.cap * 12);
-  if (qc < 1024) qc = 1024;
-  w.q_chunk = qc < Q ? qc : Q;
-  auto a256 = [](size_t v) { return (v + 255) & ~(size_t)255; };
-  size_t off = 0;
-  w.d = off;     off += a256((size_t)w.q_chunk * w.cap * 4);
-  w.id = off;    off += a256((size_t)w.q_chunk * w.cap * 8);
-  w.n = off;     off += a256((size_t)w.q_chunk * 4);
-  w.bound = off; off += a256((size_t)w.q_chunk * 4);
-  w.qmap = off;  off += a256((size_t)w.q_chunk * 4);
+  WideWorkspace w = plan_wide(ix, Q, k, mode);
+  if (w.total == 0) return w;
   w.first = wide_first(ix, w, nprobe, k, strategy);
-  w.lm_off = off;
+  w.lm_off = w.total;
   if (w.first > 0) {
     w.lm.first = w.first;
     w.lm.cap = w.cap;
     plan_list_major_tables(w.lm, ix->nlist, w.q_chunk, nprobe);
-    off += w.lm.total;
+    w.total += w.lm.total;
   }
-  w.total = off;
   return w;
 }
 

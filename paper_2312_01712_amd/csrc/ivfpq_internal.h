@@ -177,6 +177,8 @@ inline int32_t wide_next(const WideWorkspace &w, int32_t k, int32_t p0, int32_t 
   return p1 < nprobe ? (int32_t)p1 : nprobe;
 }
 // total == 0 unless the wide selection serves this call (L2 distances, 128 < k <= 1024).
+WideWorkspace plan_wide(const ivfpq_index *ix, int64_t Q, int32_t k, int32_t mode);
+// ... with the tables of the list-major stages behind the slots where they serve (first > 0).
 WideWorkspace plan_wide(const ivfpq_index *ix, int64_t Q, int32_t nprobe, int32_t k, int32_t mode, int32_t strategy);
 void set_wide_cap(int v);  // slots per query of the wide selection (1024 .. 65536)
 

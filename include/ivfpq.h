@@ -220,14 +220,17 @@ typedef enum {
  *     two per pass over the list's codes, with their tables interleaved so that one look-up
  *     serves both.  The nearest list of every query is ranked first (its k-th distance is the
  *     bound that filters the query's other lists).  Best where the per-query fixed costs or
- *     the look-up rate dominate: short lists, data without cluster structure.
+ *     the look-up rate dominate: short lists, lists that many queries share, data without
+ *     cluster structure.
  *     Needs the L2 metric, k <= 128 and an (M, dsub) of (48, 2), (64, 2) or (16, 4); any other
  *     call is served query-major.  Takes a larger workspace.  (For 128 < k <= 1024 with distance
  *     scoring, either setting but QUERY_MAJOR lets large batches of these shapes be selected list-major
  *     in stages; ivfpq_resolve_strategy calls that query-major.)
  *   IVFPQ_SCAN_AUTO         the library chooses: list-major where it is available, when the
  *     batch has at least 16 384 (query, list) pairs and the index's mean list length is at
- *     most 4096; query-major otherwise.
+ *     most 4096, or, with distance scoring, at most 16 384 and the batch large enough that its
+ *     queries share their nearest lists (two a list, 16 million points in all); query-major
+ *     otherwise.
  * ivfpq_search_workspace_bytes sizes the workspace for AUTO with distance scoring;
  * ivfpq_search_workspace_bytes_ex for the scoring actually passed. */
 typedef enum { IVFPQ_SCAN_AUTO = 0, IVFPQ_SCAN_QUERY_MAJOR = 1, IVFPQ_SCAN_LIST_MAJOR = 2 } ivfpq_scan_strategy;

@@ -207,8 +207,23 @@ static bool use_list_major(const ivfpq_index *ix, int64_t Q, int32_t nprobe, int
                            int32_t requested) {
   if (requested == IVFPQ_SCAN_QUERY_MAJOR || !list_major_supported(ix, nprobe, k)) return false;
   if (requested == IVFPQ_SCAN_LIST_MAJOR) return true;
-  (void)mode;
-  return Q * (int64_t)nprobe >= 16384 && ix->N <= (int64_t)4096 * ix->nlist;
+  if (Q * (int64_t)nprobe < 16384) return false;
+  if (ix->N <= (int64_t)4096 * ix->nlist) return true;
+  // Longer lists: the query-major scan prunes block by block, the list-major one shares each pass over a list among the
+  // queries that probe it.  Distances only (the hit counts' first lists are ranked query-major either way).  Query-major /
+  // list-major, us, k = 100, 64 probes, 64 subspaces of clustered data unless said:
+  //   queries                          512         1024         2048         4096          8192
+  //   lists of 5000              149 / 271    257 / 295    315 / 351    590 / 492    1145 / 791
+  //   7812                       358 / 550    540 / 706    898 / 810   1272 / 1052   2123 / 1570
+  //   15 625 (32 probes)         776 / 994  1241 / 1156  1860 / 1577   3567 / 2305   6247 / 3728
+  //   5000, two components a list
+  //                             1301 / 858  2509 / 1425  5184 / 2370   9609 / 4285  18753 / 8297
+  //   5000, 48 subspaces without structure
+  //                             2210 / 883  4209 / 1281  7886 / 1905  15441 / 3312  30708 / 6035
+  // The line is where clustered data gains; two queries a list at least.  (100M points in 16 384 lists, fewer than one
+  // query a list, the nearest ones eight times the mean: query-major.)
+  return mode == IVFPQ_SCORE_DISTANCE && ix->N <= (int64_t)16384 * ix->nlist && Q >= (int64_t)2 * ix->nlist &&
+         (double)Q * (double)ix->N / ix->nlist >= 1.6e7 && ix->max_list_len < (1 << 20);
 }
 
 }  // namespace ivfpq

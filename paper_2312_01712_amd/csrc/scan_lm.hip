@@ -71,6 +71,7 @@ struct LmArgs {
   int32_t p0, p1;               // the probes [p0, p1) of every query that the current main pass serves
   int32_t later;                // this is not the first main pass: qmap already names queries to be redone
   int32_t stage;                // which of the passes of a call with candidates to settle
+  int32_t fresh;                // byte tables in the head pass: the queries have no result yet
   int32_t group;                // queries per group of the pass the pairs are bucketed for
   int32_t head_done;            // the head pass has run: queries it left out (qmap_head) have no first-list result yet
   const float *tau;             // [Q] x tau_stride: the k-th distance that filters the main pass (NaN: none yet)
@@ -101,6 +102,7 @@ __global__ __launch_bounds__(256) void lm_pairs_kernel(LmArgs a, int fill, int h
     if (r >= 0) a.pairs[a.base[c] + r] = make_int2((int)q, c);
     return;
   }
+  if (head) a.gcnt[q] = 0u;
   if (!head && p == a.p0) a.gcnt[q] = a.wide_n && a.wide_n[q] > 0 ? (uint32_t)a.wide_n[q] : 0u;
   bool take = true;
   // a query the head pass left out has no bound yet: it takes no part here and is redone
@@ -712,8 +714,10 @@ struct LmbFetch {
 // Floats of a (subspace, query) record, padded to whole 16-byte reads.
 constexpr int lmb_rec(int dsub) { return dsub == 2 ? 4 : 8; }
 constexpr int LMB_SMALL = 64;   // words: two sets of a task's limits and queries, and the two queue counters
-constexpr size_t lmb_lds(int mt, int dsub) {
-  return (size_t)mt * 2048 + (size_t)LMB_G * mt * (4 * lmb_rec(dsub) + 4 + 2) + (size_t)mt * 4 + (size_t)LMB_QUEUE * 4 + LMB_SMALL * 4;
+constexpr int LMB_BINS = 256;   // head pass: bins of a query's byte sums
+constexpr int lmb_shift(int mt) { return mt > 16 ? 4 : 2; }   // 63 mt >> shift < LMB_BINS
+constexpr size_t lmb_lds(int mt, int dsub, bool head) {
+  return (head ? (size_t)LMB_G * LMB_BINS * 4 : 0) + (size_t)mt * 2048 + (size_t)LMB_G * mt * (4 * lmb_rec(dsub) + 4 + 2) + (size_t)mt * 4 + (size_t)LMB_QUEUE * 4 + LMB_SMALL * 4;
 }
 
 template <int J>
@@ -726,7 +730,14 @@ __device__ __forceinline__ float xor_f32(float v) { return __uint_as_float(xor_u
 // table, and their fp32 distances are formed by lm_settle_kernel, query by query: settled here they cost
 // 8.5 of a task's 30 thousand clocks, since every task had to put the codebook where the table was and had
 // candidates (125) for half of the lanes.
-template <int MT, int DSUB, int MODE>
+//
+// HEAD: the pass over every query's nearest list, without a k-th distance to compare with.  The list is passed over
+// twice: the first pass counts the byte sums in a histogram per query (256 bins in LDS), the second one offers every
+// point up to the bin of the k-th smallest sum and as much beyond as the bytes can have lost.  A byte is less than 1 below
+// s v + offset and at most twice the raise above it, so k points have s distance + offsets < sum_k + MT, and one as near
+// has a sum of at most sum_k + MT + the raises.
+// 8192 queries on lists of 4000 points, 64 subspaces: 1248 us a search with the fp32 head pass, 881 so.
+template <int MT, int DSUB, int MODE, bool HEAD = false>
 __global__ __launch_bounds__(LMB_NW * 64) __attribute__((amdgpu_waves_per_eu(4))) void lm_byte_kernel(LmArgs a, RadiiSq r2) {
   constexpr int NW = LMB_NW;
   constexpr int ITER = (MT + NW - 1) / NW;
@@ -748,6 +759,7 @@ __global__ __launch_bounds__(LMB_NW * 64) __attribute__((amdgpu_waves_per_eu(4))
   LDS uint32_t *sT = small;                        // [2][8] sums below this are candidates
   LDS int32_t *sq = (LDS int32_t *)(small + 16);   // [2][8] queries
   LDS uint32_t *qn = small + 32;                   // [2] candidates offered to the queue
+  LDS uint32_t *hist = small + LMB_SMALL;          // head pass: [8][LMB_BINS]
 
   int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -820,7 +832,7 @@ __global__ __launch_bounds__(LMB_NW * 64) __attribute__((amdgpu_waves_per_eu(4))
         const float r = a.query_radii[q * MT + lane];
         f.r2 = r * r;
       }
-      f.tau = a.tau[q * a.tau_stride];
+      if constexpr (!HEAD) f.tau = a.tau[q * a.tau_stride];
     }
   };
   // ... and writes them to the records and to set `par` of the small words
@@ -845,28 +857,35 @@ __global__ __launch_bounds__(LMB_NW * 64) __attribute__((amdgpu_waves_per_eu(4))
       rmax = fmaxf(rmax, xor_f32<4>(rmax));
       rmax = fmaxf(rmax, xor_f32<2>(rmax));
       rmax = fmaxf(rmax, xor_f32<1>(rmax));
-      const float cap = fmaxf(fminf(rmax, tau * (4.0f / (float)MT)), 1e-30f);
+      // Head pass: no value is cut off; where radii are infinite the largest distance to any entry bounds them.
+      float rr = 0.0f;
+#pragma unroll
+      for (int j = 0; j < DSUB; ++j) rr = fmaf(res[j], res[j], rr);
+      const float far = on ? sqrtf(rr) + sqrtf(semax[lane]) : 0.0f;
+      float widest = tau * (4.0f / (float)MT);
+      if constexpr (HEAD) {
+        widest = far * far * 1.0001f;
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) widest = fmaxf(widest, __shfl_xor(widest, off));
+      }
+      const float cap = fmaxf(fminf(rmax, widest), 1e-30f);
       const float s = ((float)LMB_TOP - 0.01f) / cap;   // infinite radii and no k-th distance: 0
       // Offset of a row: up to the next integer at the row's cap, so that entries outside the
       // radius (most of them) lose nothing to the floor; what the offsets add is known.
       const float x = fminf(f.r2, cap) * s, top = ceilf(x), off = top - x;
-      float rr = 0.0f;
-#pragma unroll
-      for (int j = 0; j < DSUB; ++j) rr = fmaf(res[j], res[j], rr);
       // A byte is taken from the bits of 2^15 + value, whose last place is 2^-8: the four roundings at
       // that magnitude move a value by 2^-9 each, together below 0.01, those of |r|^2 - 2 r.e + |e|^2 in place
       // of |r - e|^2 by 2^-24 of s (|r| + |e|)^2 each: fewer than 2 DSUB + 10 of them, counted as 32.
       // The values are raised by that much, so that none is below 0.
       float add = 0.0f;
       if (on) {
-        const float far = sqrtf(rr) + sqrtf(semax[lane]);
         const float err = fmaf(s * far, far * 1.9073486e-06f, 0.01f);
 #pragma unroll
         for (int j = 0; j < DSUB; ++j) rec[j] = -2.0f * s * res[j];
         rec[DSUB] = s;
         scon[lane * LMB_G + g] = fmaf(rr, s, off + err) + 32768.0f;
         stop[lane * LMB_G + g] = (uint16_t)top;   // NaN (0 x inf): 0
-        add = off + 2.0f * err;
+        add = HEAD ? 2.0f * err : off + 2.0f * err;
       }
       // Limit on the byte sum of a point with distance <= tau: s tau, relative roundings (the fp32
       // sum, the scaling: 2^-23 each, at most 70 of them), the offsets, the raise and the roundings again.
@@ -876,7 +895,8 @@ __global__ __launch_bounds__(LMB_NW * 64) __attribute__((amdgpu_waves_per_eu(4))
       add += xor_f32<4>(add);
       add += xor_f32<2>(add);
       add += xor_f32<1>(add);
-      const float lim = fmaf(tau * s, 1.00001f, add) + 0.25f;
+      // (Head pass: what lies between the k-th smallest sum and the limit.)
+      const float lim = HEAD ? add + (float)MT + 2.0f : fmaf(tau * s, 1.00001f, add) + 0.25f;
       T = lim < 60000.0f ? (uint32_t)lim : 60000u;   // NaN (0 x inf, or no k-th distance): every point
     } else {
       if (on) {
@@ -918,6 +938,8 @@ __global__ __launch_bounds__(LMB_NW * 64) __attribute__((amdgpu_waves_per_eu(4))
     if (p_has && slot < (uint32_t)a.cap) a.cand[(int64_t)p_q * a.cap + slot] = make_uint2(p_x, p_row);
     p_has = false;
   };
+  if constexpr (HEAD)
+    for (int i = tid; i < LMB_G * LMB_BINS; i += NW * 64) hist[i] = 0u;
   __syncthreads();   // semax
   {
     const int2 pv = fetch_pairs(t);
@@ -1025,16 +1047,9 @@ __global__ __launch_bounds__(LMB_NW * 64) __attribute__((amdgpu_waves_per_eu(4))
     if (__ballot(p_has) != 0) drain();
     __syncthreads();   // the table is complete; the queue has been read
     // ---- one pass over the list's codes serves all queries of the group ----
-    // sums of queries (0, 2), (1, 3), (4, 6), (5, 7) as 16-bit halves, and the limits to compare with
-    uint32_t lim[4];
-    {
-      const LDS uint32_t *T = sT + par * 8;
-      lim[0] = (uint32_t)__builtin_amdgcn_readfirstlane((int)(T[0] | (T[2] << 16)));
-      lim[1] = (uint32_t)__builtin_amdgcn_readfirstlane((int)(T[1] | (T[3] << 16)));
-      lim[2] = (uint32_t)__builtin_amdgcn_readfirstlane((int)(T[4] | (T[6] << 16)));
-      lim[3] = (uint32_t)__builtin_amdgcn_readfirstlane((int)(T[5] | (T[7] << 16)));
-    }
+    // sums of queries (0, 2), (1, 3), (4, 6), (5, 7) as 16-bit halves
     const int last = nb - 1;
+    auto each_block = [&](auto use) __attribute__((always_inline)) {
     for (int blk = wave; blk < nb; blk += NW) {
       CodeRegs<MT / 4> cur = nxt;
       load_chunks<MT, 0, NCH>(base, nb, blk + NW < last ? blk + NW : last, lane, nxt);   // past the end: the last block again
@@ -1065,6 +1080,7 @@ __global__ __launch_bounds__(LMB_NW * 64) __attribute__((amdgpu_waves_per_eu(4))
             raw1 += x1;
           }
         }
+        if constexpr (MODE != 0) asm volatile("" : "+v"(raw0), "+v"(raw1));   // (nor are these left for the end)
         __builtin_amdgcn_sched_barrier(0);
       }
       if constexpr (MODE != 0) {
@@ -1073,14 +1089,68 @@ __global__ __launch_bounds__(LMB_NW * 64) __attribute__((amdgpu_waves_per_eu(4))
         s[2] = raw1 & 0x00FF00FFu;
         s[3] = high_bytes(raw1);
       }
-      const int i = blk * 64 + lane;
+      if constexpr (HEAD)   // (the sums of queries 4 to 7 are formed here, not where they are first wanted, with every look-up kept until then)
+        asm volatile("" : "+v"(s[0]), "+v"(s[1]), "+v"(s[2]), "+v"(s[3]));
+      use(blk * 64 + lane, s);
+    }
+    };
+    if constexpr (HEAD) {
+      each_block([&](int i, const uint32_t (&s)[4]) __attribute__((always_inline)) {
+        if (i >= len) return;
+#pragma unroll
+        for (int x = 0; x < 4; ++x) {
+          const int g0 = (x >> 1) * 4 + (x & 1);
+          if (x < 2 || five) {
+            lds_add(&hist[g0 * LMB_BINS + ((s[x] & 0xFFFFu) >> lmb_shift(MT))]);
+            lds_add(&hist[(g0 + 2) * LMB_BINS + (s[x] >> (16 + lmb_shift(MT)))]);
+          }
+        }
+      });
+      __syncthreads();
+      if (wave < LMB_G) {   // wavefront g: the bin of query g's k-th smallest sum, four bins a lane
+        const uintx4 c = *(const LDS uintx4 *)(hist + wave * LMB_BINS + 4 * lane);
+        const uint32_t sum = c[0] + c[1] + c[2] + c[3];
+        uint32_t incl = sum;
+        for (int off = 1; off < 64; off <<= 1) {
+          const uint32_t v = (uint32_t)__shfl_up((int)incl, off);
+          if (lane >= off) incl += v;
+        }
+        uint32_t run = incl - sum, need = (uint32_t)a.k, bin = LMB_BINS;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          if (run < need && need <= run + c[j]) bin = (uint32_t)(4 * lane + j);
+          run += c[j];
+        }
+        const unsigned long long bal = __ballot(bin != (uint32_t)LMB_BINS);
+        const uint32_t slack = sT[par * 8 + wave];   // 0: no query
+        if (bal == 0ull) {   // fewer than k points: all of them
+          if (lane == 0 && slack != 0u) sT[par * 8 + wave] = 60001u;
+        } else if (bin != (uint32_t)LMB_BINS && slack != 0u) {   // one lane
+          sT[par * 8 + wave] = umin32(((bin + 1u) << lmb_shift(MT)) - 1u + slack, 60001u);
+        }
+      }
+      __syncthreads();
+      asm volatile("" : "+v"(tid), "+v"(lane));
+      for (int i = tid; i < LMB_G * LMB_BINS; i += NW * 64) hist[i] = 0u;   // for the next task
+      load_chunks<MT, 0, NCH>(base, nb, wave < nb ? wave : nb - 1, lane, nxt);   // the second pass starts over
+    }
+    // the limits to compare with
+    uint32_t lim[4];
+    {
+      const LDS uint32_t *T = sT + par * 8;
+      lim[0] = (uint32_t)__builtin_amdgcn_readfirstlane((int)(T[0] | (T[2] << 16)));
+      lim[1] = (uint32_t)__builtin_amdgcn_readfirstlane((int)(T[1] | (T[3] << 16)));
+      lim[2] = (uint32_t)__builtin_amdgcn_readfirstlane((int)(T[4] | (T[6] << 16)));
+      lim[3] = (uint32_t)__builtin_amdgcn_readfirstlane((int)(T[5] | (T[7] << 16)));
+    }
+    each_block([&](int i, const uint32_t (&s)[4]) __attribute__((always_inline)) {
       uint32_t z[4], any = 0u;   // limit - sum, saturated at 0: non-zero halves are candidates
 #pragma unroll
       for (int x = 0; x < 4; ++x) {
         z[x] = __builtin_bit_cast(uint32_t, __builtin_elementwise_sub_sat(__builtin_bit_cast(ushortx2, lim[x]), __builtin_bit_cast(ushortx2, s[x])));
         any |= z[x];
       }
-      if (__ballot(i < len && any != 0u) == 0) continue;
+      if (__ballot(i < len && any != 0u) == 0) return;
       uint32_t mask = 0u;   // bit g: the point is a candidate of query g
 #pragma unroll
       for (int x = 0; x < 4; ++x) {
@@ -1111,7 +1181,7 @@ __global__ __launch_bounds__(LMB_NW * 64) __attribute__((amdgpu_waves_per_eu(4))
           }
         }
       }
-    }
+    });
     if (more) put_params(fx, par ^ 1);
     __syncthreads();   // the list is scanned: the queue is complete, the next task's records are there
     const int n = (int)umin32(qn[par], (uint32_t)LMB_QUEUE);
@@ -1166,9 +1236,10 @@ __global__ __launch_bounds__(256) void lm_sort_out_kernel(LmArgs a, int list_red
     else if (active) a.wide_n[q] = (int32_t)n;
   } else if (q < a.Q) {
     const uint32_t n = a.gcnt[q];
-    named = n > (uint32_t)a.cap || (a.head_done && a.qmap_head[q] >= 0) || (a.later && a.qmap[q] >= 0);
+    named = n > (uint32_t)a.cap || ((a.head_done || a.fresh) && a.qmap_head[q] >= 0) || (a.later && a.qmap[q] >= 0);
     active = !named && n > 0u;
-    a.qmap[q] = named ? (int32_t)q : -1;
+    if (!a.fresh) a.qmap[q] = named ? (int32_t)q : -1;
+    else if (named) a.qmap_head[q] = (int32_t)q;
   }
   auto put = [&](bool on, int32_t *count, int32_t *list) __attribute__((always_inline)) {
     const unsigned long long bal = __ballot(on);
@@ -1251,7 +1322,7 @@ __global__ __launch_bounds__(LMS_NW * 64) __attribute__((amdgpu_waves_per_eu(4))
       };
       if constexpr (!WIDE) {
         const int64_t o = q * k;
-        const bool in0 = lane < k, in1 = 64 + lane < k;
+        const bool in0 = !a.fresh && lane < k, in1 = !a.fresh && 64 + lane < k;
         const int64_t id0 = in0 ? a.out_ids[o + lane] : -1, id1 = in1 ? a.out_ids[o + 64 + lane] : -1;
         L0.d = id0 >= 0 ? __float_as_uint(a.out_dist[o + lane]) : SENT_D;
         L0.id = id0 >= 0 ? id0 : SENT_ID;
@@ -1260,7 +1331,7 @@ __global__ __launch_bounds__(LMS_NW * 64) __attribute__((amdgpu_waves_per_eu(4))
         take_tau();
       }
       int waiting = 0;
-      bool changed = false;
+      bool changed = a.fresh;
       auto fold = [&](int from, int count) __attribute__((always_inline)) {   // at most 64 of the queue
         Key c;
         c.d = SENT_D;
@@ -1503,13 +1574,13 @@ int launch_lm_scan_t(const LmArgs &a, const RadiiSq &r2, int grid, hipStream_t s
   return IVFPQ_OK;
 }
 
-template <int MT, int DSUB, int MODE>
+template <int MT, int DSUB, int MODE, bool HEAD = false>
 int launch_lm_byte_t(const LmArgs &a, const RadiiSq &r2, int grid, hipStream_t s) {
-  auto kern = lm_byte_kernel<MT, DSUB, MODE>;
+  auto kern = lm_byte_kernel<MT, DSUB, MODE, HEAD>;
   static std::atomic<uint64_t> prepared;
   if (int rc = prepare_kernel(kern, prepared)) return rc;
-  static_assert(lmb_lds(MT, DSUB) <= (size_t)LDS_PER_CU, "byte tables, records and queue fit a CU");
-  hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(LMB_NW * 64), lmb_lds(MT, DSUB), s, a, r2);
+  static_assert(lmb_lds(MT, DSUB, HEAD) <= (size_t)LDS_PER_CU, "byte tables, records and queue fit a CU");
+  hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(LMB_NW * 64), lmb_lds(MT, DSUB, HEAD), s, a, r2);
   return IVFPQ_OK;
 }
 
@@ -1542,6 +1613,12 @@ int launch_lm_byte(const LmArgs &a, const RadiiSq &r2, int grid, hipStream_t s) 
   if (a.mode == 0) return launch_lm_byte_m<0>(a, r2, grid, s);
   if (a.mode == 1) return launch_lm_byte_m<1>(a, r2, grid, s);
   return launch_lm_byte_m<2>(a, r2, grid, s);
+}
+
+int launch_lm_byte_head(const LmArgs &a, const RadiiSq &r2, int grid, hipStream_t s) {
+  if (a.M == 48) return launch_lm_byte_t<48, 2, 0, true>(a, r2, grid, s);
+  if (a.M == 64) return launch_lm_byte_t<64, 2, 0, true>(a, r2, grid, s);
+  return launch_lm_byte_t<16, 4, 0, true>(a, r2, grid, s);
 }
 
 template <bool HEAD>
@@ -1699,16 +1776,41 @@ int launch_scan_list_major(const ivfpq_index *ix, const float *d_queries, int64_
   // share a nearest list share its table pass); what the head pass leaves out (qmap_head) skips
   // the list-major scan and is redone query-major at the end.  Otherwise (several first lists, or the hit-count scorings,
   // whose masses of equal scores the head pass's selection is not made for): query-major.
-  const bool head_pass = w.first == 1 && mode == IVFPQ_SCORE_DISTANCE && a.head_max >= 64;
+  // The head pass with byte tables where lists are long: those that do not fit the fp32 form's LDS cost a query-major
+  // pass each, and the longer a list the more the eight queries of a look-up save against settling the candidates.
+  // us of a search with the fp32 head pass / with byte tables (64 probes, k = 100):
+  //   queries                                      1024         2048         4096         8192
+  //   64 subspaces, clustered, lists of 977 (10 000 queries)                             418 / 488
+  //   64, clustered, 2441 (10 000 queries, 2.4 a list; the scan alone)                   666 / 820
+  //   64, clustered, 1953                     129 / 228    176 / 276    267 / 339    492 / 542
+  //   64, clustered, 4000                     253 / 361    406 / 408    684 / 590   1248 / 881
+  //   64, clustered, 7812                     590 / 706    943 / 810   1310 / 1052  2162 / 1570
+  //   48, without structure, 3906            2558 / 1038  3141 / 1621  5021 / 2766  7402 / 5093
+  const int64_t head_points = (int64_t)((double)Q * (double)ix->N / ix->nlist);
+  const bool long_lists = ix->N > (int64_t)4096 * ix->nlist || (ix->max_list_len > a.head_max && ix->N >= (int64_t)2800 * ix->nlist);
+  const bool head_bytes = w.first == 1 && mode == IVFPQ_SCORE_DISTANCE && ix->max_list_len < (1 << 20) && !(get_scan_ablate() & 8) &&
+                          long_lists && head_points >= 8000000;
+  const bool head_pass = w.first == 1 && mode == IVFPQ_SCORE_DISTANCE && (head_bytes || a.head_max >= 64);
+  if (head_bytes) {
+    a.head_max = INT_MAX;
+    a.group = LMB_G;
+    a.fresh = 1;
+  }
   if (head_pass) {
     const unsigned qgrid = (unsigned)((Q + 255) / 256);
     hipLaunchKernelGGL(lm_pairs_kernel, dim3(qgrid), dim3(256), 0, s, a, 0, 1);
     hipLaunchKernelGGL(lm_offsets_kernel, dim3(1), dim3(1024), 0, s, a);
     hipLaunchKernelGGL(lm_pairs_kernel, dim3(qgrid), dim3(256), 0, s, a, 1, 1);
-    rc = launch_lm_scan<true>(ix, a, r2, cus, s);
+    rc = head_bytes ? launch_lm_byte_head(a, r2, cus, s) : launch_lm_scan<true>(ix, a, r2, cus, s);
     if (rc) return rc;
+    if (head_bytes) {
+      hipLaunchKernelGGL(lm_sort_out_kernel, dim3((unsigned)((Q + 255) / 256)), dim3(256), 0, s, a, 0);
+      rc = launch_lm_settle<false>(a, r2, cus, s);
+      if (rc) return rc;
+    }
   }
   a.head_done = head_pass ? 1 : 0;
+  a.fresh = 0;
   if (!head_pass) {
     ScanView head = {nprobe, nullptr, true};
     rc = launch_scan(ix, d_queries, Q, w.first, d_probe_ids, k, r2, 1, nullptr, nullptr, d_out_ids, d_out_dist,
@@ -1744,7 +1846,8 @@ int launch_scan_list_major(const ivfpq_index *ix, const float *d_queries, int64_
   for (int p0 = w.first, p1 = split; p0 < nprobe; p0 = p1, p1 = nprobe) {
     a.p0 = p0;
     a.p1 = p1;
-    a.later = a.stage = p0 > w.first ? 1 : 0;
+    a.later = p0 > w.first ? 1 : 0;
+    a.stage = a.later + 1;
     const int64_t npairs = Q * (p1 - p0);
     const unsigned pair_grid = (unsigned)((npairs + 255) / 256);
     hipLaunchKernelGGL(lm_pairs_kernel, dim3(pair_grid), dim3(256), 0, s, a, 0, 0);

@@ -247,3 +247,37 @@ def test_more_than_128_neighbours_of_large_batches(D, M, k, cap, radius):
     finally:
         b.set_option("wide_cap", 8192)
         gi.close()
+
+
+@pytest.mark.parametrize("D,M", [(96, 48), (128, 64), (64, 16)])
+@pytest.mark.parametrize("k,cap,radius", [(1, 0, 0.6), (100, 0, 0.6), (128, 64, 0.6), (10, 0, np.inf)])
+def test_long_lists_shared_by_many_queries(D, M, k, cap, radius):
+    """Lists above 4096 points on average and batches that share them: the head pass with byte tables (histogram of the
+    byte sums, candidates up to the k-th and what the bytes can have lost).  Nearest lists that are empty or hold fewer
+    points than k, queries between the lists, runs of equal distances, candidate buffers of 64 slots, infinite, shared and
+    per-query radii; groups of eight queries and of fewer; the query-major scan of the same call."""
+    b = _binding()
+    rng = np.random.default_rng(7 * M + k)
+    sizes = np.array([9100, 0, 8300, 90, 12_000, 1, 8800, 9900])
+    nlist, nprobe, distinct, reps = len(sizes), 6, 60, 46
+    idx = _index(rng, D, M, sizes, centre=0.2)
+    idx.codes[idx.list_offsets[2] + 50:idx.list_offsets[2] + 400] = idx.codes[0]   # runs of equal distances
+    q = (idx.centroids[rng.integers(0, nlist, distinct)] + 0.25 * rng.normal(size=(distinct, D))).astype(np.float32)
+    q[::3] = idx.centroids[rng.integers(0, nlist, len(q[::3]))]
+    radii = np.full(M, radius * np.sqrt(D / M), dtype=np.float32)
+    per_query = np.where(np.isinf(radius), np.inf, rng.uniform(0.3, 0.9, size=(distinct, M)) * np.sqrt(D / M)).astype(np.float32)
+    gi = b.IvfPqIndex.from_index(idx)
+    try:
+        b.set_option("lm_cap", cap)
+        assert gi.resolve_strategy(distinct * reps, nprobe, k) == b.SCAN_LIST_MAJOR
+        assert gi.resolve_strategy(distinct, nprobe, k) == b.SCAN_QUERY_MAJOR
+        for own in (None, per_query):
+            want = oracle.search(q, idx, nprobe, k, radii if own is None else own, threads=8)
+            for n, strategy in ((reps, b.SCAN_AUTO), (reps - 20, b.SCAN_LIST_MAJOR), (1, b.SCAN_LIST_MAJOR), (1, b.SCAN_QUERY_MAJOR)):
+                dq = torch.from_numpy(q).cuda().repeat(n, 1)
+                rq = None if own is None else torch.from_numpy(own).cuda().repeat(n, 1)
+                got = gi.search(dq, nprobe, k, radii if own is None else None, query_radii=rq, strategy=strategy)
+                _same(got, (np.tile(want[0], (n, 1)), np.tile(want[1], (n, 1))), (D, M, k, cap, n, own is not None, strategy))
+    finally:
+        b.set_option("lm_cap", 0)
+        gi.close()

@@ -664,6 +664,15 @@ static int scan_query_major(const ivfpq_index *ix, const float *d_queries, int64
                      reinterpret_cast<float *>(base + w.probe_dist), s, &view);
 }
 
+// Whether a call goes list-major with the workspace it has: AUTO on long lists serves one that only has room for the
+// query-major scan with that.
+static bool goes_list_major(const ivfpq_index *ix, int64_t Q, int32_t nprobe, int32_t k, int32_t mode, int32_t strategy,
+                            const Workspace &w, size_t ws_bytes) {
+  if (!use_list_major(ix, Q, nprobe, k, mode, strategy)) return false;
+  if (strategy == IVFPQ_SCAN_LIST_MAJOR || ix->N <= (int64_t)4096 * ix->nlist) return true;
+  return ws_bytes >= align256(w.total) + plan_list_major(ix, Q, nprobe).total;
+}
+
 // Stages 2-4 list-major: the usual workspace, then the list-major part behind it.
 static int scan_list_major(const ivfpq_index *ix, const float *d_queries, int64_t Q, int32_t nprobe,
                            const int32_t *d_probe_ids, int32_t k, const RadiiSq &r2, int32_t mode, const float *qr,
@@ -717,7 +726,7 @@ int ivfpq_scan_topk_ex(const ivfpq_index *ix, const float *d_queries, int64_t Q,
   if (!d_probe_ids || !d_out_ids || !d_out_dist) { set_error("%s: NULL pointer", fn); return IVFPQ_ERR_INVALID_ARGUMENT; }
   const Workspace w = plan_workspace(ix, Q, nprobe, k);
   char *base = static_cast<char *>(ws);
-  if (use_list_major(ix, Q, nprobe, k, mode, strategy))
+  if (goes_list_major(ix, Q, nprobe, k, mode, strategy, w, ws_bytes))
     return scan_list_major(ix, d_queries, Q, nprobe, d_probe_ids, k, r2, mode, qr, d_out_ids, d_out_dist, w, ws,
                            ws_bytes, static_cast<hipStream_t>(stream), fn);
   if ((rc = check_workspace(w, ws, ws_bytes, fn))) return rc;
@@ -818,7 +827,7 @@ int ivfpq_search_ex(const ivfpq_index *ix, const float *d_queries, int64_t Q, in
   if (Q == 0) return IVFPQ_OK;
   if (!d_out_ids || !d_out_dist) { set_error("%s: NULL pointer", fn); return IVFPQ_ERR_INVALID_ARGUMENT; }
   const Workspace w = plan_workspace(ix, Q, nprobe, k);
-  if (use_list_major(ix, Q, nprobe, k, mode, strategy)) {
+  if (goes_list_major(ix, Q, nprobe, k, mode, strategy, w, ws_bytes)) {
     Workspace both = w;
     both.total = align256(w.total) + plan_list_major(ix, Q, nprobe).total;
     if ((rc = check_workspace(both, ws, ws_bytes, fn))) return rc;   // before anything is enqueued

@@ -271,6 +271,10 @@ def test_long_lists_shared_by_many_queries(D, M, k, cap, radius):
         b.set_option("lm_cap", cap)
         assert gi.resolve_strategy(distinct * reps, nprobe, k) == b.SCAN_LIST_MAJOR
         assert gi.resolve_strategy(distinct, nprobe, k) == b.SCAN_QUERY_MAJOR
+        small = gi.workspace(distinct * reps, nprobe, k, strategy=b.SCAN_QUERY_MAJOR)   # serves AUTO query-major
+        want = oracle.search(q, idx, nprobe, k, radii, threads=8)
+        _same(gi.search(torch.from_numpy(q).cuda().repeat(reps, 1), nprobe, k, radii, workspace=small),
+              (np.tile(want[0], (reps, 1)), np.tile(want[1], (reps, 1))), (D, M, k, cap, "small workspace"))
         for own in (None, per_query):
             want = oracle.search(q, idx, nprobe, k, radii if own is None else own, threads=8)
             for n, strategy in ((reps, b.SCAN_AUTO), (reps - 20, b.SCAN_LIST_MAJOR), (1, b.SCAN_LIST_MAJOR), (1, b.SCAN_QUERY_MAJOR)):

@@ -208,7 +208,7 @@ def run_workload(args, name: str, steps: int, warmup: int, cpu_seconds: float, p
               "kernel": ("probe_bound_kernel + lm_pairs / lm_offsets + lm_scan_kernel (head pass: every query's nearest list, "
                          "ranked list-major, two queries per fp32 table) + lm_byte_kernel (main pass: the other lists that the "
                          "list-level bound does not rule out, eight queries per byte table, fp32 distances for what passes; "
-                         "lm_scan_kernel where lists are short against k) + lm_merge_kernel, as shipped") if resolved == binding.SCAN_LIST_MAJOR else
+                         "lm_scan_kernel where lists are short against k) + lm_settle_kernel or lm_merge_kernel, as shipped") if resolved == binding.SCAN_LIST_MAJOR else
                         "probe_bound_kernel + scan_kernel as shipped (list-level bound, early exit of the sums, chunked loads: "
                         "bytes that cannot change the result are not read)",
               "bound": ("lds + per-task phases: one workgroup per CU alternates between building the table of a group of "

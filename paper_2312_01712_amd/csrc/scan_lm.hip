@@ -958,7 +958,8 @@ __global__ __launch_bounds__(LMB_NW * 64) __attribute__((amdgpu_waves_per_eu(4))
     // Distances: s |r - e|^2 + offset as a product of depth DSUB + 1 on the matrix units, four
     // queries (rows) by 64 entries (columns, a lane each) at a time.  The sums carry 2^15, so bits 8
     // to 23 are a value's whole part, or 2^15 and more where it does not fit (from 3 x 2^15 on any number, a lower bound
-    // all the same): per four values two permutations that pair those bits, two minima with the rows' highest bytes and
+    // all the same; the head pass, which needs the row's highest byte for such a value, cuts the sums off there): per four
+    // values two permutations that pair those bits, two minima with the rows' highest bytes and
     // one permutation that collects the bytes.  This phase is bound by what a SIMD's four wavefronts issue (9.2
     // thousand clocks for 48 subspaces): a median and a conversion to a byte per value, conversions to normalised
     // 16 bits, or half of the products on the vector ALU all took as long to 3 %.
@@ -986,8 +987,14 @@ __global__ __launch_bounds__(LMB_NW * 64) __attribute__((amdgpu_waves_per_eu(4))
           const LDS ushortx2 *top = (const LDS ushortx2 *)(stop + m * LMB_G + 4 * h);
           const ushortx2 top01 = top[0], top23 = top[1];
           auto bytes_of = [&](const floatx4 &acc) __attribute__((always_inline)) {
-            const uint32_t v01 = __builtin_amdgcn_perm(__float_as_uint(acc[1]), __float_as_uint(acc[0]), 0x06050201u);
-            const uint32_t v23 = __builtin_amdgcn_perm(__float_as_uint(acc[3]), __float_as_uint(acc[2]), 0x06050201u);
+            uint32_t b[4];
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+              b[g] = __float_as_uint(acc[g]);
+              if constexpr (HEAD) b[g] = umin32(b[g], 0x47C00000u);   // 3 x 2^15 (bits of positive numbers order like them)
+            }
+            const uint32_t v01 = __builtin_amdgcn_perm(b[1], b[0], 0x06050201u);
+            const uint32_t v23 = __builtin_amdgcn_perm(b[3], b[2], 0x06050201u);
             const ushortx2 lo = __builtin_elementwise_min(__builtin_bit_cast(ushortx2, v01), top01);
             const ushortx2 hi = __builtin_elementwise_min(__builtin_bit_cast(ushortx2, v23), top23);
             return __builtin_amdgcn_perm(__builtin_bit_cast(uint32_t, hi), __builtin_bit_cast(uint32_t, lo), 0x06040200u);

@@ -285,3 +285,32 @@ def test_long_lists_shared_by_many_queries(D, M, k, cap, radius):
     finally:
         b.set_option("lm_cap", 0)
         gi.close()
+
+
+@pytest.mark.parametrize("D,M,spread,sigma,radius,wide", [
+    (64, 16, 0.3, 1.0, 0.049, 1.0), (64, 16, 0.3, 1.0, 0.053, 1.0), (64, 16, 0.3, 3.0, 0.1, 1.0), (64, 16, 0.3, 3.0, 0.164, 1.0),
+    (64, 16, 1.0, 1.0, 0.1, 1.0), (64, 16, 1.0, 0.3, 0.6, 35.0), (96, 48, 0.3, 3.0, 0.122, 1.0), (96, 48, 0.3, 3.0, 0.05, 1.0),
+    (128, 64, 0.3, 3.0, 0.09, 1.0), (128, 64, 0.3, 1.0, 0.0, 1.0)])
+def test_long_lists_with_radii_far_below_the_residuals(D, M, spread, sigma, radius, wide):
+    """The nearest list ranked with byte tables where squared distances to the entries lie a thousand times and more above
+    the largest squared radius (values in the tables' units beyond 2^16, where a byte is cut from bits that wrap), and
+    where one subspace is much wider than the others."""
+    b = _binding()
+    rng = np.random.default_rng(M + int(1000 * radius))
+    sizes = np.array([9100, 0, 8300, 90, 12_000, 1, 8800, 9900])
+    nlist, nprobe, distinct, reps = len(sizes), 6, 60, 46
+    idx = _index(rng, D, M, sizes, spread=spread, centre=0.01)
+    idx.codebooks[0] *= np.float32(wide)
+    q = (idx.centroids[rng.integers(0, nlist, distinct)] + sigma * rng.normal(size=(distinct, D))).astype(np.float32)
+    radii = np.full(M, radius, dtype=np.float32)
+    gi = b.IvfPqIndex.from_index(idx)
+    dq = torch.from_numpy(q).cuda().repeat(reps, 1)
+    try:
+        b.set_option("lm_cap", 65536)   # (no query is redone for want of slots, which would cover up what the tables miss)
+        assert gi.resolve_strategy(distinct * reps, nprobe, 10) == b.SCAN_LIST_MAJOR
+        for k in (1, 10, 100):
+            want = oracle.search(q, idx, nprobe, k, radii, threads=8)
+            _same(gi.search(dq, nprobe, k, radii), (np.tile(want[0], (reps, 1)), np.tile(want[1], (reps, 1))), (D, M, sigma, radius, k))
+    finally:
+        b.set_option("lm_cap", 0)
+        gi.close()

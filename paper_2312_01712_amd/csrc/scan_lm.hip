@@ -66,6 +66,7 @@ struct LmArgs {
   int32_t *qmap_head;           // [Q] head pass: q for a query whose nearest list is left to the query-major kernel, else -1
   int32_t head_max;             // head pass: longest list (points) whose distances fit the workgroup's LDS
   const float *query_radii;     // [Q][M] or NULL
+  float rmax;                   // largest r_m^2 of the shared radii
   int64_t Q;
   int32_t D, M, dsub, Mp, nlist, nprobe, first, k, cap, mode;
   int32_t p0, p1;               // the probes [p0, p1) of every query that the current main pass serves
@@ -699,6 +700,7 @@ __global__ __launch_bounds__(LM_NW * 64) __attribute__((amdgpu_waves_per_eu(LM_N
 constexpr int LMB_NW = 16;      // wavefronts: one workgroup per CU (the table takes 2 KiB per subspace), 4 per SIMD
 constexpr int LMB_QUEUE = 3072; // candidates a task holds; more go to the queries' slots one by one
 constexpr int LMB_TOP = 63;
+constexpr float LMB_RANGE = 9.0e4f;   // a value below it, and what is added to it, stay below 3 x 2^15
 
 typedef uint16_t ushortx2 __attribute__((ext_vector_type(2)));
 typedef uint32_t uintx2 __attribute__((ext_vector_type(2)));
@@ -759,6 +761,7 @@ __global__ __launch_bounds__(LMB_NW * 64) __attribute__((amdgpu_waves_per_eu(4))
   LDS uint32_t *sT = small;                        // [2][8] sums below this are candidates
   LDS int32_t *sq = (LDS int32_t *)(small + 16);   // [2][8] queries
   LDS uint32_t *qn = small + 32;                   // [2] candidates offered to the queue
+  LDS uint32_t *wraps = small + 48;                // [2][8] values of the query's table may wrap
   LDS uint32_t *hist = small + LMB_SMALL;          // head pass: [8][LMB_BINS]
 
   int tid = threadIdx.x, lane = tid & 63;
@@ -845,41 +848,44 @@ __global__ __launch_bounds__(LMB_NW * 64) __attribute__((amdgpu_waves_per_eu(4))
     for (int j = 0; j < DSUB; ++j) res[j] = f.q[j] - f.c[j];
     const float tau = __uint_as_float((uint32_t)__builtin_amdgcn_readfirstlane((int)__float_as_uint(f.tau)));
     LDS float *rec = srec + (lane * LMB_G + g) * PW;
-    uint32_t T;
+    uint32_t T, wrap = 0u;
     if constexpr (MODE == 0) {
       // Units: the largest r_m^2 (no table value exceeds it), or, where that is wider, four times
       // the mean value of a point within tau, maps to LMB_TOP; values beyond are cut off, which
-      // keeps the sum a lower bound.
-      float rmax = on ? f.r2 : 0.0f;
-#pragma unroll
-      for (int off = 32; off > 8; off >>= 1) rmax = fmaxf(rmax, __shfl_xor(rmax, off));
-      rmax = fmaxf(rmax, xor_f32<8>(rmax));
-      rmax = fmaxf(rmax, xor_f32<4>(rmax));
-      rmax = fmaxf(rmax, xor_f32<2>(rmax));
-      rmax = fmaxf(rmax, xor_f32<1>(rmax));
-      // Head pass: no value is cut off; where radii are infinite the largest distance to any entry bounds them.
+      // keeps the sum a lower bound.  (Head pass: no value is cut off; where radii are
+      // infinite the largest distance to any entry bounds them.)
       float rr = 0.0f;
 #pragma unroll
       for (int j = 0; j < DSUB; ++j) rr = fmaf(res[j], res[j], rr);
       const float far = on ? sqrtf(rr) + sqrtf(semax[lane]) : 0.0f;
-      float widest = tau * (4.0f / (float)MT);
-      if constexpr (HEAD) {
-        widest = far * far * 1.0001f;
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) widest = fmaxf(widest, __shfl_xor(widest, off));
+      float rmax = a.rmax, widest = far * far * 1.0001f;
+      auto over_lanes = [&](auto fold) __attribute__((always_inline)) {
+        fold([](float v) __attribute__((always_inline)) { return __shfl_xor(v, 32); });
+        fold([](float v) __attribute__((always_inline)) { return __shfl_xor(v, 16); });
+        fold([](float v) __attribute__((always_inline)) { return xor_f32<8>(v); });
+        fold([](float v) __attribute__((always_inline)) { return xor_f32<4>(v); });
+        fold([](float v) __attribute__((always_inline)) { return xor_f32<2>(v); });
+        fold([](float v) __attribute__((always_inline)) { return xor_f32<1>(v); });
+      };
+      if (a.query_radii) {
+        rmax = on ? f.r2 : 0.0f;
+        over_lanes([&](auto other) __attribute__((always_inline)) { rmax = fmaxf(rmax, other(rmax)); });
       }
-      const float cap = fmaxf(fminf(rmax, widest), 1e-30f);
+      if constexpr (HEAD) over_lanes([&](auto other) __attribute__((always_inline)) { widest = fmaxf(widest, other(widest)); });
+      const float cap = fmaxf(fminf(rmax, HEAD ? widest : tau * (4.0f / (float)MT)), 1e-30f);
       const float s = ((float)LMB_TOP - 0.01f) / cap;   // infinite radii and no k-th distance: 0
+      wrap = __ballot(on && !(s * far * far < LMB_RANGE)) != 0ull ? 1u : 0u;
       // Offset of a row: up to the next integer at the row's cap, so that entries outside the
       // radius (most of them) lose nothing to the floor; what the offsets add is known.
       const float x = fminf(f.r2, cap) * s, top = ceilf(x), off = top - x;
-      // A byte is taken from the bits of 2^15 + value, whose last place is 2^-8: the four roundings at
-      // that magnitude move a value by 2^-9 each, together below 0.01, those of |r|^2 - 2 r.e + |e|^2 in place
-      // of |r - e|^2 by 2^-24 of s (|r| + |e|)^2 each: fewer than 2 DSUB + 10 of them, counted as 32.
+      // A byte is taken from the bits of 2^15 + value, whose last place is 2^-8: the DSUB + 2 roundings at
+      // that magnitude move a value by 2^-9 each (RAISE counts one more), those of |r|^2 - 2 r.e + |e|^2 in place
+      // of |r - e|^2 by 2^-24 of s (|r| + |e|)^2 each: fewer than 3 DSUB + 4 of them, counted as 32.
       // The values are raised by that much, so that none is below 0.
+      constexpr float RAISE = (DSUB + 3) / 512.0f;
       float add = 0.0f;
       if (on) {
-        const float err = fmaf(s * far, far * 1.9073486e-06f, 0.01f);
+        const float err = fmaf(s * far, far * 1.9073486e-06f, RAISE);
 #pragma unroll
         for (int j = 0; j < DSUB; ++j) rec[j] = -2.0f * s * res[j];
         rec[DSUB] = s;
@@ -889,12 +895,7 @@ __global__ __launch_bounds__(LMB_NW * 64) __attribute__((amdgpu_waves_per_eu(4))
       }
       // Limit on the byte sum of a point with distance <= tau: s tau, relative roundings (the fp32
       // sum, the scaling: 2^-23 each, at most 70 of them), the offsets, the raise and the roundings again.
-#pragma unroll
-      for (int o = 32; o > 8; o >>= 1) add += __shfl_xor(add, o);
-      add += xor_f32<8>(add);
-      add += xor_f32<4>(add);
-      add += xor_f32<2>(add);
-      add += xor_f32<1>(add);
+      over_lanes([&](auto other) __attribute__((always_inline)) { add += other(add); });
       // (Head pass: what lies between the k-th smallest sum and the limit.)
       const float lim = HEAD ? add + (float)MT + 2.0f : fmaf(tau * s, 1.00001f, add) + 0.25f;
       T = lim < 60000.0f ? (uint32_t)lim : 60000u;   // NaN (0 x inf, or no k-th distance): every point
@@ -907,6 +908,7 @@ __global__ __launch_bounds__(LMB_NW * 64) __attribute__((amdgpu_waves_per_eu(4))
       T = tau < 60000.0f ? (uint32_t)tau : 60000u;
     }
     if (lane == 0) {
+      wraps[par * 8 + g] = wrap;
       sT[par * 8 + g] = f.qid >= 0 ? T + 1u : 0u;
       sq[par * 8 + g] = f.qid;
       if (g == 0) qn[par] = 0u;
@@ -957,13 +959,14 @@ __global__ __launch_bounds__(LMB_NW * 64) __attribute__((amdgpu_waves_per_eu(4))
     // ---- the table: row m holds, entry by entry, one byte per query ----
     // Distances: s |r - e|^2 + offset as a product of depth DSUB + 1 on the matrix units, four
     // queries (rows) by 64 entries (columns, a lane each) at a time.  The sums carry 2^15, so bits 8
-    // to 23 are a value's whole part, or 2^15 and more where it does not fit (from 3 x 2^15 on any number, a lower bound
-    // all the same; the head pass, which needs the row's highest byte for such a value, cuts the sums off there): per four
+    // to 23 are a value's whole part, or 2^15 and more where it does not fit.  From 3 x 2^15 on they wrap: where entries lie that
+    // far out (the largest radius is 1/38 of the way to them or less) the sums are cut off there.  Per four
     // values two permutations that pair those bits, two minima with the rows' highest bytes and
     // one permutation that collects the bytes.  This phase is bound by what a SIMD's four wavefronts issue (9.2
     // thousand clocks for 48 subspaces): a median and a conversion to a byte per value, conversions to normalised
     // 16 bits, or half of the products on the vector ALU all took as long to 3 %.
     const bool five = sq[par * 8 + 4] >= 0;   // uniform
+    auto build_table = [&](auto cut) __attribute__((always_inline)) {
 #pragma unroll
     for (int it = 0; it < ITER; ++it) {
       const int m = wave + it * NW;
@@ -991,7 +994,7 @@ __global__ __launch_bounds__(LMB_NW * 64) __attribute__((amdgpu_waves_per_eu(4))
 #pragma unroll
             for (int g = 0; g < 4; ++g) {
               b[g] = __float_as_uint(acc[g]);
-              if constexpr (HEAD) b[g] = umin32(b[g], 0x47C00000u);   // 3 x 2^15 (bits of positive numbers order like them)
+              if constexpr (decltype(cut)::value) b[g] = umin32(b[g], 0x47C00000u);   // 3 x 2^15 (bits of positive numbers order like them)
             }
             const uint32_t v01 = __builtin_amdgcn_perm(b[1], b[0], 0x06050201u);
             const uint32_t v23 = __builtin_amdgcn_perm(b[3], b[2], 0x06050201u);
@@ -1042,6 +1045,9 @@ __global__ __launch_bounds__(LMB_NW * 64) __attribute__((amdgpu_waves_per_eu(4))
       for (int x = 0; x < 4; ++x) *(LDS uintx2 *)(smem3 + m * 2048 + (x * 64 + lane) * 8) = uintx2{w[0][x], w[1][x]};
       __builtin_amdgcn_sched_barrier(0);   // a row at a time: their temporaries together do not fit the registers
     }
+    };
+    if (MODE == 0 && __ballot(wraps[par * 8 + (lane & 7)] != 0u) != 0ull) build_table(std::true_type{});
+    else build_table(std::false_type{});
     const int tn = t + nwg;
     const bool more = tn < ntasks;
     int64_t nmv = 0;
@@ -1684,7 +1690,7 @@ LmWorkspace plan_list_major(const ivfpq_index *ix, int64_t Q, int32_t nprobe) {
 }
 
 static LmArgs lm_args(const ivfpq_index *ix, const float *d_queries, int64_t Q, int32_t nprobe, const int32_t *d_probe_ids,
-                      const float *d_query_radii, const float *d_probe_lb, const LmWorkspace &w, char *lm_base) {
+                      const RadiiSq &r2, const float *d_query_radii, const float *d_probe_lb, const LmWorkspace &w, char *lm_base) {
   LmArgs a = {};
   a.queries = d_queries;
   a.probe_ids = d_probe_ids;
@@ -1711,6 +1717,7 @@ static LmArgs lm_args(const ivfpq_index *ix, const float *d_queries, int64_t Q, 
   a.p0 = w.first;
   a.p1 = nprobe;
   a.group = LM_G;
+  for (int m = 0; m < ix->M; ++m) a.rmax = r2.v[m] > a.rmax ? r2.v[m] : a.rmax;
   return a;
 }
 
@@ -1742,7 +1749,7 @@ int launch_wide_stage(const ivfpq_index *ix, const float *d_queries, int64_t Q, 
                       const RadiiSq &r2, const float *d_query_radii, const float *d_probe_lb, uint32_t *wide_d, int64_t *wide_id,
                       int32_t *wide_n, uint32_t *wide_bound, int32_t cap, const LmWorkspace &w, char *lm_base, int stage,
                       int32_t p0, int32_t p1, hipStream_t s) {
-  LmArgs a = lm_args(ix, d_queries, Q, nprobe, d_probe_ids, d_query_radii, d_probe_lb, w, lm_base);
+  LmArgs a = lm_args(ix, d_queries, Q, nprobe, d_probe_ids, r2, d_query_radii, d_probe_lb, w, lm_base);
   a.cand = reinterpret_cast<uint2 *>(wide_id);
   a.cap = cap;
   a.tau = reinterpret_cast<const float *>(wide_bound);   // (keys of distances are their bits; none yet: a NaN)
@@ -1779,7 +1786,7 @@ int launch_scan_list_major(const ivfpq_index *ix, const float *d_queries, int64_
     return IVFPQ_ERR_UNSUPPORTED;
   }
 
-  LmArgs a = lm_args(ix, d_queries, Q, nprobe, d_probe_ids, d_query_radii, (get_scan_ablate() & 64) ? nullptr : d_probe_lb, w, lm_base);
+  LmArgs a = lm_args(ix, d_queries, Q, nprobe, d_probe_ids, r2, d_query_radii, (get_scan_ablate() & 64) ? nullptr : d_probe_lb, w, lm_base);
   a.out_ids = d_out_ids;
   a.out_dist = d_out_dist;
   a.tau = d_out_dist + k - 1;

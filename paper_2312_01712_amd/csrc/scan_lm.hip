@@ -710,6 +710,7 @@ template <int DSUB>
 struct LmbFetch {
   float q[DSUB], c[DSUB];   // lane m: subspace m of the query and of the list's centroid
   float r2, tau;
+  uint32_t n;               // its candidates so far
   int32_t qid;              // the query (-1: the group has fewer)
 };
 
@@ -720,6 +721,23 @@ constexpr int LMB_BINS = 256;   // head pass: bins of a query's byte sums
 constexpr int lmb_shift(int mt) { return mt > 16 ? 4 : 2; }   // 63 mt >> shift < LMB_BINS
 constexpr size_t lmb_lds(int mt, int dsub, bool head) {
   return (head ? (size_t)LMB_G * LMB_BINS * 4 : 0) + (size_t)mt * 2048 + (size_t)LMB_G * mt * (4 * lmb_rec(dsub) + 4 + 2) + (size_t)mt * 4 + (size_t)LMB_QUEUE * 4 + LMB_SMALL * 4;
+}
+
+// Candidates that a task's queue has no room for go straight to their queries' slots, with one atomic for all lanes: radii that
+// hold next to nothing make most points of a list candidates, and an atomic for each took 20 ms of a search of 5.
+// (A function of its own, so that the pass's registers are not shaped by it.)
+__device__ __attribute__((noinline)) void lmb_spill(uint32_t *gcnt, uint2 *cand, uint32_t cap, const LDS int32_t *sq, bool over,
+                                                    uint32_t g, uint32_t x, uint32_t row, int lane) {
+  uint32_t mine = 0, before = 0;
+  for (int y = 0; y < LMB_G; ++y) {
+    const unsigned long long b = __ballot(over && g == (uint32_t)y);
+    if (lane == y) mine = (uint32_t)__popcll(b);
+    if (g == (uint32_t)y) before = (uint32_t)__popcll(b & ((1ull << lane) - 1ull));
+  }
+  uint32_t slot = 0;
+  if (lane < LMB_G && mine > 0) slot = atomicAdd(&gcnt[sq[lane]], mine);
+  slot = (uint32_t)__shfl((int)slot, (int)g) + before;
+  if (over && slot < cap) cand[(int64_t)sq[g] * cap + slot] = make_uint2(x, row);
 }
 
 template <int J>
@@ -812,6 +830,7 @@ __global__ __launch_bounds__(LMB_NW * 64) __attribute__((amdgpu_waves_per_eu(4))
   auto fetch_params = [&](const int2 &pv, LmbFetch<DSUB> &f) __attribute__((always_inline)) {
     f.qid = -1;
     f.r2 = f.tau = 0.0f;
+    f.n = 0u;
 #pragma unroll
     for (int j = 0; j < DSUB; ++j) f.q[j] = f.c[j] = 0.0f;
     if (wave < W0) return;
@@ -835,7 +854,10 @@ __global__ __launch_bounds__(LMB_NW * 64) __attribute__((amdgpu_waves_per_eu(4))
         const float r = a.query_radii[q * MT + lane];
         f.r2 = r * r;
       }
-      if constexpr (!HEAD) f.tau = a.tau[q * a.tau_stride];
+      if constexpr (!HEAD) {
+        f.tau = a.tau[q * a.tau_stride];
+        f.n = a.gcnt[q];
+      }
     }
   };
   // ... and writes them to the records and to set `par` of the small words
@@ -880,12 +902,12 @@ __global__ __launch_bounds__(LMB_NW * 64) __attribute__((amdgpu_waves_per_eu(4))
       const float x = fminf(f.r2, cap) * s, top = ceilf(x), off = top - x;
       // A byte is taken from the bits of 2^15 + value, whose last place is 2^-8: the DSUB + 2 roundings at
       // that magnitude move a value by 2^-9 each (RAISE counts one more), those of |r|^2 - 2 r.e + |e|^2 in place
-      // of |r - e|^2 by 2^-24 of s (|r| + |e|)^2 each: fewer than 3 DSUB + 4 of them, counted as 32.
+      // of |r - e|^2 by 2^-24 of s (|r| + |e|)^2 each: fewer than 3 DSUB + 4 of them (REL counts four more).
       // The values are raised by that much, so that none is below 0.
-      constexpr float RAISE = (DSUB + 3) / 512.0f;
+      constexpr float RAISE = (DSUB + 3) / 512.0f, REL = (3 * DSUB + 8) / 16777216.0f;
       float add = 0.0f;
       if (on) {
-        const float err = fmaf(s * far, far * 1.9073486e-06f, RAISE);
+        const float err = fmaf(s * far, far * REL, RAISE);
 #pragma unroll
         for (int j = 0; j < DSUB; ++j) rec[j] = -2.0f * s * res[j];
         rec[DSUB] = s;
@@ -909,7 +931,7 @@ __global__ __launch_bounds__(LMB_NW * 64) __attribute__((amdgpu_waves_per_eu(4))
     }
     if (lane == 0) {
       wraps[par * 8 + g] = wrap;
-      sT[par * 8 + g] = f.qid >= 0 ? T + 1u : 0u;
+      sT[par * 8 + g] = f.qid >= 0 && f.n <= (uint32_t)a.cap ? T + 1u : 0u;   // (a query out of slots is redone, and offers no more)
       sq[par * 8 + g] = f.qid;
       if (g == 0) qn[par] = 0u;
     }
@@ -1176,22 +1198,30 @@ __global__ __launch_bounds__(LMB_NW * 64) __attribute__((amdgpu_waves_per_eu(4))
         uint32_t first = 0;
         if (lane == 0) first = __hip_atomic_fetch_add(&qn[par], (uint32_t)__popcll(bal), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         first = (uint32_t)__builtin_amdgcn_readfirstlane((int)first);
+        bool over = false;   // no room in the queue
+        uint32_t g = 0u, word = 0u;
         if (mask != 0u) {
-          const uint32_t g = (uint32_t)__ffs((int)mask) - 1u;
+          g = (uint32_t)__ffs((int)mask) - 1u;
           mask &= mask - 1u;
           const uint32_t pos = first + (uint32_t)__popcll(bal & ((1ull << lane) - 1ull));
-          uint32_t word = ((uint32_t)i << 3) | g;
+          word = ((uint32_t)i << 3) | g;
           if constexpr (MODE != 0) {   // the score travels with the point (at most 2 MT <= 128)
             const uint32_t zz = (g & 4u) ? ((g & 1u) ? s[3] : s[2]) : ((g & 1u) ? s[1] : s[0]);
             word = ((uint32_t)i << 11) | (((g & 2u) ? zz >> 16 : zz & 0xFFFFu) << 3) | g;
           }
           if (pos < (uint32_t)LMB_QUEUE) queue[pos] = word;
-          else {   // no room: straight to the query's slots
+          else over = true;
+        }
+        // straight to the queries' slots (the head pass offers a query a thousand points at most)
+        if constexpr (HEAD) {
+          if (over) {
             const int64_t q = sq[par * 8 + g];
             const uint32_t slot = atomicAdd(&a.gcnt[q], 1u);
-            if (slot < (uint32_t)a.cap)
-              a.cand[q * a.cap + slot] = make_uint2(MODE == 0 ? (uint32_t)list : __float_as_uint((float)((word >> 3) & 255u)), (uint32_t)(row0 + i));
+            if (slot < (uint32_t)a.cap) a.cand[q * a.cap + slot] = make_uint2((uint32_t)list, (uint32_t)(row0 + i));
           }
+        } else if (__ballot(over) != 0) {
+          lmb_spill(a.gcnt, a.cand, (uint32_t)a.cap, sq + par * 8, over, g,
+                    MODE == 0 ? (uint32_t)list : __float_as_uint((float)((word >> 3) & 255u)), (uint32_t)(row0 + i), lane);
         }
       }
     });

@@ -17,8 +17,8 @@ def _constant(pattern):
 
 TOP = int(_constant(r"constexpr int LMB_TOP = ([0-9]+);"))
 RANGE = _constant(r"constexpr float LMB_RANGE = ([0-9.e]+)f;")
-REL = _constant(r"const float err = fmaf\(s \* far, far \* ([0-9.e-]+)f, RAISE\);")
-assert "constexpr float RAISE = (DSUB + 3) / 512.0f;" in SOURCE
+assert "constexpr float RAISE = (DSUB + 3) / 512.0f, REL = (3 * DSUB + 8) / 16777216.0f;" in SOURCE
+assert "const float err = fmaf(s * far, far * REL, RAISE);" in SOURCE
 
 
 def _fma(a, b, c):
@@ -36,7 +36,7 @@ def _table(res, cb, r2, cap, cut=True):
     x = np.minimum(r2, max(cap, f32(1e-30))) * s
     top = np.ceil(x)
     off = top - x
-    err = _fma(s * far, far * f32(REL), f32((dsub + 3) / 512.0))
+    err = _fma(s * far, far * f32((3 * dsub + 8) / 16777216.0), f32((dsub + 3) / 512.0))
     acc = np.repeat((_fma(rr, s, off + err) + f32(32768.0))[:, None], 256, 1)
     for j in range(dsub):
         acc = _fma((f32(-2.0) * s * res[:, j])[:, None], cb[:, :, j], acc)

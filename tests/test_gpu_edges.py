@@ -314,3 +314,28 @@ def test_long_lists_with_radii_far_below_the_residuals(D, M, spread, sigma, radi
     finally:
         b.set_option("lm_cap", 0)
         gi.close()
+
+
+@pytest.mark.parametrize("D,M", [(96, 48), (128, 64), (64, 16)])
+@pytest.mark.parametrize("radius", [0.0, 0.02, 0.06])
+def test_more_candidates_than_a_task_holds(D, M, radius):
+    """Radii that hold next to nothing: most points of most lists are candidates of all eight queries of a task, more than
+    its queue takes and, of all lists, more than a query has slots."""
+    b = _binding()
+    rng = np.random.default_rng(M)
+    nlist, nprobe, distinct, reps = 40, 32, 64, 8
+    idx = _index(rng, D, M, rng.integers(600, 1100, size=nlist), centre=0.05)
+    q = (idx.centroids[rng.integers(0, nlist, distinct)] + 0.3 * rng.normal(size=(distinct, D))).astype(np.float32)
+    radii = np.full(M, radius, dtype=np.float32)
+    gi = b.IvfPqIndex.from_index(idx)
+    dq = torch.from_numpy(q).cuda().repeat(reps, 1)
+    try:
+        for cap in (0, 65536):
+            b.set_option("lm_cap", cap)
+            assert gi.resolve_strategy(distinct * reps, nprobe, 10) == b.SCAN_LIST_MAJOR
+            for k in (1, 10, 100):
+                want = oracle.search(q, idx, nprobe, k, radii, threads=8)
+                _same(gi.search(dq, nprobe, k, radii), (np.tile(want[0], (reps, 1)), np.tile(want[1], (reps, 1))), (D, M, radius, cap, k))
+    finally:
+        b.set_option("lm_cap", 0)
+        gi.close()

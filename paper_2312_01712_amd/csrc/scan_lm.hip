@@ -38,6 +38,7 @@ constexpr int LM_NW = 8;       // wavefronts per workgroup: one workgroup per CU
 constexpr int LM_STAGE1 = 7;   // probes of the first of two main passes (behind the lists ranked first)
 constexpr int LM_QUEUE = 64;   // accepted candidates a wavefront holds per query before it appends them
 constexpr int LM_SEL_WORDS = 16;     // head pass: small LDS block of selection state
+constexpr int32_t LM_SEEDED = -2;
 constexpr int LM_BINS = 1024;        // head pass: bins of the selection histogram
 constexpr int LM_COLLECT = 128;      // head pass: candidates a query may collect (the sorted list of a wavefront)
 
@@ -63,7 +64,8 @@ struct LmArgs {
   uint2 *cand;                  // [Q][cap] (distance bits, row in the index); from byte tables of distances (list, row)
   int32_t *qmap;                // [Q] q for a query to be redone query-major, -1 otherwise
   int32_t *redo;                // [Q] those queries, in any order (the place of rank)
-  int32_t *qmap_head;           // [Q] head pass: q for a query whose nearest list is left to the query-major kernel, else -1
+  int32_t *qmap_head;           // [Q] head pass: q for a query whose nearest list is left to the query-major kernel, else -1, or
+                                // LM_SEEDED: its result holds any k points of that list, which bound its k-th distance
   int32_t head_max;             // head pass: longest list (points) whose distances fit the workgroup's LDS
   const float *query_radii;     // [Q][M] or NULL
   float rmax;                   // largest r_m^2 of the shared radii
@@ -73,6 +75,7 @@ struct LmArgs {
   int32_t later;                // this is not the first main pass: qmap already names queries to be redone
   int32_t stage;                // which of the passes of a call with candidates to settle
   int32_t fresh;                // byte tables in the head pass: the queries have no result yet
+  int32_t seeded;               // behind that pass: qmap_head may be LM_SEEDED
   int32_t group;                // queries per group of the pass the pairs are bucketed for
   int32_t head_done;            // the head pass has run: queries it left out (qmap_head) have no first-list result yet
   const float *tau;             // [Q] x tau_stride: the k-th distance that filters the main pass (NaN: none yet)
@@ -110,6 +113,7 @@ __global__ __launch_bounds__(256) void lm_pairs_kernel(LmArgs a, int fill, int h
   // query-major over all of its lists (lm_merge_kernel puts it on that list)
   if (!head && a.head_done && a.qmap_head[q] >= 0) take = false;
   if (!head && a.later && a.qmap[q] >= 0) take = false;   // nor does one whose slots have overflowed
+  if (!head && a.seeded && p == 0 && a.qmap_head[q] != LM_SEEDED) take = false;   // the head pass has ranked this list
   if (a.wide_n && a.wide_n[q] < 0) take = false;
   const bool exists = (uint32_t)c < (uint32_t)a.nlist;
   const int64_t len = exists ? a.list_offsets[c + 1] - a.list_offsets[c] : 0;
@@ -716,11 +720,12 @@ struct LmbFetch {
 
 // Floats of a (subspace, query) record, padded to whole 16-byte reads.
 constexpr int lmb_rec(int dsub) { return dsub == 2 ? 4 : 8; }
-constexpr int LMB_SMALL = 64;   // words: two sets of a task's limits and queries, and the two queue counters
+constexpr int LMB_SMALL = 64;   // words: two sets of a task's limits and queries, the two queue counters, the head pass's counts
 constexpr int LMB_BINS = 256;   // head pass: bins of a query's byte sums
+constexpr int LMB_SPARE = 64;   // head pass: points of the k-th sum's bin offered beyond k
 constexpr int lmb_shift(int mt) { return mt > 16 ? 4 : 2; }   // 63 mt >> shift < LMB_BINS
 constexpr size_t lmb_lds(int mt, int dsub, bool head) {
-  return (head ? (size_t)LMB_G * LMB_BINS * 4 : 0) + (size_t)mt * 2048 + (size_t)LMB_G * mt * (4 * lmb_rec(dsub) + 4 + 2) + (size_t)mt * 4 + (size_t)LMB_QUEUE * 4 + LMB_SMALL * 4;
+  return (head ? (size_t)LMB_G * LMB_BINS * 4 + (size_t)mt * 4 : 0) + (size_t)mt * 2048 + (size_t)LMB_G * mt * (4 * lmb_rec(dsub) + 4 + 2) + (size_t)mt * 4 + (size_t)LMB_QUEUE * 4 + LMB_SMALL * 4;
 }
 
 // Candidates that a task's queue has no room for go straight to their queries' slots, with one atomic for all lanes: radii that
@@ -752,11 +757,20 @@ __device__ __forceinline__ float xor_f32(float v) { return __uint_as_float(xor_u
 // candidates (125) for half of the lanes.
 //
 // HEAD: the pass over every query's nearest list, without a k-th distance to compare with.  The list is passed over
-// twice: the first pass counts the byte sums in a histogram per query (256 bins in LDS), the second one offers every
-// point up to the bin of the k-th smallest sum and as much beyond as the bytes can have lost.  A byte is less than 1 below
-// s v + offset and at most twice the raise above it, so k points have s distance + offsets < sum_k + MT, and one as near
-// has a sum of at most sum_k + MT + the raises.
-// 8192 queries on lists of 4000 points, 64 subspaces: 1248 us a search with the fp32 head pass, 881 so.
+// twice: the first pass counts the byte sums in a histogram per query (256 bins in LDS), the second one offers points up
+// to a limit that the histogram gives:
+//  - every point up to the bin of the k-th smallest sum and as much beyond as the bytes can have lost.  Where the units
+//    are those of the largest radius, nothing but what lies outside its radius is cut off, at that radius' own value: a
+//    byte is less than 1 below s v + offset and at most twice the raise above it, so k points have
+//    s distance + offsets < sum_k + MT, and one as near has a sum of at most sum_k + MT + the raises.
+//  - or, where that is more points than are worth settling (radii that hold next to nothing or, with units of their own,
+//    nearly everything), the points below the bin of the k-th smallest sum and of that bin as many as make k and
+//    LMB_SPARE.  Any k points will do: the k-th of their distances bounds the query's k-th distance, and the main pass starts over
+//    from that with this list among the others (LM_SEEDED).  Nothing is asked of the bytes then but a good order.
+// A point to settle costs about what 8 to 16 byte sums do, a table about a thousand.
+// 8192 queries of 64 probes, k = 100, us with the fp32 head pass / with byte tables, every point the bytes cannot rule out offered /
+// so: 64 subspaces, clustered, lists of 3906, radii that hold 0.25 of the entries 1253 / 983 / 1011, 0.5 1081 / 1789 / 994, 0.9
+// 1076 / 4331 / 990; 16 subspaces, lists of 7812, infinite radii (query-major before) 889 / 3895 / 877.
 template <int MT, int DSUB, int MODE, bool HEAD = false>
 __global__ __launch_bounds__(LMB_NW * 64) __attribute__((amdgpu_waves_per_eu(4))) void lm_byte_kernel(LmArgs a, RadiiSq r2) {
   constexpr int NW = LMB_NW;
@@ -779,8 +793,10 @@ __global__ __launch_bounds__(LMB_NW * 64) __attribute__((amdgpu_waves_per_eu(4))
   LDS uint32_t *sT = small;                        // [2][8] sums below this are candidates
   LDS int32_t *sq = (LDS int32_t *)(small + 16);   // [2][8] queries
   LDS uint32_t *qn = small + 32;                   // [2] candidates offered to the queue
+  LDS int32_t *room = (LDS int32_t *)(small + 40); // head pass: [8] points of the last bin below the limit that may still be offered
   LDS uint32_t *wraps = small + 48;                // [2][8] values of the query's table may wrap
-  LDS uint32_t *hist = small + LMB_SMALL;          // head pass: [8][LMB_BINS]
+  LDS uint32_t *hist = small + LMB_SMALL;          // head pass: [8][LMB_BINS], then the mean |entry|^2 of a subspace [MT]
+  LDS float *semean = (LDS float *)(hist + LMB_G * LMB_BINS);
 
   int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -796,7 +812,7 @@ __global__ __launch_bounds__(LMB_NW * 64) __attribute__((amdgpu_waves_per_eu(4))
 #pragma unroll
   for (int it = 0; it < ITER; ++it) {
     const int m = wave + it * NW;   // < MT or not: MT is a multiple of NW
-    float emax = 0.0f;
+    float emax = 0.0f, esum = 0.0f;
 #pragma unroll
     for (int x = 0; x < 4; ++x) {
       const float *src = a.codebooks + ((int64_t)m * 256 + x * 64 + lane) * DSUB;
@@ -807,10 +823,16 @@ __global__ __launch_bounds__(LMB_NW * 64) __attribute__((amdgpu_waves_per_eu(4))
         n2 = fmaf(src[j], src[j], n2);
       }
       emax = fmaxf(emax, n2);
+      esum += n2;
     }
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) emax = fmaxf(emax, __shfl_xor(emax, off));
     if (lane == 0) semax[m] = emax;
+    if constexpr (HEAD) {
+#pragma unroll
+      for (int off = 32; off > 0; off >>= 1) esum += __shfl_xor(esum, off);
+      if (lane == 0) semean[m] = esum * (1.0f / 256.0f);
+    }
   }
 
   // (vector loads for what all lanes want alike: see lm_scan_kernel)
@@ -852,7 +874,7 @@ __global__ __launch_bounds__(LMB_NW * 64) __attribute__((amdgpu_waves_per_eu(4))
       f.r2 = r2.v[lane];
       if (a.query_radii) {
         const float r = a.query_radii[q * MT + lane];
-        f.r2 = r * r;
+        f.r2 = fminf(r * r, __builtin_inff());   // (a NaN cuts nothing off, like an infinite radius)
       }
       if constexpr (!HEAD) {
         f.tau = a.tau[q * a.tau_stride];
@@ -874,13 +896,12 @@ __global__ __launch_bounds__(LMB_NW * 64) __attribute__((amdgpu_waves_per_eu(4))
     if constexpr (MODE == 0) {
       // Units: the largest r_m^2 (no table value exceeds it), or, where that is wider, four times
       // the mean value of a point within tau, maps to LMB_TOP; values beyond are cut off, which
-      // keeps the sum a lower bound.  (Head pass: no value is cut off; where radii are
-      // infinite the largest distance to any entry bounds them.)
+      // keeps the sum a lower bound.  (Head pass: of a point at the mean distance, |r|^2 + the mean |e|^2.)
       float rr = 0.0f;
 #pragma unroll
       for (int j = 0; j < DSUB; ++j) rr = fmaf(res[j], res[j], rr);
       const float far = on ? sqrtf(rr) + sqrtf(semax[lane]) : 0.0f;
-      float rmax = a.rmax, widest = far * far * 1.0001f;
+      float rmax = a.rmax, mean = HEAD && on ? rr + semean[lane] : 0.0f;
       auto over_lanes = [&](auto fold) __attribute__((always_inline)) {
         fold([](float v) __attribute__((always_inline)) { return __shfl_xor(v, 32); });
         fold([](float v) __attribute__((always_inline)) { return __shfl_xor(v, 16); });
@@ -893,8 +914,8 @@ __global__ __launch_bounds__(LMB_NW * 64) __attribute__((amdgpu_waves_per_eu(4))
         rmax = on ? f.r2 : 0.0f;
         over_lanes([&](auto other) __attribute__((always_inline)) { rmax = fmaxf(rmax, other(rmax)); });
       }
-      if constexpr (HEAD) over_lanes([&](auto other) __attribute__((always_inline)) { widest = fmaxf(widest, other(widest)); });
-      const float cap = fmaxf(fminf(rmax, HEAD ? widest : tau * (4.0f / (float)MT)), 1e-30f);
+      if constexpr (HEAD) over_lanes([&](auto other) __attribute__((always_inline)) { mean += other(mean); });
+      const float cap = fmaxf(fminf(rmax, (HEAD ? mean : tau) * (4.0f / (float)MT)), 1e-30f);
       const float s = ((float)LMB_TOP - 0.01f) / cap;   // infinite radii and no k-th distance: 0
       wrap = __ballot(on && !(s * far * far < LMB_RANGE)) != 0ull ? 1u : 0u;
       // Offset of a row: up to the next integer at the row's cap, so that entries outside the
@@ -921,6 +942,7 @@ __global__ __launch_bounds__(LMB_NW * 64) __attribute__((amdgpu_waves_per_eu(4))
       // (Head pass: what lies between the k-th smallest sum and the limit.)
       const float lim = HEAD ? add + (float)MT + 2.0f : fmaf(tau * s, 1.00001f, add) + 0.25f;
       T = lim < 60000.0f ? (uint32_t)lim : 60000u;   // NaN (0 x inf, or no k-th distance): every point
+      if (HEAD && !(rmax <= cap)) T = 0u;            // values inside a radius are cut off
     } else {
       if (on) {
 #pragma unroll
@@ -1150,19 +1172,42 @@ __global__ __launch_bounds__(LMB_NW * 64) __attribute__((amdgpu_waves_per_eu(4))
           const uint32_t v = (uint32_t)__shfl_up((int)incl, off);
           if (lane >= off) incl += v;
         }
-        uint32_t run = incl - sum, need = (uint32_t)a.k, bin = LMB_BINS;
+        uint32_t run = incl - sum, need = (uint32_t)a.k, bin = LMB_BINS, below = 0u;
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-          if (run < need && need <= run + c[j]) bin = (uint32_t)(4 * lane + j);
+          if (run < need && need <= run + c[j]) {
+            bin = (uint32_t)(4 * lane + j);
+            below = run;
+          }
           run += c[j];
         }
-        const unsigned long long bal = __ballot(bin != (uint32_t)LMB_BINS);
-        const uint32_t slack = sT[par * 8 + wave];   // 0: no query
-        if (bal == 0ull) {   // fewer than k points: all of them
-          if (lane == 0 && slack != 0u) sT[par * 8 + wave] = 60001u;
-        } else if (bin != (uint32_t)LMB_BINS && slack != 0u) {   // one lane
-          sT[par * 8 + wave] = umin32(((bin + 1u) << lmb_shift(MT)) - 1u + slack, 60001u);
+        const unsigned long long bal = __ballot(bin != (uint32_t)LMB_BINS);   // at most one lane
+        const uint32_t has = sT[par * 8 + wave];                              // 0: no query
+        int32_t spare = INT_MAX;
+        if (has != 0u) {
+          uint32_t limit = 60001u;   // fewer than k points: all of them
+          if (bal != 0ull) {
+            const int at = (int)__builtin_ctzll(bal);
+            bin = (uint32_t)__builtin_amdgcn_readlane((int)bin, at);
+            below = (uint32_t)__builtin_amdgcn_readlane((int)below, at);
+            limit = umin32(((bin + 1u) << lmb_shift(MT)) - 1u + has, 60001u);
+            const uint32_t last = (limit - 1u) >> lmb_shift(MT);
+            uint32_t n = 0;   // points in the bins up to the limit's
+#pragma unroll
+            for (int j = 0; j < 4; ++j) n += (uint32_t)(4 * lane + j) <= last ? c[j] : 0u;
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1) n += (uint32_t)__shfl_xor((int)n, off);
+            if (has == 1u || n > (uint32_t)a.cap || 8u * n > (uint32_t)len + 1024u + 8u * (need + 2u * LMB_SPARE)) {
+              limit = (bin + 1u) << lmb_shift(MT);
+              spare = (int32_t)(need - below + LMB_SPARE);
+            }
+          }
+          if (lane == 0) {
+            sT[par * 8 + wave] = limit;
+            if (spare != INT_MAX) a.qmap_head[sq[par * 8 + wave]] = LM_SEEDED;
+          }
         }
+        if (lane == 0) room[wave] = spare;
       }
       __syncthreads();
       asm volatile("" : "+v"(tid), "+v"(lane));
@@ -1170,7 +1215,8 @@ __global__ __launch_bounds__(LMB_NW * 64) __attribute__((amdgpu_waves_per_eu(4))
       load_chunks<MT, 0, NCH>(base, nb, wave < nb ? wave : nb - 1, lane, nxt);   // the second pass starts over
     }
     // the limits to compare with
-    uint32_t lim[4];
+    uint32_t lim[4], seeds = 0u;   // head pass: bit g: query g is offered just enough points
+    if constexpr (HEAD) seeds = (uint32_t)(__ballot(room[lane & (LMB_G - 1)] != INT_MAX) & 0xFFull);
     {
       const LDS uint32_t *T = sT + par * 8;
       lim[0] = (uint32_t)__builtin_amdgcn_readfirstlane((int)(T[0] | (T[2] << 16)));
@@ -1195,14 +1241,25 @@ __global__ __launch_bounds__(LMB_NW * 64) __attribute__((amdgpu_waves_per_eu(4))
       }
       if (i >= len) mask = 0u;
       for (unsigned long long bal = __ballot(mask != 0u); bal != 0; bal = __ballot(mask != 0u)) {
+        bool take = mask != 0u, over = false;   // (over: no room in the queue)
+        uint32_t g = 0u, word = 0u;
+        if (take) {
+          g = (uint32_t)__ffs((int)mask) - 1u;
+          mask &= mask - 1u;
+        }
+        if constexpr (HEAD) {   // of the last bin no more than there is room for
+          if (take && ((seeds >> g) & 1u)) {
+            const uint32_t zz = (g & 4u) ? ((g & 1u) ? z[3] : z[2]) : ((g & 1u) ? z[1] : z[0]);
+            if (((g & 2u) ? zz >> 16 : zz & 0xFFFFu) <= (1u << lmb_shift(MT)))
+              take = room[g] > 0 && __hip_atomic_fetch_sub(&room[g], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) > 0;
+          }
+          bal = __ballot(take);
+          if (bal == 0ull) continue;
+        }
         uint32_t first = 0;
         if (lane == 0) first = __hip_atomic_fetch_add(&qn[par], (uint32_t)__popcll(bal), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         first = (uint32_t)__builtin_amdgcn_readfirstlane((int)first);
-        bool over = false;   // no room in the queue
-        uint32_t g = 0u, word = 0u;
-        if (mask != 0u) {
-          g = (uint32_t)__ffs((int)mask) - 1u;
-          mask &= mask - 1u;
+        if (take) {
           const uint32_t pos = first + (uint32_t)__popcll(bal & ((1ull << lane) - 1ull));
           word = ((uint32_t)i << 3) | g;
           if constexpr (MODE != 0) {   // the score travels with the point (at most 2 MT <= 128)
@@ -1212,7 +1269,7 @@ __global__ __launch_bounds__(LMB_NW * 64) __attribute__((amdgpu_waves_per_eu(4))
           if (pos < (uint32_t)LMB_QUEUE) queue[pos] = word;
           else over = true;
         }
-        // straight to the queries' slots (the head pass offers a query a thousand points at most)
+        // straight to the queries' slots (the head pass offers no query more than it has slots)
         if constexpr (HEAD) {
           if (over) {
             const int64_t q = sq[par * 8 + g];
@@ -1359,13 +1416,20 @@ __global__ __launch_bounds__(LMS_NW * 64) __attribute__((amdgpu_waves_per_eu(4))
     if (n > n0) {
       uint2 *slots = a.cand + q * a.cap;
       Key L0, L1, tau;
+      uint32_t bound = SENT_D;   // on the k-th distance, besides the list's
+      const bool none = a.fresh || (a.seeded && a.qmap_head[q] == LM_SEEDED);   // no result to merge into
       auto take_tau = [&]() __attribute__((always_inline)) {
         const Key t0 = bcast_key(L0, (k - 1) & 63), t1 = bcast_key(L1, (k - 1) & 63);
         tau = (k - 1) < 64 ? t0 : t1;
+        if (tau.d > bound) {
+          tau.d = bound;
+          tau.id = SENT_ID;
+        }
       };
       if constexpr (!WIDE) {
         const int64_t o = q * k;
-        const bool in0 = !a.fresh && lane < k, in1 = !a.fresh && 64 + lane < k;
+        const bool in0 = !none && lane < k, in1 = !none && 64 + lane < k;
+        if (none && !a.fresh) bound = (uint32_t)__builtin_amdgcn_readfirstlane((int)__float_as_uint(a.out_dist[o + k - 1]));
         const int64_t id0 = in0 ? a.out_ids[o + lane] : -1, id1 = in1 ? a.out_ids[o + 64 + lane] : -1;
         L0.d = id0 >= 0 ? __float_as_uint(a.out_dist[o + lane]) : SENT_D;
         L0.id = id0 >= 0 ? id0 : SENT_ID;
@@ -1374,7 +1438,7 @@ __global__ __launch_bounds__(LMS_NW * 64) __attribute__((amdgpu_waves_per_eu(4))
         take_tau();
       }
       int waiting = 0;
-      bool changed = a.fresh;
+      bool changed = none;
       auto fold = [&](int from, int count) __attribute__((always_inline)) {   // at most 64 of the queue
         Key c;
         c.d = SENT_D;
@@ -1705,6 +1769,12 @@ bool list_major_supported(const ivfpq_index *ix, int32_t nprobe, int32_t k) {
   return nprobe > g_lm_first.load(std::memory_order_relaxed);
 }
 
+// Indexes on which the head pass may run with byte tables: lists that are long, or do not fit the fp32 form's LDS.
+static bool byte_head_lists(const ivfpq_index *ix) {
+  return ix->max_list_len < (1 << 20) &&
+         (ix->N > (int64_t)4096 * ix->nlist || (ix->max_list_len > lm_head_max(ix->M, ix->D) && ix->N >= (int64_t)2800 * ix->nlist));
+}
+
 LmWorkspace plan_list_major(const ivfpq_index *ix, int64_t Q, int32_t nprobe) {
   LmWorkspace w;
   w.first = g_lm_first.load(std::memory_order_relaxed);
@@ -1713,7 +1783,8 @@ LmWorkspace plan_list_major(const ivfpq_index *ix, int64_t Q, int32_t nprobe) {
   // 1M x 96 configuration (64 probes): 4096 slots 11.39 ms per batch, 8192 10.88, 16384 10.71.
   w.cap = g_lm_cap.load(std::memory_order_relaxed);
   if (w.cap == 0) w.cap = nprobe >= 64 ? 16384 : (nprobe * 256 > 4096 ? nprobe * 256 : 4096);
-  plan_list_major_tables(w, ix->nlist, Q, nprobe);
+  // (a main pass that starts over behind a head pass with byte tables has the first lists among its pairs)
+  plan_list_major_tables(w, ix->nlist, Q, byte_head_lists(ix) ? nprobe + w.first : nprobe);
   w.cand = w.total;
   w.total += lm_align((size_t)Q * w.cap * 8);
   return w;
@@ -1852,9 +1923,8 @@ int launch_scan_list_major(const ivfpq_index *ix, const float *d_queries, int64_
   //   64, clustered, 7812                     590 / 706    943 / 810   1310 / 1052  2162 / 1570
   //   48, without structure, 3906            2558 / 1038  3141 / 1621  5021 / 2766  7402 / 5093
   const int64_t head_points = (int64_t)((double)Q * (double)ix->N / ix->nlist);
-  const bool long_lists = ix->N > (int64_t)4096 * ix->nlist || (ix->max_list_len > a.head_max && ix->N >= (int64_t)2800 * ix->nlist);
-  const bool head_bytes = w.first == 1 && mode == IVFPQ_SCORE_DISTANCE && ix->max_list_len < (1 << 20) && !(get_scan_ablate() & 8) &&
-                          long_lists && head_points >= 8000000;
+  const bool head_bytes = byte_head_lists(ix) && w.first == 1 && mode == IVFPQ_SCORE_DISTANCE && !(get_scan_ablate() & 8) &&
+                          head_points >= 8000000;
   const bool head_pass = w.first == 1 && mode == IVFPQ_SCORE_DISTANCE && (head_bytes || a.head_max >= 64);
   if (head_bytes) {
     a.head_max = INT_MAX;
@@ -1876,6 +1946,7 @@ int launch_scan_list_major(const ivfpq_index *ix, const float *d_queries, int64_
   }
   a.head_done = head_pass ? 1 : 0;
   a.fresh = 0;
+  const int32_t main_first = head_bytes ? 0 : w.first;   // (the nearest list of queries that are only seeded)
   if (!head_pass) {
     ScanView head = {nprobe, nullptr, true};
     rc = launch_scan(ix, d_queries, Q, w.first, d_probe_ids, k, r2, 1, nullptr, nullptr, d_out_ids, d_out_dist,
@@ -1908,10 +1979,11 @@ int launch_scan_list_major(const ivfpq_index *ix, const float *d_queries, int64_
   // (2000 queries, 64 clustered: 131 / 143 at 32 probes, 143 / 156 at 64).  The line is where the two rounds cost
   // clustered data 3 % or less of a large batch.
   const int split = bytes && nprobe - w.first >= 2 * LM_STAGE1 + 32 ? w.first + LM_STAGE1 : nprobe;
-  for (int p0 = w.first, p1 = split; p0 < nprobe; p0 = p1, p1 = nprobe) {
+  for (int p0 = main_first, p1 = split; p0 < nprobe; p0 = p1, p1 = nprobe) {
     a.p0 = p0;
     a.p1 = p1;
-    a.later = p0 > w.first ? 1 : 0;
+    a.later = p0 > main_first ? 1 : 0;
+    a.seeded = head_bytes && !a.later ? 1 : 0;
     a.stage = a.later + 1;
     const int64_t npairs = Q * (p1 - p0);
     const unsigned pair_grid = (unsigned)((npairs + 255) / 256);

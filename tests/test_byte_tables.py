@@ -75,3 +75,31 @@ def test_bytes_bound_table_values_from_both_sides(M, dsub):
                         bare = _table(res, cb, r2, cap, cut=False)[0]
                         wraps += int(np.any(bare != byte))
     assert wraps > 10   # the ranges reach values whose bits wrap
+
+
+@pytest.mark.parametrize("M,dsub", [(16, 4), (48, 2), (64, 2)])
+def test_head_pass_offers_every_nearest_point(M, dsub):
+    """Where the head pass ranks a list by itself (units of the largest radius), the points up to the bin of the k-th byte sum
+    and the slack behind it hold the k nearest."""
+    rng = np.random.default_rng(M + 1)
+    shift = 4 if M > 16 else 2
+    assert "constexpr int lmb_shift(int mt) { return mt > 16 ? 4 : 2; }" in SOURCE
+    assert "const float lim = HEAD ? add + (float)MT + 2.0f" in SOURCE and "add = HEAD ? 2.0f * err" in SOURCE
+    rows = np.arange(M)[None, :]
+    for sigma in (0.3, 1.0, 3.0):
+        for radius in (0.02, 0.05, 0.1, 0.164, 0.3, 0.6):
+            for wide in (1.0, 35.0):
+                cb = (0.3 * rng.normal(size=(M, 256, dsub))).astype(f32)
+                cb[0] *= f32(wide)
+                res = (sigma * rng.normal(size=(M, dsub))).astype(f32)
+                r2 = np.full(M, f32(radius) * f32(radius))
+                codes = rng.integers(0, 256, size=(5000, M))
+                byte, s, off, err = _table(res, cb, r2, r2.max())
+                sums = byte[rows, codes].sum(1).astype(np.int64)
+                d2 = ((res.astype(np.float64)[:, None, :] - cb.astype(np.float64)) ** 2).sum(2)
+                dist = np.minimum(d2, r2[:, None].astype(np.float64))[rows, codes].sum(1)
+                slack = int((2 * err).sum() + M + 2) + 1
+                for k in (1, 10, 100):
+                    kth = np.sort(sums >> shift)[k - 1]
+                    limit = ((kth + 1) << shift) - 1 + slack
+                    assert np.all(sums[dist <= np.sort(dist)[k - 1] * (1 + 1e-6)] < limit)

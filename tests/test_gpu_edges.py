@@ -339,3 +339,57 @@ def test_more_candidates_than_a_task_holds(D, M, radius):
     finally:
         b.set_option("lm_cap", 0)
         gi.close()
+
+
+@pytest.mark.parametrize("D,M", [(96, 48), (128, 64), (64, 16)])
+@pytest.mark.parametrize("k,radius", [(1, 0.6), (100, 0.6), (100, 1.5), (100, 0.05), (10, np.inf)])
+def test_long_lists_in_two_main_passes(D, M, k, radius):
+    """Enough probes for two main passes behind a head pass with byte tables: queries whose nearest list it ranks, queries it
+    only finds any k points for (wide, infinite and very small radii), lists shorter than k, empty ones and runs of equal
+    distances; radii per query that are NaN (they cut nothing off)."""
+    b = _binding()
+    rng = np.random.default_rng(M + k)
+    nlist, nprobe, distinct, reps = 56, 50, 40, 110
+    sizes = rng.integers(3900, 5000, size=nlist)
+    sizes[:3] = (0, 40, 11_000)
+    idx = _index(rng, D, M, sizes, centre=0.05)
+    idx.codes[idx.list_offsets[9] + 50:idx.list_offsets[9] + 400] = idx.codes[0]
+    q = (idx.centroids[rng.integers(0, nlist, distinct)] + 0.25 * rng.normal(size=(distinct, D))).astype(np.float32)
+    q[::3] = idx.centroids[rng.integers(0, nlist, len(q[::3]))]
+    radii = np.full(M, radius * np.sqrt(D / M), dtype=np.float32)
+    gi = b.IvfPqIndex.from_index(idx)
+    dq = torch.from_numpy(q).cuda().repeat(reps, 1)
+    assert gi.resolve_strategy(distinct * reps, nprobe, k) == b.SCAN_LIST_MAJOR
+    want = oracle.search(q, idx, nprobe, k, radii, threads=8)
+    want = (np.tile(want[0], (reps, 1)), np.tile(want[1], (reps, 1)))
+    for strategy in (b.SCAN_AUTO, b.SCAN_LIST_MAJOR, b.SCAN_QUERY_MAJOR):
+        _same(gi.search(dq, nprobe, k, radii, strategy=strategy), want, (D, M, k, radius, strategy))
+    own = np.tile(radii, (distinct, 1))
+    own[::2, 3] = np.nan
+    rq = torch.from_numpy(own).cuda().repeat(reps, 1)
+    ref = gi.search(dq, nprobe, k, None, query_radii=rq, strategy=b.SCAN_QUERY_MAJOR)
+    ref = (ref[0].cpu().numpy(), ref[1].cpu().numpy())
+    _same(gi.search(dq, nprobe, k, None, query_radii=rq), ref, (D, M, k, radius, "NaN radii"))
+    gi.close()
+
+
+@pytest.mark.parametrize("D,M", [(96, 48), (64, 16)])
+def test_long_lists_with_entries_that_are_nan(D, M):
+    """Codebook entries that are NaN count as outside of every radius: list-major as query-major."""
+    b = _binding()
+    rng = np.random.default_rng(D)
+    sizes = np.array([9100, 8300, 5000, 12_000, 8800, 9900])
+    nprobe, distinct, reps = 5, 50, 56
+    idx = _index(rng, D, M, sizes, centre=0.2)
+    idx.codebooks[2, 5:40] = np.nan
+    idx.codebooks[M - 1, 100, 0] = np.nan
+    q = (idx.centroids[rng.integers(0, len(sizes), distinct)] + 0.25 * rng.normal(size=(distinct, D))).astype(np.float32)
+    gi = b.IvfPqIndex.from_index(idx)
+    dq = torch.from_numpy(q).cuda().repeat(reps, 1)
+    for radius in (0.6, 3.0, 20.0):
+        radii = np.full(M, radius, dtype=np.float32)
+        for k in (1, 100):
+            ref = gi.search(dq, nprobe, k, radii, strategy=b.SCAN_QUERY_MAJOR)
+            ref = (ref[0].cpu().numpy(), ref[1].cpu().numpy())
+            _same(gi.search(dq, nprobe, k, radii, strategy=b.SCAN_LIST_MAJOR), ref, (D, M, radius, k))
+    gi.close()

@@ -230,7 +230,9 @@ typedef enum {
  *     batch has at least 16 384 (query, list) pairs and the index's mean list length is at
  *     most 4096, or, with distance scoring, at most 16 384 and the batch large enough that its
  *     queries share their nearest lists (two a list, 16 million points in all); query-major
- *     otherwise.
+ *     otherwise.  On lists above 4096 points the workspace's candidate slots are bounded by 1 GiB or
+ *     4096 queries, whichever is more, larger batches go through them in pieces, and a workspace
+ *     sized for QUERY_MAJOR is accepted too; the call then runs query-major.
  * ivfpq_search_workspace_bytes sizes the workspace for AUTO with distance scoring;
  * ivfpq_search_workspace_bytes_ex for the scoring actually passed. */
 typedef enum { IVFPQ_SCAN_AUTO = 0, IVFPQ_SCAN_QUERY_MAJOR = 1, IVFPQ_SCAN_LIST_MAJOR = 2 } ivfpq_scan_strategy;
@@ -245,8 +247,8 @@ typedef struct {
 size_t ivfpq_search_workspace_bytes_ex(const ivfpq_index *index, int64_t Q, int32_t nprobe, int32_t k,
                                        const ivfpq_scoring *scoring);
 
-/* The strategy such a call will run with: IVFPQ_SCAN_QUERY_MAJOR or IVFPQ_SCAN_LIST_MAJOR
- * (scoring NULL: AUTO, distance scoring); a negative ivfpq_status on invalid arguments. */
+/* The strategy such a call will run with, given the workspace that ivfpq_search_workspace_bytes_ex asks
+ * for: IVFPQ_SCAN_QUERY_MAJOR or IVFPQ_SCAN_LIST_MAJOR (scoring NULL: AUTO, distance scoring); a negative ivfpq_status on invalid arguments. */
 int ivfpq_resolve_strategy(const ivfpq_index *index, int64_t Q, int32_t nprobe, int32_t k,
                            const ivfpq_scoring *scoring);
 

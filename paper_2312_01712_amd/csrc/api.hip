@@ -196,6 +196,16 @@ static int check_workspace(const Workspace &w, const void *ws, size_t bytes, con
   return IVFPQ_OK;
 }
 
+// Queries that go through the list-major scan together.  Where AUTO takes it on long lists, calls that the query-major
+// scan serves with a few KiB of workspace a query, the candidates' slots (up to 128 KiB a query) take 1 GiB at most, or
+// what 4096 queries want of them; larger batches go through them in pieces.  Anywhere else all queries of the call.
+static int64_t lm_together(const ivfpq_index *ix, int64_t Q, int32_t nprobe, int32_t requested) {
+  if (requested == IVFPQ_SCAN_LIST_MAJOR || ix->N <= (int64_t)4096 * ix->nlist) return Q;
+  int64_t fit = ((int64_t)1 << 30) / ((int64_t)plan_list_major(ix, 1, nprobe).cap * 8) & ~(int64_t)63;
+  if (fit < 4096) fit = 4096;
+  return Q < fit ? Q : fit;
+}
+
 // Which way stages 2-4 run.  A request for the list-major scan is honoured where that scan is
 // built (L2, k <= 128, the specialised shapes), anything else runs query-major.  Left to the
 // library (AUTO), the list-major scan serves batches with enough (query, list) pairs to group,
@@ -221,9 +231,10 @@ static bool use_list_major(const ivfpq_index *ix, int64_t Q, int32_t nprobe, int
   //   5000, 48 subspaces without structure
   //                             2210 / 883  4209 / 1281  7886 / 1905  15441 / 3312  30708 / 6035
   // The line is where clustered data gains; two queries a list at least.  (100M points in 16 384 lists, fewer than one
-  // query a list, the nearest ones eight times the mean: query-major.)
-  return mode == IVFPQ_SCORE_DISTANCE && ix->N <= (int64_t)16384 * ix->nlist && Q >= (int64_t)2 * ix->nlist &&
-         (double)Q * (double)ix->N / ix->nlist >= 1.6e7 && ix->max_list_len < (1 << 20);
+  // query a list, the nearest ones eight times the mean: query-major.)  What counts are the queries that go together.
+  const int64_t together = lm_together(ix, Q, nprobe, requested);
+  return mode == IVFPQ_SCORE_DISTANCE && ix->N <= (int64_t)16384 * ix->nlist && together >= (int64_t)2 * ix->nlist &&
+         (double)together * (double)ix->N / ix->nlist >= 1.6e7 && ix->max_list_len < (1 << 20);
 }
 
 }  // namespace ivfpq
@@ -579,7 +590,7 @@ size_t ivfpq_search_workspace_bytes_ex(const ivfpq_index *ix, int64_t Q, int32_t
   const Workspace w = plan_workspace(ix, Q, nprobe, k);
   size_t n = w.total;
   if (use_list_major(ix, Q, nprobe, k, sc ? sc->mode : IVFPQ_SCORE_DISTANCE, sc ? sc->strategy : IVFPQ_SCAN_AUTO))
-    n = align256(w.total) + plan_list_major(ix, Q, nprobe).total;
+    n = align256(w.total) + plan_list_major(ix, lm_together(ix, Q, nprobe, sc ? sc->strategy : IVFPQ_SCAN_AUTO), nprobe).total;
   else if (const size_t wide = plan_wide(ix, Q, nprobe, k, sc ? sc->mode : IVFPQ_SCORE_DISTANCE, sc ? sc->strategy : IVFPQ_SCAN_AUTO).total)
     n = align256(w.total) + wide;
   return n < 256 ? 256 : n;
@@ -670,22 +681,29 @@ static bool goes_list_major(const ivfpq_index *ix, int64_t Q, int32_t nprobe, in
                             const Workspace &w, size_t ws_bytes) {
   if (!use_list_major(ix, Q, nprobe, k, mode, strategy)) return false;
   if (strategy == IVFPQ_SCAN_LIST_MAJOR || ix->N <= (int64_t)4096 * ix->nlist) return true;
-  return ws_bytes >= align256(w.total) + plan_list_major(ix, Q, nprobe).total;
+  return ws_bytes >= align256(w.total) + plan_list_major(ix, lm_together(ix, Q, nprobe, strategy), nprobe).total;
 }
 
 // Stages 2-4 list-major: the usual workspace, then the list-major part behind it.
 static int scan_list_major(const ivfpq_index *ix, const float *d_queries, int64_t Q, int32_t nprobe,
                            const int32_t *d_probe_ids, int32_t k, const RadiiSq &r2, int32_t mode, const float *qr,
                            int64_t *d_out_ids, float *d_out_dist, const Workspace &w, void *ws, size_t ws_bytes,
-                           hipStream_t s, const char *fn) {
-  const LmWorkspace lw = plan_list_major(ix, Q, nprobe);
+                           hipStream_t s, int32_t strategy, const char *fn) {
+  const int64_t step = lm_together(ix, Q, nprobe, strategy);
+  const LmWorkspace lw = plan_list_major(ix, step, nprobe);
   Workspace both = w;
   both.total = align256(w.total) + lw.total;
   if (int rc = check_workspace(both, ws, ws_bytes, fn)) return rc;
   char *base = static_cast<char *>(ws);
-  return launch_scan_list_major(ix, d_queries, Q, nprobe, d_probe_ids, k, r2, mode, qr,
-                                reinterpret_cast<float *>(base + w.probe_dist), d_out_ids, d_out_dist, lw,
-                                base + align256(w.total), s);
+  float *probe_lb = reinterpret_cast<float *>(base + w.probe_dist);
+  for (int64_t q0 = 0; q0 < Q; q0 += step) {
+    const int64_t n = Q - q0 < step ? Q - q0 : step;
+    if (int rc = launch_scan_list_major(ix, d_queries + q0 * ix->D, n, nprobe, d_probe_ids + q0 * nprobe, k, r2, mode,
+                                        qr ? qr + q0 * ix->M : nullptr, probe_lb + q0 * nprobe, d_out_ids + q0 * k,
+                                        d_out_dist + q0 * k, lw, base + align256(w.total), s))
+      return rc;
+  }
+  return IVFPQ_OK;
 }
 
 int ivfpq_build_lut_ex(const ivfpq_index *ix, const float *d_queries, int64_t Q, int32_t nprobe,
@@ -728,7 +746,7 @@ int ivfpq_scan_topk_ex(const ivfpq_index *ix, const float *d_queries, int64_t Q,
   char *base = static_cast<char *>(ws);
   if (goes_list_major(ix, Q, nprobe, k, mode, strategy, w, ws_bytes))
     return scan_list_major(ix, d_queries, Q, nprobe, d_probe_ids, k, r2, mode, qr, d_out_ids, d_out_dist, w, ws,
-                           ws_bytes, static_cast<hipStream_t>(stream), fn);
+                           ws_bytes, static_cast<hipStream_t>(stream), strategy, fn);
   if ((rc = check_workspace(w, ws, ws_bytes, fn))) return rc;
   return scan_query_major(ix, d_queries, Q, nprobe, d_probe_ids, k, r2, mode, qr, d_out_ids, d_out_dist, w, base,
                           ws_bytes, static_cast<hipStream_t>(stream), strategy);
@@ -829,7 +847,7 @@ int ivfpq_search_ex(const ivfpq_index *ix, const float *d_queries, int64_t Q, in
   const Workspace w = plan_workspace(ix, Q, nprobe, k);
   if (goes_list_major(ix, Q, nprobe, k, mode, strategy, w, ws_bytes)) {
     Workspace both = w;
-    both.total = align256(w.total) + plan_list_major(ix, Q, nprobe).total;
+    both.total = align256(w.total) + plan_list_major(ix, lm_together(ix, Q, nprobe, strategy), nprobe).total;
     if ((rc = check_workspace(both, ws, ws_bytes, fn))) return rc;   // before anything is enqueued
     char *base = static_cast<char *>(ws);
     int32_t *probe_ids = reinterpret_cast<int32_t *>(base + w.probe_ids);
@@ -838,7 +856,7 @@ int ivfpq_search_ex(const ivfpq_index *ix, const float *d_queries, int64_t Q, in
                        static_cast<hipStream_t>(stream));
     if (rc) return rc;
     return scan_list_major(ix, d_queries, Q, nprobe, probe_ids, k, r2, mode, qr, d_out_ids, d_out_dist, w, ws,
-                           ws_bytes, static_cast<hipStream_t>(stream), fn);
+                           ws_bytes, static_cast<hipStream_t>(stream), strategy, fn);
   }
   if ((rc = check_workspace(w, ws, ws_bytes, fn))) return rc;
   return search_in_workspace(ix, d_queries, Q, nprobe, k, r2, mode, qr, d_out_ids, d_out_dist, w,

@@ -393,3 +393,40 @@ def test_long_lists_with_entries_that_are_nan(D, M):
             ref = (ref[0].cpu().numpy(), ref[1].cpu().numpy())
             _same(gi.search(dq, nprobe, k, radii, strategy=b.SCAN_LIST_MAJOR), ref, (D, M, radius, k))
     gi.close()
+
+
+def test_large_batches_on_long_lists_go_in_pieces():
+    """AUTO on long lists: the workspace's candidate slots do not grow with the batch beyond 1 GiB (or 4096 queries), and
+    batches beyond that return what the query-major scan does: two pieces, the last one short, shared and per-query
+    radii, search and scan_topk."""
+    b = _binding()
+    rng = np.random.default_rng(11)
+    D, M, nprobe, k, distinct, reps = 64, 16, 6, 10, 60, 75
+    sizes = np.array([9100, 0, 8300, 90, 12_000, 1, 8800, 9900])
+    idx = _index(rng, D, M, sizes, centre=0.2)
+    q = (idx.centroids[rng.integers(0, len(sizes), distinct)] + 0.25 * rng.normal(size=(distinct, D))).astype(np.float32)
+    radii = np.full(M, 1.2, dtype=np.float32)
+    per_query = rng.uniform(0.6, 1.8, size=(distinct, M)).astype(np.float32)
+    gi = b.IvfPqIndex.from_index(idx)
+
+    def slots(Q, nprobe):
+        return gi.workspace_bytes(Q, nprobe, k) - gi.workspace_bytes(Q, nprobe, k, strategy=b.SCAN_QUERY_MAJOR)
+
+    try:
+        for Q in (8192, 100_000, 1_000_000):
+            assert gi.resolve_strategy(Q, nprobe, k) == b.SCAN_LIST_MAJOR
+            assert slots(Q, nprobe) < (1 << 30) + (16 << 20), Q
+        b.set_option("lm_cap", 65536)   # 4096 queries a piece
+        assert slots(1_000_000, nprobe) == slots(distinct * reps, nprobe) == slots(4096, nprobe) > slots(4000, nprobe)
+        assert gi.resolve_strategy(distinct * reps, nprobe, k) == b.SCAN_LIST_MAJOR
+        dq = torch.from_numpy(q).cuda().repeat(reps, 1)
+        for own in (None, per_query):
+            want = oracle.search(q, idx, nprobe, k, radii if own is None else own, threads=8)
+            want = (np.tile(want[0], (reps, 1)), np.tile(want[1], (reps, 1)))
+            rq = None if own is None else torch.from_numpy(own).cuda().repeat(reps, 1)
+            shared = radii if own is None else None
+            _same(gi.search(dq, nprobe, k, shared, query_radii=rq), want, "search")
+            _same(gi.scan_topk(dq, gi.coarse(dq, nprobe)[0], k, shared, query_radii=rq), want, "scan_topk")
+    finally:
+        b.set_option("lm_cap", 0)
+        gi.close()

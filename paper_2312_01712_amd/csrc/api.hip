@@ -105,12 +105,34 @@ WideWorkspace plan_wide(const ivfpq_index *ix, int64_t Q, int32_t k, int32_t mod
 
 // Lists of the list-major wide selection's first stage: as many as hold 2 k points on average.  0 where it does not
 // serve: shapes without list-major kernels, few pairs or long lists (the lines of the list-major scan), slots that
-// do not hold twice the first lists (those near a query are longer than the mean) or so few that the stages crawl.
+// do not hold twice the first lists (those near a query are longer than the mean) or so few that the stages crawl,
+// and batches too small for the stages' twenty launches against clustered data, whose k neighbours the query-major scan
+// finds in a part of the nearest list.  us of a search, query-major / in stages, clustered data and data without structure:
+//   points a list, k, queries     48 subspaces                  64 subspaces                  16 subspaces
+//   977    129     512            97 / 135,   339 / 247         92 / 124,   391 / 258         75 / 124,   274 / 204
+//          129    1024           135 / 148,   586 / 326        143 / 142,   672 / 347         99 / 140,   337 / 259
+//          129    2048           222 / 187,  1102 / 493        228 / 188,  1283 / 542        165 / 180,   618 / 379
+//          129    8192           707 / 498,  4128 / 1511       739 / 518,  4785 / 1727       520 / 471,  2138 / 1118
+//          300     512           140 / 151,   371 / 273        106 / 130,   393 / 278         83 / 131,   300 / 233
+//          300    1024           193 / 170,   655 / 357        159 / 149,   715 / 371        111 / 150,   381 / 294
+//         1000     512           496 / 336,   527 / 382        555 / 370,   575 / 388        402 / 285,   451 / 339
+//   3906   129    2048           283 / 309,  2620 / 788        303 / 336,  3348 / 938        215 / 254,  1138 / 515
+//          129    4096           512 / 534,  5115 / 1442       560 / 596,  6496 / 1743       367 / 438,  2137 / 955
+//          300    2048           325 / 342,  2677 / 824        340 / 352,  3407 / 951        252 / 270,  1232 / 552
+//         1000     512           201 / 245,   845 / 465        193 / 213,  1016 / 489        177 / 192,   543 / 376
+//         1000    2048           512 / 441,  2940 / 1020       507 / 436,  3500 / 1116       452 / 350,  1765 / 742
+//   244    129     512           765 / 155,   855 / 270        798 / 148,   946 / 287        214 / 138,   251 / 239
+//          300    8192          1145 / 1101                   1234 / 1224                    833 / 976,  4364 / -
+// (32 probes.)  The line is where clustered data pays a tenth at most; without structure the stages take a half to a quarter.
 static int32_t wide_first(const ivfpq_index *ix, const WideWorkspace &w, int32_t nprobe, int32_t k, int32_t strategy) {
   const int64_t Q = w.q_chunk;
   if (strategy == IVFPQ_SCAN_QUERY_MAJOR || !list_major_shape(ix)) return 0;
   if (Q * (int64_t)nprobe < 16384 || ix->N > (int64_t)4096 * ix->nlist || ix->N < (int64_t)ix->nlist * 128) return 0;
   if (ix->max_list_len >= (1 << 20) || Q * (int64_t)nprobe > 0x3FFFFFFFll) return 0;
+  const bool few = 2 * (int64_t)k * ix->nlist < ix->N;   // neighbours against the points of a list
+  const double share = (double)Q * k * ix->nlist / (double)ix->N;
+  if (share < (few && ix->M > 16 ? 128.0 : 240.0)) return 0;
+  if (few && (Q < (ix->M > 16 ? 1024 : 2048) || (ix->M == 16 && 8 * (int64_t)k * ix->nlist < ix->N))) return 0;
   const int64_t first = (2 * (int64_t)k * ix->nlist + ix->N - 1) / ix->N;
   if (first * 2 > nprobe || first * 2 * ix->N > (int64_t)w.cap * ix->nlist) return 0;
   int stages = 1;

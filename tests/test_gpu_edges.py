@@ -395,6 +395,31 @@ def test_long_lists_with_entries_that_are_nan(D, M):
     gi.close()
 
 
+@pytest.mark.parametrize("D,M", [(96, 48), (128, 64), (64, 16)])
+def test_which_batches_are_selected_list_major_above_128_neighbours(D, M):
+    """The stages' tables are asked for where the batch is large against the share of a list that k is, and not for small
+    batches of few neighbours, which the query-major scan serves in fewer launches; both return the same."""
+    b = _binding()
+    rng = np.random.default_rng(M)
+    nlist, nprobe, distinct = 60, 32, 64
+    idx = _index(rng, D, M, rng.integers(900, 1050, size=nlist), centre=0.3)
+    gi = b.IvfPqIndex.from_index(idx)
+
+    def staged(Q, k):
+        return gi.workspace_bytes(Q, nprobe, k) > gi.workspace_bytes(Q, nprobe, k, strategy=b.SCAN_QUERY_MAJOR)
+
+    assert not staged(512, 129) and not staged(512, 300)
+    assert staged(512, 1000) and staged(8192, 129) and staged(8192, 300)
+    assert staged(1200, 129) == (M > 16)
+    q = (idx.centroids[rng.integers(0, nlist, distinct)] + 0.25 * rng.normal(size=(distinct, D))).astype(np.float32)
+    radii = np.full(M, 0.6 * np.sqrt(D / M), dtype=np.float32)
+    dq = torch.from_numpy(q).cuda()
+    for k, reps in ((129, 8), (600, 8), (300, 35)):
+        want = oracle.search(q, idx, nprobe, k, radii, threads=8)
+        _same(gi.search(dq.repeat(reps, 1), nprobe, k, radii), (np.tile(want[0], (reps, 1)), np.tile(want[1], (reps, 1))), (D, M, k, reps))
+    gi.close()
+
+
 def test_large_batches_on_long_lists_go_in_pieces():
     """AUTO on long lists: the workspace's candidate slots do not grow with the batch beyond 1 GiB (or 4096 queries), and
     batches beyond that return what the query-major scan does: two pieces, the last one short, shared and per-query

@@ -595,17 +595,19 @@ __global__ __launch_bounds__(256) void probe_bound_kernel(const float *__restric
 // A query whose slots overflowed, or that has more than WIDE_SORT keys within the bound
 // (long runs of equal distances), gets map[q] = 0 and is served pass by pass afterwards;
 // every other query gets map[q] = -1.
-// Where more than WIDE_EXTRA keys beyond k lie within the bound, the k-th key is looked for first, in a histogram
-// of the keys' range, and only what lies up to its bin is sorted: fewer keys than the next power of two, and the
-// slots may hold any number (a list-major pass over the later lists leaves thousands).
+// Where more keys lie within the bound than k pads to for the sort, the k-th key is looked for first, in a histogram
+// of the keys' range, and only what lies up to its bin is sorted: the slots may hold any number (a list-major pass over
+// the later lists leaves thousands).  (With the histogram from WIDE_EXTRA keys beyond k on, 8192 queries of 32 probes,
+// lists of 3906, us before it / with / so: k = 300, 16 subspaces 833 / 864 / 851, k = 1000 1567 / 1338 / 1330, k = 129, 64
+// subspaces 1097 / 1137 / 1117.)
 // only: the other queries' entries of it are negative, or NULL (it may be map itself).
 constexpr int WIDE_SORT = 2048;
-constexpr int WIDE_EXTRA = 24;   // at most: k = 1000 is sorted among 1024
+constexpr int WIDE_EXTRA = 24;   // keys beyond k: k = 1000 is sorted among 1024
 constexpr int WIDE_BINS = 2048;
 
-// The bound, tightened to the end of the bin that holds the k-th key where more than WIDE_EXTRA keys beyond k lie
+// The bound, tightened to the end of the bin that holds the k-th key where more than `few` (at least k) keys lie
 // within it.  256 threads; bins: WIDE_BINS words.  Begins and ends with a barrier.
-__device__ inline uint32_t wide_cut(const uint32_t *d, int n, uint32_t bound, int k, uint32_t *bins, uint32_t *part, int tid) {
+__device__ inline uint32_t wide_cut(const uint32_t *d, int n, uint32_t bound, int k, int few, uint32_t *bins, uint32_t *part, int tid) {
   __shared__ uint32_t cnt, lo, hi, cut;
   __syncthreads();
   if (tid == 0) {
@@ -640,7 +642,7 @@ __device__ inline uint32_t wide_cut(const uint32_t *d, int n, uint32_t bound, in
     }
   }
   __syncthreads();
-  if (cnt <= (uint32_t)(k + WIDE_EXTRA)) return cnt >= (uint32_t)k && hi < bound ? hi : bound;   // (cnt and hi are written no more)
+  if (cnt <= (uint32_t)few) return cnt >= (uint32_t)k && hi < bound ? hi : bound;   // (cnt and hi are written no more)
   const uint32_t first = lo;
   const int width = 32 - __clz((int)((hi - first) | 1u));   // bits of the range
   const int shift = width > 11 ? width - 11 : 0;            // 2^11 bins
@@ -685,7 +687,7 @@ __global__ __launch_bounds__(256) void wide_tighten_kernel(uint32_t *wd, int64_t
   if (n < k) return;   // a bound takes k keys (-1: the query's slots did not suffice)
   uint32_t *d = wd + q * cap;
   int64_t *id = wid + q * cap;
-  const uint32_t bound = wide_cut(d, n, wbound[q], k, bins, part, tid);
+  const uint32_t bound = wide_cut(d, n, wbound[q], k, k + WIDE_EXTRA, bins, part, tid);
   int out = 0;
   for (int base = 0; base < n; base += 256) {
     const int i = base + tid;
@@ -735,7 +737,9 @@ __global__ __launch_bounds__(256) void wide_select_kernel(const uint32_t *__rest
   }
   const uint32_t *d = wd + q * cap;
   const int64_t *id = wid + q * cap;
-  const uint32_t bound = wide_cut(d, n, wbound[q], k, sd, reinterpret_cast<uint32_t *>(sid), tid);
+  int few = 256;   // sorted as they are: what k keys pad to
+  while (few < k + WIDE_EXTRA) few <<= 1;
+  const uint32_t bound = wide_cut(d, n, wbound[q], k, few, sd, reinterpret_cast<uint32_t *>(sid), tid);
   if (tid == 0) cnt = 0u;
   __syncthreads();
   for (int i = tid; i < n; i += 256) {

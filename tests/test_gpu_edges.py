@@ -219,9 +219,9 @@ def test_row_proposals_that_are_not_accepted(name, metric):
 @pytest.mark.parametrize("k,cap,radius", [(129, 8192, 0.6), (500, 8192, 0.6), (1000, 8192, 0.6), (700, 1024, 0.6), (300, 2048, np.inf)])
 def test_more_than_128_neighbours_of_large_batches(D, M, k, cap, radius):
     """k above 128 in batches whose later probes are scanned list-major behind the first few: queries that one list
-    answers, queries between the lists (slots and queues that overflow: with 1024 slots most of them, redone by the
-    plain wide selection and then pass by pass), many equal distances, empty lists, probes that hold fewer than k
-    points at first, shared and per-query radii, and the query-major scan of the same call."""
+    answers, queries between the lists, many equal distances, empty lists, probes that hold fewer than k
+    points at first, shared and per-query radii, and the query-major scan of the same call.  (1024 slots do not hold
+    twice the first lists of k = 700: query-major throughout, with slots that overflow.)"""
     b = _binding()
     rng = np.random.default_rng(M + k)
     nlist, nprobe, distinct, reps = 60, 40, 100, 5
@@ -454,4 +454,64 @@ def test_large_batches_on_long_lists_go_in_pieces():
             _same(gi.scan_topk(dq, gi.coarse(dq, nprobe)[0], k, shared, query_radii=rq), want, "scan_topk")
     finally:
         b.set_option("lm_cap", 0)
+        gi.close()
+
+
+@pytest.mark.parametrize("D,M", [(96, 48), (128, 64), (64, 16)])
+@pytest.mark.parametrize("radius", [0.6, np.inf])
+def test_first_lists_that_the_wide_slots_do_not_hold(D, M, radius):
+    """k above 128 selected list-major in stages where some queries' first lists are several times the mean and alone hold
+    more points than a query has slots (those queries start over query-major), beside queries whose first lists fit."""
+    b = _binding()
+    rng = np.random.default_rng(M)
+    nlist, nprobe, distinct, reps, k, cap, first = 60, 40, 96, 6, 300, 2048, 3
+    sizes = rng.integers(100, 300, size=nlist)
+    sizes[:6] = rng.integers(950, 1250, size=6)
+    idx = _index(rng, D, M, sizes, centre=0.3)
+    near = np.float32(0.05) * rng.normal(size=(6, D)).astype(np.float32)
+    idx.centroids[:6] = idx.centroids[0] + near        # the long lists lie together
+    assert -(-2 * k * nlist // int(sizes.sum())) == first and first * 2 * sizes.sum() <= cap * nlist
+    q = (idx.centroids[rng.integers(0, nlist, distinct)] + 0.25 * rng.normal(size=(distinct, D))).astype(np.float32)
+    q[::3] = idx.centroids[0] + np.float32(0.1) * rng.normal(size=(len(q[::3]), D)).astype(np.float32)
+    radii = np.full(M, radius * np.sqrt(D / M), dtype=np.float32)
+    gi = b.IvfPqIndex.from_index(idx)
+    dq = torch.from_numpy(q).cuda()
+    try:
+        b.set_option("wide_cap", cap)
+        seeds = sizes[gi.coarse(dq, nprobe)[0].cpu().numpy()[:, :first]].sum(1)
+        assert np.any(seeds > cap) and np.any(seeds <= cap)
+        dq = dq.repeat(reps, 1)
+        assert gi.workspace_bytes(len(dq), nprobe, k) > gi.workspace_bytes(len(dq), nprobe, k, strategy=b.SCAN_QUERY_MAJOR)
+        want = oracle.search(q, idx, nprobe, k, radii, threads=8)
+        _same(gi.search(dq, nprobe, k, radii), (np.tile(want[0], (reps, 1)), np.tile(want[1], (reps, 1))), (D, M, radius))
+    finally:
+        b.set_option("wide_cap", 8192)
+        gi.close()
+
+
+@pytest.mark.parametrize("D,M", [(96, 48), (64, 16)])
+def test_stages_above_128_neighbours_in_two_chunks(D, M):
+    """So many slots a query that the batch goes through them in two chunks, the second one short: counters and tables of
+    the stages serve both, with shared and with per-query radii."""
+    b = _binding()
+    rng = np.random.default_rng(M + 1)
+    nlist, nprobe, distinct, reps, k = 60, 32, 60, 25, 300
+    idx = _index(rng, D, M, rng.integers(150, 400, size=nlist), centre=0.15)
+    q = (idx.centroids[rng.integers(0, nlist, distinct)] + 0.25 * rng.normal(size=(distinct, D))).astype(np.float32)
+    radii = np.full(M, 0.6 * np.sqrt(D / M), dtype=np.float32)
+    per_query = (rng.uniform(0.3, 0.9, size=(distinct, M)) * np.sqrt(D / M)).astype(np.float32)
+    gi = b.IvfPqIndex.from_index(idx)
+    dq = torch.from_numpy(q).cuda().repeat(reps, 1)
+    try:
+        b.set_option("wide_cap", 65536)
+        chunk = (1 << 30) // (65536 * 12)
+        assert chunk < len(dq) < 2 * chunk
+        assert gi.workspace_bytes(len(dq), nprobe, k) > gi.workspace_bytes(len(dq), nprobe, k, strategy=b.SCAN_QUERY_MAJOR)
+        for own in (None, per_query):
+            want = oracle.search(q, idx, nprobe, k, radii if own is None else own, threads=8)
+            rq = None if own is None else torch.from_numpy(own).cuda().repeat(reps, 1)
+            _same(gi.search(dq, nprobe, k, radii if own is None else None, query_radii=rq),
+                  (np.tile(want[0], (reps, 1)), np.tile(want[1], (reps, 1))), (D, M, own is not None))
+    finally:
+        b.set_option("wide_cap", 8192)
         gi.close()

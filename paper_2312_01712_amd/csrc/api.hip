@@ -252,7 +252,22 @@ static bool use_list_major(const ivfpq_index *ix, int64_t Q, int32_t nprobe, int
   //                             1301 / 858  2509 / 1425  5184 / 2370   9609 / 4285  18753 / 8297
   //   5000, 48 subspaces without structure
   //                             2210 / 883  4209 / 1281  7886 / 1905  15441 / 3312  30708 / 6035
-  // The line is where clustered data gains; two queries a list at least.  (100M points in 16 384 lists, fewer than one
+  // and by shape and by the share of the entries that the radii hold, lists of 7812, k = 100 (another index: 512 lists):
+  //   queries                                       2048              4096              8192
+  //   64 subspaces, clustered, 0.25            381 / 415         721 / 581        1437 / 978
+  //   64, clustered, 0.9                       382 / 578         724 / 814        1439 / 1343
+  //   48, clustered, 0.25                      330 / 336         627 / 497        1220 / 772
+  //   48, clustered, 0.9                       330 / 495         625 / 672        1220 / 1000
+  //   16, clustered, 0.25                      245 / 370         448 / 505         856 / 774
+  //   16, clustered, 0.9                       245 / 357         448 / 501         856 / 763
+  //   16, components that touch, 0.25         3441 / 884        6421 / 1562      12199 / 2937
+  //   64, without structure, 0.25            11512 / 2223      22336 / 4117      44167 / 7953
+  //   48, without structure, 0.25             9529 / 1877      18205 / 3384      35900 / 6408
+  //   16, without structure, 0.25             3472 / 1001       6726 / 1700      13090 / 3098
+  // The line is where clustered data whose radii hold a part of the entries breaks even with 48 and 64 subspaces; with 16,
+  // and with radii that hold nearly everything, such data pays up to half there and gains from 8192 queries on, and any
+  // other data takes a third to a fifth of the time all the way (which a caller knows, and can ask for either way).
+  // Two queries a list at least.  (100M points in 16 384 lists, fewer than one
   // query a list, the nearest ones eight times the mean: query-major.)  What counts are the queries that go together.
   const int64_t together = lm_together(ix, Q, nprobe, requested);
   return mode == IVFPQ_SCORE_DISTANCE && ix->N <= (int64_t)16384 * ix->nlist && together >= (int64_t)2 * ix->nlist &&

@@ -15,18 +15,22 @@
 //
 // A query's lists are now scanned by different workgroups at different times, so the running
 // k-th distance is not at hand.  Instead:
-//   A  the query-major kernel scans the first few probed lists of every query (the nearest
-//      ones) and leaves each query's top-k of those; tau_q = its k-th distance bounds the
-//      final k-th distance from above;
+//   A  the nearest list of every query (with hit counts, or several first lists, the first few) is
+//      ranked first and leaves each query's top-k of it; tau_q = its k-th distance bounds the
+//      final k-th distance from above.  Three ways: list-major with fp32 tables (the head pass:
+//      lm_scan_kernel<HEAD>), on long lists with byte tables (lm_byte_kernel<HEAD>, whose candidates
+//      lm_settle_kernel ranks; some queries only get a bound from it), else the query-major kernel;
 //   B  (query, list) pairs of the remaining probes whose list-level lower bound exceeds tau_q
 //      are dropped; the others are bucketed by list (count, offsets, fill);
-//   C  the list-major scan appends every point with distance <= tau_q to the query's
-//      candidate buffer (a few hundred per query: anything above tau_q cannot be in the
-//      result);
-//   D  one wavefront per query merges its buffer into the top-k of phase A by (distance, id);
-//      behind byte tables (lm_byte_kernel) it forms the candidates' distances first.
-// A query whose buffer overflows is redone by the query-major kernel, so the result is
-// always that of the plain loop.
+//   C  the list-major scan appends to the query's candidate buffer what may lie within tau_q (anything
+//      above cannot be in the result): from fp32 tables every point with distance <= tau_q as (distance,
+//      row), with hit counts from byte tables every point with score <= tau_q likewise; from byte tables
+//      of distances every point whose byte sum is within the query's limit, as (list, row);
+//   D  one wavefront per query merges its buffer into the top-k of phase A by (distance, id):
+//      lm_merge_kernel, or, behind byte tables of distances, lm_sort_out_kernel and lm_settle_kernel,
+//      which form the candidates' distances first.
+// B to D run twice where a query has many probes.  A query whose buffer overflows is redone by the
+// query-major kernel, so the result is always that of the plain loop.
 
 #include "scan_device.h"
 
@@ -109,8 +113,8 @@ __global__ __launch_bounds__(256) void lm_pairs_kernel(LmArgs a, int fill, int h
   if (head) a.gcnt[q] = 0u;
   if (!head && p == a.p0) a.gcnt[q] = a.wide_n && a.wide_n[q] > 0 ? (uint32_t)a.wide_n[q] : 0u;
   bool take = true;
-  // a query the head pass left out has no bound yet: it takes no part here and is redone
-  // query-major over all of its lists (lm_merge_kernel puts it on that list)
+  // a query the head pass left out has no bound yet: it takes no part here and is redone query-major
+  // over all of its lists (lm_sort_out_kernel or, where that does not run, lm_merge_kernel names it)
   if (!head && a.head_done && a.qmap_head[q] >= 0) take = false;
   if (!head && a.later && a.qmap[q] >= 0) take = false;   // nor does one whose slots have overflowed
   if (!head && a.seeded && p == 0 && a.qmap_head[q] != LM_SEEDED) take = false;   // the head pass has ranked this list
@@ -745,6 +749,8 @@ __device__ __attribute__((noinline)) void lmb_spill(uint32_t *gcnt, uint2 *cand,
   if (over && slot < cap) cand[(int64_t)sq[g] * cap + slot] = make_uint2(x, row);
 }
 
+__device__ __forceinline__ uint32_t pick(uint32_t c, uint32_t a, uint32_t b) { return c ? a : b; }
+
 template <int J>
 __device__ __forceinline__ float xor_f32(float v) { return __uint_as_float(xor_u32<J, true>(__float_as_uint(v))); }
 
@@ -771,6 +777,7 @@ __device__ __forceinline__ float xor_f32(float v) { return __uint_as_float(xor_u
 // 8192 queries of 64 probes, k = 100, us with the fp32 head pass / with byte tables, every point the bytes cannot rule out offered /
 // so: 64 subspaces, clustered, lists of 3906, radii that hold 0.25 of the entries 1253 / 983 / 1011, 0.5 1081 / 1789 / 994, 0.9
 // 1076 / 4331 / 990; 16 subspaces, lists of 7812, infinite radii (query-major before) 889 / 3895 / 877.
+// (With 64 subspaces eight registers spill, all of them once a task and outside of the passes over the list.)
 template <int MT, int DSUB, int MODE, bool HEAD = false>
 __global__ __launch_bounds__(LMB_NW * 64) __attribute__((amdgpu_waves_per_eu(4))) void lm_byte_kernel(LmArgs a, RadiiSq r2) {
   constexpr int NW = LMB_NW;
@@ -1263,7 +1270,8 @@ __global__ __launch_bounds__(LMB_NW * 64) __attribute__((amdgpu_waves_per_eu(4))
           const uint32_t pos = first + (uint32_t)__popcll(bal & ((1ull << lane) - 1ull));
           word = ((uint32_t)i << 3) | g;
           if constexpr (MODE != 0) {   // the score travels with the point (at most 2 MT <= 128)
-            const uint32_t zz = (g & 4u) ? ((g & 1u) ? s[3] : s[2]) : ((g & 1u) ? s[1] : s[0]);
+            const uint32_t s0 = s[0], s1 = s[1], s2 = s[2], s3 = s[3];   // (picked by value: by place, every block's sums went to scratch memory)
+            const uint32_t lo = pick(g & 1u, s1, s0), hi = pick(g & 1u, s3, s2), zz = pick(g & 4u, hi, lo);
             word = ((uint32_t)i << 11) | (((g & 2u) ? zz >> 16 : zz & 0xFFFFu) << 3) | g;
           }
           if (pos < (uint32_t)LMB_QUEUE) queue[pos] = word;
@@ -1922,6 +1930,17 @@ int launch_scan_list_major(const ivfpq_index *ix, const float *d_queries, int64_
   //   64, clustered, 4000                     253 / 361    406 / 408    684 / 590   1248 / 881
   //   64, clustered, 7812                     590 / 706    943 / 810   1310 / 1052  2162 / 1570
   //   48, without structure, 3906            2558 / 1038  3141 / 1621  5021 / 2766  7402 / 5093
+  // and lists of 3636, the longest of 10 000, 64 probes, k = 100, the radii holding 0.25 / 0.9 of the entries (where they hold
+  // much, the pass only finds bounds and the nearest lists are scanned again):
+  //   queries                                  2200                       4096                       8192
+  //   64 subspaces, clustered       896 / 830,  408 / 672    1645 / 1222,  677 / 822    2744 / 2138, 1234 / 1169
+  //   48, clustered                1447 / 1018, 446 / 569    2072 / 1606,  724 / 728    3415 / 2857, 1143 / 1037
+  //   16, clustered                 321 / 361,  341 / 417     424 / 458,   478 / 536     688 / 712,   817 / 800
+  //   64, without structure        9121 / 2106, 7446 / 2184 16022 / 3507, 13098 / 3531 31495 / 6311, 25446 / 6448
+  //   48, without structure        3073 / 1720, 2933 / 1734  4200 / 2667, 4019 / 2680   6536 / 4800, 6286 / 4843
+  //   16, without structure        1690 / 984,  1599 / 982   2323 / 1477, 2196 / 1445   3617 / 2515, 3429 / 2485
+  // The line is where data without structure, and clustered data whose radii hold a part of the entries, gains; clustered
+  // data with wide radii pays for it in the smaller batches.
   const int64_t head_points = (int64_t)((double)Q * (double)ix->N / ix->nlist);
   const bool head_bytes = byte_head_lists(ix) && w.first == 1 && mode == IVFPQ_SCORE_DISTANCE && !(get_scan_ablate() & 8) &&
                           head_points >= 8000000;

@@ -27,8 +27,9 @@
 //      row), with hit counts from byte tables every point with score <= tau_q likewise; from byte tables
 //      of distances every point whose byte sum is within the query's limit, as (list, row);
 //   D  one wavefront per query merges its buffer into the top-k of phase A by (distance, id):
-//      lm_merge_kernel, or, behind byte tables of distances, lm_sort_out_kernel and lm_settle_kernel,
-//      which form the candidates' distances first.
+//      lm_merge_kernel, or, behind byte tables of distances, lm_settle_kernel, which forms the
+//      candidates' distances first (its wavefronts together; behind a head pass with byte tables and in the
+//      largest batches a wavefront by itself, the queries sorted out by lm_sort_out_kernel).
 // B to D run twice where a query has many probes.  A query whose buffer overflows is redone by the
 // query-major kernel, so the result is always that of the plain loop.
 
@@ -79,6 +80,7 @@ struct LmArgs {
   int32_t later;                // this is not the first main pass: qmap already names queries to be redone
   int32_t stage;                // which of the passes of a call with candidates to settle
   int32_t fresh;                // byte tables in the head pass: the queries have no result yet
+  int32_t list_redo;            // lm_settle_kernel in place: this is the last pass, queries to be redone are listed too
   int32_t seeded;               // behind that pass: qmap_head may be LM_SEEDED
   int32_t group;                // queries per group of the pass the pairs are bucketed for
   int32_t head_done;            // the head pass has run: queries it left out (qmap_head) have no first-list result yet
@@ -114,7 +116,7 @@ __global__ __launch_bounds__(256) void lm_pairs_kernel(LmArgs a, int fill, int h
   if (!head && p == a.p0) a.gcnt[q] = a.wide_n && a.wide_n[q] > 0 ? (uint32_t)a.wide_n[q] : 0u;
   bool take = true;
   // a query the head pass left out has no bound yet: it takes no part here and is redone query-major
-  // over all of its lists (lm_sort_out_kernel or, where that does not run, lm_merge_kernel names it)
+  // over all of its lists (lm_sort_out_kernel or, where that does not run, name_query names it)
   if (!head && a.head_done && a.qmap_head[q] >= 0) take = false;
   if (!head && a.later && a.qmap[q] >= 0) take = false;   // nor does one whose slots have overflowed
   if (!head && a.seeded && p == 0 && a.qmap_head[q] != LM_SEEDED) take = false;   // the head pass has ranked this list
@@ -1361,6 +1363,88 @@ __global__ __launch_bounds__(256) void lm_sort_out_kernel(LmArgs a, int list_red
   if (list_redo) put(named, a.cnt + a.nlist, a.redo);
 }
 
+// One wavefront per query: the candidates of the list-major scan are merged into the top-k of
+// the first lists by (distance, id).  Queries whose buffer overflowed are handed to the
+// query-major kernel through qmap.  What may enter is queued in LDS and folded in 64 at a time, the next 64 slots on
+// their way meanwhile (a sort and a fetch of ids for every 64 slots of which one may enter, each after its loads:
+// hit counts of 5000 queries, 1M x 96, both rounds: 227 us, 88 so).
+constexpr int LMQ_WORDS = 128;   // of a queue: fewer than 64 waiting and the 64 of a group
+
+// Names a query that is to be redone; whether it is.
+__device__ __forceinline__ bool name_query(const LmArgs &a, int64_t q, bool write) {
+  const bool overflow = a.gcnt[q] > (uint32_t)a.cap || (a.head_done && a.qmap_head[q] >= 0) || (a.later && a.qmap[q] >= 0);
+  if (write) a.qmap[q] = overflow ? (int32_t)q : -1;
+  return overflow;
+}
+
+__device__ __forceinline__ void merge_query(const LmArgs &a, int64_t q, int lane, LDS uint32_t *qd, LDS uint32_t *qrow) {
+  const uint32_t n = a.gcnt[q];
+  if (name_query(a, q, lane == 0) || n == 0) return;   // redone elsewhere / phase A's result stands
+  const int k = a.k;
+  Key L0, L1;
+  {
+    const int64_t o = q * k;
+    const bool in0 = lane < k, in1 = 64 + lane < k;
+    const int64_t id0 = in0 ? a.out_ids[o + lane] : -1, id1 = in1 ? a.out_ids[o + 64 + lane] : -1;
+    L0.d = id0 >= 0 ? __float_as_uint(a.out_dist[o + lane]) : SENT_D;
+    L0.id = id0 >= 0 ? id0 : SENT_ID;
+    L1.d = id1 >= 0 ? __float_as_uint(a.out_dist[o + 64 + lane]) : SENT_D;
+    L1.id = id1 >= 0 ? id1 : SENT_ID;
+  }
+  Key tau;
+  {
+    const Key t0 = bcast_key(L0, (k - 1) & 63), t1 = bcast_key(L1, (k - 1) & 63);
+    tau = (k - 1) < 64 ? t0 : t1;
+  }
+  const uint2 *slots = a.cand + q * a.cap;
+  auto slot_of = [&](uint32_t u) __attribute__((always_inline)) { return slots[u + lane < n ? u + lane : n - 1]; };
+  int waiting = 0;
+  uint2 e = slot_of(0);
+  for (uint32_t off = 0; off < n; off += 64) {
+    const uint2 next = slot_of(off + 64);
+    const bool in = off + lane < n && e.x <= tau.d;   // a larger distance fails whatever its id
+    const unsigned long long bal = __ballot(in);
+    if (in) {
+      const int pos = waiting + __popcll(bal & ((1ull << lane) - 1ull));
+      qd[pos] = e.x;
+      qrow[pos] = e.y;
+    }
+    waiting += __popcll(bal);
+    while (waiting >= 64 || (waiting > 0 && off + 64 >= n)) {   // the last 64, at the end all
+      const int m = waiting < 64 ? waiting : 64;
+      waiting -= m;
+      Key c;
+      c.d = SENT_D;
+      c.id = SENT_ID;
+      if (lane < m) {
+        c.d = qd[waiting + lane];
+        if (c.d <= tau.d) c.id = a.ids[qrow[waiting + lane]];
+      }
+      const bool pass = kless(c, tau);
+      if (__ballot(pass) == 0) continue;
+      if (!pass) {
+        c.d = SENT_D;
+        c.id = SENT_ID;
+      }
+      wave_sort_desc<true>(c, lane);
+      wave_merge<true>(L0, L1, c, lane);
+      const Key t0 = bcast_key(L0, (k - 1) & 63), t1 = bcast_key(L1, (k - 1) & 63);
+      tau = (k - 1) < 64 ? t0 : t1;
+    }
+    e = next;
+  }
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const Key e = h ? L1 : L0;
+    const int i = h * 64 + lane;
+    if (i < k) {
+      const bool real = e.d != SENT_D;
+      a.out_ids[q * k + i] = real ? e.id : -1;
+      a.out_dist[q * k + i] = real ? __uint_as_float(e.d) : __builtin_inff();
+    }
+  }
+}
+
 // ---- the candidates of the byte tables: distances in fp32, merged into the queries' results --------
 // One wavefront per query at a time, a lane per candidate: the entries come from the codebook, which the
 // workgroup keeps in its LDS (one workgroup of 16 wavefronts per CU; the queries that have candidates are taken up one by one), the
@@ -1373,28 +1457,67 @@ constexpr int LMS_NW = 16;
 // Slots a wavefront settles at a time for the wide selection, where a query's are independent.  1M x 128, 2000 queries
 // of 32 probes, k = 1000: 581 us with a query a wavefront, 224 so.
 constexpr int LMS_PIECE = 512;
-constexpr int LMS_QUEUE = 128;   // per wavefront: fewer than 64 waiting and the 64 of a group
+constexpr int LMS_QUEUE = LMQ_WORDS;
 constexpr size_t lms_lds(int mt, int dsub) { return (size_t)mt * 1024 * dsub + (size_t)LMS_NW * (LMS_QUEUE * 8 + mt * 4) + 16; }
 #define CONSTANT __attribute__((address_space(4)))
 
 // WIDE: behind the wide selection's first lists.  A candidate's distance and row take its slot; those beyond the bound
 // are left to wide_select_kernel, which picks the k nearest of a query's slots.
-template <int MT, int DSUB, bool WIDE>
+// PLACE: the wavefronts of a workgroup share its queries' slots piece by piece; a candidate's distance and row take its
+// slot, and when all are settled a wavefront each ranks the queries, as lm_merge_kernel does.  With a wavefront a query (MERGE)
+// few queries leave most wavefronts idle, and one that has many candidates keeps its workgroup waiting.  1M points, 32
+// probes, without structure, us of a search with every task settling its own candidates / MERGE / PLACE: 512 queries,
+// 16 subspaces, k = 10 129 / 166 / 122, k = 100 201 / 222 / 149, 48, k = 100 200 / 225 / 176; 2048, 16, k = 100 409 / 376 / 310;
+// 8192, 16, k = 100 1255 / 1026 / 959, 48 1695 / 1384 / 1325; clustered, 512 queries, 16, k = 10 69 / 73 / 68 (a launch less than MERGE).
+enum { LMS_MERGE, LMS_WIDE, LMS_PLACE };
+constexpr int LMS_SHARE = 128;   // slots of such a piece
+template <int MT, int DSUB, int HOW>
 __global__ __launch_bounds__(LMS_NW * 64) __attribute__((amdgpu_waves_per_eu(4))) void lm_settle_kernel(LmArgs a, RadiiSq r2) {
   constexpr int NCH = MT / 16;
+  constexpr bool WIDE = HOW == LMS_WIDE, PLACE = HOW == LMS_PLACE;
   extern __shared__ __align__(16) unsigned char smem[];
   LDS unsigned char *smem3 = (LDS unsigned char *)smem;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int32_t *active = (const int32_t *)a.pairs;   // queries with candidates, listed by lm_sort_out_kernel
   const int pieces = WIDE ? (a.cap + LMS_PIECE - 1) / LMS_PIECE : 1;   // of a query
-  const int nqueries = a.cnt[a.nlist + 2 + 2 * a.stage], nactive = nqueries * pieces, nwg = gridDim.x;
-  if ((int)blockIdx.x >= nactive) return;
+  const int nwg = gridDim.x;
+  LDS uint32_t *taken = (LDS uint32_t *)(smem3 + lms_lds(MT, DSUB) - 16);
+  int nqueries, nactive;
+  int32_t own = 0, upto = 0;   // PLACE, lane i: candidates of the workgroup's query i, pieces up to and with it
+  auto list_named = [&](bool named, int32_t q) __attribute__((always_inline)) {
+    const unsigned long long bal = __ballot(named);
+    if (!a.list_redo || bal == 0ull) return;
+    int first = 0;
+    if (lane == 0) first = atomicAdd(a.cnt + a.nlist, __popcll(bal));
+    first = __builtin_amdgcn_readfirstlane(first);
+    if (named) a.redo[first + __popcll(bal & ((1ull << lane) - 1ull))] = q;
+  };
+  const int32_t lane_q = (int32_t)blockIdx.x + lane * nwg;
+  if constexpr (PLACE) {   // the queries blockIdx.x, blockIdx.x + nwg, ..., at most 64
+    nqueries = ((int)a.Q - (int)blockIdx.x + nwg - 1) / nwg;
+    if (lane < nqueries) own = (int32_t)a.gcnt[lane_q];
+    if ((uint32_t)own > (uint32_t)a.cap) own = 0;   // (redone)
+    upto = (own + LMS_SHARE - 1) / LMS_SHARE;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+      const int32_t v = __shfl_up(upto, off);
+      if (lane >= off) upto += v;
+    }
+    nactive = __builtin_amdgcn_readlane(upto, 63);
+    if (nactive == 0) {
+      if (wave == 0) list_named(lane < nqueries && name_query(a, lane_q, true), lane_q);
+      return;
+    }
+  } else {
+    nqueries = a.cnt[a.nlist + 2 + 2 * a.stage];
+    nactive = nqueries * pieces;
+    if ((int)blockIdx.x >= nactive) return;
+  }
   for (int i = tid; i < MT * 256 * DSUB / 4; i += LMS_NW * 64)
     ((LDS floatx4 *)smem3)[i] = ((const floatx4 *)a.codebooks)[i];
   LDS uint32_t *qd = (LDS uint32_t *)(smem3 + (size_t)MT * 1024 * DSUB) + wave * LMS_QUEUE * 2, *qrow = qd + LMS_QUEUE;
   LDS float *sr2 = (LDS float *)(smem3 + (size_t)MT * 1024 * DSUB + (size_t)LMS_NW * LMS_QUEUE * 8) + wave * MT;   // r_m^2 of the wavefront's query
-  LDS uint32_t *taken = (LDS uint32_t *)(smem3 + lms_lds(MT, DSUB) - 16);
   if (tid == 0) *taken = 0u;
   __syncthreads();   // the last one: from here on every wavefront is by itself
   const int k = a.k;
@@ -1403,20 +1526,25 @@ __global__ __launch_bounds__(LMS_NW * 64) __attribute__((amdgpu_waves_per_eu(4))
   // others are taken up by whoever is free.  (All of them so, an atomic on one word of global memory for each: 454 us
   // instead of 322 for the two passes of 10 000 queries of the 1M x 96 configuration.)  The wide selection's
   // pieces are dealt out altogether, the first pieces of all queries first.
-  const int dealt = WIDE ? nactive : nactive - nactive / 4;
+  const int dealt = WIDE || PLACE ? nactive : nactive - nactive / 4;
   for (;;) {
     uint32_t turn = 0;
     if (lane == 0) turn = lds_add(taken);
-    int x = (int)blockIdx.x + nwg * __builtin_amdgcn_readfirstlane((int)turn);
+    int x = PLACE ? __builtin_amdgcn_readfirstlane((int)turn) : (int)blockIdx.x + nwg * __builtin_amdgcn_readfirstlane((int)turn);
     if (x >= dealt) {
-      if (WIDE) break;
+      if (WIDE || PLACE) break;
       int32_t next = 0;
       if (lane == 0) next = atomicAdd(ticket, 1);
       x = dealt + __builtin_amdgcn_readfirstlane(next);
       if (x >= nactive) break;
     }
-    const int64_t q = __builtin_amdgcn_readfirstlane(active[WIDE ? x % nqueries : x]);
-    int n = __builtin_amdgcn_readfirstlane((int)a.gcnt[q]), n0 = 0;   // 1 .. cap
+    const int i = PLACE ? __popcll(__ballot(upto <= x)) : WIDE ? x % nqueries : x;   // (pieces of the queries before it: at most x)
+    const int64_t q = PLACE ? (int)blockIdx.x + i * nwg : __builtin_amdgcn_readfirstlane(active[i]);
+    int n = PLACE ? __builtin_amdgcn_readlane(own, i) : __builtin_amdgcn_readfirstlane((int)a.gcnt[q]), n0 = 0;   // 1 .. cap
+    if constexpr (PLACE) {
+      n0 = (x - (i > 0 ? __builtin_amdgcn_readlane(upto, i - 1) : 0)) * LMS_SHARE;
+      n = n < n0 + LMS_SHARE ? n : n0 + LMS_SHARE;
+    }
     if constexpr (WIDE) {
       n0 = __builtin_amdgcn_readfirstlane(a.qmap[q]) + x / nqueries * LMS_PIECE;
       n = n < n0 + LMS_PIECE ? n : n0 + LMS_PIECE;
@@ -1425,7 +1553,7 @@ __global__ __launch_bounds__(LMS_NW * 64) __attribute__((amdgpu_waves_per_eu(4))
       uint2 *slots = a.cand + q * a.cap;
       Key L0, L1, tau;
       uint32_t bound = SENT_D;   // on the k-th distance, besides the list's
-      const bool none = a.fresh || (a.seeded && a.qmap_head[q] == LM_SEEDED);   // no result to merge into
+      const bool none = !PLACE && (a.fresh || (a.seeded && a.qmap_head[q] == LM_SEEDED));   // no result to merge into
       auto take_tau = [&]() __attribute__((always_inline)) {
         const Key t0 = bcast_key(L0, (k - 1) & 63), t1 = bcast_key(L1, (k - 1) & 63);
         tau = (k - 1) < 64 ? t0 : t1;
@@ -1434,7 +1562,7 @@ __global__ __launch_bounds__(LMS_NW * 64) __attribute__((amdgpu_waves_per_eu(4))
           tau.id = SENT_ID;
         }
       };
-      if constexpr (!WIDE) {
+      if constexpr (HOW == LMS_MERGE) {
         const int64_t o = q * k;
         const bool in0 = !none && lane < k, in1 = !none && 64 + lane < k;
         if (none && !a.fresh) bound = (uint32_t)__builtin_amdgcn_readfirstlane((int)__float_as_uint(a.out_dist[o + k - 1]));
@@ -1551,6 +1679,8 @@ __global__ __launch_bounds__(LMS_NW * 64) __attribute__((amdgpu_waves_per_eu(4))
             a.wide_d[q * a.cap + u + lane] = bits;
             slots[u + lane] = make_uint2(e.y, 0u);
           }
+        } else if constexpr (PLACE) {
+          if (u + lane < n) slots[u + lane] = make_uint2(bits, e.y);
         } else {
           const bool pass = u + lane < n && bits <= tau.d;
           const unsigned long long bal = __ballot(pass);
@@ -1573,7 +1703,7 @@ __global__ __launch_bounds__(LMS_NW * 64) __attribute__((amdgpu_waves_per_eu(4))
 #pragma unroll
         for (int x = 0; x < MT / 4; ++x) cw[x] = cwn[x];
       }
-      if (!WIDE && changed) {
+      if (HOW == LMS_MERGE && changed) {
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
           const Key x = h ? L1 : L0;
@@ -1587,86 +1717,21 @@ __global__ __launch_bounds__(LMS_NW * 64) __attribute__((amdgpu_waves_per_eu(4))
       }
     }
   }
+  if constexpr (PLACE) {
+    __syncthreads();   // all slots are settled
+    for (int i = wave; i < nqueries; i += LMS_NW) merge_query(a, (int)blockIdx.x + i * nwg, lane, qd, qrow);
+    if (a.list_redo) {
+      __syncthreads();   // all queries are named
+      if (wave == 0) list_named(lane < nqueries && a.qmap[lane_q] >= 0, lane_q);
+    }
+  }
 }
 
-// One wavefront per query: the candidates of the list-major scan are merged into the top-k of
-// the first lists by (distance, id).  Queries whose buffer overflowed are handed to the
-// query-major kernel through qmap.  What may enter is queued in LDS and folded in 64 at a time, the next 64 slots on
-// their way meanwhile (a sort and a fetch of ids for every 64 slots of which one may enter, each after its loads:
-// hit counts of 5000 queries, 1M x 96, both rounds: 227 us, 88 so).
 __global__ __launch_bounds__(256) void lm_merge_kernel(LmArgs a) {
-  __shared__ uint32_t sqd[4][128], sqrow[4][128];   // fewer than 64 waiting and 64 of a group
-  const int lane = threadIdx.x & 63;
-  uint32_t *qd = sqd[threadIdx.x >> 6], *qrow = sqrow[threadIdx.x >> 6];
+  __shared__ uint32_t sqd[4][LMQ_WORDS], sqrow[4][LMQ_WORDS];
   const int64_t q = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   if (q >= a.Q) return;
-  const uint32_t n = a.gcnt[q];
-  const bool overflow = n > (uint32_t)a.cap || (a.head_done && a.qmap_head[q] >= 0) || (a.later && a.qmap[q] >= 0);
-  if (lane == 0) a.qmap[q] = overflow ? (int32_t)q : -1;
-  if (overflow || n == 0) return;   // redone elsewhere / phase A's result stands
-  const int k = a.k;
-  Key L0, L1;
-  {
-    const int64_t o = q * k;
-    const bool in0 = lane < k, in1 = 64 + lane < k;
-    const int64_t id0 = in0 ? a.out_ids[o + lane] : -1, id1 = in1 ? a.out_ids[o + 64 + lane] : -1;
-    L0.d = id0 >= 0 ? __float_as_uint(a.out_dist[o + lane]) : SENT_D;
-    L0.id = id0 >= 0 ? id0 : SENT_ID;
-    L1.d = id1 >= 0 ? __float_as_uint(a.out_dist[o + 64 + lane]) : SENT_D;
-    L1.id = id1 >= 0 ? id1 : SENT_ID;
-  }
-  Key tau;
-  {
-    const Key t0 = bcast_key(L0, (k - 1) & 63), t1 = bcast_key(L1, (k - 1) & 63);
-    tau = (k - 1) < 64 ? t0 : t1;
-  }
-  const uint2 *slots = a.cand + q * a.cap;
-  auto slot_of = [&](uint32_t u) __attribute__((always_inline)) { return slots[u + lane < n ? u + lane : n - 1]; };
-  int waiting = 0;
-  uint2 e = slot_of(0);
-  for (uint32_t off = 0; off < n; off += 64) {
-    const uint2 next = slot_of(off + 64);
-    const bool in = off + lane < n && e.x <= tau.d;   // a larger distance fails whatever its id
-    const unsigned long long bal = __ballot(in);
-    if (in) {
-      const int pos = waiting + __popcll(bal & ((1ull << lane) - 1ull));
-      qd[pos] = e.x;
-      qrow[pos] = e.y;
-    }
-    waiting += __popcll(bal);
-    while (waiting >= 64 || (waiting > 0 && off + 64 >= n)) {   // the last 64, at the end all
-      const int m = waiting < 64 ? waiting : 64;
-      waiting -= m;
-      Key c;
-      c.d = SENT_D;
-      c.id = SENT_ID;
-      if (lane < m) {
-        c.d = qd[waiting + lane];
-        if (c.d <= tau.d) c.id = a.ids[qrow[waiting + lane]];
-      }
-      const bool pass = kless(c, tau);
-      if (__ballot(pass) == 0) continue;
-      if (!pass) {
-        c.d = SENT_D;
-        c.id = SENT_ID;
-      }
-      wave_sort_desc<true>(c, lane);
-      wave_merge<true>(L0, L1, c, lane);
-      const Key t0 = bcast_key(L0, (k - 1) & 63), t1 = bcast_key(L1, (k - 1) & 63);
-      tau = (k - 1) < 64 ? t0 : t1;
-    }
-    e = next;
-  }
-#pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    const Key e = h ? L1 : L0;
-    const int i = h * 64 + lane;
-    if (i < k) {
-      const bool real = e.d != SENT_D;
-      a.out_ids[q * k + i] = real ? e.id : -1;
-      a.out_dist[q * k + i] = real ? __uint_as_float(e.d) : __builtin_inff();
-    }
-  }
+  merge_query(a, q, threadIdx.x & 63, (LDS uint32_t *)sqd[threadIdx.x >> 6], (LDS uint32_t *)sqrow[threadIdx.x >> 6]);
 }
 
 std::atomic<int> g_lm_first{1};     // lists per query that are ranked first (their k-th distance filters the rest)
@@ -1720,9 +1785,9 @@ int launch_lm_byte_t(const LmArgs &a, const RadiiSq &r2, int grid, hipStream_t s
   return IVFPQ_OK;
 }
 
-template <int MT, int DSUB, bool WIDE>
+template <int MT, int DSUB, int HOW>
 int launch_lm_settle_t(const LmArgs &a, const RadiiSq &r2, int grid, hipStream_t s) {
-  auto kern = lm_settle_kernel<MT, DSUB, WIDE>;
+  auto kern = lm_settle_kernel<MT, DSUB, HOW>;
   static std::atomic<uint64_t> prepared;
   if (int rc = prepare_kernel(kern, prepared)) return rc;
   static_assert(lms_lds(MT, DSUB) <= (size_t)LDS_PER_CU, "codebook and queues fit a CU");
@@ -1730,12 +1795,12 @@ int launch_lm_settle_t(const LmArgs &a, const RadiiSq &r2, int grid, hipStream_t
   return IVFPQ_OK;
 }
 
-template <bool WIDE>
+template <int HOW>
 int launch_lm_settle(const LmArgs &a, const RadiiSq &r2, int cus, hipStream_t s) {
   const int grid = a.Q < cus ? (int)a.Q : cus;   // (a workgroup without a query of its own leaves at once)
-  if (a.M == 48) return launch_lm_settle_t<48, 2, WIDE>(a, r2, grid, s);
-  if (a.M == 64) return launch_lm_settle_t<64, 2, WIDE>(a, r2, grid, s);
-  return launch_lm_settle_t<16, 4, WIDE>(a, r2, grid, s);
+  if (a.M == 48) return launch_lm_settle_t<48, 2, HOW>(a, r2, grid, s);
+  if (a.M == 64) return launch_lm_settle_t<64, 2, HOW>(a, r2, grid, s);
+  return launch_lm_settle_t<16, 4, HOW>(a, r2, grid, s);
 }
 
 template <int MODE>
@@ -1883,7 +1948,7 @@ int launch_wide_stage(const ivfpq_index *ix, const float *d_queries, int64_t Q, 
     if (int rc = launch_lm_byte(a, r2, cus, s)) return rc;
   }
   hipLaunchKernelGGL(lm_sort_out_kernel, dim3((unsigned)((Q + 255) / 256)), dim3(256), 0, s, a, 0);
-  return launch_lm_settle<true>(a, r2, cus, s);
+  return launch_lm_settle<LMS_WIDE>(a, r2, cus, s);
 }
 
 int launch_scan_list_major(const ivfpq_index *ix, const float *d_queries, int64_t Q, int32_t nprobe,
@@ -1959,7 +2024,7 @@ int launch_scan_list_major(const ivfpq_index *ix, const float *d_queries, int64_
     if (rc) return rc;
     if (head_bytes) {
       hipLaunchKernelGGL(lm_sort_out_kernel, dim3((unsigned)((Q + 255) / 256)), dim3(256), 0, s, a, 0);
-      rc = launch_lm_settle<false>(a, r2, cus, s);
+      rc = launch_lm_settle<LMS_MERGE>(a, r2, cus, s);
       if (rc) return rc;
     }
   }
@@ -1997,6 +2062,10 @@ int launch_scan_list_major(const ivfpq_index *ix, const float *d_queries, int64_
   //   16, clustered               315 / 330    389 / 403    460 / 474    541 / 555    965 / 980
   // (2000 queries, 64 clustered: 131 / 143 at 32 probes, 143 / 156 at 64).  The line is where the two rounds cost
   // clustered data 3 % or less of a large batch.
+  // The candidates of byte tables of distances are settled where they stand by the wavefronts that share a workgroup's
+  // queries, and ranked behind that; up to 64 queries a workgroup.  Queries without a result of the head pass (LM_SEEDED), and
+  // larger batches, take a wavefront a query (lm_sort_out_kernel, lm_settle_kernel<LMS_MERGE>).
+  const bool in_place = bytes && mode == 0 && !head_bytes && Q <= (int64_t)64 * cus;
   const int split = bytes && nprobe - w.first >= 2 * LM_STAGE1 + 32 ? w.first + LM_STAGE1 : nprobe;
   for (int p0 = main_first, p1 = split; p0 < nprobe; p0 = p1, p1 = nprobe) {
     a.p0 = p0;
@@ -2011,9 +2080,13 @@ int launch_scan_list_major(const ivfpq_index *ix, const float *d_queries, int64_
     hipLaunchKernelGGL(lm_pairs_kernel, dim3(pair_grid), dim3(256), 0, s, a, 1, 0);
     rc = bytes ? launch_lm_byte(a, r2, cus, s) : launch_lm_scan<false>(ix, a, r2, cus, s);
     if (rc) return rc;
-    if (bytes && mode == 0) {
+    if (in_place) {
+      a.list_redo = p1 == nprobe && Q > 4096 ? 1 : 0;
+      rc = launch_lm_settle<LMS_PLACE>(a, r2, cus, s);
+      if (rc) return rc;
+    } else if (bytes && mode == 0) {
       hipLaunchKernelGGL(lm_sort_out_kernel, dim3((unsigned)((Q + 255) / 256)), dim3(256), 0, s, a, p1 == nprobe && Q > 4096 ? 1 : 0);
-      rc = launch_lm_settle<false>(a, r2, cus, s);
+      rc = launch_lm_settle<LMS_MERGE>(a, r2, cus, s);
       if (rc) return rc;
     } else {
       hipLaunchKernelGGL(lm_merge_kernel, dim3((unsigned)((Q + 3) / 4)), dim3(256), 0, s, a);

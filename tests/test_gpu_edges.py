@@ -515,3 +515,30 @@ def test_stages_above_128_neighbours_in_two_chunks(D, M):
     finally:
         b.set_option("wide_cap", 8192)
         gi.close()
+
+
+@pytest.mark.parametrize("D,M", [(96, 48), (128, 64), (64, 16)])
+@pytest.mark.parametrize("lm_cap", [0, 64])
+def test_candidates_settled_together(D, M, lm_cap):
+    """Byte tables in batches of one query, of fewer and of more than one per workgroup, of 4097 (queries to be redone are
+    listed) and of more than 64 per workgroup (a wavefront a query); queries without candidates, with a few and with
+    thousands, in one main pass and in two, and buffers of 64 slots that overflow."""
+    b = _binding()
+    rng = np.random.default_rng(M + lm_cap)
+    nlist, distinct = 72, 41
+    idx = _index(rng, D, M, rng.integers(600, 1100, size=nlist), centre=0.05)
+    idx.centroids[:20] *= np.float32(8.0)   # lists of their own: nothing elsewhere is near their queries
+    q = (idx.centroids[rng.integers(0, nlist, distinct)] + 0.3 * rng.normal(size=(distinct, D))).astype(np.float32)
+    radii = np.full(M, 0.5 * np.sqrt(D / M), dtype=np.float32)
+    gi = b.IvfPqIndex.from_index(idx)
+    try:
+        b.set_option("lm_cap", lm_cap)
+        for nprobe, k in ((24, 10), (64, 100)):
+            want = oracle.search(q, idx, nprobe, k, radii, threads=8)
+            for Q in (1, 255, 257, 4097, 16_385 if nprobe == 24 else 1000):
+                rows = np.arange(Q) % distinct
+                got = gi.search(torch.from_numpy(q[rows]).cuda(), nprobe, k, radii, strategy=b.SCAN_LIST_MAJOR)
+                _same(got, (want[0][rows], want[1][rows]), (D, M, lm_cap, nprobe, k, Q))
+    finally:
+        b.set_option("lm_cap", 0)
+        gi.close()

@@ -1519,7 +1519,7 @@ __global__ __launch_bounds__(LMS_NW * 64) __attribute__((amdgpu_waves_per_eu(4))
   LDS uint32_t *qd = (LDS uint32_t *)(smem3 + (size_t)MT * 1024 * DSUB) + wave * LMS_QUEUE * 2, *qrow = qd + LMS_QUEUE;
   LDS float *sr2 = (LDS float *)(smem3 + (size_t)MT * 1024 * DSUB + (size_t)LMS_NW * LMS_QUEUE * 8) + wave * MT;   // r_m^2 of the wavefront's query
   if (tid == 0) *taken = 0u;
-  __syncthreads();   // the last one: from here on every wavefront is by itself
+  __syncthreads();   // from here on every wavefront is by itself, until PLACE has settled all
   const int k = a.k;
   int32_t *ticket = a.cnt + a.nlist + 3 + 2 * a.stage;
   // Three quarters of the queries are dealt to the workgroups, whose wavefronts take them up by a counter in LDS; the

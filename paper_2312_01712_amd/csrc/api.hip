@@ -340,6 +340,7 @@ void ivfpq_index_destroy(ivfpq_index *ix) {
   (void)hipFree(ix->d_cnorm);
   (void)hipFree(ix->d_csplit);
   (void)hipFree(ix->d_box);
+  (void)hipFree(ix->d_cb_split);
   (void)hipFree(ix->d_grid);
   (void)hipFree(ix->d_grid_par);
   (void)hipFree(ix->d_codebooks);
@@ -470,6 +471,33 @@ int ivfpq_index_create(const ivfpq_index_desc *d, ivfpq_index **out) {
         }
       TRY_OR_FAIL(hipMalloc(&ix->d_csplit, split.size() * 2));
       TRY_OR_FAIL(hipMemcpy(ix->d_csplit, split.data(), split.size() * 2, hipMemcpyHostToDevice));
+    }
+    // list-major byte tables (lm_part_kernel): per entry (high part, rest) of both coordinates and of |entry|^2 as bf16, two
+    // zeros.  Nothing in it is infinite or not a number: the products would spread that to other rows by way of the zeros
+    // they multiply it with.  (The kernel looks at the entries themselves for what is not held here.)
+    if (list_major_shape(ix) && ix->dsub == 2) {
+      const size_t n = (size_t)d->M * 256;
+      std::vector<float> cb_h(2 * n);
+      TRY_OR_FAIL(hipMemcpy(cb_h.data(), ix->d_codebooks, kb, hipMemcpyDeviceToHost));
+      std::vector<uint16_t> split(8 * n, 0);
+      for (size_t i = 0; i < n; ++i) {
+        float v[3] = {cb_h[2 * i], cb_h[2 * i + 1], 0.0f};
+        v[2] = fmaf(v[1], v[1], v[0] * v[0]);
+        if (!(v[2] < SPLIT_FAR)) {
+          v[0] = v[1] = 0.0f;
+          v[2] = SPLIT_FAR;
+        }
+        for (int j = 0; j < 3; ++j) {
+          const uint16_t hi = bf16_bits(v[j]);
+          const uint32_t hb = (uint32_t)hi << 16;
+          float hf;
+          memcpy(&hf, &hb, 4);
+          split[8 * i + 2 * j] = hi;
+          split[8 * i + 2 * j + 1] = bf16_bits(v[j] - hf);
+        }
+      }
+      TRY_OR_FAIL(hipMalloc(&ix->d_cb_split, split.size() * 2));
+      TRY_OR_FAIL(hipMemcpy(ix->d_cb_split, split.data(), split.size() * 2, hipMemcpyHostToDevice));
     }
     // per list and subspace, the bounding box of the entries the list's points use (filled
     // below from the codes; an empty list keeps the all-zero box)

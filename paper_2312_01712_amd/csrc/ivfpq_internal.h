@@ -22,6 +22,7 @@ struct ivfpq_index {
   float *d_grid;            // dsub == 2, L2 metric: [M][GRID_G * GRID_G] lower bound on the squared distance from any point of a grid cell to the subspace's nearest entry; else NULL
   float *d_grid_par;        // [M][8]: low corner (x, y), high corner (x, y), cells per unit (x, y), 0, 0
   float *d_codebooks;       // [M][256][dsub]
+  uint16_t *d_cb_split;     // [M][256][8] the entries as pairs of bf16, where the list-major scan builds byte tables from them (scan_lm_parts.h); else NULL
   int64_t *d_list_offsets;  // [nlist+1] in points
   int64_t *d_list_blocks;   // [nlist+1] in 64-point blocks of the interleaved layout
   uint8_t *d_codes;         // interleaved blocks, see layout note below
@@ -96,6 +97,8 @@ inline size_t coarse_scratch_floats(int32_t nlist_pad, int32_t nkeys, int64_t qc
   return (((size_t)qc * nkeys + 63) & ~(size_t)63) + (size_t)((qc + 15) / 16 + FB_SLOTS) * nlist_pad + FB_SLOTS + 64;
 }
 
+constexpr float SPLIT_FAR = 1.0e38f;   // |entry|^2 from which on d_cb_split holds a point at the origin with this |entry|^2
+
 // ---- workspace carving (all offsets 256-byte aligned) -----------------------
 struct Workspace {
   size_t coarse_dist;   // scratch of the filtering stage for one query chunk (coarse_scratch_floats)
@@ -133,7 +136,11 @@ struct LmWorkspace {      // offsets into the list-major part of the workspace, 
 };
 inline size_t lm_align(size_t v) { return (v + 255) & ~(size_t)255; }
 constexpr int LM_STAGES = 8;   // passes of a call with candidates to settle
-inline int64_t lm_counters(int32_t nlist) { return (int64_t)nlist + 2 + 2 * LM_STAGES; }
+// Counters: pairs per list; two words on queries to be redone; two per pass on queries to settle; per pass and XCD the tasks
+// taken up, a cache line each: atomics on words of one line take 11 ns each, one after the other (80 000 tasks: 0.9 ms).
+constexpr int LM_TICKET_STEP = 64;
+__host__ __device__ inline int64_t lm_tickets(int32_t nlist, int pass) { return (((int64_t)nlist + 2 + 2 * LM_STAGES + 63) & ~(int64_t)63) + 8 * LM_TICKET_STEP * pass; }
+inline int64_t lm_counters(int32_t nlist) { return lm_tickets(nlist, LM_STAGES); }
 // Everything but the candidates' slots, for w.first.  A group of the byte tables has 8 queries.
 inline void plan_list_major_tables(LmWorkspace &w, int32_t nlist, int64_t Q, int32_t nprobe) {
   w.pairs_cap = Q * (nprobe - w.first > 1 ? nprobe - w.first : 1) + (int64_t)7 * nlist;   // also holds the head pass's Q pairs

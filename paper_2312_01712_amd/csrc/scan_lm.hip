@@ -55,6 +55,7 @@ struct LmArgs {
   const float *probe_lb;        // [Q][nprobe] list-level lower bounds, or NULL
   const float *centroids;       // [nlist][D]
   const float *codebooks;       // [M][256][dsub]
+  const uint16_t *cb_split;     // [M][256][8] its entries as pairs of bf16 (lm_part_kernel), or NULL
   const int64_t *list_offsets;  // [nlist+1]
   const int64_t *list_blocks;   // [nlist+1]
   const uint8_t *codes;         // interleaved blocks
@@ -81,6 +82,7 @@ struct LmArgs {
   int32_t stage;                // which of the passes of a call with candidates to settle
   int32_t fresh;                // byte tables in the head pass: the queries have no result yet
   int32_t list_redo;            // lm_settle_kernel in place: this is the last pass, queries to be redone are listed too
+  int32_t parts;                // byte tables of distances go by in parts (lm_part_kernel)
   int32_t seeded;               // behind that pass: qmap_head may be LM_SEEDED
   int32_t group;                // queries per group of the pass the pairs are bucketed for
   int32_t head_done;            // the head pass has run: queries it left out (qmap_head) have no first-list result yet
@@ -1330,6 +1332,8 @@ __global__ __launch_bounds__(LMB_NW * 64) __attribute__((amdgpu_waves_per_eu(4))
   }
 }
 
+#include "scan_lm_parts.h"
+
 // What follows a pass with byte tables of distances: the queries that have candidates are listed (in the place of
 // the pairs, whose groups have all been served), the queries to be redone marked and, behind the last pass of a
 // large batch (list_redo), listed too.  (One atomic per list and wavefront of 64 queries.)
@@ -1785,6 +1789,16 @@ int launch_lm_byte_t(const LmArgs &a, const RadiiSq &r2, int grid, hipStream_t s
   return IVFPQ_OK;
 }
 
+template <int MT, int DSUB>
+int launch_lm_part_t(const LmArgs &a, const RadiiSq &r2, int cus, hipStream_t s) {
+  auto kern = lm_part_kernel<MT, DSUB>;
+  static std::atomic<uint64_t> prepared;
+  if (int rc = prepare_kernel(kern, prepared)) return rc;
+  static_assert(LMP_WG * lmp_lds(MT, DSUB) <= (size_t)LDS_PER_CU, "the workgroups fit a CU");
+  hipLaunchKernelGGL(kern, dim3((unsigned)(LMP_WG * cus)), dim3(LMP_NW * 64), lmp_lds(MT, DSUB), s, a, r2);
+  return IVFPQ_OK;
+}
+
 template <int MT, int DSUB, int HOW>
 int launch_lm_settle_t(const LmArgs &a, const RadiiSq &r2, int grid, hipStream_t s) {
   auto kern = lm_settle_kernel<MT, DSUB, HOW>;
@@ -1811,6 +1825,7 @@ int launch_lm_byte_m(const LmArgs &a, const RadiiSq &r2, int grid, hipStream_t s
 }
 
 int launch_lm_byte(const LmArgs &a, const RadiiSq &r2, int grid, hipStream_t s) {
+  if (a.parts && a.mode == 0) return a.M == 48 ? launch_lm_part_t<48, 2>(a, r2, grid, s) : launch_lm_part_t<64, 2>(a, r2, grid, s);
   if (a.mode == 0) return launch_lm_byte_m<0>(a, r2, grid, s);
   if (a.mode == 1) return launch_lm_byte_m<1>(a, r2, grid, s);
   return launch_lm_byte_m<2>(a, r2, grid, s);
@@ -1871,6 +1886,7 @@ static LmArgs lm_args(const ivfpq_index *ix, const float *d_queries, int64_t Q, 
   a.probe_lb = d_probe_lb;
   a.centroids = ix->d_centroids;
   a.codebooks = ix->d_codebooks;
+  a.cb_split = ix->d_cb_split;
   a.list_offsets = ix->d_list_offsets;
   a.list_blocks = ix->d_list_blocks;
   a.codes = ix->d_codes;
@@ -1892,6 +1908,11 @@ static LmArgs lm_args(const ivfpq_index *ix, const float *d_queries, int64_t Q, 
   a.p1 = nprobe;
   a.group = LM_G;
   for (int m = 0; m < ix->M; ++m) a.rmax = r2.v[m] > a.rmax ? r2.v[m] : a.rmax;
+  // A table in parts serves LMP_SEG points of a list, and with a longer one it is made again.  us of a search with whole byte
+  // tables / in parts, 64 probes (48 subspaces, 10 000 queries, without structure), 32 probes (64, 8192, without structure), k = 100,
+  // by the mean list: 48: 500 2421 / 2105, 977 3439 / 3073, 1515 3982 / 3895, 1953 3573 / 3690, 2500 3994 / 4349, 3906 5212 / 5996;
+  // 64: 977 2203 / 1996, 1515 2308 / 2040, 1953 2498 / 2184, 2941 2812 / 2907, 3906 3090 / 3146.  The line is where both gain.
+  a.parts = ix->d_cb_split && ix->N <= (int64_t)1536 * ix->nlist ? 1 : 0;
   return a;
 }
 

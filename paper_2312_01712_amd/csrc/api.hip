@@ -126,7 +126,7 @@ WideWorkspace plan_wide(const ivfpq_index *ix, int64_t Q, int32_t k, int32_t mod
 // (32 probes.)  The line is where clustered data pays a tenth at most; without structure the stages take a half to a quarter.
 static int32_t wide_first(const ivfpq_index *ix, const WideWorkspace &w, int32_t nprobe, int32_t k, int32_t strategy) {
   const int64_t Q = w.q_chunk;
-  if (strategy == IVFPQ_SCAN_QUERY_MAJOR || !list_major_shape(ix)) return 0;
+  if (strategy == IVFPQ_SCAN_QUERY_MAJOR || !byte_table_shape(ix)) return 0;
   if (Q * (int64_t)nprobe < 16384 || ix->N > (int64_t)4096 * ix->nlist || ix->N < (int64_t)ix->nlist * 128) return 0;
   if (ix->max_list_len >= (1 << 20) || Q * (int64_t)nprobe > 0x3FFFFFFFll) return 0;
   const bool few = 2 * (int64_t)k * ix->nlist < ix->N;   // neighbours against the points of a list
@@ -238,9 +238,11 @@ static int64_t lm_together(const ivfpq_index *ix, int64_t Q, int32_t nprobe, int
 static bool use_list_major(const ivfpq_index *ix, int64_t Q, int32_t nprobe, int32_t k, int32_t mode,
                            int32_t requested) {
   if (requested == IVFPQ_SCAN_QUERY_MAJOR || !list_major_supported(ix, nprobe, k)) return false;
+  if (!byte_table_shape(ix) && mode != IVFPQ_SCORE_DISTANCE) return false;   // (the hit counts' byte tables serve them query-major)
   if (requested == IVFPQ_SCAN_LIST_MAJOR) return true;
   if (Q * (int64_t)nprobe < 16384) return false;
   if (ix->N <= (int64_t)4096 * ix->nlist) return true;
+  if (!byte_table_shape(ix)) return false;   // (no byte tables for the head pass on long lists)
   // Longer lists: the query-major scan prunes block by block, the list-major one shares each pass over a list among the
   // queries that probe it.  Distances only (the hit counts' first lists are ranked query-major either way).  Query-major /
   // list-major, us, k = 100, 64 probes, 64 subspaces of clustered data unless said:
@@ -475,7 +477,7 @@ int ivfpq_index_create(const ivfpq_index_desc *d, ivfpq_index **out) {
     // list-major byte tables (lm_part_kernel): per entry (high part, rest) of both coordinates and of |entry|^2 as bf16, two
     // zeros.  Nothing in it is infinite or not a number: the products would spread that to other rows by way of the zeros
     // they multiply it with.  (The kernel looks at the entries themselves for what is not held here.)
-    if (list_major_shape(ix) && ix->dsub == 2) {
+    if (byte_table_shape(ix) && ix->dsub == 2) {
       const size_t n = (size_t)d->M * 256;
       std::vector<float> cb_h(2 * n);
       TRY_OR_FAIL(hipMemcpy(cb_h.data(), ix->d_codebooks, kb, hipMemcpyDeviceToHost));
@@ -740,12 +742,12 @@ static int scan_query_major(const ivfpq_index *ix, const float *d_queries, int64
                      reinterpret_cast<float *>(base + w.probe_dist), s, &view);
 }
 
-// Whether a call goes list-major with the workspace it has: AUTO on long lists serves one that only has room for the
-// query-major scan with that.
+// Whether a call goes list-major with the workspace it has: AUTO on long lists, and every call on shapes without byte
+// tables, is served query-major where the workspace only has room for that.
 static bool goes_list_major(const ivfpq_index *ix, int64_t Q, int32_t nprobe, int32_t k, int32_t mode, int32_t strategy,
                             const Workspace &w, size_t ws_bytes) {
   if (!use_list_major(ix, Q, nprobe, k, mode, strategy)) return false;
-  if (strategy == IVFPQ_SCAN_LIST_MAJOR || ix->N <= (int64_t)4096 * ix->nlist) return true;
+  if (byte_table_shape(ix) && (strategy == IVFPQ_SCAN_LIST_MAJOR || ix->N <= (int64_t)4096 * ix->nlist)) return true;
   return ws_bytes >= align256(w.total) + plan_list_major(ix, lm_together(ix, Q, nprobe, strategy), nprobe).total;
 }
 

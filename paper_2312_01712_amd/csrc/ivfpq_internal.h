@@ -155,10 +155,12 @@ inline void plan_list_major_tables(LmWorkspace &w, int32_t nlist, int64_t Q, int
   w.cand = off;
   w.total = off;
 }
-// Shapes that have list-major kernels.
-inline bool list_major_shape(const ivfpq_index *ix) {
+// Shapes whose list-major kernels have byte tables.
+inline bool byte_table_shape(const ivfpq_index *ix) {
   return (ix->M == 48 && ix->dsub == 2) || (ix->M == 64 && ix->dsub == 2) || (ix->M == 16 && ix->dsub == 4);
 }
+// Shapes that have list-major kernels.  (100 subspaces: distances only, in calls whose workspace has room for it.)
+inline bool list_major_shape(const ivfpq_index *ix) { return byte_table_shape(ix) || (ix->M == 100 && ix->dsub == 2); }
 
 // Workspace of the wide selection (more than 128 neighbours per query in one pass of the
 // query-major scan): offsets into its part of the workspace, 256-byte aligned.

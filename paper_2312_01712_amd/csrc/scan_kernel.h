@@ -593,7 +593,7 @@ int launch_scan_t(const ScanArgs &a, const RadiiSq &r2, int64_t grid, bool dump,
   const int kind = dump ? SCAN_ALL : (a.nsplit > 1 ? SCAN_SPLIT : (a.qlist ? SCAN_LISTED : SCAN_TOPK));
   auto kern = kind == SCAN_ALL ? scan_kernel<MT, DSUB, NW, SCAN_ALL, BYTE>
                                : (kind == SCAN_SPLIT ? scan_kernel<MT, DSUB, NW, SCAN_SPLIT, BYTE> : scan_kernel<MT, DSUB, NW, SCAN_TOPK, BYTE>);
-  if constexpr (DSUB != 0 && MT <= 64)   // (the shapes the list-major scan hands queries over for)
+  if constexpr (DSUB != 0)   // (the shapes the list-major scan hands queries over for)
     if (kind == SCAN_LISTED) {
       kern = scan_kernel<MT, DSUB, NW, SCAN_LISTED, BYTE>;
       // as many as the chip holds at once: what a CU's LDS and its SIMDs' registers allow

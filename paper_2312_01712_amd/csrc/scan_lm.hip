@@ -300,6 +300,164 @@ struct LmTask {
   float tauv;          // main pass: lane 0 holds tau of q0, the other lanes tau of q1 (a vector load, like the metadata)
 };
 
+// Head pass: the histogram's window.  No table entry exceeds its row's r_m^2, so a distance lies in [0, sum of the r_m^2]: with
+// finite radii the window is known before the scan and every distance is counted as it is produced.  Otherwise (infinite
+// radii) the window is the range the distances turn out to span, and they are counted in a pass of their own.  Bins have
+// equal width in value; bin_of is monotone in the distance, which is all the selection needs.
+struct LmWindow {
+  float lo[2], scale[2];
+  bool known;
+  __device__ __forceinline__ uint32_t bin_of(int g, uint32_t key) const {
+    const float x = (__uint_as_float(key) - (g ? lo[1] : lo[0])) * (g ? scale[1] : scale[0]);   // (selected: indexed, they would be in scratch)
+    return x >= (float)(LM_BINS - 1) ? (uint32_t)(LM_BINS - 1) : (x > 0.0f ? (uint32_t)x : 0u);
+  }
+};
+template <int MT>
+__device__ __forceinline__ LmWindow lm_window(const LDS float *sr2, int lane) {
+  float s0 = lane < MT ? sr2[lane] : 0.0f, s1 = lane < MT ? sr2[IVFPQ_MAX_M + lane] : 0.0f;
+  if constexpr (MT > 64) {
+    if (lane + 64 < MT) {
+      s0 += sr2[lane + 64];
+      s1 += sr2[IVFPQ_MAX_M + lane + 64];
+    }
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) {
+    s0 += __shfl_xor(s0, off);
+    s1 += __shfl_xor(s1, off);
+  }
+  LmWindow w;
+  w.known = s0 > 0.0f && s0 < __builtin_inff() && s1 > 0.0f && s1 < __builtin_inff();   // same in every wavefront
+  w.lo[0] = w.lo[1] = 0.0f;
+  w.scale[0] = (float)LM_BINS / s0;
+  w.scale[1] = (float)LM_BINS / s1;
+  return w;
+}
+
+// Head pass: the k nearest of a scanned list, for the queries of its task, from the distances in LDS.  The collected keys
+// are held where the table was (`coll`).  AHEAD: LDS reads of the rank sort in flight.
+template <int AHEAD>
+__device__ __forceinline__ void lm_select_head(const LmArgs &a, const LmTask &done, LmWindow &w, uint32_t mn0, uint32_t mn1, uint32_t mx0, uint32_t mx1,
+                                               LDS unsigned char *coll, LDS uint32_t *ssel, LDS uint32_t *hist, const LDS uint32_t *sdist,
+                                               int tid, int lane, int wave) {
+  LDS uint32_t *coll_d = (LDS uint32_t *)coll;             // [2][LM_COLLECT] collected keys: distance bits ...
+  LDS uint32_t *coll_pos = coll_d + LM_G * LM_COLLECT;     // ... their positions in the list ...
+  LDS uint32_t *coll_rank = coll_pos + LM_G * LM_COLLECT;  // ... and in sorted order
+  const int L = done.len, k = a.k;
+  const int ng = done.has1 ? 2 : 1;
+  // window not known: smallest and largest key of each query's list (this wavefront's share first)
+  if (!w.known)
+    for (int g = 0; g < ng; ++g) {
+      uint32_t lo = g ? mn1 : mn0, hi = g ? mx1 : mx0;
+#pragma unroll
+      for (int off = 32; off > 0; off >>= 1) {
+        const uint32_t ol = (uint32_t)__shfl_xor((int)lo, off), oh = (uint32_t)__shfl_xor((int)hi, off);
+        lo = ol < lo ? ol : lo;
+        hi = oh > hi ? oh : hi;
+      }
+      if (lane == 0) {
+        __hip_atomic_fetch_min(&ssel[4 + g], lo, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        __hip_atomic_fetch_max(&ssel[6 + g], hi, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      }
+    }
+  __syncthreads();   // the list is scanned: every distance is in LDS and the table's LDS is free
+  uint32_t top[2] = {LM_BINS, LM_BINS};   // collect keys whose bin is <= top (everything when the list is short)
+  if (tid < LM_G * LM_COLLECT) {           // empty slots: the sentinel, and rank 0
+    coll_d[tid] = SENT_D;
+    coll_rank[tid] = 0u;
+  }
+  if (L <= LM_COLLECT) __syncthreads();    // (else the barriers of the histogram come before the slots are filled)
+  if (L > LM_COLLECT) {                    // uniform; then k <= LM_COLLECT < L: the k-th smallest exists
+    if (!w.known) {
+      for (int g = 0; g < 2; ++g) {
+        w.lo[g] = __uint_as_float(ssel[4 + g]);
+        w.scale[g] = (float)LM_BINS / (__uint_as_float(ssel[6 + g]) - w.lo[g]);   // one value only: every key in bin 0
+      }
+      for (int i = tid; i < L; i += LM_NW * 64)
+        for (int g = 0; g < ng; ++g) lds_add(&hist[g * LM_BINS + lm_hidx(w.bin_of(g, sdist[g * a.head_max + i]))]);
+      __syncthreads();
+    }
+    if (wave < ng) {                       // wavefront g ranks query g's histogram
+      uint32_t bin, below;
+      lm_find_bin(hist + wave * LM_BINS, (uint32_t)k, lane, bin, below);
+      if (lane == 0) ssel[2 + wave] = bin;
+    }
+    __syncthreads();
+    top[0] = ssel[2];
+    top[1] = ssel[3];
+  }
+  // collect (distance, position in the list) of the keys up to that bin; a wavefront reserves
+  // the slots of its keys with one atomic operation
+  for (int i0 = wave * 64; i0 < L; i0 += LM_NW * 64) {
+    const int i = i0 + lane;
+    for (int g = 0; g < ng; ++g) {
+      const uint32_t key = i < L ? sdist[g * a.head_max + i] : 0u;
+      const bool take = i < L && w.bin_of(g, key) <= top[g];
+      const unsigned long long bal = __ballot(take);
+      if (bal == 0ull) continue;
+      uint32_t first = 0;
+      if (lane == 0) first = __hip_atomic_fetch_add(&ssel[g], (uint32_t)__popcll(bal), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      first = (uint32_t)__builtin_amdgcn_readfirstlane((int)first);
+      const uint32_t slot = first + (uint32_t)__popcll(bal & ((1ull << lane) - 1ull));
+      if (take && slot < (uint32_t)LM_COLLECT) {
+        coll_d[g * LM_COLLECT + slot] = key;
+        coll_pos[g * LM_COLLECT + slot] = (uint32_t)i;
+      }
+    }
+  }
+  __syncthreads();
+  // Rank sort, all wavefronts: thread (query g, key i, half h) counts the keys of half h of
+  // query g's collected keys that precede key i in (distance, id) order; the two halves add
+  // up to the key's position in the sorted order.  Unused slots hold the sentinel, which
+  // precedes nothing, so the count runs over a fixed 64 slots, four per LDS read.  The id of
+  // a key is requested before the count and only needed after it; where distances tie (rare)
+  // the ids of the tying keys are fetched on the spot.
+  {
+    const int g = tid >> 8, i = tid & (LM_COLLECT - 1), h = (tid >> 7) & 1;
+    const uint32_t n = ssel[g];
+    const bool live = g < ng && n <= (uint32_t)LM_COLLECT && (uint32_t)i < n;
+    const uint32_t md = live ? coll_d[g * LM_COLLECT + i] : SENT_D;
+    const uint32_t mpos = live ? coll_pos[g * LM_COLLECT + i] : 0u;
+    int64_t mid = SENT_ID;
+    if (live) mid = a.ids[done.row0 + mpos];
+    uint32_t before = 0, ties = 0;
+    const LDS uintx4 *half = (const LDS uintx4 *)(coll_d + g * LM_COLLECT + h * (LM_COLLECT / 2));
+#pragma unroll AHEAD
+    for (int j = 0; j < LM_COLLECT / 8; ++j) {
+      const uintx4 od = half[j];
+#pragma unroll
+      for (int x = 0; x < 4; ++x) {
+        before += od[x] < md ? 1u : 0u;
+        ties += od[x] == md ? 1u : 0u;
+      }
+    }
+    if (live) {
+      if (ties > ((i >> 6) == h ? 1u : 0u)) {
+        const int j0 = h * (LM_COLLECT / 2);
+        for (int j = j0; j < j0 + LM_COLLECT / 2 && j < (int)n; ++j)
+          if (coll_d[g * LM_COLLECT + j] == md && a.ids[done.row0 + coll_pos[g * LM_COLLECT + j]] < mid) ++before;
+      }
+      if (before) __hip_atomic_fetch_add(&coll_rank[g * LM_COLLECT + i], before, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+    __syncthreads();
+    const int64_t q = g ? done.q1 : done.q0;
+    if (g < ng && h == 0) {
+      if (n > (uint32_t)LM_COLLECT) {
+        if (i == 0) a.qmap_head[q] = (int32_t)q;   // too many equal distances: left to the query-major kernel
+      } else if ((uint32_t)i < n) {
+        const uint32_t r = coll_rank[g * LM_COLLECT + i];
+        if (r < (uint32_t)k) {
+          a.out_ids[q * k + r] = mid;
+          a.out_dist[q * k + r] = __uint_as_float(md);
+        }
+      } else if (i < k) {                           // fewer than k points in the list
+        a.out_ids[q * k + i] = -1;
+        a.out_dist[q * k + i] = __builtin_inff();
+      }
+    }
+  }
+}
+
 // Persistent workgroups, one per CU.  Tasks are sorted by list; in every round the grid takes
 // the next gridDim.x tasks, and within a round the workgroups of one XCD (workgroup b runs on
 // XCD b % 8) take a run of consecutive tasks, so that the tasks which stream the same list's
@@ -331,9 +489,6 @@ __global__ __launch_bounds__(LM_NW * 64) __attribute__((amdgpu_waves_per_eu(LM_N
   LDS uint32_t *ssel = queue;                      // [LM_SEL_WORDS]
   LDS uint32_t *hist = queue + LM_SEL_WORDS;       // [2][LM_BINS]
   LDS uint32_t *sdist = hist + LM_G * LM_BINS;     // [2][head_max]
-  LDS uint32_t *coll_d = (LDS uint32_t *)smem3;    // [2][LM_COLLECT] collected keys: distance bits ...
-  LDS uint32_t *coll_pos = coll_d + LM_G * LM_COLLECT;    // ... their positions in the list ...
-  LDS uint32_t *coll_rank = coll_pos + LM_G * LM_COLLECT;  // ... and in sorted order
 
   int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -486,29 +641,8 @@ __global__ __launch_bounds__(LM_NW * 64) __attribute__((amdgpu_waves_per_eu(LM_N
     // ---- one pass over the list's codes serves both queries ----
     int qc0 = 0, qc1 = 0;
     uint32_t mn0 = 0xFFFFFFFFu, mn1 = 0xFFFFFFFFu, mx0 = 0u, mx1 = 0u;   // head pass: key range of this wavefront's points
-    // Head pass: the histogram's window.  No table entry exceeds its row's r_m^2, so a distance
-    // lies in [0, sum of the r_m^2]: with finite radii the window is known before the scan and
-    // every distance is counted as it is produced.  Otherwise (infinite radii) the window is
-    // the range the distances turn out to span, and they are counted in a pass of their own.
-    // Bins have equal width in value; bin_of is monotone in the distance, which is all the
-    // selection needs.
-    float wlo[2] = {0.0f, 0.0f}, wscale[2] = {0.0f, 0.0f};
-    bool window_known = false;
-    if constexpr (HEAD) {
-      float s0 = lane < MT ? sr2[lane] : 0.0f, s1 = lane < MT ? sr2[IVFPQ_MAX_M + lane] : 0.0f;
-#pragma unroll
-      for (int off = 32; off > 0; off >>= 1) {
-        s0 += __shfl_xor(s0, off);
-        s1 += __shfl_xor(s1, off);
-      }
-      window_known = s0 > 0.0f && s0 < __builtin_inff() && s1 > 0.0f && s1 < __builtin_inff();   // same in every wavefront
-      wscale[0] = (float)LM_BINS / s0;
-      wscale[1] = (float)LM_BINS / s1;
-    }
-    auto bin_of = [&](int g, uint32_t key) __attribute__((always_inline)) {
-      const float x = (__uint_as_float(key) - wlo[g]) * wscale[g];
-      return x >= (float)(LM_BINS - 1) ? (uint32_t)(LM_BINS - 1) : (x > 0.0f ? (uint32_t)x : 0u);
-    };
+    LmWindow win;
+    if constexpr (HEAD) win = lm_window<MT>(sr2, lane);
     // tau_q as the bit pattern of a non-negative float (orders like the value; +inf when the
     // first lists held fewer than k points)
     const uint32_t tau0 = (uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(tk.tauv), 0);
@@ -529,9 +663,9 @@ __global__ __launch_bounds__(LM_NW * 64) __attribute__((amdgpu_waves_per_eu(LM_N
           const uint32_t k0 = __float_as_uint(d0), k1 = __float_as_uint(d1);
           sdist[i] = k0;
           sdist[a.head_max + i] = k1;
-          if (window_known) {
-            lds_add(&hist[lm_hidx(bin_of(0, k0))]);
-            lds_add(&hist[LM_BINS + lm_hidx(bin_of(1, k1))]);
+          if (win.known) {
+            lds_add(&hist[lm_hidx(win.bin_of(0, k0))]);
+            lds_add(&hist[LM_BINS + lm_hidx(win.bin_of(1, k1))]);
           } else {
             mn0 = k0 < mn0 ? k0 : mn0;
             mx0 = k0 > mx0 ? k0 : mx0;
@@ -552,119 +686,7 @@ __global__ __launch_bounds__(LM_NW * 64) __attribute__((amdgpu_waves_per_eu(LM_N
       npv = nnv;
     }
     if constexpr (HEAD) {
-      const int L = done.len, k = a.k;
-      const int ng = done.has1 ? 2 : 1;
-      // window not known: smallest and largest key of each query's list (this wavefront's share first)
-      if (!window_known)
-        for (int g = 0; g < ng; ++g) {
-          uint32_t lo = g ? mn1 : mn0, hi = g ? mx1 : mx0;
-#pragma unroll
-          for (int off = 32; off > 0; off >>= 1) {
-            const uint32_t ol = (uint32_t)__shfl_xor((int)lo, off), oh = (uint32_t)__shfl_xor((int)hi, off);
-            lo = ol < lo ? ol : lo;
-            hi = oh > hi ? oh : hi;
-          }
-          if (lane == 0) {
-            __hip_atomic_fetch_min(&ssel[4 + g], lo, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-            __hip_atomic_fetch_max(&ssel[6 + g], hi, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-          }
-        }
-      __syncthreads();   // the list is scanned: every distance is in LDS and the table's LDS is free
-      uint32_t top[2] = {LM_BINS, LM_BINS};   // collect keys whose bin is <= top (everything when the list is short)
-      if (tid < LM_G * LM_COLLECT) {           // empty slots: the sentinel, and rank 0
-        coll_d[tid] = SENT_D;
-        coll_rank[tid] = 0u;
-      }
-      if (L <= LM_COLLECT) __syncthreads();    // (else the barriers of the histogram come before the slots are filled)
-      if (L > LM_COLLECT) {                    // uniform; then k <= LM_COLLECT < L: the k-th smallest exists
-        if (!window_known) {
-          for (int g = 0; g < 2; ++g) {
-            wlo[g] = __uint_as_float(ssel[4 + g]);
-            wscale[g] = (float)LM_BINS / (__uint_as_float(ssel[6 + g]) - wlo[g]);   // one value only: every key in bin 0
-          }
-          for (int i = tid; i < L; i += NW * 64)
-            for (int g = 0; g < ng; ++g) lds_add(&hist[g * LM_BINS + lm_hidx(bin_of(g, sdist[g * a.head_max + i]))]);
-          __syncthreads();
-        }
-        if (wave < ng) {                       // wavefront g ranks query g's histogram
-          uint32_t bin, below;
-          lm_find_bin(hist + wave * LM_BINS, (uint32_t)k, lane, bin, below);
-          if (lane == 0) ssel[2 + wave] = bin;
-        }
-        __syncthreads();
-        top[0] = ssel[2];
-        top[1] = ssel[3];
-      }
-      // collect (distance, position in the list) of the keys up to that bin; a wavefront reserves
-      // the slots of its keys with one atomic operation
-      for (int i0 = wave * 64; i0 < L; i0 += NW * 64) {
-        const int i = i0 + lane;
-        for (int g = 0; g < ng; ++g) {
-          const uint32_t key = i < L ? sdist[g * a.head_max + i] : 0u;
-          const bool take = i < L && bin_of(g, key) <= top[g];
-          const unsigned long long bal = __ballot(take);
-          if (bal == 0ull) continue;
-          uint32_t first = 0;
-          if (lane == 0) first = __hip_atomic_fetch_add(&ssel[g], (uint32_t)__popcll(bal), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-          first = (uint32_t)__builtin_amdgcn_readfirstlane((int)first);
-          const uint32_t slot = first + (uint32_t)__popcll(bal & ((1ull << lane) - 1ull));
-          if (take && slot < (uint32_t)LM_COLLECT) {
-            coll_d[g * LM_COLLECT + slot] = key;
-            coll_pos[g * LM_COLLECT + slot] = (uint32_t)i;
-          }
-        }
-      }
-      __syncthreads();
-      // Rank sort, all wavefronts: thread (query g, key i, half h) counts the keys of half h of
-      // query g's collected keys that precede key i in (distance, id) order; the two halves add
-      // up to the key's position in the sorted order.  Unused slots hold the sentinel, which
-      // precedes nothing, so the count runs over a fixed 64 slots, four per LDS read.  The id of
-      // a key is requested before the count and only needed after it; where distances tie (rare)
-      // the ids of the tying keys are fetched on the spot.
-      {
-        const int g = tid >> 8, i = tid & (LM_COLLECT - 1), h = (tid >> 7) & 1;
-        const uint32_t n = ssel[g];
-        const bool live = g < ng && n <= (uint32_t)LM_COLLECT && (uint32_t)i < n;
-        const uint32_t md = live ? coll_d[g * LM_COLLECT + i] : SENT_D;
-        const uint32_t mpos = live ? coll_pos[g * LM_COLLECT + i] : 0u;
-        int64_t mid = SENT_ID;
-        if (live) mid = a.ids[done.row0 + mpos];
-        uint32_t before = 0, ties = 0;
-        const LDS uintx4 *half = (const LDS uintx4 *)(coll_d + g * LM_COLLECT + h * (LM_COLLECT / 2));
-#pragma unroll
-        for (int j = 0; j < LM_COLLECT / 8; ++j) {
-          const uintx4 od = half[j];
-#pragma unroll
-          for (int x = 0; x < 4; ++x) {
-            before += od[x] < md ? 1u : 0u;
-            ties += od[x] == md ? 1u : 0u;
-          }
-        }
-        if (live) {
-          if (ties > ((i >> 6) == h ? 1u : 0u)) {
-            const int j0 = h * (LM_COLLECT / 2);
-            for (int j = j0; j < j0 + LM_COLLECT / 2 && j < (int)n; ++j)
-              if (coll_d[g * LM_COLLECT + j] == md && a.ids[done.row0 + coll_pos[g * LM_COLLECT + j]] < mid) ++before;
-          }
-          if (before) __hip_atomic_fetch_add(&coll_rank[g * LM_COLLECT + i], before, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        }
-        __syncthreads();
-        const int64_t q = g ? done.q1 : done.q0;
-        if (g < ng && h == 0) {
-          if (n > (uint32_t)LM_COLLECT) {
-            if (i == 0) a.qmap_head[q] = (int32_t)q;   // too many equal distances: left to the query-major kernel
-          } else if ((uint32_t)i < n) {
-            const uint32_t r = coll_rank[g * LM_COLLECT + i];
-            if (r < (uint32_t)k) {
-              a.out_ids[q * k + r] = mid;
-              a.out_dist[q * k + r] = __uint_as_float(md);
-            }
-          } else if (i < k) {                           // fewer than k points in the list
-            a.out_ids[q * k + i] = -1;
-            a.out_dist[q * k + i] = __builtin_inff();
-          }
-        }
-      }
+      lm_select_head<16>(a, done, win, mn0, mn1, mx0, mx1, smem3, ssel, hist, sdist, tid, lane, wave);
     } else {
       // One atomic instruction reserves the space of both queues: lane g for query g.  Its
       // result is not waited for here: the queued candidates are written to the reserved slots
@@ -1333,6 +1355,7 @@ __global__ __launch_bounds__(LMB_NW * 64) __attribute__((amdgpu_waves_per_eu(4))
 }
 
 #include "scan_lm_parts.h"
+#include "scan_lm_pairs.h"
 
 // What follows a pass with byte tables of distances: the queries that have candidates are listed (in the place of
 // the pairs, whose groups have all been served), the queries to be redone marked and, behind the last pass of a
@@ -1799,6 +1822,21 @@ int launch_lm_part_t(const LmArgs &a, const RadiiSq &r2, int cus, hipStream_t s)
   return IVFPQ_OK;
 }
 
+template <int MT, bool HEAD>
+int launch_lm_pair_t(const LmArgs &a, const RadiiSq &r2, int cus, hipStream_t s) {
+  auto kern = lm_pair_kernel<MT, HEAD>;
+  static std::atomic<uint64_t> prepared;
+  if (int rc = prepare_kernel(kern, prepared)) return rc;
+  hipLaunchKernelGGL(kern, dim3((unsigned)(LPP_WG * cus)), dim3(LPP_NW * 64), HEAD ? lpp_head_lds(a.D) : lpp_main_lds(a.D), s, a, r2);
+  return IVFPQ_OK;
+}
+
+int launch_lm_pair_head(const LmArgs &a, const RadiiSq &r2, int cus, hipStream_t s) {
+  if (a.M == 48) return launch_lm_pair_t<48, true>(a, r2, cus, s);
+  if (a.M == 64) return launch_lm_pair_t<64, true>(a, r2, cus, s);
+  return launch_lm_pair_t<100, true>(a, r2, cus, s);
+}
+
 template <int MT, int DSUB, int HOW>
 int launch_lm_settle_t(const LmArgs &a, const RadiiSq &r2, int grid, hipStream_t s) {
   auto kern = lm_settle_kernel<MT, DSUB, HOW>;
@@ -1853,13 +1891,14 @@ void set_lm_cap(int v) { g_lm_cap.store(v, std::memory_order_relaxed); }
 
 bool list_major_supported(const ivfpq_index *ix, int32_t nprobe, int32_t k) {
   if (ix->metric != IVFPQ_METRIC_L2 || k > KP) return false;
-  if (!list_major_shape(ix) || lm_scan_lds(ix->M, ix->D) > (size_t)LDS_PER_CU || LM_G * ix->D > LM_NW * 64 || LM_G * ix->M > LM_NW * 64) return false;
+  if (!list_major_shape(ix) || LM_G * ix->D > LM_NW * 64 || LM_G * ix->M > LM_NW * 64) return false;
+  if (byte_table_shape(ix) && lm_scan_lds(ix->M, ix->D) > (size_t)LDS_PER_CU) return false;
   return nprobe > g_lm_first.load(std::memory_order_relaxed);
 }
 
 // Indexes on which the head pass may run with byte tables: lists that are long, or do not fit the fp32 form's LDS.
 static bool byte_head_lists(const ivfpq_index *ix) {
-  return ix->max_list_len < (1 << 20) &&
+  return byte_table_shape(ix) && ix->max_list_len < (1 << 20) &&
          (ix->N > (int64_t)4096 * ix->nlist || (ix->max_list_len > lm_head_max(ix->M, ix->D) && ix->N >= (int64_t)2800 * ix->nlist));
 }
 
@@ -1986,7 +2025,25 @@ int launch_scan_list_major(const ivfpq_index *ix, const float *d_queries, int64_
   a.out_dist = d_out_dist;
   a.tau = d_out_dist + k - 1;
   a.tau_stride = k;
-  a.head_max = lm_head_max(ix->M, ix->D);
+  // The tables of two queries in parts (lm_pair_kernel), two workgroups per CU, or whole (lm_scan_kernel).  us of a search of 32
+  // probes, clustered data, k = 100, whole / in parts, by the mean list:
+  //   queries                      600         1000         1500         2200         4000         6000        10 000
+  //   64 subspaces, 400                    133 / 129                 188 / 185                 357 / 336
+  //   64, 500                                                                                               467 / 430
+  //   64, 977                   83 / 79     97 / 102    117 / 109    152 / 138    213 / 203                 413 / 364
+  //   64, 1430                              98 / 100                 142 / 139                 311 / 271
+  //   64, 1953                                                                                              485 / 411
+  //   64, 2700                                                                                              655 / 499
+  //   64, 3906                             172 / 142                (byte tables from 8 million points on)
+  //   48, 977                   93 / 93    108 / 112    130 / 125    163 / 154    238 / 232
+  // The line is where the kernel in parts is faster for good: below it most workgroups have one task, and nothing to hide the
+  // codebook's way from the L2 behind.
+  int dev = 0, cus = 0;
+  IVFPQ_HIP_TRY(hipGetDevice(&dev));
+  IVFPQ_HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
+  if (cus < 1) cus = 1;
+  const bool table_parts = ix->dsub == 2 && (!byte_table_shape(ix) || Q > (int64_t)4 * cus || ix->N >= (int64_t)2048 * ix->nlist);
+  a.head_max = table_parts ? lpp_head_max(ix->D) : lm_head_max(ix->M, ix->D);
   a.k = k;
   a.mode = mode;
 
@@ -1995,11 +2052,6 @@ int launch_scan_list_major(const ivfpq_index *ix, const float *d_queries, int64_
   int rc = launch_probe_bounds(ix, d_queries, Q, nprobe, d_probe_ids, r2, mode, d_query_radii, d_probe_lb, s, a.cnt,
                                lm_counters(ix->nlist));
   if (rc) return rc;
-
-  int dev = 0, cus = 0;
-  IVFPQ_HIP_TRY(hipGetDevice(&dev));
-  IVFPQ_HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
-  if (cus < 1) cus = 1;
 
   // ---- the first lists of every query: they give the bound tau_q that filters the rest ----
   // One list per query under distance scoring: the head pass ranks it list-major (queries that
@@ -2041,7 +2093,7 @@ int launch_scan_list_major(const ivfpq_index *ix, const float *d_queries, int64_
     hipLaunchKernelGGL(lm_pairs_kernel, dim3(qgrid), dim3(256), 0, s, a, 0, 1);
     hipLaunchKernelGGL(lm_offsets_kernel, dim3(1), dim3(1024), 0, s, a);
     hipLaunchKernelGGL(lm_pairs_kernel, dim3(qgrid), dim3(256), 0, s, a, 1, 1);
-    rc = head_bytes ? launch_lm_byte_head(a, r2, cus, s) : launch_lm_scan<true>(ix, a, r2, cus, s);
+    rc = head_bytes ? launch_lm_byte_head(a, r2, cus, s) : (table_parts ? launch_lm_pair_head(a, r2, cus, s) : launch_lm_scan<true>(ix, a, r2, cus, s));
     if (rc) return rc;
     if (head_bytes) {
       hipLaunchKernelGGL(lm_sort_out_kernel, dim3((unsigned)((Q + 255) / 256)), dim3(256), 0, s, a, 0);
@@ -2070,7 +2122,7 @@ int launch_scan_list_major(const ivfpq_index *ix, const float *d_queries, int64_
   // 3903, 8.9 2581 / 2460, 9.8 4057 / 3984, 64 subspaces 2.9 3436 / 3962, 4.9 3902 / 3903, 6.8 4248 / 3936;
   // 16 subspaces 2.9 2343 / 2276, 9.8 2742 / 2302.  So from 6 on, with 16 subspaces from 2 on, and with the
   // hit counts, whose byte sums are the result.
-  const bool bytes = ix->N >= (int64_t)(mode == 0 && ix->M > 16 ? 6 : 2) * k * ix->nlist && ix->max_list_len < (1 << 20) && !(get_scan_ablate() & 8);
+  const bool bytes = byte_table_shape(ix) && ix->N >= (int64_t)(mode == 0 && ix->M > 16 ? 6 : 2) * k * ix->nlist && ix->max_list_len < (1 << 20) && !(get_scan_ablate() & 8);
   a.group = bytes ? LMB_G : LM_G;
   // Many probes: the nearest few lists first, merged, so that the rest is filtered by a k-th distance
   // over eight lists instead of one.  That costs five launches (14 us of 10 000 queries) where the bounds rule
@@ -2099,7 +2151,7 @@ int launch_scan_list_major(const ivfpq_index *ix, const float *d_queries, int64_
     hipLaunchKernelGGL(lm_pairs_kernel, dim3(pair_grid), dim3(256), 0, s, a, 0, 0);
     hipLaunchKernelGGL(lm_offsets_kernel, dim3(1), dim3(1024), 0, s, a);
     hipLaunchKernelGGL(lm_pairs_kernel, dim3(pair_grid), dim3(256), 0, s, a, 1, 0);
-    rc = bytes ? launch_lm_byte(a, r2, cus, s) : launch_lm_scan<false>(ix, a, r2, cus, s);
+    rc = bytes ? launch_lm_byte(a, r2, cus, s) : (byte_table_shape(ix) ? launch_lm_scan<false>(ix, a, r2, cus, s) : launch_lm_pair_t<100, false>(a, r2, cus, s));
     if (rc) return rc;
     if (in_place) {
       a.list_redo = p1 == nprobe && Q > 4096 ? 1 : 0;

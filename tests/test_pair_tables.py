@@ -1,0 +1,78 @@
+"""fp32 tables of two queries that go by in parts (lm_pair_kernel): searches that take them, at the edges of blocks, segments
+and of what the head pass holds, against the oracle bit for bit."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2312_01712_amd import workloads as wl
+
+
+def _index(rng, D, M, sizes, spread=0.3, centre=0.05):
+    offs = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+    N, nlist = int(offs[-1]), len(sizes)
+    return wl.Index(N=N, D=D, nlist=nlist, M=M, centroids=(centre * rng.normal(size=(nlist, D))).astype(np.float32),
+                    codebooks=(spread * rng.normal(size=(M, 256, D // M))).astype(np.float32), list_offsets=offs,
+                    codes=rng.integers(0, 256, size=(N, M), dtype=np.uint8), ids=rng.permutation(N).astype(np.int64))
+
+
+def _same(got, want, what):
+    got = [x.cpu().numpy() for x in got]
+    assert np.array_equal(got[0], want[0]) and np.array_equal(got[1].view(np.uint32), want[1].view(np.uint32)), what
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("D,M", [(96, 48), (128, 64), (200, 100)])
+@pytest.mark.parametrize("k,radius", [(1, 0.6), (128, 0.6), (10, 0.05), (100, np.inf)])
+def test_segments_and_groups(D, M, k, radius):
+    """Lists of a block, of whole segments and one point more or less, of what the head pass holds (4600 to 4750 points) and
+    more; groups of one and two queries; points alike; radii per query, some of them not a number; few candidate slots."""
+    import torch
+    from paper_2312_01712_amd import binding as b
+    rng = np.random.default_rng(M + k)
+    sizes = np.array([2048, 2047, 2049, 4097, 4600, 4672, 4750, 6200, 64, 65, 63, 1, 0, 128, 129, 300, 513, 511, 1100, 700] + [90] * 12)
+    nprobe, distinct, reps = 9, 61, 17   # 1037 queries
+    idx = _index(rng, D, M, sizes)
+    idx.codes[100:1500] = idx.codes[100]   # more equal distances than the head pass can rank
+    q = (idx.centroids[rng.integers(0, len(sizes), distinct)] + 0.3 * rng.normal(size=(distinct, D))).astype(np.float32)
+    radii = np.full(M, radius * np.sqrt(D / M), dtype=np.float32)
+    gi = b.IvfPqIndex.from_index(idx)
+    try:
+        dq = torch.from_numpy(q).cuda().repeat(reps, 1)
+        want = oracle.search(q, idx, nprobe, k, radii, threads=8)
+        tiled = (np.tile(want[0], (reps, 1)), np.tile(want[1], (reps, 1)))
+        own = np.tile(radii, (distinct, 1)) * rng.uniform(0.7, 1.3, (distinct, M)).astype(np.float32)
+        own[::2, 3] = np.nan
+        rq = torch.from_numpy(own).cuda().repeat(reps, 1)
+        ref = [x.cpu().numpy() for x in gi.search(dq, nprobe, k, None, query_radii=rq, strategy=b.SCAN_QUERY_MAJOR)]
+        for cap in (0, 64):
+            b.set_option("lm_cap", cap)
+            _same(gi.search(dq, nprobe, k, radii, strategy=b.SCAN_LIST_MAJOR), tiled, (cap, "whole batch"))
+            _same(gi.search(dq[:distinct].contiguous(), nprobe, k, radii, strategy=b.SCAN_LIST_MAJOR), want, (cap, "small batch"))
+            _same(gi.search(dq, nprobe, k, None, query_radii=rq, strategy=b.SCAN_LIST_MAJOR), ref, (cap, "radii per query"))
+    finally:
+        b.set_option("lm_cap", 0)
+        gi.close()
+
+
+@pytest.mark.gpu
+def test_100_subspaces_with_little_workspace():
+    """AUTO, and a request for the list-major scan, with a workspace that only has room for the query-major one; hit counts."""
+    import torch
+    from paper_2312_01712_amd import binding as b
+    rng = np.random.default_rng(5)
+    D, M, nprobe, k, Q = 200, 100, 16, 10, 1100
+    idx = _index(rng, D, M, rng.integers(40, 400, size=64))
+    q = (idx.centroids[rng.integers(0, 64, Q)] + 0.3 * rng.normal(size=(Q, D))).astype(np.float32)
+    radii = np.full(M, 0.6 * np.sqrt(2), dtype=np.float32)
+    gi = b.IvfPqIndex.from_index(idx)
+    dq = torch.from_numpy(q).cuda()
+    small = gi.workspace(Q, nprobe, k, strategy=b.SCAN_QUERY_MAJOR)
+    want = oracle.search(q, idx, nprobe, k, radii, threads=8)
+    assert gi.resolve_strategy(Q, nprobe, k) == b.SCAN_LIST_MAJOR
+    assert gi.resolve_strategy(Q, nprobe, k, mode=1) == b.SCAN_QUERY_MAJOR
+    for strategy in (b.SCAN_AUTO, b.SCAN_LIST_MAJOR):
+        _same(gi.search(dq, nprobe, k, radii, strategy=strategy), want, (strategy, "own workspace"))
+        _same(gi.search(dq, nprobe, k, radii, strategy=strategy, workspace=small), want, (strategy, "small workspace"))
+    ref = oracle.search(q, idx, nprobe, k, radii, threads=8, mode=1)
+    _same(gi.search(dq, nprobe, k, radii, mode=1, strategy=b.SCAN_LIST_MAJOR), ref, "hit counts")
+    gi.close()

@@ -155,7 +155,7 @@ inline void plan_list_major_tables(LmWorkspace &w, int32_t nlist, int64_t Q, int
   w.cand = off;
   w.total = off;
 }
-// Shapes whose list-major kernels have byte tables.
+// Shapes whose list-major kernels have byte tables for everything.
 inline bool byte_table_shape(const ivfpq_index *ix) {
   return (ix->M == 48 && ix->dsub == 2) || (ix->M == 64 && ix->dsub == 2) || (ix->M == 16 && ix->dsub == 4);
 }

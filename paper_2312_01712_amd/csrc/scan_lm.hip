@@ -1485,7 +1485,9 @@ constexpr int LMS_NW = 16;
 // of 32 probes, k = 1000: 581 us with a query a wavefront, 224 so.
 constexpr int LMS_PIECE = 512;
 constexpr int LMS_QUEUE = LMQ_WORDS;
-constexpr size_t lms_lds(int mt, int dsub) { return (size_t)mt * 1024 * dsub + (size_t)LMS_NW * (LMS_QUEUE * 8 + mt * 4) + 16; }
+// Rows of the codebook in LDS.  200 KiB of 100 rows do not fit: the last 36 are looked up in the L2.
+constexpr int lms_rows(int mt) { return mt <= 64 ? mt : 64; }
+constexpr size_t lms_lds(int mt, int dsub) { return (size_t)lms_rows(mt) * 1024 * dsub + (size_t)LMS_NW * (LMS_QUEUE * 8 + mt * 4) + 16; }
 #define CONSTANT __attribute__((address_space(4)))
 
 // WIDE: behind the wide selection's first lists.  A candidate's distance and row take its slot; those beyond the bound
@@ -1500,7 +1502,9 @@ enum { LMS_MERGE, LMS_WIDE, LMS_PLACE };
 constexpr int LMS_SHARE = 128;   // slots of such a piece
 template <int MT, int DSUB, int HOW>
 __global__ __launch_bounds__(LMS_NW * 64) __attribute__((amdgpu_waves_per_eu(4))) void lm_settle_kernel(LmArgs a, RadiiSq r2) {
-  constexpr int NCH = MT / 16;
+  constexpr int NCH = MT / 16, TAIL = MT % 16, ROWS = lms_rows(MT);
+  constexpr bool AT_ONCE = MT <= 64;
+  static_assert(AT_ONCE ? TAIL == 0 : TAIL == 4, "16-byte chunks, and one of 4 bytes");
   constexpr bool WIDE = HOW == LMS_WIDE, PLACE = HOW == LMS_PLACE;
   extern __shared__ __align__(16) unsigned char smem[];
   LDS unsigned char *smem3 = (LDS unsigned char *)smem;
@@ -1541,10 +1545,10 @@ __global__ __launch_bounds__(LMS_NW * 64) __attribute__((amdgpu_waves_per_eu(4))
     nactive = nqueries * pieces;
     if ((int)blockIdx.x >= nactive) return;
   }
-  for (int i = tid; i < MT * 256 * DSUB / 4; i += LMS_NW * 64)
+  for (int i = tid; i < ROWS * 256 * DSUB / 4; i += LMS_NW * 64)
     ((LDS floatx4 *)smem3)[i] = ((const floatx4 *)a.codebooks)[i];
-  LDS uint32_t *qd = (LDS uint32_t *)(smem3 + (size_t)MT * 1024 * DSUB) + wave * LMS_QUEUE * 2, *qrow = qd + LMS_QUEUE;
-  LDS float *sr2 = (LDS float *)(smem3 + (size_t)MT * 1024 * DSUB + (size_t)LMS_NW * LMS_QUEUE * 8) + wave * MT;   // r_m^2 of the wavefront's query
+  LDS uint32_t *qd = (LDS uint32_t *)(smem3 + (size_t)ROWS * 1024 * DSUB) + wave * LMS_QUEUE * 2, *qrow = qd + LMS_QUEUE;
+  LDS float *sr2 = (LDS float *)(smem3 + (size_t)ROWS * 1024 * DSUB + (size_t)LMS_NW * LMS_QUEUE * 8) + wave * MT;   // r_m^2 of the wavefront's query
   if (tid == 0) *taken = 0u;
   __syncthreads();   // from here on every wavefront is by itself, until PLACE has settled all
   const int k = a.k;
@@ -1639,17 +1643,37 @@ __global__ __launch_bounds__(LMS_NW * 64) __attribute__((amdgpu_waves_per_eu(4))
         }
       };
       uintptr_t qaddr = (uintptr_t)(a.queries + q * a.D);
-      if (lane < MT) {
-        float r = r2.v[lane];
+      for (int m = lane; m < MT; m += 64) {
+        float r = r2.v[m];
         if (a.query_radii) {
-          r = a.query_radii[q * MT + lane];
+          r = a.query_radii[q * MT + m];
           r = r * r;
         }
-        sr2[lane] = r;
+        sr2[m] = r;
       }
       uint2 e = slot_of(n0), en = slot_of(n0 + 64);
-      uint32_t cw[MT / 4];   // one word per four subspaces
-      codes_of(e, where_of(e.x), cw);
+      // One word per four subspaces: a candidate's codes all at once, or, where their registers spill, 16 at a time.
+      uint32_t cw[AT_ONCE ? MT / 4 : 4];
+      const uint8_t *here = nullptr;
+      uint32_t chunk = 0;   // from a candidate's 16 codes to the next
+      int32_t last = 0;     // from its last 16 to those behind them
+      auto load_chunk = [&](const uint8_t *src, uint32_t *w) __attribute__((always_inline)) {
+        const uintx4 v = *(const GLOBAL uintx4 *)src;
+#pragma unroll
+        for (int x = 0; x < 4; ++x) w[x] = v[x];
+      };
+      auto go_to = [&](const uint2 &e, const Where &w) __attribute__((always_inline)) {
+        const uint32_t i = e.y - (uint32_t)w.o0;
+        here = a.codes + w.blk * ivfpq_block_bytes(MT) + (int64_t)(i >> 6) * 1024 + (i & 63u) * 16;
+        chunk = (uint32_t)((w.o1 - w.o0 + 63) >> 6) << 10;
+        last = (int32_t)chunk - (int32_t)(i >> 6) * 768 - (int32_t)(i & 63u) * 12;
+      };
+      if constexpr (AT_ONCE) {
+        codes_of(e, where_of(e.x), cw);
+      } else {
+        go_to(e, where_of(e.x));
+        load_chunk(here, cw);
+      }
       for (int u = n0; u < n; u += 64) {
         asm volatile("" : "+s"(qaddr) : : "memory");   // (the query's row and radii are read anew: kept across groups they spill)
         const CONSTANT float *qp = (const CONSTANT float *)qaddr;
@@ -1657,31 +1681,35 @@ __global__ __launch_bounds__(LMS_NW * 64) __attribute__((amdgpu_waves_per_eu(4))
         const uint2 enn = slot_of(u + 128);
         const float *cp = a.centroids + (int64_t)e.x * (MT * DSUB);
         float dist = 0.0f;
-        uint32_t cwn[MT / 4];
+        uint32_t cwn[AT_ONCE ? MT / 4 : 1];
         // (one piece of code for all steps: with the loads of all hoisted to the front the registers spill)
         constexpr int STEP = DSUB == 2 ? 16 : 4;   // subspaces whose part of the centroid's row is requested together
         constexpr int LK = MT == 48 ? 8 : 4;       // look-ups in flight (more spill)
-#pragma unroll 1
-        for (int m0 = 0; m0 < MT; m0 += STEP) {
-          floatx4 cv[STEP * DSUB / 4];
+        typedef float entry __attribute__((ext_vector_type(DSUB)));
+        // `count` subspaces from m0 on, their codes in w; behind the centroid's rows, which are wanted sooner, `then` is requested
+        auto add_up = [&](int m0, auto count, const uint32_t *w, auto then) __attribute__((always_inline)) {
+          constexpr int N = decltype(count)::value;
+          floatx4 cv[N * DSUB / 4];
 #pragma unroll
-          for (int x = 0; x < STEP * DSUB / 4; ++x) cv[x] = *(const GLOBAL floatx4 *)(cp + m0 * DSUB + 4 * x);
-          if (m0 + STEP == MT) codes_of(en, wn, cwn);   // behind this group's last rows, which are wanted sooner
-          uint32_t w[STEP / 4];
-#pragma unroll
-          for (int x = 0; x < STEP / 4; ++x) w[x] = cw[x];
-#pragma unroll
-          for (int x = STEP / 4; x < MT / 4; ++x) cw[x - STEP / 4] = cw[x];
+          for (int x = 0; x < N * DSUB / 4; ++x) cv[x] = *(const GLOBAL floatx4 *)(cp + m0 * DSUB + 4 * x);
+          then();
           const LDS unsigned char *rows = smem3 + m0 * 1024 * DSUB;
-          typedef float entry __attribute__((ext_vector_type(DSUB)));
 #pragma unroll
-          for (int h = 0; h < STEP; h += LK) {
+          for (int h = 0; h < N; h += LK) {
             entry ev[LK];
             floatx4 rm2[LK / 4];
+            if (ROWS == MT || m0 < ROWS) {
 #pragma unroll
-            for (int x = 0; x < LK; ++x) {
-              const uint32_t code = (w[(h + x) >> 2] >> (8 * (x & 3))) & 0xFFu;
-              ev[x] = *(const LDS entry *)(rows + (h + x) * 1024 * DSUB + code * (4 * DSUB));
+              for (int x = 0; x < LK; ++x) {
+                const uint32_t code = (w[(h + x) >> 2] >> (8 * (x & 3))) & 0xFFu;
+                ev[x] = *(const LDS entry *)(rows + (h + x) * 1024 * DSUB + code * (4 * DSUB));
+              }
+            } else {
+#pragma unroll
+              for (int x = 0; x < LK; ++x) {
+                const uint32_t code = (w[(h + x) >> 2] >> (8 * (x & 3))) & 0xFFu;
+                ev[x] = *(const GLOBAL entry *)(uniform_ptr(a.codebooks + (m0 + h + x) * 256 * DSUB) + code * (4 * DSUB));
+              }
             }
 #pragma unroll
             for (int x = 0; x < LK / 4; ++x) rm2[x] = *(const LDS floatx4 *)(sr2 + m0 + h + 4 * x);
@@ -1699,6 +1727,40 @@ __global__ __launch_bounds__(LMS_NW * 64) __attribute__((amdgpu_waves_per_eu(4))
             }
             __builtin_amdgcn_sched_barrier(0);
           }
+        };
+        std::integral_constant<int, STEP> whole;
+        if constexpr (AT_ONCE) {
+#pragma unroll 1
+          for (int m0 = 0; m0 < MT; m0 += STEP) {
+            uint32_t w[STEP / 4];
+#pragma unroll
+            for (int x = 0; x < STEP / 4; ++x) w[x] = cw[x];
+            add_up(m0, whole, w, [&]() __attribute__((always_inline)) {
+              if (m0 + STEP == MT) codes_of(en, wn, cwn);
+#pragma unroll
+              for (int x = STEP / 4; x < MT / 4; ++x) cw[x - STEP / 4] = cw[x];
+            });
+          }
+        } else {
+#pragma unroll 1
+          for (int m0 = 0; m0 < MT - TAIL; m0 += STEP) {
+            uint32_t w[STEP / 4];
+#pragma unroll
+            for (int x = 0; x < STEP / 4; ++x) w[x] = cw[x];
+            add_up(m0, whole, w, [&]() __attribute__((always_inline)) {
+              if (m0 + STEP < MT - TAIL) {
+                here += chunk;
+                load_chunk(here, cw);
+              } else {
+                cw[0] = *(const GLOBAL uint32_t *)(here + last);
+              }
+            });
+          }
+          const uint32_t w = cw[0];
+          add_up(MT - TAIL, std::integral_constant<int, TAIL == 0 ? STEP : TAIL>{}, &w, [&]() __attribute__((always_inline)) {
+            go_to(en, wn);
+            load_chunk(here, cw);
+          });
         }
         const uint32_t bits = __float_as_uint(dist);
         if constexpr (WIDE) {
@@ -1727,8 +1789,10 @@ __global__ __launch_bounds__(LMS_NW * 64) __attribute__((amdgpu_waves_per_eu(4))
         }
         e = en;
         en = enn;
+        if constexpr (AT_ONCE) {
 #pragma unroll
-        for (int x = 0; x < MT / 4; ++x) cw[x] = cwn[x];
+          for (int x = 0; x < MT / 4; ++x) cw[x] = cwn[x];
+        }
       }
       if (HOW == LMS_MERGE && changed) {
 #pragma unroll
@@ -1852,6 +1916,8 @@ int launch_lm_settle(const LmArgs &a, const RadiiSq &r2, int cus, hipStream_t s)
   const int grid = a.Q < cus ? (int)a.Q : cus;   // (a workgroup without a query of its own leaves at once)
   if (a.M == 48) return launch_lm_settle_t<48, 2, HOW>(a, r2, grid, s);
   if (a.M == 64) return launch_lm_settle_t<64, 2, HOW>(a, r2, grid, s);
+  if constexpr (HOW != LMS_WIDE)
+    if (a.M == 100) return launch_lm_settle_t<100, 2, HOW>(a, r2, grid, s);
   return launch_lm_settle_t<16, 4, HOW>(a, r2, grid, s);
 }
 
@@ -1863,6 +1929,7 @@ int launch_lm_byte_m(const LmArgs &a, const RadiiSq &r2, int grid, hipStream_t s
 }
 
 int launch_lm_byte(const LmArgs &a, const RadiiSq &r2, int grid, hipStream_t s) {
+  if (a.M == 100) return launch_lm_part_t<100, 2>(a, r2, grid, s);
   if (a.parts && a.mode == 0) return a.M == 48 ? launch_lm_part_t<48, 2>(a, r2, grid, s) : launch_lm_part_t<64, 2>(a, r2, grid, s);
   if (a.mode == 0) return launch_lm_byte_m<0>(a, r2, grid, s);
   if (a.mode == 1) return launch_lm_byte_m<1>(a, r2, grid, s);
@@ -2120,9 +2187,9 @@ int launch_scan_list_major(const ivfpq_index *ix, const float *d_queries, int64_
   // / with byte tables at a mean list of so many k: data with cluster structure, 48 subspaces 2.9 2363 / 1887,
   // 6.8 2929 / 1992, 9.8 3275 / 2064; data without, 48 subspaces 2.9 3008 / 3809, 4.9 3405 / 3819, 6.8 3666 /
   // 3903, 8.9 2581 / 2460, 9.8 4057 / 3984, 64 subspaces 2.9 3436 / 3962, 4.9 3902 / 3903, 6.8 4248 / 3936;
-  // 16 subspaces 2.9 2343 / 2276, 9.8 2742 / 2302.  So from 6 on, with 16 subspaces from 2 on, and with the
+  // 16 subspaces 2.9 2343 / 2276, 9.8 2742 / 2302; 100 (2000 queries, 64 probes) without 9.8 4768 / 3810, k = 10 4623 / 2768.  So from 6 on, with 16 subspaces from 2 on, and with the
   // hit counts, whose byte sums are the result.
-  const bool bytes = byte_table_shape(ix) && ix->N >= (int64_t)(mode == 0 && ix->M > 16 ? 6 : 2) * k * ix->nlist && ix->max_list_len < (1 << 20) && !(get_scan_ablate() & 8);
+  const bool bytes = ix->N >= (int64_t)(mode == 0 && ix->M > 16 ? 6 : 2) * k * ix->nlist && ix->max_list_len < (1 << 20) && !(get_scan_ablate() & 8);
   a.group = bytes ? LMB_G : LM_G;
   // Many probes: the nearest few lists first, merged, so that the rest is filtered by a k-th distance
   // over eight lists instead of one.  That costs five launches (14 us of 10 000 queries) where the bounds rule
@@ -2134,12 +2201,14 @@ int launch_scan_list_major(const ivfpq_index *ix, const float *d_queries, int64_
   //   64, without structure      2239 / 1930  3994 / 3062  5584 / 4126  7298 / 5318  13494 / 9868
   //   16, clustered               315 / 330    389 / 403    460 / 474    541 / 555    965 / 980
   // (2000 queries, 64 clustered: 131 / 143 at 32 probes, 143 / 156 at 64).  The line is where the two rounds cost
-  // clustered data 3 % or less of a large batch.
+  // clustered data 3 % or less of a large batch.  With 100 subspaces, whose filtering and bounds are dearer, they don't pay where
+  // lists have a structure at all: 10 000 queries of clustered data 666 / 700, 1000 165 / 202, two components a list, 4000
+  // 10456 / 11065, radii per query 1150 / 1231; without structure, 2000, k = 10 2768 / 2774, k = 100 3809 / 3096 (7619 query-major).
   // The candidates of byte tables of distances are settled where they stand by the wavefronts that share a workgroup's
   // queries, and ranked behind that; up to 64 queries a workgroup.  Queries without a result of the head pass (LM_SEEDED), and
   // larger batches, take a wavefront a query (lm_sort_out_kernel, lm_settle_kernel<LMS_MERGE>).
   const bool in_place = bytes && mode == 0 && !head_bytes && Q <= (int64_t)64 * cus;
-  const int split = bytes && nprobe - w.first >= 2 * LM_STAGE1 + 32 ? w.first + LM_STAGE1 : nprobe;
+  const int split = bytes && ix->M != 100 && nprobe - w.first >= 2 * LM_STAGE1 + 32 ? w.first + LM_STAGE1 : nprobe;
   for (int p0 = main_first, p1 = split; p0 < nprobe; p0 = p1, p1 = nprobe) {
     a.p0 = p0;
     a.p1 = p1;

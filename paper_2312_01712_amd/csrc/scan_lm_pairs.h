@@ -89,7 +89,7 @@ __global__ __launch_bounds__(LPP_NW * 64) __attribute__((amdgpu_waves_per_eu(LPP
         r[i] = *(const GLOBAL uintx4 *)(sp + (uint32_t)(lane * 16));
       } else {
         const GLOBAL uint8_t *sp = uniform_ptr(base + (int64_t)(MT / 16) * nb * 1024 + (int64_t)blk * 256);
-        r[i][0] = *(const GLOBAL uint32_t *)(sp + (uint32_t)(lane * 4));
+        r[i] = uintx4{*(const GLOBAL uint32_t *)(sp + (uint32_t)(lane * 4)), 0u, 0u, 0u};
       }
     }
   };

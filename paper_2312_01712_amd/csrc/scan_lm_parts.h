@@ -13,7 +13,8 @@
 // The points of a list are scanned LMP_SEG at a time, their sums in registers; a longer list costs another table for each.
 // A part's codes are one 16-byte chunk of the lists' layout.
 // 1M x 96, 64 probes, 10 000 queries, both passes: 2.59 ms with lm_byte_kernel, 2.21 so; 1M x 128, 2000 queries of 32 probes,
-// the stages of k = 1000: 270 and 254 us.
+// the stages of k = 1000: 270 and 254 us.  100 subspaces, for which whole tables do not fit a CU: 2000 queries of 64 probes,
+// without structure, a search with fp32 tables of two queries (lm_pair_kernel) 4768 us, so 3810 (k = 10: 4623, 2768).
 
 constexpr int LMP_NW = 8;        // wavefronts of a workgroup
 constexpr int LMP_WG = 2;        // workgroups per CU: 4 wavefronts per SIMD, 128 vector registers each
@@ -27,10 +28,10 @@ constexpr size_t lmp_lds(int mt, int dsub) {
   return LMP_BUF + (size_t)LMB_G * mt * (4 * dsub + 4) + (size_t)mt * 4 + LMP_QUEUE * 4 + LMP_SMALL * 4;
 }
 
-// What is wanted of a task, kept between its request and its use: lane m holds subspace m.
-template <int DSUB>
+// What is wanted of a task, kept between its request and its use: lane m holds subspaces m and, of H = 2, 64 + m.
+template <int DSUB, int H>
 struct LmpFetch {
-  float q[DSUB], c[DSUB], r2, tau;
+  float q[H][DSUB], c[H][DSUB], r2[H], tau;
   uint32_t n;
   int32_t qid;
 };
@@ -69,8 +70,10 @@ __device__ __forceinline__ void lmp_spill(const LmArgs &a, const LDS int32_t *sq
 template <int MT, int DSUB>
 __global__ __launch_bounds__(LMP_NW * 64) __attribute__((amdgpu_waves_per_eu(LMP_WG * LMP_NW / 4))) void lm_part_kernel(LmArgs a, RadiiSq r2) {
   constexpr int NW = LMP_NW, NB = LMP_NB;
-  constexpr int P = MT / LMP_PART;
-  static_assert(MT % LMP_PART == 0 && MT <= 64 && P >= 3 && DSUB == 2, "whole chunks, a lane per subspace; the queue is read, cleared and filled again in three parts");
+  constexpr int P = (MT + LMP_PART - 1) / LMP_PART, TAIL = MT % LMP_PART;   // parts; subspaces of the last one where it is short
+  constexpr int H = (MT + 63) / 64;   // subspaces of a lane
+  static_assert((TAIL == 0 || TAIL == 4) && MT <= 128 && P >= 3 && DSUB == 2, "16-byte chunks and one of 4 bytes; the queue is read, cleared and filled again in three parts");
+  static_assert(MT * LMB_TOP < 1 << 16, "sums");
   static_assert(NW == LMB_G, "a wavefront per query of a group forms its parameters");
   extern __shared__ __align__(16) unsigned char smem[];
   LDS unsigned char *smem3 = (LDS unsigned char *)smem;
@@ -106,7 +109,8 @@ __global__ __launch_bounds__(LMP_NW * 64) __attribute__((amdgpu_waves_per_eu(LMP
   constexpr int STEPS = 8;
   uintx4 ent[STEPS];
   auto load_rows = [&](int part) __attribute__((always_inline)) {
-    const GLOBAL uint8_t *rows = uniform_ptr(a.cb_split + (int64_t)(part * LMP_PART + (wave >> 1) * 4) * (256 * 8));
+    const int m0 = part * LMP_PART + (wave >> 1) * 4;
+    const GLOBAL uint8_t *rows = uniform_ptr(a.cb_split + (int64_t)(TAIL == 0 || m0 < MT ? m0 : MT - 4) * (256 * 8));   // no such rows: the last ones
 #pragma unroll
     for (int x = 0; x < STEPS; ++x)
       ent[x] = *(const GLOBAL uintx4 *)(rows + (uint32_t)((lane >> 4) * 4096 + (wave & 1) * 2048 + lmp_entry(x, lane) * 16));
@@ -139,40 +143,53 @@ __global__ __launch_bounds__(LMP_NW * 64) __attribute__((amdgpu_waves_per_eu(LMP
     return (int64_t)(((uint64_t)hi << 32) | lo);
   };
   // wavefront g brings the parameters of query g: a lane per subspace
-  LmpFetch<DSUB> fx;
+  LmpFetch<DSUB, H> fx;
   auto fetch_params = [&](const int2 &pv) __attribute__((always_inline)) {
     const int c = __builtin_amdgcn_readlane(pv.y, 0);
     const int q0 = __builtin_amdgcn_readlane(pv.x, 0);   // a task's first query exists
     fx.qid = __builtin_amdgcn_readlane(pv.x, wave);
     const int64_t q = fx.qid >= 0 ? fx.qid : q0;
-    const int m = lane < MT ? lane : MT - 1;
-    const float2 qv = *reinterpret_cast<const float2 *>(a.queries + q * a.D + 2 * m);
-    const float2 cv = *reinterpret_cast<const float2 *>(a.centroids + (int64_t)c * a.D + 2 * m);
-    fx.q[0] = qv.x; fx.q[1] = qv.y; fx.c[0] = cv.x; fx.c[1] = cv.y;
-    fx.r2 = a.query_radii ? a.query_radii[q * MT + m] : r2.v[m];   // (squared where it is used)
+#pragma unroll
+    for (int x = 0; x < H; ++x) {
+      const int m = lane + 64 * x < MT ? lane + 64 * x : MT - 1;
+      const float2 qv = *reinterpret_cast<const float2 *>(a.queries + q * a.D + 2 * m);
+      const float2 cv = *reinterpret_cast<const float2 *>(a.centroids + (int64_t)c * a.D + 2 * m);
+      fx.q[x][0] = qv.x; fx.q[x][1] = qv.y; fx.c[x][0] = cv.x; fx.c[x][1] = cv.y;
+      fx.r2[x] = a.query_radii ? a.query_radii[q * MT + m] : r2.v[m];   // (squared where it is used)
+    }
     fx.tau = a.tau[q * a.tau_stride];
     fx.n = a.gcnt[q];
   };
-  // ... and writes them to the records and to set `par` of the small words
+  // ... and writes them to the records and to set `par` of the small words.  LOST: every rounding of the fp32 sums of a point's
+  // distance and of what is formed here, 2^-23 each, at most MT + 6.
+  constexpr float LOST = MT <= 64 ? 1.0e-5f : 1.6e-5f;
+  static_assert((MT + 6) * 1.1920929e-7f < LOST, "roundings");
   auto put_params = [&](int par) __attribute__((always_inline)) {
-    const bool on = lane < MT;
-    const int at = lane * LMB_G + wave;
-    float rm2 = fx.r2;
-    if (a.query_radii) rm2 = fminf(rm2 * rm2, __builtin_inff());   // (a NaN cuts nothing off, like an infinite radius)
-    float res[DSUB];
-#pragma unroll
-    for (int j = 0; j < DSUB; ++j) res[j] = fx.q[j] - fx.c[j];
+    bool on[H];
+    float rm2[H], res[H][DSUB], rr[H], far[H];
     const float tau = __uint_as_float((uint32_t)__builtin_amdgcn_readfirstlane((int)__float_as_uint(fx.tau)));
     // A byte holds what an entry GAINS on the clamp: s (cap_m - |r - e|^2), cap_m being r_m^2 or, where that is smaller,
     // the unit's end: the largest r_m^2 (no table value exceeds it), or, where that is wider, four times the mean value of
     // a point within tau.  Rounded up, so that the sum of a point's bytes is no less than what it gains in all, and
     // cut off at 0 by the conversion itself: entries outside the radius (most of them), infinitely far ones and those
     // that are not a number lose nothing.  A point within tau gains at least s (sum of cap_m - tau).
-    float rr = 0.0f;
+    float farthest = 0.0f, widest = 0.0f;
 #pragma unroll
-    for (int j = 0; j < DSUB; ++j) rr = fmaf(res[j], res[j], rr);
-    float far = on ? sqrtf(rr) + sqrtf(semax[lane]) : 0.0f;
-    far *= far;
+    for (int x = 0; x < H; ++x) {
+      on[x] = lane + 64 * x < MT;
+      rm2[x] = fx.r2[x];
+      if (a.query_radii) rm2[x] = fminf(rm2[x] * rm2[x], __builtin_inff());   // (a NaN cuts nothing off, like an infinite radius)
+      rr[x] = 0.0f;
+#pragma unroll
+      for (int j = 0; j < DSUB; ++j) {
+        res[x][j] = fx.q[x][j] - fx.c[x][j];
+        rr[x] = fmaf(res[x][j], res[x][j], rr[x]);
+      }
+      far[x] = on[x] ? sqrtf(rr[x]) + sqrtf(semax[lane + 64 * x]) : 0.0f;
+      far[x] *= far[x];
+      farthest = fmaxf(farthest, far[x]);
+      widest = fmaxf(widest, on[x] ? rm2[x] : 0.0f);
+    }
     auto over_lanes = [&](auto fold) __attribute__((always_inline)) {
       fold([](float v) __attribute__((always_inline)) { return xor_f32<32>(v); });
       fold([](float v) __attribute__((always_inline)) { return xor_f32<16>(v); });
@@ -181,23 +198,28 @@ __global__ __launch_bounds__(LMP_NW * 64) __attribute__((amdgpu_waves_per_eu(LMP
       fold([](float v) __attribute__((always_inline)) { return xor_f32<2>(v); });
       fold([](float v) __attribute__((always_inline)) { return xor_f32<1>(v); });
     };
-    float rmax = a.rmax, farthest = far;
+    float rmax = a.rmax;
     over_lanes([&](auto other) __attribute__((always_inline)) { farthest = fmaxf(farthest, other(farthest)); });
     if (a.query_radii) {
-      rmax = on ? rm2 : 0.0f;
+      rmax = widest;
       over_lanes([&](auto other) __attribute__((always_inline)) { rmax = fmaxf(rmax, other(rmax)); });
     }
     const float cap = fmaxf(fminf(rmax, tau * (4.0f / (float)MT)), 1e-30f);
     const float s = ((float)LMB_TOP - 0.6f) / fmaf(farthest, LMP_REL, cap);   // (the error's room included; infinite radii and no k-th distance: 0)
-    const float most = fminf(rm2, cap) * s, err = fmaf(s * far, LMP_REL, LMP_RAISE);
-    if (on) {
+    float least = 0.0f;
 #pragma unroll
-      for (int j = 0; j < DSUB; ++j) srec[at * DSUB + j] = split_bf16(2.0f * s * res[j]);
-      scon[at] = most - s * rr + (0.5f + err);   // (rounded to nearest: half a unit up)
+    for (int x = 0; x < H; ++x) {
+      const float most = fminf(rm2[x], cap) * s, err = fmaf(s * far[x], LMP_REL, LMP_RAISE);
+      if (on[x]) {
+        const int at = (lane + 64 * x) * LMB_G + wave;
+#pragma unroll
+        for (int j = 0; j < DSUB; ++j) srec[at * DSUB + j] = split_bf16(2.0f * s * res[x][j]);
+        scon[at] = most - s * rr[x] + (0.5f + err);   // (rounded to nearest: half a unit up)
+        least += most - LOST * (most + 1.0f);
+      }
     }
-    float least = on ? most - 1.0e-5f * (most + 1.0f) : 0.0f;   // (every rounding of the fp32 sums and of this one: 2^-23 each, at most 70)
     over_lanes([&](auto other) __attribute__((always_inline)) { least += other(least); });
-    least -= tau * s * 1.00001f;
+    least -= tau * s * (1.0f + LOST);
     const int32_t start = least > 1.0f ? (int32_t)least - 1 : -1;   // NaN (0 x inf, or no k-th distance): every point
     if (lane == 0) {
       sT[par * 8 + wave] = fx.qid >= 0 && fx.n <= (uint32_t)a.cap ? start : 0x40000000;   // (a query out of slots is redone, and offers no more)
@@ -216,6 +238,7 @@ __global__ __launch_bounds__(LMP_NW * 64) __attribute__((amdgpu_waves_per_eu(LMP
   // v_mfma_f32_4x4x1 with an addition beside each takes the sum of both times and more, v_mfma_f32_16x16x32_bf16 takes 16
   // for as many with the vector ALU free.)
   auto build = [&](int part, int par) __attribute__((always_inline)) {
+    if (TAIL != 0 && part == P - 1 && wave >= TAIL / 2) return;
     const bool five = sq[par * 8 + 4] >= 0;   // uniform
     const int h = lane >> 4, m = part * LMP_PART + (wave >> 1) * 4 + h;
     const bool mine = ((lane & 15) >> 2) == h;   // the lanes that hold the factors of their own quarter's rows
@@ -344,8 +367,11 @@ __global__ __launch_bounds__(LMP_NW * 64) __attribute__((amdgpu_waves_per_eu(LMP
 #pragma unroll
     for (int i = 0; i < NB; ++i) {
       const int blk = seg + wave + i * NW;
-      const uint32_t at = (uint32_t)(part * nb + (blk < nb ? blk : nb - 1)) << 10;   // no such block: the last one
-      code[i] = *(const GLOBAL uintx4 *)((const GLOBAL uint8_t *)(uintptr_t)base + (at + (uint32_t)(lane * 16)));
+      const uint32_t in = (uint32_t)(blk < nb ? blk : nb - 1);   // no such block: the last one
+      if (TAIL == 0 || !last_part)
+        code[i] = *(const GLOBAL uintx4 *)((const GLOBAL uint8_t *)(uintptr_t)base + ((((uint32_t)(part * nb) + in) << 10) + (uint32_t)(lane * 16)));
+      else
+        code[i] = uintx4{*(const GLOBAL uint32_t *)((const GLOBAL uint8_t *)(uintptr_t)base + (((uint32_t)((P - 1) * nb) << 10) + (in << 8) + (uint32_t)(lane * 4))), 0u, 0u, 0u};
     }
     __syncthreads();   // the part's rows are complete
     if (new_task && more) {
@@ -375,27 +401,32 @@ __global__ __launch_bounds__(LMP_NW * 64) __attribute__((amdgpu_waves_per_eu(LMP
     const intx4 low_four = {pick_byte, 0, pick_byte, 0}, high_four = {0, pick_byte, 0, pick_byte};
     // Two bytes below 64 add up within a byte; the matrix units spread four look-ups' to the sums of eight queries.  (On
     // the vector ALU -- four bytes added up, spread to 16 bits and accumulated -- 10 clocks a look-up, 5 so.)
+    auto look_up = [&](auto count) __attribute__((always_inline)) {   // so many subspaces of the part
+      constexpr int N = decltype(count)::value, G = N < 8 ? N : 8;
 #pragma unroll
-    for (int i = 0; i < NB; ++i) {
-      if (seg + wave + i * NW >= end) break;
+      for (int i = 0; i < NB; ++i) {
+        if (seg + wave + i * NW >= end) break;
 #pragma unroll
-      for (int h = 0; h < LMP_PART; h += 8) {
-        uintx2 v[8];
+        for (int h = 0; h < N; h += G) {
+          uintx2 v[G];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-          const uint32_t off = code_offset8(code[i][(h + j) >> 2], j & 3);   // the table starts at LDS address 0
-          v[j] = *(const LDS uintx2 *)(uintptr_t)(uint32_t)((h + j) * 2048 + off);
+          for (int j = 0; j < G; ++j) {
+            const uint32_t off = code_offset8(code[i][(h + j) >> 2], j & 3);   // the table starts at LDS address 0
+            v[j] = *(const LDS uintx2 *)(uintptr_t)(uint32_t)((h + j) * 2048 + off);
+          }
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int j = 0; j < G; j += 4) {
+            const intx4 b = {(int)(v[j][0] + v[j + 1][0]), (int)(v[j][1] + v[j + 1][1]), (int)(v[j + 2][0] + v[j + 3][0]), (int)(v[j + 2][1] + v[j + 3][1])};
+            sums[i][0] = __builtin_amdgcn_mfma_i32_16x16x64_i8(low_four, b, sums[i][0], 0, 0, 0);
+            if (five) sums[i][1] = __builtin_amdgcn_mfma_i32_16x16x64_i8(high_four, b, sums[i][1], 0, 0, 0);
+          }
+          __builtin_amdgcn_sched_barrier(0);
         }
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int j = 0; j < 8; j += 4) {
-          const intx4 b = {(int)(v[j][0] + v[j + 1][0]), (int)(v[j][1] + v[j + 1][1]), (int)(v[j + 2][0] + v[j + 3][0]), (int)(v[j + 2][1] + v[j + 3][1])};
-          sums[i][0] = __builtin_amdgcn_mfma_i32_16x16x64_i8(low_four, b, sums[i][0], 0, 0, 0);
-          if (five) sums[i][1] = __builtin_amdgcn_mfma_i32_16x16x64_i8(high_four, b, sums[i][1], 0, 0, 0);
-        }
-        __builtin_amdgcn_sched_barrier(0);
       }
-    }
+    };
+    if (TAIL == 0 || !last_part) look_up(std::integral_constant<int, LMP_PART>{});
+    else look_up(std::integral_constant<int, TAIL == 0 ? LMP_PART : TAIL>{});
     // ---- the list's points are summed: those that may gain what their queries need are candidates ----
     if (last_part) {
       const int first = (seg + wave) * 64 + lane;

@@ -26,7 +26,7 @@ def _split(x):
     return hi, _bf16(x - hi)
 
 
-@pytest.mark.parametrize("M", [48, 64])
+@pytest.mark.parametrize("M", [48, 64, 100])
 def test_bytes_are_no_less_than_what_an_entry_gains(M):
     """Rounded up by less than a unit and twice the error, never more than 63 (two of them add up within a signed byte),
     and 0 for what lies clearly outside; radii from nothing to far beyond the data, residuals near and far."""
@@ -66,7 +66,7 @@ def _index(rng, D, M, sizes, spread=0.3, centre=0.05):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("D,M", [(96, 48), (128, 64)])
+@pytest.mark.parametrize("D,M", [(96, 48), (128, 64), (200, 100)])
 @pytest.mark.parametrize("k,radius", [(1, 0.6), (10, 0.6), (10, 0.05), (10, np.inf)])
 def test_segments_groups_and_parts(D, M, k, radius):
     """Lists of a block, of whole segments and one point more or less, of two segments and a bit; groups of one to eight

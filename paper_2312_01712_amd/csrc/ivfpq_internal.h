@@ -211,6 +211,7 @@ int launch_scan(const ivfpq_index *ix, const float *d_queries, int64_t Q, int32_
 int launch_probe_bounds(const ivfpq_index *ix, const float *d_queries, int64_t Q, int32_t nprobe,
                         const int32_t *d_probe_ids, const RadiiSq &r2, int32_t mode, const float *d_query_radii,
                         float *d_probe_lb, hipStream_t s, int32_t *d_zero = nullptr, int64_t zero_n = 0);
+bool bounds_use_grid(const ivfpq_index *ix);   // whether the list-level bounds look up the grid of nearest-entry distances
 // ---- list-major batched scan (scan_lm.hip) --------------------------------------------------
 bool list_major_supported(const ivfpq_index *ix, int32_t nprobe, int32_t k);
 LmWorkspace plan_list_major(const ivfpq_index *ix, int64_t Q, int32_t nprobe);

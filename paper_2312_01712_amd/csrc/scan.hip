@@ -1296,18 +1296,22 @@ int launch_scan(const ivfpq_index *ix, const float *d_queries, int64_t Q, int32_
   return IVFPQ_OK;
 }
 
+// The grid of nearest-entry distances tightens the bound (on the 100M-point configuration it
+// rules out 59.4 instead of 55.9 of a query's 64 lists, and the tables built per query drop
+// from 8.1 to 4.6) at the price of a slower bound kernel (three more loads per pair and
+// subspace, one of them a gather): it pays where a list that slips through is expensive,
+// i.e. on long lists (measured: 4 % faster there, 7-14 % slower on the 1M-point ones).
+bool bounds_use_grid(const ivfpq_index *ix) {
+  const int grid_mode = g_bound_grid.load(std::memory_order_relaxed);
+  return ix->d_grid && grid_mode != 2 && (grid_mode == 1 || ix->N > (int64_t)4096 * ix->nlist);
+}
+
 int launch_probe_bounds(const ivfpq_index *ix, const float *d_queries, int64_t Q, int32_t nprobe,
                         const int32_t *d_probe_ids, const RadiiSq &r2, int32_t mode, const float *d_query_radii,
                         float *d_probe_lb, hipStream_t s, int32_t *d_zero, int64_t zero_n) {
   const int64_t total = Q * nprobe;
   if (total == 0) return zero_n > 0 ? launch_fill_i32(d_zero, zero_n, 0, s) : IVFPQ_OK;
-  // The grid of nearest-entry distances tightens the bound (on the 100M-point configuration it
-  // rules out 59.4 instead of 55.9 of a query's 64 lists, and the tables built per query drop
-  // from 8.1 to 4.6) at the price of a slower bound kernel (three more loads per pair and
-  // subspace, one of them a gather): it pays where a list that slips through is expensive,
-  // i.e. on long lists (measured: 4 % faster there, 7-14 % slower on the 1M-point ones).
-  const int grid_mode = g_bound_grid.load(std::memory_order_relaxed);
-  const bool use_grid = ix->d_grid && grid_mode != 2 && (grid_mode == 1 || ix->N > (int64_t)4096 * ix->nlist);
+  const bool use_grid = bounds_use_grid(ix);
   const int64_t per_block = 4 * BOUND_PAIRS;
   if ((total + per_block - 1) / per_block > 0x7FFFFFFFll) {
     set_error("scan: %lld (query, probe) pairs exceed the grid limit of the bound kernel", (long long)total);

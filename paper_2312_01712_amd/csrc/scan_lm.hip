@@ -138,6 +138,105 @@ __global__ __launch_bounds__(256) void lm_pairs_kernel(LmArgs a, int fill, int h
   a.rank[idx] = take ? atomicAdd(&a.cnt[c], 1) : -1;
 }
 
+template <int J>
+__device__ __forceinline__ float xor_f32(float v) { return __uint_as_float(xor_u32<J, true>(__float_as_uint(v))); }
+
+// The list-level bounds of a main pass behind the head pass, and the count of its pairs (lm_pairs_kernel's, fill == 0): the
+// bounds of probe_bound_kernel, two-dimensional subspaces and distances, a quarter of a wavefront per pair and 16 subspaces at
+// a time, ended where they pass the query's k-th distance so far: the terms are not negative, so what is summed by then is
+// a lower bound too.  A list that is too far is so by half of its subspaces or a few more, and what the bounds cost is their
+// way from the L2 (24 bytes per pair and subspace).  Queries that are left to the query-major scan get theirs in full.
+// 10 000 queries, clustered data, bounds up front and count / so: 64 subspaces of 32 probes 64 + 5 / 39 us, 100 of 64 184 + 5 / 109;
+// 48 of 64 without structure, where none ends early, 117 + 118 / 245.
+constexpr int LM_BOUND_SETS = 2;   // pairs of a quarter of a wavefront, whose loads are issued together
+template <bool GRID>
+__global__ __launch_bounds__(256) void lm_bound_kernel(LmArgs a, RadiiSq r2, const float *__restrict__ box, const float *__restrict__ grid,
+                                                       const float *__restrict__ grid_par, float *__restrict__ lb) {
+  const int lane = threadIdx.x & 63, l = lane & 15;
+  const uint32_t np2 = (uint32_t)(a.p1 - a.p0), total = (uint32_t)a.Q * np2;   // (below 2^31)
+  const uint32_t idx0 = (blockIdx.x * 4 + (threadIdx.x >> 6)) * (4 * LM_BOUND_SETS) + (lane >> 4);
+  if (idx0 - (lane >> 4) >= total) return;
+  uint32_t q[LM_BOUND_SETS];
+  int32_t c[LM_BOUND_SETS];
+  bool want[LM_BOUND_SETS], named[LM_BOUND_SETS], exists[LM_BOUND_SETS], alive[LM_BOUND_SETS];
+  float tau[LM_BOUND_SETS], acc[LM_BOUND_SETS], sum[LM_BOUND_SETS];
+#pragma unroll
+  for (int s = 0; s < LM_BOUND_SETS; ++s) {
+    const uint32_t idx = idx0 + 4 * s, in = idx < total ? idx : total - 1;   // (a pair past the end is computed and not stored)
+    q[s] = in / np2;
+    const int p = a.p0 + (int)(in % np2);
+    c[s] = a.probe_ids[(int64_t)q[s] * a.nprobe + p];
+    exists[s] = (uint32_t)c[s] < (uint32_t)a.nlist;
+    if (!exists[s]) c[s] = 0;
+    const int32_t left = a.qmap_head[q[s]];
+    // left out by the head pass or out of slots in the pass before: redone over all lists
+    named[s] = left >= 0 || (a.later && a.qmap[q[s]] >= 0);
+    want[s] = exists[s] && a.list_offsets[c[s] + 1] > a.list_offsets[c[s]] && !(a.seeded && p == 0 && left != LM_SEEDED);   // (else the head pass has ranked this list)
+    tau[s] = named[s] ? __builtin_inff() : a.tau[(int64_t)q[s] * a.tau_stride];
+    acc[s] = sum[s] = 0.0f;
+    alive[s] = want[s];
+  }
+#pragma unroll 1
+  for (int m0 = 0; m0 < a.M; m0 += 16) {
+    const int m = m0 + l;
+    const bool on = m < a.M;
+#pragma unroll
+    for (int s = 0; s < LM_BOUND_SETS; ++s) {
+      if (!on || !alive[s]) continue;
+      const float2 qv = *reinterpret_cast<const float2 *>(a.queries + (int64_t)q[s] * a.D + 2 * m);
+      const float2 cv = *reinterpret_cast<const float2 *>(a.centroids + (int64_t)c[s] * a.D + 2 * m);
+      const float4 v = reinterpret_cast<const float4 *>(box + (int64_t)c[s] * a.D * 2)[m];
+      const float x0 = qv.x - cv.x, x1 = qv.y - cv.y;
+      const float t0 = fmaxf(fmaxf(v.x - x0, x0 - v.z), 0.0f);
+      const float t1 = fmaxf(fmaxf(v.y - x1, x1 - v.w), 0.0f);
+      float best = fmaf(t1, t1, t0 * t0);
+      if constexpr (GRID) {   // see probe_bound_kernel
+        const float4 gp0 = reinterpret_cast<const float4 *>(grid_par)[2 * m];
+        const float2 gp1 = reinterpret_cast<const float2 *>(grid_par)[4 * m + 2];
+        const float fx = fminf(fmaxf((x0 - gp0.x) * gp1.x, 0.0f), (float)(ivfpq::GRID_G - 1));
+        const float fy = fminf(fmaxf((x1 - gp0.y) * gp1.y, 0.0f), (float)(ivfpq::GRID_G - 1));
+        const float cell = grid[(int64_t)m * (ivfpq::GRID_G * ivfpq::GRID_G) + (int)fy * ivfpq::GRID_G + (int)fx];
+        const float o0 = fmaxf(fmaxf(gp0.x - x0, x0 - gp0.z), 0.0f);
+        const float o1 = fmaxf(fmaxf(gp0.y - x1, x1 - gp0.w), 0.0f);
+        best = fmaxf(best, cell + fmaf(o1, o1, o0 * o0));
+      }
+      float rm2 = r2.v[m];
+      if (a.query_radii) {
+        const float r = a.query_radii[(int64_t)q[s] * a.M + m];
+        rm2 = r * r;
+      }
+      acc[s] += fminf(best, rm2);
+    }
+    bool any = false;
+#pragma unroll
+    for (int s = 0; s < LM_BOUND_SETS; ++s) {
+      float v = acc[s];
+      v += xor_f32<1>(v);
+      v += xor_f32<2>(v);
+      v += xor_f32<4>(v);
+      v += xor_f32<8>(v);
+      sum[s] = v * 0.999755859375f;   // (the roundings of this evaluation against the table's)
+      alive[s] = alive[s] && !(sum[s] > tau[s]);
+      any = any || alive[s];
+    }
+    if (__ballot(any) == 0ull) break;
+  }
+#pragma unroll
+  for (int s = 0; s < LM_BOUND_SETS; ++s) {
+    const uint32_t idx = idx0 + 4 * s;
+    if (l != 0 || idx >= total) continue;
+    const int p = a.p0 + (int)(idx % np2);
+    float *row = lb + (int64_t)q[s] * a.nprobe;
+    row[p] = exists[s] ? sum[s] : 0.0f;
+    if (p == a.p0) {
+      a.gcnt[q[s]] = 0u;
+      if (!a.later)
+        for (int x = 0; x < a.p0; ++x) row[x] = 0.0f;   // (lists ranked by the head pass: no bound, wherever they are scanned again)
+    }
+    a.rank[idx] = alive[s] && !named[s] ? atomicAdd(&a.cnt[c[s]], 1) : -1;
+  }
+}
+
 // Slot ranges of the lists: base[c] = sum over c' < c of cnt[c'] rounded up to a.group.  The
 // padding slots of a range are marked (query -1), the counts are cleared.
 // One workgroup.
@@ -776,9 +875,6 @@ __device__ __attribute__((noinline)) void lmb_spill(uint32_t *gcnt, uint2 *cand,
 }
 
 __device__ __forceinline__ uint32_t pick(uint32_t c, uint32_t a, uint32_t b) { return c ? a : b; }
-
-template <int J>
-__device__ __forceinline__ float xor_f32(float v) { return __uint_as_float(xor_u32<J, true>(__float_as_uint(v))); }
 
 // A task has two phases and a barrier behind each: the table (vector ALU and matrix units) and the pass
 // over the codes (LDS).  What else a task needs is out of their way.  The next task's parameters are
@@ -2114,12 +2210,6 @@ int launch_scan_list_major(const ivfpq_index *ix, const float *d_queries, int64_
   a.k = k;
   a.mode = mode;
 
-  // list-level lower bounds of every (query, probe); the same launch clears the per-list counts
-  // (lm_offsets_kernel leaves them clear for the pass after it)
-  int rc = launch_probe_bounds(ix, d_queries, Q, nprobe, d_probe_ids, r2, mode, d_query_radii, d_probe_lb, s, a.cnt,
-                               lm_counters(ix->nlist));
-  if (rc) return rc;
-
   // ---- the first lists of every query: they give the bound tau_q that filters the rest ----
   // One list per query under distance scoring: the head pass ranks it list-major (queries that
   // share a nearest list share its table pass); what the head pass leaves out (qmap_head) skips
@@ -2146,6 +2236,7 @@ int launch_scan_list_major(const ivfpq_index *ix, const float *d_queries, int64_
   //   16, without structure        1690 / 984,  1599 / 982   2323 / 1477, 2196 / 1445   3617 / 2515, 3429 / 2485
   // The line is where data without structure, and clustered data whose radii hold a part of the entries, gains; clustered
   // data with wide radii pays for it in the smaller batches.
+  int rc = IVFPQ_OK;
   const int64_t head_points = (int64_t)((double)Q * (double)ix->N / ix->nlist);
   const bool head_bytes = byte_head_lists(ix) && w.first == 1 && mode == IVFPQ_SCORE_DISTANCE && !(get_scan_ablate() & 8) &&
                           head_points >= 8000000;
@@ -2155,6 +2246,12 @@ int launch_scan_list_major(const ivfpq_index *ix, const float *d_queries, int64_
     a.group = LMB_G;
     a.fresh = 1;
   }
+  // List-level lower bounds of every (query, probe): behind the head pass, where its k-th distances end most of them early
+  // (lm_bound_kernel), or up front.  Either way the per-list counts are cleared (lm_offsets_kernel leaves them clear for the pass after it).
+  const bool late_bounds = head_pass && a.probe_lb && ix->dsub == 2;
+  if (late_bounds) rc = launch_fill_i32(a.cnt, lm_counters(ix->nlist), 0, s);
+  else rc = launch_probe_bounds(ix, d_queries, Q, nprobe, d_probe_ids, r2, mode, d_query_radii, d_probe_lb, s, a.cnt, lm_counters(ix->nlist));
+  if (rc) return rc;
   if (head_pass) {
     const unsigned qgrid = (unsigned)((Q + 255) / 256);
     hipLaunchKernelGGL(lm_pairs_kernel, dim3(qgrid), dim3(256), 0, s, a, 0, 1);
@@ -2217,7 +2314,13 @@ int launch_scan_list_major(const ivfpq_index *ix, const float *d_queries, int64_
     a.stage = a.later + 1;
     const int64_t npairs = Q * (p1 - p0);
     const unsigned pair_grid = (unsigned)((npairs + 255) / 256);
-    hipLaunchKernelGGL(lm_pairs_kernel, dim3(pair_grid), dim3(256), 0, s, a, 0, 0);
+    if (late_bounds) {
+      const unsigned bound_grid = (unsigned)((npairs + 16 * LM_BOUND_SETS - 1) / (16 * LM_BOUND_SETS));
+      if (bounds_use_grid(ix)) hipLaunchKernelGGL(lm_bound_kernel<true>, dim3(bound_grid), dim3(256), 0, s, a, r2, ix->d_box, ix->d_grid, ix->d_grid_par, d_probe_lb);
+      else hipLaunchKernelGGL(lm_bound_kernel<false>, dim3(bound_grid), dim3(256), 0, s, a, r2, ix->d_box, nullptr, nullptr, d_probe_lb);
+    } else {
+      hipLaunchKernelGGL(lm_pairs_kernel, dim3(pair_grid), dim3(256), 0, s, a, 0, 0);
+    }
     hipLaunchKernelGGL(lm_offsets_kernel, dim3(1), dim3(1024), 0, s, a);
     hipLaunchKernelGGL(lm_pairs_kernel, dim3(pair_grid), dim3(256), 0, s, a, 1, 0);
     rc = bytes ? launch_lm_byte(a, r2, cus, s) : (byte_table_shape(ix) ? launch_lm_scan<false>(ix, a, r2, cus, s) : launch_lm_pair_t<100, false>(a, r2, cus, s));

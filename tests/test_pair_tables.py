@@ -76,3 +76,32 @@ def test_100_subspaces_with_little_workspace():
     ref = oracle.search(q, idx, nprobe, k, radii, threads=8, mode=1)
     _same(gi.search(dq, nprobe, k, radii, mode=1, strategy=b.SCAN_LIST_MAJOR), ref, "hit counts")
     gi.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("D,M", [(96, 48), (128, 64), (200, 100)])
+@pytest.mark.parametrize("centre", [0.1, 0.3, 3.0])
+def test_bounds_that_end_early(D, M, centre):
+    """Lists that are ruled out by few of their subspaces, by many and not at all; probes that name no list, or an empty one;
+    with and without the grid of nearest entries; a number of pairs that fills no workgroup."""
+    import torch
+    from paper_2312_01712_amd import binding as b
+    rng = np.random.default_rng(M)
+    nlist, nprobe, k, Q = 90, 50, 10, 333
+    idx = _index(rng, D, M, rng.integers(0, 200, size=nlist), centre=centre)
+    q = (idx.centroids[rng.integers(0, nlist, Q)] + 0.3 * rng.normal(size=(Q, D))).astype(np.float32)
+    radii = np.full(M, 0.7 * np.sqrt(2), dtype=np.float32)
+    pid, _ = oracle.coarse(q, idx.centroids, nprobe)
+    pid[::7, 3] = -1
+    pid[1::7, 5] = nlist
+    gi = b.IvfPqIndex.from_index(idx)
+    dq, dp = torch.from_numpy(q).cuda(), torch.from_numpy(pid.astype(np.int32)).cuda()
+    try:
+        want = [x.cpu().numpy() for x in gi.scan_topk(dq, dp, k, radii, strategy=b.SCAN_QUERY_MAJOR)]
+        for grid in (1, 2):
+            b.set_option("bound_grid", grid)
+            _same(gi.scan_topk(dq, dp, k, radii, strategy=b.SCAN_LIST_MAJOR), want, ("grid", grid))
+            _same(gi.search(dq, nprobe, k, radii, strategy=b.SCAN_LIST_MAJOR), oracle.search(q, idx, nprobe, k, radii, threads=8), ("search", grid))
+    finally:
+        b.set_option("bound_grid", 0)
+        gi.close()

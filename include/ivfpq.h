@@ -222,14 +222,14 @@ typedef enum {
  *     bound that filters the query's other lists).  Best where the per-query fixed costs or
  *     the look-up rate dominate: short lists, lists that many queries share, data without
  *     cluster structure.
- *     Needs the L2 metric, k <= 128 and an (M, dsub) of (48, 2), (64, 2) or (16, 4), or of (100, 2) with
- *     distance scoring; any other call is served query-major.  Takes a larger workspace ((100, 2): a call with
- *     less than that is served query-major).  (For 128 < k <= 1024 with distance
+ *     Needs the L2 metric, k <= 128 and an (M, dsub) of (48, 2), (64, 2) or (16, 4), or, with distance scoring,
+ *     73 to 128 subspaces of up to three dimensions, 256 in all; any other call is served query-major.  Takes a larger
+ *     workspace (with 73 subspaces and more, a call with less than that is served query-major).  (For 128 < k <= 1024 with distance
  *     scoring, either setting but QUERY_MAJOR lets large batches of the first three be selected list-major
  *     in stages; ivfpq_resolve_strategy calls that query-major.)
  *   IVFPQ_SCAN_AUTO         the library chooses: list-major where it is available, when the
  *     batch has at least 16 384 (query, list) pairs and the index's mean list length is at
- *     most 4096, or, with distance scoring and not on (100, 2), at most 16 384 and the batch large enough that its
+ *     most 4096, or, with distance scoring and up to 64 subspaces, at most 16 384 and the batch large enough that its
  *     queries share their nearest lists (two a list, 16 million points in all); query-major
  *     otherwise.  On lists above 4096 points the workspace's candidate slots are bounded by 1 GiB or
  *     4096 queries, whichever is more, larger batches go through them in pieces, and a workspace

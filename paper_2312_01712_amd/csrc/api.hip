@@ -477,7 +477,7 @@ int ivfpq_index_create(const ivfpq_index_desc *d, ivfpq_index **out) {
     // list-major byte tables (lm_part_kernel): per entry (high part, rest) of both coordinates and of |entry|^2 as bf16, two
     // zeros.  Nothing in it is infinite or not a number: the products would spread that to other rows by way of the zeros
     // they multiply it with.  (The kernel looks at the entries themselves for what is not held here.)
-    if (list_major_shape(ix) && ix->dsub == 2) {
+    if (part_table_shape(ix)) {
       const size_t n = (size_t)d->M * 256;
       std::vector<float> cb_h(2 * n);
       TRY_OR_FAIL(hipMemcpy(cb_h.data(), ix->d_codebooks, kb, hipMemcpyDeviceToHost));

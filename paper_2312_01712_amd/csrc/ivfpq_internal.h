@@ -159,8 +159,20 @@ inline void plan_list_major_tables(LmWorkspace &w, int32_t nlist, int64_t Q, int
 inline bool byte_table_shape(const ivfpq_index *ix) {
   return (ix->M == 48 && ix->dsub == 2) || (ix->M == 64 && ix->dsub == 2) || (ix->M == 16 && ix->dsub == 4);
 }
-// Shapes that have list-major kernels.  (100 subspaces: distances only, in calls whose workspace has room for it.)
-inline bool list_major_shape(const ivfpq_index *ix) { return byte_table_shape(ix) || (ix->M == 100 && ix->dsub == 2); }
+// ... for distances behind a head pass (lm_part_kernel).
+inline bool part_table_shape(const ivfpq_index *ix) { return ix->dsub == 2 && (ix->M == 48 || ix->M == 64 || ix->M == 100); }
+// Shapes that have list-major kernels: those, and 73 to 128 subspaces (up to three dimensions each, 256 in all) for distances only,
+// in calls whose workspace has room for it.  From 73 subspaces on one workgroup of the query-major scan fills a CU, and its
+// phases follow one another.  us of a search, 500k points, 24 or 48 probes, query-major / list-major (lm_pair_kernel), data
+// without much structure unless said:
+//   80 x 2, lists of 713, 999 queries    1326 / 720     80 x 3, 713, 999        1286 / 820     120 x 2, 1666, 1000   1280 / 829
+//   80 x 2, 1666, 6250                 13 313 / 7413    80 x 3, 2307, 4500      7947 / 7211    120 x 2, 2307, 1500   6535 / 5820
+//   80 x 2, 713, clustered, 5000          526 / 227     80 x 3, 2307, 3000      4628 / 4701    120 x 2, 713, 3000    5475 / 3911
+// Fewer subspaces, with the same kernel: 30 x 2 326 / 313, 30 x 4 360 / 397, 64 x 3 722 / 1015, 33 x 2, lists of 2307 671 / 894,
+// 56 x 2, 1666 2077 / 3480: partial sums and row minima, which the query-major scan has and this one has not, are worth more.
+inline bool list_major_shape(const ivfpq_index *ix) {
+  return byte_table_shape(ix) || (ix->M > 72 && ix->M <= 128 && ix->dsub <= 3 && ix->D <= 256);
+}
 
 // Workspace of the wide selection (more than 128 neighbours per query in one pass of the
 // query-major scan): offsets into its part of the workspace, 256-byte aligned.

@@ -411,14 +411,11 @@ struct LmWindow {
     return x >= (float)(LM_BINS - 1) ? (uint32_t)(LM_BINS - 1) : (x > 0.0f ? (uint32_t)x : 0u);
   }
 };
-template <int MT>
-__device__ __forceinline__ LmWindow lm_window(const LDS float *sr2, int lane) {
-  float s0 = lane < MT ? sr2[lane] : 0.0f, s1 = lane < MT ? sr2[IVFPQ_MAX_M + lane] : 0.0f;
-  if constexpr (MT > 64) {
-    if (lane + 64 < MT) {
-      s0 += sr2[lane + 64];
-      s1 += sr2[IVFPQ_MAX_M + lane + 64];
-    }
+__device__ __forceinline__ LmWindow lm_window(const LDS float *sr2, int M, int lane) {
+  float s0 = lane < M ? sr2[lane] : 0.0f, s1 = lane < M ? sr2[IVFPQ_MAX_M + lane] : 0.0f;
+  if (lane + 64 < M) {   // (at most 128)
+    s0 += sr2[lane + 64];
+    s1 += sr2[IVFPQ_MAX_M + lane + 64];
   }
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) {
@@ -741,7 +738,7 @@ __global__ __launch_bounds__(LM_NW * 64) __attribute__((amdgpu_waves_per_eu(LM_N
     int qc0 = 0, qc1 = 0;
     uint32_t mn0 = 0xFFFFFFFFu, mn1 = 0xFFFFFFFFu, mx0 = 0u, mx1 = 0u;   // head pass: key range of this wavefront's points
     LmWindow win;
-    if constexpr (HEAD) win = lm_window<MT>(sr2, lane);
+    if constexpr (HEAD) win = lm_window(sr2, MT, lane);
     // tau_q as the bit pattern of a non-negative float (orders like the value; +inf when the
     // first lists held fewer than k points)
     const uint32_t tau0 = (uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(tk.tauv), 0);
@@ -1982,19 +1979,27 @@ int launch_lm_part_t(const LmArgs &a, const RadiiSq &r2, int cus, hipStream_t s)
   return IVFPQ_OK;
 }
 
-template <int MT, bool HEAD>
+template <int MT, int DSUB, bool HEAD>
 int launch_lm_pair_t(const LmArgs &a, const RadiiSq &r2, int cus, hipStream_t s) {
-  auto kern = lm_pair_kernel<MT, HEAD>;
+  auto kern = lm_pair_kernel<MT, DSUB, HEAD>;
   static std::atomic<uint64_t> prepared;
   if (int rc = prepare_kernel(kern, prepared)) return rc;
   hipLaunchKernelGGL(kern, dim3((unsigned)(LPP_WG * cus)), dim3(LPP_NW * 64), HEAD ? lpp_head_lds(a.D) : lpp_main_lds(a.D), s, a, r2);
   return IVFPQ_OK;
 }
 
-int launch_lm_pair_head(const LmArgs &a, const RadiiSq &r2, int cus, hipStream_t s) {
-  if (a.M == 48) return launch_lm_pair_t<48, true>(a, r2, cus, s);
-  if (a.M == 64) return launch_lm_pair_t<64, true>(a, r2, cus, s);
-  return launch_lm_pair_t<100, true>(a, r2, cus, s);
+template <bool HEAD>
+int launch_lm_pair(const LmArgs &a, const RadiiSq &r2, int cus, hipStream_t s) {
+  if constexpr (HEAD) {   // (the further lists of these shapes: lm_scan_kernel)
+    if (a.M == 48 && a.dsub == 2) return launch_lm_pair_t<48, 2, true>(a, r2, cus, s);
+    if (a.M == 64 && a.dsub == 2) return launch_lm_pair_t<64, 2, true>(a, r2, cus, s);
+  }
+  if (a.M == 100 && a.dsub == 2) return launch_lm_pair_t<100, 2, HEAD>(a, r2, cus, s);
+  switch (a.dsub) {
+    case 1: return launch_lm_pair_t<0, 1, HEAD>(a, r2, cus, s);
+    case 2: return launch_lm_pair_t<0, 2, HEAD>(a, r2, cus, s);
+    default: return launch_lm_pair_t<0, 3, HEAD>(a, r2, cus, s);
+  }
 }
 
 template <int MT, int DSUB, int HOW>
@@ -2205,7 +2210,7 @@ int launch_scan_list_major(const ivfpq_index *ix, const float *d_queries, int64_
   IVFPQ_HIP_TRY(hipGetDevice(&dev));
   IVFPQ_HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
   if (cus < 1) cus = 1;
-  const bool table_parts = ix->dsub == 2 && (!byte_table_shape(ix) || Q > (int64_t)4 * cus || ix->N >= (int64_t)2048 * ix->nlist);
+  const bool table_parts = !byte_table_shape(ix) || (ix->dsub == 2 && (Q > (int64_t)4 * cus || ix->N >= (int64_t)2048 * ix->nlist));
   a.head_max = table_parts ? lpp_head_max(ix->D) : lm_head_max(ix->M, ix->D);
   a.k = k;
   a.mode = mode;
@@ -2257,7 +2262,7 @@ int launch_scan_list_major(const ivfpq_index *ix, const float *d_queries, int64_
     hipLaunchKernelGGL(lm_pairs_kernel, dim3(qgrid), dim3(256), 0, s, a, 0, 1);
     hipLaunchKernelGGL(lm_offsets_kernel, dim3(1), dim3(1024), 0, s, a);
     hipLaunchKernelGGL(lm_pairs_kernel, dim3(qgrid), dim3(256), 0, s, a, 1, 1);
-    rc = head_bytes ? launch_lm_byte_head(a, r2, cus, s) : (table_parts ? launch_lm_pair_head(a, r2, cus, s) : launch_lm_scan<true>(ix, a, r2, cus, s));
+    rc = head_bytes ? launch_lm_byte_head(a, r2, cus, s) : (table_parts ? launch_lm_pair<true>(a, r2, cus, s) : launch_lm_scan<true>(ix, a, r2, cus, s));
     if (rc) return rc;
     if (head_bytes) {
       hipLaunchKernelGGL(lm_sort_out_kernel, dim3((unsigned)((Q + 255) / 256)), dim3(256), 0, s, a, 0);
@@ -2286,7 +2291,7 @@ int launch_scan_list_major(const ivfpq_index *ix, const float *d_queries, int64_
   // 3903, 8.9 2581 / 2460, 9.8 4057 / 3984, 64 subspaces 2.9 3436 / 3962, 4.9 3902 / 3903, 6.8 4248 / 3936;
   // 16 subspaces 2.9 2343 / 2276, 9.8 2742 / 2302; 100 (2000 queries, 64 probes) without 9.8 4768 / 3810, k = 10 4623 / 2768.  So from 6 on, with 16 subspaces from 2 on, and with the
   // hit counts, whose byte sums are the result.
-  const bool bytes = ix->N >= (int64_t)(mode == 0 && ix->M > 16 ? 6 : 2) * k * ix->nlist && ix->max_list_len < (1 << 20) && !(get_scan_ablate() & 8);
+  const bool bytes = (byte_table_shape(ix) || part_table_shape(ix)) && ix->N >= (int64_t)(mode == 0 && ix->M > 16 ? 6 : 2) * k * ix->nlist && ix->max_list_len < (1 << 20) && !(get_scan_ablate() & 8);
   a.group = bytes ? LMB_G : LM_G;
   // Many probes: the nearest few lists first, merged, so that the rest is filtered by a k-th distance
   // over eight lists instead of one.  That costs five launches (14 us of 10 000 queries) where the bounds rule
@@ -2323,7 +2328,7 @@ int launch_scan_list_major(const ivfpq_index *ix, const float *d_queries, int64_
     }
     hipLaunchKernelGGL(lm_offsets_kernel, dim3(1), dim3(1024), 0, s, a);
     hipLaunchKernelGGL(lm_pairs_kernel, dim3(pair_grid), dim3(256), 0, s, a, 1, 0);
-    rc = bytes ? launch_lm_byte(a, r2, cus, s) : (byte_table_shape(ix) ? launch_lm_scan<false>(ix, a, r2, cus, s) : launch_lm_pair_t<100, false>(a, r2, cus, s));
+    rc = bytes ? launch_lm_byte(a, r2, cus, s) : (byte_table_shape(ix) ? launch_lm_scan<false>(ix, a, r2, cus, s) : launch_lm_pair<false>(a, r2, cus, s));
     if (rc) return rc;
     if (in_place) {
       a.list_redo = p1 == nprobe && Q > 4096 ? 1 : 0;
@@ -2343,7 +2348,7 @@ int launch_scan_list_major(const ivfpq_index *ix, const float *d_queries, int64_
   // that looks whether it is named takes as long where none is, and where all are (lists too long for the head
   // pass: 2771 queries, 64 subspaces, 48 probes) 562 us against 625, since every query starts with fresh registers.
   ScanView redo = {0, a.qmap, true};
-  if (Q > 4096) {
+  if (Q > 4096 && (byte_table_shape(ix) || part_table_shape(ix))) {   // (shapes whose query-major kernel takes a list)
     redo.qmap = nullptr;
     redo.qlist = a.redo;
     redo.qlist_n = a.cnt + ix->nlist;

@@ -1,5 +1,5 @@
 // List-major scan with fp32 tables of two queries, a table in parts of 16 subspaces (included by scan_lm.hip, which says what
-// a group, the head pass and the main pass are).  Two-dimensional subspaces, distances.
+// a group, the head pass and the main pass are).  Distances.
 //
 // lm_scan_kernel holds a whole table in LDS, 2 KiB a subspace: one workgroup per CU whose table, scan and selection follow
 // one another (23, 36 and 33 of a hundred clocks of the head pass with 64 subspaces), and nothing at all beyond 78
@@ -27,15 +27,18 @@ int lpp_head_max(int D) {
 }
 size_t lpp_head_lds(int D) { return lpp_fixed_lds(D) + (size_t)LM_G * lpp_head_max(D) * 4 + LM_SEL_WORDS * 4 + LM_G * LM_BINS * 4; }
 
-template <int MT, bool HEAD>
+template <int MT, int DSUB, bool HEAD>
 __global__ __launch_bounds__(LPP_NW * 64) __attribute__((amdgpu_waves_per_eu(LPP_WG * LPP_NW / 4))) void lm_pair_kernel(LmArgs a, RadiiSq r2) {
   constexpr int NW = LPP_NW, NB = LPP_NB;
-  constexpr int P = (MT + LPP_PART - 1) / LPP_PART, TAIL = MT % LPP_PART;   // parts; subspaces of the last one where it is short
+  constexpr bool RT = MT == 0;   // any number of subspaces, up to 128
+  const int M = RT ? a.M : MT, Mp = RT ? a.Mp : (MT + 3) / 4 * 4;
+  const int P = (M + LPP_PART - 1) / LPP_PART;
+  constexpr int TAIL = MT % LPP_PART;   // subspaces of the last part where it is short
   constexpr int ROWS = LPP_PART / NW;   // rows of a part that a wavefront makes
-  static_assert((TAIL == 0 || TAIL == 4) && P >= 3, "16-byte chunks and one of 4 bytes; a ticket is drawn, written and read in three parts");
+  static_assert(TAIL == 0 || TAIL == 4, "16-byte chunks and one of 4 bytes");
   extern __shared__ __align__(16) unsigned char smem[];
   LDS unsigned char *smem3 = (LDS unsigned char *)smem;
-  const int D = a.D;   // LM_G * D <= NT and LM_G * MT <= NT: one element per thread (checked by the launcher)
+  const int D = a.D;   // LM_G * D <= NT and LM_G * M <= NT: one element per thread (checked by the launcher)
   const int dpad = (D + 3) & ~3;
   // LDS carve: table [16][256][2] | residuals [2][dpad] | r_m^2 [2][MAX_M] | the task after the next | head pass: selection
   // state, histograms, distances [2][head_max]; main pass: queues
@@ -65,18 +68,18 @@ __global__ __launch_bounds__(LPP_NW * 64) __attribute__((amdgpu_waves_per_eu(LPP
   // what this thread contributes to a task's residuals and radii: element tid of [2][D] / [2][MT]
   const int rg = tid >= D ? 1 : 0, rd = tid - rg * D;
   const bool r_on = tid < LM_G * D;
-  const int mg = tid >= MT ? 1 : 0, mm = tid - mg * MT;
-  const bool m_on = tid < LM_G * MT;
+  const int mg = tid >= M ? 1 : 0, mm = tid - mg * M;
+  const bool m_on = tid < LM_G * M;
 
   // this wavefront's rows of a part: 16 part + wave, and 8 further on
-  float4 row[ROWS][2];
+  float4 row[ROWS][DSUB];
   auto load_rows = [&](int part) __attribute__((always_inline)) {
 #pragma unroll
     for (int it = 0; it < ROWS; ++it) {
       const int m = part * LPP_PART + it * NW + wave;
-      const GLOBAL uint8_t *cb = uniform_ptr(a.codebooks + (int64_t)(m < MT ? m : MT - 1) * 256 * 2);
-      row[it][0] = load_f4(cb, (uint32_t)(lane * 32));
-      row[it][1] = load_f4(cb, (uint32_t)(lane * 32 + 16));
+      const GLOBAL uint8_t *cb = uniform_ptr(a.codebooks + (int64_t)(m < M ? m : M - 1) * 256 * DSUB);
+#pragma unroll
+      for (int x = 0; x < DSUB; ++x) row[it][x] = load_f4(cb, (uint32_t)(lane * 16 * DSUB + 16 * x));
     }
   };
   uintx4 code[NB];   // a part's codes of the wavefront's blocks
@@ -84,9 +87,17 @@ __global__ __launch_bounds__(LPP_NW * 64) __attribute__((amdgpu_waves_per_eu(LPP
 #pragma unroll
     for (int i = 0; i < NB; ++i) {
       const int at = seg + wave + i * NW, blk = at < nb ? at : nb - 1;   // no such block: the last one
-      if (TAIL == 0 || part < P - 1) {
+      if (RT ? part < (Mp >> 4) : (TAIL == 0 || part < P - 1)) {
         const GLOBAL uint8_t *sp = uniform_ptr(base + ((int64_t)part * nb + blk) * 1024);
         r[i] = *(const GLOBAL uintx4 *)(sp + (uint32_t)(lane * 16));
+      } else if constexpr (RT) {
+        r[i] = uintx4{0u, 0u, 0u, 0u};
+#pragma unroll
+        for (int t = 0; t < 3; ++t)
+          if (t < ((Mp >> 2) & 3)) {
+            const GLOBAL uint8_t *sp = uniform_ptr(base + (int64_t)(Mp >> 4) * nb * 1024 + ((int64_t)t * nb + blk) * 256);
+            r[i][t] = *(const GLOBAL uint32_t *)(sp + (uint32_t)(lane * 4));
+          }
       } else {
         const GLOBAL uint8_t *sp = uniform_ptr(base + (int64_t)(MT / 16) * nb * 1024 + (int64_t)blk * 256);
         r[i] = uintx4{*(const GLOBAL uint32_t *)(sp + (uint32_t)(lane * 4)), 0u, 0u, 0u};
@@ -115,7 +126,7 @@ __global__ __launch_bounds__(LPP_NW * 64) __attribute__((amdgpu_waves_per_eu(LPP
     tk.row0 = lane64(mv, 0);
     tk.len = (int)(lane64(mv, 1) - tk.row0);
     tk.nb = (tk.len + 63) >> 6;   // >= 1: only non-empty lists have tasks
-    tk.base = a.codes + lane64(mv, 2) * ivfpq_block_bytes((MT + 3) / 4 * 4);
+    tk.base = a.codes + lane64(mv, 2) * ivfpq_block_bytes(Mp);
     tk.tauv = 0.0f;
     if constexpr (!HEAD) tk.tauv = a.tau[(lane == 0 ? tk.q0 : tk.q1) * a.tau_stride];
     if (r_on) {
@@ -125,7 +136,7 @@ __global__ __launch_bounds__(LPP_NW * 64) __attribute__((amdgpu_waves_per_eu(LPP
     if (m_on) {
       rv = r2.v[mm];
       if (a.query_radii) {
-        const float r = a.query_radii[(mg ? tk.q1 : tk.q0) * MT + mm];
+        const float r = a.query_radii[(mg ? tk.q1 : tk.q0) * M + mm];
         rv = r * r;
       }
     }
@@ -162,6 +173,7 @@ __global__ __launch_bounds__(LPP_NW * 64) __attribute__((amdgpu_waves_per_eu(LPP
   };
 
   int part = 0, seg = 0;   // the part of the table; the first block of the points that are scanned with it
+  bool behind = false;     // this is not the first task
   int32_t drawn = 0;
   int qc0 = 0, qc1 = 0;
   uint32_t mn0 = 0xFFFFFFFFu, mn1 = 0xFFFFFFFFu, mx0 = 0u, mx1 = 0u;   // head pass: key range of this wavefront's points
@@ -169,6 +181,10 @@ __global__ __launch_bounds__(LPP_NW * 64) __attribute__((amdgpu_waves_per_eu(LPP
   for (;;) {
     asm volatile("" : "+v"(tid), "+v"(lane));   // (addresses formed anew for every part: kept across parts they spill)
     __syncthreads();   // the task's residuals and radii are there, and nobody reads the part before any more
+    if (part == 0 && seg == 0 && behind) {   // the task after this one is known by now
+      t_next = __builtin_amdgcn_readfirstlane(*t_after);
+      if (t_next < ntasks) npv = fetch_pairs(t_next);
+    }
     const bool last_part = part == P - 1, last_seg = seg + NB * NW >= tk.nb, more = t_next < ntasks;
     const bool new_task = last_part && last_seg;
     load_codes(tk.base, tk.nb, seg, part, code);   // (requested a part ahead, their registers spill)
@@ -176,11 +192,15 @@ __global__ __launch_bounds__(LPP_NW * 64) __attribute__((amdgpu_waves_per_eu(LPP
 #pragma unroll
     for (int it = 0; it < ROWS; ++it) {
       const int m = part * LPP_PART + it * NW + wave;
-      if (TAIL == 0 || m < MT) {
-        const floatx2 x0 = *(const LDS floatx2 *)(sres + 2 * m), x1 = *(const LDS floatx2 *)(sres + dpad + 2 * m);
-        const float res0[2] = {x0[0], x0[1]}, res1[2] = {x1[0], x1[1]};
-        const float4 v0 = lut_entry4<2, 0>(res0, row[it], sr2[m]);
-        const float4 v1 = lut_entry4<2, 0>(res1, row[it], sr2[IVFPQ_MAX_M + m]);
+      if ((!RT && TAIL == 0) || m < M) {
+        float res0[DSUB], res1[DSUB];
+#pragma unroll
+        for (int j = 0; j < DSUB; ++j) {
+          res0[j] = sres[m * DSUB + j];
+          res1[j] = sres[dpad + m * DSUB + j];
+        }
+        const float4 v0 = lut_entry4<DSUB, 0>(res0, row[it], sr2[m]);
+        const float4 v1 = lut_entry4<DSUB, 0>(res1, row[it], sr2[IVFPQ_MAX_M + m]);
         LDS floatx4 *dst = (LDS floatx4 *)(smem3 + (it * NW + wave) * 2048 + lane * 32);
         dst[0] = floatx4{v0.x, v1.x, v0.y, v1.y};
         dst[1] = floatx4{v0.z, v1.z, v0.w, v1.w};
@@ -191,13 +211,12 @@ __global__ __launch_bounds__(LPP_NW * 64) __attribute__((amdgpu_waves_per_eu(LPP
     __syncthreads();   // the part's rows are complete
     // ---- on their way while the part is scanned: the next part's rows, what the next task wants ----
     LmTask ntk = tk;
-    if (new_task && more) fetch_task(npv, nmv, ntk);
-    load_rows(last_part ? 0 : part + 1);
     if (part == 0 && last_seg && more) {
       nmv = fetch_meta(npv);
       if (tid == 0) drawn = atomicAdd(ticket, 1);
     }
-    if (part == 1 && tid == 0) *t_after = task_of(2 * run + drawn);
+    if (new_task && more) fetch_task(npv, nmv, ntk);
+    load_rows(last_part ? 0 : part + 1);
     // ---- look-ups ----
     if (part == 0) {
 #pragma unroll
@@ -227,12 +246,40 @@ __global__ __launch_bounds__(LPP_NW * 64) __attribute__((amdgpu_waves_per_eu(LPP
         }
       }
     };
-    if (TAIL == 0 || !last_part) look_up(std::integral_constant<int, LPP_PART>{});
-    else look_up(std::integral_constant<int, TAIL == 0 ? LPP_PART : TAIL>{});
+    if constexpr (RT) {
+      const int left = M - part * LPP_PART;
+      if (left >= LPP_PART) {
+        look_up(std::integral_constant<int, LPP_PART>{});
+      } else {   // four at a time; what is behind the last subspace adds nothing (no sum is below zero: + 0 leaves it)
+#pragma unroll
+        for (int i = 0; i < NB; ++i) {
+          if (seg + wave + i * NW >= tk.nb) break;
+          uintx4 w = code[i];
+#pragma unroll 1
+          for (int h = 0; h < left; h += 4) {
+            floatx2 v[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+              v[j] = *(const LDS floatx2 *)(uintptr_t)(uint32_t)((h + j) * 2048 + code_offset8(w[0], j));
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+              sum[i][0] += h + j < left ? v[j][0] : 0.0f;
+              sum[i][1] += h + j < left ? v[j][1] : 0.0f;
+            }
+            w = uintx4{w[1], w[2], w[3], 0u};
+          }
+        }
+      }
+    } else if (TAIL == 0 || !last_part) {
+      look_up(std::integral_constant<int, LPP_PART>{});
+    } else {
+      look_up(std::integral_constant<int, TAIL == 0 ? LPP_PART : TAIL>{});
+    }
     // ---- these points are summed ----
     if (last_part) {
       if constexpr (HEAD) {
-        LmWindow win = lm_window<MT>(sr2, lane);
+        LmWindow win = lm_window(sr2, M, lane);
 #pragma unroll
         for (int i = 0; i < NB; ++i) {
           if (seg + wave + i * NW >= tk.nb) break;
@@ -285,10 +332,10 @@ __global__ __launch_bounds__(LPP_NW * 64) __attribute__((amdgpu_waves_per_eu(LPP
     // ---- what is up next ----
     if (new_task) {
       put_task();
+      if (tid == 0) *t_after = task_of(2 * run + drawn);
+      behind = true;
       tk = ntk;
       seg = 0;
-      t_next = __builtin_amdgcn_readfirstlane(*t_after);
-      if (t_next < ntasks) npv = fetch_pairs(t_next);
     } else if (last_part) {
       seg += NB * NW;
     }

@@ -21,7 +21,7 @@ def _same(got, want, what):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("D,M", [(96, 48), (128, 64), (200, 100)])
+@pytest.mark.parametrize("D,M", [(96, 48), (128, 64), (200, 100), (146, 73), (80, 80), (246, 82), (256, 128), (255, 85), (95, 95)])
 @pytest.mark.parametrize("k,radius", [(1, 0.6), (128, 0.6), (10, 0.05), (100, np.inf)])
 def test_segments_and_groups(D, M, k, radius):
     """Lists of a block, of whole segments and one point more or less, of what the head pass holds (4600 to 4750 points) and
@@ -79,7 +79,7 @@ def test_100_subspaces_with_little_workspace():
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("D,M", [(96, 48), (128, 64), (200, 100)])
+@pytest.mark.parametrize("D,M", [(96, 48), (128, 64), (200, 100), (146, 73), (80, 80), (246, 82), (256, 128), (255, 85), (95, 95)])
 @pytest.mark.parametrize("centre", [0.1, 0.3, 3.0])
 def test_bounds_that_end_early(D, M, centre):
     """Lists that are ruled out by few of their subspaces, by many and not at all; probes that name no list, or an empty one;

@@ -267,6 +267,69 @@ __global__ __launch_bounds__(1024) void lm_offsets_kernel(LmArgs a) {
   if (tid == 1023) a.base[a.nlist] = part[1023];
 }
 
+// Head pass of a batch that one workgroup can sort: what lm_pairs_kernel, lm_offsets_kernel and lm_pairs_kernel do, the counts
+// in LDS, and the clearing of zero_n counters, which would be a launch each (4.7 us, nearly all of it the launch).  us of a
+// search, 64 subspaces, 32 probes, four launches / so: 512 queries 76.5 / 71.4, 1000 93.5 / 90.0, 2000 125.9 / 124.3, 3000
+// 159.8 / 160.2, 4096 189.9 / 193.7, 10 000 344 / 353 (one CU waits for a line of the probes per query): up to 2048.
+constexpr int LMH_THREADS = 1024, LMH_QUERIES = 2, LMH_LISTS = 16384;   // queries of a thread
+__global__ __launch_bounds__(LMH_THREADS) void lm_head_pairs_kernel(LmArgs a, int64_t zero_n) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  LDS uint32_t *cnt = (LDS uint32_t *)smem, *part = cnt + a.nlist;   // [nlist] pairs of a list, then where they begin; [LMH_THREADS]
+  const int tid = threadIdx.x;
+  for (int64_t i = tid; i < zero_n; i += LMH_THREADS) a.cnt[i] = 0;
+  for (int i = tid; i < a.nlist; i += LMH_THREADS) cnt[i] = 0u;
+  int32_t c[LMH_QUERIES], rank[LMH_QUERIES];
+#pragma unroll
+  for (int j = 0; j < LMH_QUERIES; ++j) {
+    const int64_t q = tid + j * LMH_THREADS;
+    c[j] = q < a.Q ? a.probe_ids[q * a.nprobe] : -1;
+  }
+#pragma unroll
+  for (int j = 0; j < LMH_QUERIES; ++j) {
+    const bool exists = (uint32_t)c[j] < (uint32_t)a.nlist;
+    const int64_t len = exists ? a.list_offsets[c[j] + 1] - a.list_offsets[c[j]] : 0;
+    rank[j] = len > 0 && len <= a.head_max ? 0 : -1;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < LMH_QUERIES; ++j) {
+    const int64_t q = tid + j * LMH_THREADS;
+    if (q >= a.Q) break;
+    a.gcnt[q] = 0u;
+    a.qmap_head[q] = rank[j] >= 0 ? -1 : (int32_t)q;
+    if (rank[j] >= 0) rank[j] = (int32_t)__hip_atomic_fetch_add(&cnt[c[j]], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  }
+  __syncthreads();
+  const uint32_t g = (uint32_t)a.group;
+  const int chunk = (a.nlist + LMH_THREADS - 1) / LMH_THREADS;
+  const int lo = tid * chunk < a.nlist ? tid * chunk : a.nlist, hi = lo + chunk < a.nlist ? lo + chunk : a.nlist;
+  uint32_t sum = 0;
+  for (int x = lo; x < hi; ++x) sum += (cnt[x] + g - 1) / g * g;
+  part[tid] = sum;
+  __syncthreads();
+  for (int off = 1; off < LMH_THREADS; off <<= 1) {
+    const uint32_t v = tid >= off ? part[tid - off] : 0u;
+    __syncthreads();
+    part[tid] += v;
+    __syncthreads();
+  }
+  uint32_t run = part[tid] - sum;
+  for (int x = lo; x < hi; ++x) {
+    const uint32_t n = cnt[x], padded = (n + g - 1) / g * g;
+    for (uint32_t j = n; j < padded; ++j) a.pairs[run + j] = make_int2(-1, x);
+    cnt[x] = run;
+    run += padded;
+  }
+  if (tid == LMH_THREADS - 1) a.base[a.nlist] = (int32_t)part[tid];   // (all that is read of it behind this)
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < LMH_QUERIES; ++j) {
+    const int64_t q = tid + j * LMH_THREADS;
+    if (q >= a.Q) break;
+    if (rank[j] >= 0) a.pairs[cnt[c[j]] + (uint32_t)rank[j]] = make_int2((int)q, c[j]);
+  }
+}
+
 // 8-byte look-up of a point's code in an interleaved table row (2 KiB per row): the byte
 // select of the sub-dword addressing form extracts the code and scales it by 8.
 __device__ __forceinline__ uint32_t code_offset8(uint32_t w, int j) {
@@ -2254,14 +2317,22 @@ int launch_scan_list_major(const ivfpq_index *ix, const float *d_queries, int64_
   // List-level lower bounds of every (query, probe): behind the head pass, where its k-th distances end most of them early
   // (lm_bound_kernel), or up front.  Either way the per-list counts are cleared (lm_offsets_kernel leaves them clear for the pass after it).
   const bool late_bounds = head_pass && a.probe_lb && ix->dsub == 2;
-  if (late_bounds) rc = launch_fill_i32(a.cnt, lm_counters(ix->nlist), 0, s);
-  else rc = launch_probe_bounds(ix, d_queries, Q, nprobe, d_probe_ids, r2, mode, d_query_radii, d_probe_lb, s, a.cnt, lm_counters(ix->nlist));
+  const bool head_sorted = head_pass && Q <= LMH_THREADS * LMH_QUERIES && ix->nlist <= LMH_LISTS;
+  if (late_bounds && !head_sorted) rc = launch_fill_i32(a.cnt, lm_counters(ix->nlist), 0, s);
+  else if (!late_bounds) rc = launch_probe_bounds(ix, d_queries, Q, nprobe, d_probe_ids, r2, mode, d_query_radii, d_probe_lb, s, a.cnt, lm_counters(ix->nlist));
   if (rc) return rc;
   if (head_pass) {
-    const unsigned qgrid = (unsigned)((Q + 255) / 256);
-    hipLaunchKernelGGL(lm_pairs_kernel, dim3(qgrid), dim3(256), 0, s, a, 0, 1);
-    hipLaunchKernelGGL(lm_offsets_kernel, dim3(1), dim3(1024), 0, s, a);
-    hipLaunchKernelGGL(lm_pairs_kernel, dim3(qgrid), dim3(256), 0, s, a, 1, 1);
+    if (head_sorted) {
+      static std::atomic<uint64_t> prepared;
+      if (int e = prepare_kernel(lm_head_pairs_kernel, prepared)) return e;
+      hipLaunchKernelGGL(lm_head_pairs_kernel, dim3(1), dim3(LMH_THREADS), (size_t)(ix->nlist + LMH_THREADS) * 4, s, a,
+                         late_bounds ? lm_counters(ix->nlist) : 0);
+    } else {
+      const unsigned qgrid = (unsigned)((Q + 255) / 256);
+      hipLaunchKernelGGL(lm_pairs_kernel, dim3(qgrid), dim3(256), 0, s, a, 0, 1);
+      hipLaunchKernelGGL(lm_offsets_kernel, dim3(1), dim3(1024), 0, s, a);
+      hipLaunchKernelGGL(lm_pairs_kernel, dim3(qgrid), dim3(256), 0, s, a, 1, 1);
+    }
     rc = head_bytes ? launch_lm_byte_head(a, r2, cus, s) : (table_parts ? launch_lm_pair<true>(a, r2, cus, s) : launch_lm_scan<true>(ix, a, r2, cus, s));
     if (rc) return rc;
     if (head_bytes) {

@@ -105,3 +105,27 @@ def test_bounds_that_end_early(D, M, centre):
     finally:
         b.set_option("bound_grid", 0)
         gi.close()
+
+
+@pytest.mark.gpu
+def test_batches_around_what_one_workgroup_sorts():
+    """1024 and 2048 queries and one more or less; all of them with the same nearest list, or none with any."""
+    import torch
+    from paper_2312_01712_amd import binding as b
+    rng = np.random.default_rng(9)
+    D, M, nlist, nprobe, k = 128, 64, 1100, 16, 10
+    idx = _index(rng, D, M, rng.integers(0, 60, size=nlist), centre=0.5)
+    q = (idx.centroids[rng.integers(0, nlist, 2049)] + 0.3 * rng.normal(size=(2049, D))).astype(np.float32)
+    radii = np.full(M, 0.7 * np.sqrt(2), dtype=np.float32)
+    pid, _ = oracle.coarse(q, idx.centroids, nprobe)
+    gi = b.IvfPqIndex.from_index(idx)
+    dq = torch.from_numpy(q).cuda()
+    for first in (None, int(np.argmax(np.diff(idx.list_offsets))), -1):
+        p = pid.astype(np.int32).copy()
+        if first is not None:
+            p[:, 0] = first
+        dp = torch.from_numpy(p).cuda()
+        for Q in (1023, 1024, 1025, 2047, 2048, 2049):
+            want = [x.cpu().numpy() for x in gi.scan_topk(dq[:Q].contiguous(), dp[:Q].contiguous(), k, radii, strategy=b.SCAN_QUERY_MAJOR)]
+            _same(gi.scan_topk(dq[:Q].contiguous(), dp[:Q].contiguous(), k, radii, strategy=b.SCAN_LIST_MAJOR), want, (first, Q))
+    gi.close()

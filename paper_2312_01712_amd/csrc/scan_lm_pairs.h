@@ -83,25 +83,22 @@ __global__ __launch_bounds__(LPP_NW * 64) __attribute__((amdgpu_waves_per_eu(LPP
     }
   };
   uintx4 code[NB];   // a part's codes of the wavefront's blocks
-  auto load_codes = [&](const uint8_t *base, int nb, int seg, int part, uintx4 (&r)[NB]) __attribute__((always_inline)) {
+  auto load_codes = [&](const uint8_t *base, int nb, int seg, int part, int i) __attribute__((always_inline)) {
+    const int at = seg + wave + i * NW, blk = at < nb ? at : nb - 1;   // no such block: the last one
+    if (RT ? part < (Mp >> 4) : (TAIL == 0 || part < P - 1)) {
+      const GLOBAL uint8_t *sp = uniform_ptr(base + ((int64_t)part * nb + blk) * 1024);
+      code[i] = *(const GLOBAL uintx4 *)(sp + (uint32_t)(lane * 16));
+    } else if constexpr (RT) {
+      code[i] = uintx4{0u, 0u, 0u, 0u};
 #pragma unroll
-    for (int i = 0; i < NB; ++i) {
-      const int at = seg + wave + i * NW, blk = at < nb ? at : nb - 1;   // no such block: the last one
-      if (RT ? part < (Mp >> 4) : (TAIL == 0 || part < P - 1)) {
-        const GLOBAL uint8_t *sp = uniform_ptr(base + ((int64_t)part * nb + blk) * 1024);
-        r[i] = *(const GLOBAL uintx4 *)(sp + (uint32_t)(lane * 16));
-      } else if constexpr (RT) {
-        r[i] = uintx4{0u, 0u, 0u, 0u};
-#pragma unroll
-        for (int t = 0; t < 3; ++t)
-          if (t < ((Mp >> 2) & 3)) {
-            const GLOBAL uint8_t *sp = uniform_ptr(base + (int64_t)(Mp >> 4) * nb * 1024 + ((int64_t)t * nb + blk) * 256);
-            r[i][t] = *(const GLOBAL uint32_t *)(sp + (uint32_t)(lane * 4));
-          }
-      } else {
-        const GLOBAL uint8_t *sp = uniform_ptr(base + (int64_t)(MT / 16) * nb * 1024 + (int64_t)blk * 256);
-        r[i] = uintx4{*(const GLOBAL uint32_t *)(sp + (uint32_t)(lane * 4)), 0u, 0u, 0u};
-      }
+      for (int t = 0; t < 3; ++t)
+        if (t < ((Mp >> 2) & 3)) {
+          const GLOBAL uint8_t *sp = uniform_ptr(base + (int64_t)(Mp >> 4) * nb * 1024 + ((int64_t)t * nb + blk) * 256);
+          code[i][t] = *(const GLOBAL uint32_t *)(sp + (uint32_t)(lane * 4));
+        }
+    } else {
+      const GLOBAL uint8_t *sp = uniform_ptr(base + (int64_t)(MT / 16) * nb * 1024 + (int64_t)blk * 256);
+      code[i] = uintx4{*(const GLOBAL uint32_t *)(sp + (uint32_t)(lane * 4)), 0u, 0u, 0u};
     }
   };
 
@@ -159,6 +156,8 @@ __global__ __launch_bounds__(LPP_NW * 64) __attribute__((amdgpu_waves_per_eu(LPP
     load_rows(0);
     fetch_task(pv, fetch_meta(pv), tk);
     put_task();
+#pragma unroll
+    for (int i = 0; i < NB; ++i) load_codes(tk.base, tk.nb, 0, 0, i);
   }
   // main pass: the candidates of the task before, queued in LDS, and where they go
   uint32_t pend_slot = 0;
@@ -187,7 +186,6 @@ __global__ __launch_bounds__(LPP_NW * 64) __attribute__((amdgpu_waves_per_eu(LPP
     }
     const bool last_part = part == P - 1, last_seg = seg + NB * NW >= tk.nb, more = t_next < ntasks;
     const bool new_task = last_part && last_seg;
-    load_codes(tk.base, tk.nb, seg, part, code);   // (requested a part ahead, their registers spill)
     // ---- the part's rows, interleaved: (query 0, query 1) of entry 0, of entry 1, ... ----
 #pragma unroll
     for (int it = 0; it < ROWS; ++it) {
@@ -209,7 +207,8 @@ __global__ __launch_bounds__(LPP_NW * 64) __attribute__((amdgpu_waves_per_eu(LPP
     if constexpr (!HEAD)
       if (part == 0) drain_pending();   // the queues are free again before this task fills them
     __syncthreads();   // the part's rows are complete
-    // ---- on their way while the part is scanned: the next part's rows, what the next task wants ----
+    // ---- on their way while the part is scanned: the next part's rows, what the next task wants; and a block's next
+    // codes from where its look-ups are made, in the registers of the ones looked up ----
     LmTask ntk = tk;
     if (part == 0 && last_seg && more) {
       nmv = fetch_meta(npv);
@@ -217,6 +216,9 @@ __global__ __launch_bounds__(LPP_NW * 64) __attribute__((amdgpu_waves_per_eu(LPP
     }
     if (new_task && more) fetch_task(npv, nmv, ntk);
     load_rows(last_part ? 0 : part + 1);
+    const bool to_next = new_task && more;   // (behind the last task: codes that are not looked at)
+    const uint8_t *next_base = to_next ? ntk.base : tk.base;
+    const int next_nb = to_next ? ntk.nb : tk.nb, next_seg = new_task ? 0 : (last_part ? seg + NB * NW : seg), next_part = last_part ? 0 : part + 1;
     // ---- look-ups ----
     if (part == 0) {
 #pragma unroll
@@ -226,24 +228,26 @@ __global__ __launch_bounds__(LPP_NW * 64) __attribute__((amdgpu_waves_per_eu(LPP
       constexpr int N = decltype(count)::value, G = N < 8 ? N : 8;
 #pragma unroll
       for (int i = 0; i < NB; ++i) {
-        if (seg + wave + i * NW >= tk.nb) break;
+        if (seg + wave + i * NW < tk.nb) {
 #pragma unroll
-        for (int h = 0; h < N; h += G) {
-          floatx2 v[G];
+          for (int h = 0; h < N; h += G) {
+            floatx2 v[G];
 #pragma unroll
-          for (int j = 0; j < G; ++j) {
-            const uint32_t off = code_offset8(code[i][(h + j) >> 2], j & 3);   // the table starts at LDS address 0
-            v[j] = *(const LDS floatx2 *)(uintptr_t)(uint32_t)((h + j) * 2048 + off);
+            for (int j = 0; j < G; ++j) {
+              const uint32_t off = code_offset8(code[i][(h + j) >> 2], j & 3);   // the table starts at LDS address 0
+              v[j] = *(const LDS floatx2 *)(uintptr_t)(uint32_t)((h + j) * 2048 + off);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int j = 0; j < G; ++j) {
+              sum[i][0] += v[j][0];
+              sum[i][1] += v[j][1];
+            }
+            asm volatile("" : "+v"(sum[i][0]), "+v"(sum[i][1]));   // (the additions stay here: moved to where the block's loop is left, they keep all look-ups in registers)
+            __builtin_amdgcn_sched_barrier(0);
           }
-          __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-          for (int j = 0; j < G; ++j) {
-            sum[i][0] += v[j][0];
-            sum[i][1] += v[j][1];
-          }
-          asm volatile("" : "+v"(sum[i][0]), "+v"(sum[i][1]));   // (the additions stay here: moved to where the block's loop is left, they keep all look-ups in registers)
-          __builtin_amdgcn_sched_barrier(0);
         }
+        load_codes(next_base, next_nb, next_seg, next_part, i);
       }
     };
     if constexpr (RT) {
@@ -253,8 +257,9 @@ __global__ __launch_bounds__(LPP_NW * 64) __attribute__((amdgpu_waves_per_eu(LPP
       } else {   // four at a time; what is behind the last subspace adds nothing (no sum is below zero: + 0 leaves it)
 #pragma unroll
         for (int i = 0; i < NB; ++i) {
-          if (seg + wave + i * NW >= tk.nb) break;
           uintx4 w = code[i];
+          load_codes(next_base, next_nb, next_seg, next_part, i);
+          if (seg + wave + i * NW >= tk.nb) continue;
 #pragma unroll 1
           for (int h = 0; h < left; h += 4) {
             floatx2 v[4];

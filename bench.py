@@ -43,7 +43,8 @@ def log(*a):
     print(*a, file=sys.stderr, flush=True)
 
 
-KERNEL_SOURCES = ("ivfpq_internal.h", "scan.hip", "scan_device.h", "scan_ip_carve.h", "scan_kernel.h", "scan_lm.hip", "scan_rt.hip")
+KERNEL_SOURCES = ("ivfpq_internal.h", "scan.hip", "scan_device.h", "scan_ip_carve.h", "scan_kernel.h", "scan_lm.hip", "scan_lm_pairs.h",
+                  "scan_lm_parts.h", "scan_rt.hip")
 
 
 def csrc_sha256() -> str:

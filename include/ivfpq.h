@@ -228,12 +228,13 @@ typedef enum {
  *     scoring, either setting but QUERY_MAJOR lets large batches of the first three be selected list-major
  *     in stages; ivfpq_resolve_strategy calls that query-major.)
  *   IVFPQ_SCAN_AUTO         the library chooses: list-major where it is available, when the
- *     batch has at least 16 384 (query, list) pairs and the index's mean list length is at
- *     most 4096, or, with distance scoring and up to 64 subspaces, at most 16 384 and the batch large enough that its
- *     queries share their nearest lists (two a list, 16 million points in all); query-major
+ *     batch has at least 16 384 (query, list) pairs (4096 to 9600, by the shape, with 8 probes and more, k <= 112
+ *     and where the index's longest list fits the pass that ranks the nearest lists) and the index's mean
+ *     list length is at most 4096, or, with distance scoring and up to 64 subspaces, at most 16 384 and the batch
+ *     large enough that its queries share their nearest lists (two a list, 16 million points in all); query-major
  *     otherwise.  On lists above 4096 points the workspace's candidate slots are bounded by 1 GiB or
- *     4096 queries, whichever is more, larger batches go through them in pieces, and a workspace
- *     sized for QUERY_MAJOR is accepted too; the call then runs query-major.
+ *     4096 queries, whichever is more, larger batches go through them in pieces.  There, and below 16 384
+ *     pairs, a workspace sized for QUERY_MAJOR is accepted too; the call then runs query-major.
  * ivfpq_search_workspace_bytes sizes the workspace for AUTO with distance scoring;
  * ivfpq_search_workspace_bytes_ex for the scoring actually passed. */
 typedef enum { IVFPQ_SCAN_AUTO = 0, IVFPQ_SCAN_QUERY_MAJOR = 1, IVFPQ_SCAN_LIST_MAJOR = 2 } ivfpq_scan_strategy;

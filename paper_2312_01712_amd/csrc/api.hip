@@ -228,6 +228,8 @@ static int64_t lm_together(const ivfpq_index *ix, int64_t Q, int32_t nprobe, int
   return Q < fit ? Q : fit;
 }
 
+constexpr int64_t LM_ALWAYS = 16384;   // (query, list) pairs
+
 // Which way stages 2-4 run.  A request for the list-major scan is honoured where that scan is
 // built (L2, k <= 128, the specialised shapes), anything else runs query-major.  Left to the
 // library (AUTO), the list-major scan serves batches with enough (query, list) pairs to group,
@@ -240,7 +242,26 @@ static bool use_list_major(const ivfpq_index *ix, int64_t Q, int32_t nprobe, int
   if (requested == IVFPQ_SCAN_QUERY_MAJOR || !list_major_supported(ix, nprobe, k)) return false;
   if (!byte_table_shape(ix) && mode != IVFPQ_SCORE_DISTANCE) return false;   // (the hit counts' byte tables serve them query-major)
   if (requested == IVFPQ_SCAN_LIST_MAJOR) return true;
-  if (Q * (int64_t)nprobe < 16384) return false;
+  const int64_t pairs = Q * (int64_t)nprobe;
+  if (pairs < LM_ALWAYS) {
+    // Fewer pairs pay where all lists fit the head pass: a query whose nearest list does not has a workgroup to itself for
+    // all of its lists (two components a list, 64 queries, 64 subspaces 156 / 528 us, 100 subspaces 400 / 1436).  us of a search of 32
+    // probes, query-major / list-major, otherwise:
+    //   queries                               64           128           200           300           450
+    //   64 subspaces, clustered          86 / 53       87 / 54       91 / 55      102 / 65      100 / 72
+    //   48, clustered                    77 / 49       79 / 50       82 / 50       95 / 58       95 / 64
+    //   48, without structure          153 / 160     182 / 196     229 / 216     296 / 238     382 / 275
+    //   48, hit counts                 171 / 148     215 / 177     266 / 187     332 / 211     411 / 237
+    //   16, clustered                    87 / 44       76 / 45       75 / 47       74 / 48       76 / 58
+    //   16, without structure           138 / 82      115 / 93     135 / 107     164 / 120     199 / 178
+    //   100, clustered                   78 / 76      86 / 105      93 / 106     123 / 111     133 / 113
+    // The lines are where neither kind of data pays (16 subspaces: with a margin).  So it does from 8 probes on (16 subspaces, 1000 queries of 4: 51 / 55) and while the
+    // k nearest and a few more fit the head pass' 128 keys (64 subspaces, 300 queries, k = 128: 104 / 112, k = 100 104 / 66).
+    if (nprobe < 8 || k > 112) return false;
+    if (pairs < (ix->M == 16 ? 4096 : byte_table_shape(ix) ? 6144 : 9600)) return false;
+    if (mode == IVFPQ_SCORE_DISTANCE && !head_pass_holds_all(ix)) return false;
+    return ix->N <= (int64_t)4096 * ix->nlist;
+  }
   if (ix->N <= (int64_t)4096 * ix->nlist) return true;
   if (!byte_table_shape(ix)) return false;   // (no byte tables for the head pass on long lists)
   // Longer lists: the query-major scan prunes block by block, the list-major one shares each pass over a list among the
@@ -742,12 +763,13 @@ static int scan_query_major(const ivfpq_index *ix, const float *d_queries, int64
                      reinterpret_cast<float *>(base + w.probe_dist), s, &view);
 }
 
-// Whether a call goes list-major with the workspace it has: AUTO on long lists, and every call on shapes without byte
-// tables, is served query-major where the workspace only has room for that.
+// Whether a call goes list-major with the workspace it has: AUTO on long lists and below LM_ALWAYS pairs, and every call on shapes
+// without byte tables, is served query-major where the workspace only has room for that.
 static bool goes_list_major(const ivfpq_index *ix, int64_t Q, int32_t nprobe, int32_t k, int32_t mode, int32_t strategy,
                             const Workspace &w, size_t ws_bytes) {
   if (!use_list_major(ix, Q, nprobe, k, mode, strategy)) return false;
-  if (byte_table_shape(ix) && (strategy == IVFPQ_SCAN_LIST_MAJOR || ix->N <= (int64_t)4096 * ix->nlist)) return true;
+  if (byte_table_shape(ix) &&
+      (strategy == IVFPQ_SCAN_LIST_MAJOR || (ix->N <= (int64_t)4096 * ix->nlist && Q * (int64_t)nprobe >= LM_ALWAYS))) return true;
   return ws_bytes >= align256(w.total) + plan_list_major(ix, lm_together(ix, Q, nprobe, strategy), nprobe).total;
 }
 

@@ -174,6 +174,11 @@ inline bool list_major_shape(const ivfpq_index *ix) {
   return byte_table_shape(ix) || (ix->M > 72 && ix->M <= 128 && ix->dsub <= 3 && ix->D <= 256);
 }
 
+// Whether no list is too long for the head pass of a small batch (lm_head_max, lpp_head_max: these or more).
+constexpr int lm_head_fits(int M) { return M == 64 ? 2752 : (M == 48 ? 6912 : 8192); }
+constexpr int LPP_HEAD_FITS = 4480;
+inline bool head_pass_holds_all(const ivfpq_index *ix) { return ix->max_list_len <= (byte_table_shape(ix) ? lm_head_fits(ix->M) : LPP_HEAD_FITS); }
+
 // Workspace of the wide selection (more than 128 neighbours per query in one pass of the
 // query-major scan): offsets into its part of the workspace, 256-byte aligned.
 struct WideWorkspace {

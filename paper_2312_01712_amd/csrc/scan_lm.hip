@@ -1984,18 +1984,20 @@ __global__ __launch_bounds__(256) void lm_merge_kernel(LmArgs a) {
 std::atomic<int> g_lm_first{1};     // lists per query that are ranked first (their k-th distance filters the rest)
 std::atomic<int> g_lm_cap{0};       // candidate slots per query; 0: by the number of probes (lm_auto_cap)
 
-size_t lm_fixed_lds(int M, int D) {   // table, residuals, radii
+constexpr size_t lm_fixed_lds(int M, int D) {   // table, residuals, radii
   const int dpad = (D + 3) & ~3;
   return (size_t)M * 2048 + (size_t)LM_G * dpad * 4 + (size_t)LM_G * IVFPQ_MAX_M * 4;
 }
 size_t lm_scan_lds(int M, int D) { return lm_fixed_lds(M, D) + (size_t)LM_NW * LM_G * 2 * LM_QUEUE * 4; }
 // head pass: the distances of the list's points for both queries live in LDS next to the table
-int lm_head_max(int M, int D) {
+constexpr int lm_head_max(int M, int D) {
   const int64_t spare = (int64_t)LDS_PER_CU - (int64_t)lm_fixed_lds(M, D) - LM_SEL_WORDS * 4 - LM_G * LM_BINS * 4;
   int64_t n = spare / (LM_G * 4);
   n &= ~(int64_t)63;
   return (int)(n > 8192 ? 8192 : (n < 0 ? 0 : n));
 }
+static_assert(lm_head_max(64, 128) >= ivfpq::lm_head_fits(64) && lm_head_max(48, 96) >= ivfpq::lm_head_fits(48) && lm_head_max(16, 64) >= ivfpq::lm_head_fits(16) &&
+              lpp_head_max(256) >= ivfpq::LPP_HEAD_FITS, "the longest lists that AUTO counts on");
 size_t lm_head_lds(int M, int D) { return lm_fixed_lds(M, D) + (size_t)LM_G * lm_head_max(M, D) * 4 + LM_SEL_WORDS * 4 + LM_G * LM_BINS * 4; }
 
 // The queries that qmap names, as a list.  (One atomic per wavefront of 64 queries: one per query, from

@@ -17,10 +17,10 @@ constexpr int LPP_NB = 4;        // blocks of 64 points whose sums a wavefront h
 constexpr int LPP_SEG = LPP_NW * LPP_NB * 64;   // points of a list that are scanned with one table
 constexpr int LPP_BUF = LPP_PART * 2048;
 
-size_t lpp_fixed_lds(int D) { return LPP_BUF + (size_t)LM_G * ((D + 3) & ~3) * 4 + (size_t)LM_G * IVFPQ_MAX_M * 4 + 16; }
+constexpr size_t lpp_fixed_lds(int D) { return LPP_BUF + (size_t)LM_G * ((D + 3) & ~3) * 4 + (size_t)LM_G * IVFPQ_MAX_M * 4 + 16; }
 size_t lpp_main_lds(int D) { return lpp_fixed_lds(D) + (size_t)LPP_NW * LM_G * 2 * LM_QUEUE * 4; }
 // head pass: the distances of the list's points for both queries
-int lpp_head_max(int D) {
+constexpr int lpp_head_max(int D) {
   const int64_t spare = (int64_t)(LDS_PER_CU / LPP_WG) - (int64_t)lpp_fixed_lds(D) - LM_SEL_WORDS * 4 - LM_G * LM_BINS * 4;
   const int64_t n = spare / (LM_G * 4) & ~(int64_t)63;
   return n < 0 ? 0 : (int)n;

@@ -129,3 +129,32 @@ def test_batches_around_what_one_workgroup_sorts():
             want = [x.cpu().numpy() for x in gi.scan_topk(dq[:Q].contiguous(), dp[:Q].contiguous(), k, radii, strategy=b.SCAN_QUERY_MAJOR)]
             _same(gi.scan_topk(dq[:Q].contiguous(), dp[:Q].contiguous(), k, radii, strategy=b.SCAN_LIST_MAJOR), want, (first, Q))
     gi.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("D,M,line", [(128, 64, 6144), (64, 16, 4096), (200, 100, 9600)])
+def test_small_batches_that_go_list_major(D, M, line):
+    """Either side of the line of AUTO, with a workspace of their own and one that only has room for the query-major scan;
+    lists too long for the head pass, few probes and k near its limit stay query-major."""
+    import torch
+    from paper_2312_01712_amd import binding as b
+    rng = np.random.default_rng(M)
+    nprobe, k = 16, 10
+    sizes = rng.integers(20, 300, size=80)
+    for longest in (300, 9000):
+        sizes[7] = longest
+        idx = _index(rng, D, M, sizes, centre=0.3)
+        Q = line // nprobe
+        q = (idx.centroids[rng.integers(0, len(sizes), Q)] + 0.3 * rng.normal(size=(Q, D))).astype(np.float32)
+        radii = np.full(M, 0.7 * np.sqrt(D / M), dtype=np.float32)
+        gi = b.IvfPqIndex.from_index(idx)
+        assert gi.resolve_strategy(Q, nprobe, k) == (b.SCAN_LIST_MAJOR if longest == 300 else b.SCAN_QUERY_MAJOR)
+        for other in ((Q - 1, nprobe, k), (line // 4, 4, k), (Q, nprobe, 113)):
+            assert gi.resolve_strategy(*other) == b.SCAN_QUERY_MAJOR, other
+        want = oracle.search(q, idx, nprobe, k, radii, threads=8)
+        dq = torch.from_numpy(q).cuda()
+        _same(gi.search(dq, nprobe, k, radii), want, (longest, "own workspace"))
+        _same(gi.search(dq, nprobe, k, radii, workspace=gi.workspace(Q, nprobe, k, strategy=b.SCAN_QUERY_MAJOR)), want, (longest, "small workspace"))
+        for kk in (100, 112):
+            _same(gi.search(dq, nprobe, kk, radii), oracle.search(q, idx, nprobe, kk, radii, threads=8), (longest, kk))
+        gi.close()

@@ -262,8 +262,11 @@ static bool use_list_major(const ivfpq_index *ix, int64_t Q, int32_t nprobe, int
     if (mode == IVFPQ_SCORE_DISTANCE && !head_pass_holds_all(ix)) return false;
     return ix->N <= (int64_t)4096 * ix->nlist;
   }
+  // (73 subspaces and more: no byte tables for the head pass on long lists, and lists that it does not hold pay where they are
+  // short on average or the queries many.  100 subspaces, two components a list: 617 queries, lists of 2113 2674 us / 3527 list-major,
+  // 1000, 977 5022 / 4114, 4000, 977 19 661 / 10 471.)
+  if (!byte_table_shape(ix)) return ix->N <= (int64_t)4096 * ix->nlist && (head_pass_holds_all(ix) || ix->N <= (int64_t)1024 * ix->nlist || Q >= 4096);
   if (ix->N <= (int64_t)4096 * ix->nlist) return true;
-  if (!byte_table_shape(ix)) return false;   // (no byte tables for the head pass on long lists)
   // Longer lists: the query-major scan prunes block by block, the list-major one shares each pass over a list among the
   // queries that probe it.  Distances only (the hit counts' first lists are ranked query-major either way).  Query-major /
   // list-major, us, k = 100, 64 probes, 64 subspaces of clustered data unless said:

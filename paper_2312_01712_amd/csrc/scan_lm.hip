@@ -148,14 +148,17 @@ __device__ __forceinline__ float xor_f32(float v) { return __uint_as_float(xor_u
 // way from the L2 (24 bytes per pair and subspace).  Queries that are left to the query-major scan get theirs in full.
 // 10 000 queries, clustered data, bounds up front and count / so: 64 subspaces of 32 probes 64 + 5 / 39 us, 100 of 64 184 + 5 / 109;
 // 48 of 64 without structure, where none ends early, 117 + 118 / 245.
+// The pairs of a workgroup are counted by one instruction: atomics on a line are served one after the other, those of an
+// instruction together (four lanes at a time, 30 000 pairs on few lists took 70 us, the whole of probe_bound_kernel and lm_pairs_kernel 37).
 constexpr int LM_BOUND_SETS = 2;   // pairs of a quarter of a wavefront, whose loads are issued together
+constexpr int LM_BOUND_NW = 64 / (4 * LM_BOUND_SETS);   // wavefronts: 64 pairs
 template <bool GRID>
-__global__ __launch_bounds__(256) void lm_bound_kernel(LmArgs a, RadiiSq r2, const float *__restrict__ box, const float *__restrict__ grid,
+__global__ __launch_bounds__(LM_BOUND_NW * 64) void lm_bound_kernel(LmArgs a, RadiiSq r2, const float *__restrict__ box, const float *__restrict__ grid,
                                                        const float *__restrict__ grid_par, float *__restrict__ lb) {
   const int lane = threadIdx.x & 63, l = lane & 15;
   const uint32_t np2 = (uint32_t)(a.p1 - a.p0), total = (uint32_t)a.Q * np2;   // (below 2^31)
-  const uint32_t idx0 = (blockIdx.x * 4 + (threadIdx.x >> 6)) * (4 * LM_BOUND_SETS) + (lane >> 4);
-  if (idx0 - (lane >> 4) >= total) return;
+  __shared__ int32_t counted[64];   // list of a pair that is counted, or -1
+  const uint32_t slot0 = (threadIdx.x >> 6) * (4 * LM_BOUND_SETS) + (lane >> 4), idx0 = blockIdx.x * 64 + slot0;
   uint32_t q[LM_BOUND_SETS];
   int32_t c[LM_BOUND_SETS];
   bool want[LM_BOUND_SETS], named[LM_BOUND_SETS], exists[LM_BOUND_SETS], alive[LM_BOUND_SETS];
@@ -224,6 +227,7 @@ __global__ __launch_bounds__(256) void lm_bound_kernel(LmArgs a, RadiiSq r2, con
 #pragma unroll
   for (int s = 0; s < LM_BOUND_SETS; ++s) {
     const uint32_t idx = idx0 + 4 * s;
+    if (l == 0) counted[slot0 + 4 * s] = idx < total && alive[s] && !named[s] ? c[s] : -1;
     if (l != 0 || idx >= total) continue;
     const int p = a.p0 + (int)(idx % np2);
     float *row = lb + (int64_t)q[s] * a.nprobe;
@@ -233,8 +237,12 @@ __global__ __launch_bounds__(256) void lm_bound_kernel(LmArgs a, RadiiSq r2, con
       if (!a.later)
         for (int x = 0; x < a.p0; ++x) row[x] = 0.0f;   // (lists ranked by the head pass: no bound, wherever they are scanned again)
     }
-    a.rank[idx] = alive[s] && !named[s] ? atomicAdd(&a.cnt[c[s]], 1) : -1;
   }
+  __syncthreads();
+  const uint32_t idx = blockIdx.x * 64 + threadIdx.x;
+  if (threadIdx.x >= 64 || idx >= total) return;
+  const int32_t list = counted[threadIdx.x];
+  a.rank[idx] = list >= 0 ? atomicAdd(&a.cnt[list], 1) : -1;
 }
 
 // Slot ranges of the lists: base[c] = sum over c' < c of cnt[c'] rounded up to a.group.  The
@@ -2275,7 +2283,10 @@ int launch_scan_list_major(const ivfpq_index *ix, const float *d_queries, int64_
   IVFPQ_HIP_TRY(hipGetDevice(&dev));
   IVFPQ_HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
   if (cus < 1) cus = 1;
-  const bool table_parts = !byte_table_shape(ix) || (ix->dsub == 2 && (Q > (int64_t)4 * cus || ix->N >= (int64_t)2048 * ix->nlist));
+  // (48 subspaces: whole tables leave room for longer lists, and every query whose list has none is redone.  Radii per query, two
+  // components a list, 7312 queries, lists of 2035: 3362 us, in parts 4046.)
+  const bool longer_whole = byte_table_shape(ix) && lm_head_max(ix->M, ix->D) > lpp_head_max(ix->D) && ix->max_list_len > lpp_head_max(ix->D);
+  const bool table_parts = !byte_table_shape(ix) || (ix->dsub == 2 && !longer_whole && (Q > (int64_t)4 * cus || ix->N >= (int64_t)2048 * ix->nlist));
   a.head_max = table_parts ? lpp_head_max(ix->D) : lm_head_max(ix->M, ix->D);
   a.k = k;
   a.mode = mode;
@@ -2393,9 +2404,9 @@ int launch_scan_list_major(const ivfpq_index *ix, const float *d_queries, int64_
     const int64_t npairs = Q * (p1 - p0);
     const unsigned pair_grid = (unsigned)((npairs + 255) / 256);
     if (late_bounds) {
-      const unsigned bound_grid = (unsigned)((npairs + 16 * LM_BOUND_SETS - 1) / (16 * LM_BOUND_SETS));
-      if (bounds_use_grid(ix)) hipLaunchKernelGGL(lm_bound_kernel<true>, dim3(bound_grid), dim3(256), 0, s, a, r2, ix->d_box, ix->d_grid, ix->d_grid_par, d_probe_lb);
-      else hipLaunchKernelGGL(lm_bound_kernel<false>, dim3(bound_grid), dim3(256), 0, s, a, r2, ix->d_box, nullptr, nullptr, d_probe_lb);
+      const unsigned bound_grid = (unsigned)((npairs + 63) / 64);
+      if (bounds_use_grid(ix)) hipLaunchKernelGGL(lm_bound_kernel<true>, dim3(bound_grid), dim3(LM_BOUND_NW * 64), 0, s, a, r2, ix->d_box, ix->d_grid, ix->d_grid_par, d_probe_lb);
+      else hipLaunchKernelGGL(lm_bound_kernel<false>, dim3(bound_grid), dim3(LM_BOUND_NW * 64), 0, s, a, r2, ix->d_box, nullptr, nullptr, d_probe_lb);
     } else {
       hipLaunchKernelGGL(lm_pairs_kernel, dim3(pair_grid), dim3(256), 0, s, a, 0, 0);
     }

@@ -39,8 +39,9 @@ struct LmpFetch {
 typedef int intx4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
-// Errors of a table value, in units of a byte: LMP_REL of s (|r| + |e|)^2 for the split factors (either is within 2^-18 of
-// its value, and so is |e|^2; what the products' sums lose is 2^-20 of the largest of them), LMP_RAISE for the constant.
+// Errors of a table value, in units of a byte: LMP_REL of s (|r| + |e|)^2 for the split factors (either is within 2^-17 of
+// its value, and so is |e|^2: half of it; what the products' sums lose is 2^-20 of the largest of them), LMP_RAISE for the constant.
+// A value is raised by as much, so that it is no less than what an entry gains, and may be above that by twice as much.
 constexpr float LMP_RAISE = 1.0f / 1024.0f, LMP_REL = 1.0f / 32768.0f;
 
 // A value as a pair of bf16: the rest in the low half.
@@ -205,7 +206,10 @@ __global__ __launch_bounds__(LMP_NW * 64) __attribute__((amdgpu_waves_per_eu(LMP
       over_lanes([&](auto other) __attribute__((always_inline)) { rmax = fmaxf(rmax, other(rmax)); });
     }
     const float cap = fmaxf(fminf(rmax, tau * (4.0f / (float)MT)), 1e-30f);
-    const float s = ((float)LMB_TOP - 0.6f) / fmaf(farthest, LMP_REL, cap);   // (the error's room included; infinite radii and no k-th distance: 0)
+    // No byte is above LMB_TOP, which the sum of two as a signed byte needs and the conversion does not see to (it cuts off at
+    // 255): a value is at most s (cap + 2 LMP_REL farthest) + 2 LMP_RAISE + 0.5 < LMB_TOP + 0.5.  (Room for the raise alone let
+    // bytes of 70 and more through where cap is small, and points on their query were missed.)
+    const float s = ((float)LMB_TOP - 0.6f) / fmaf(farthest, 2.0f * LMP_REL, cap);   // (infinite radii and no k-th distance: 0)
     float least = 0.0f;
 #pragma unroll
     for (int x = 0; x < H; ++x) {

@@ -228,8 +228,9 @@ typedef enum {
  *     scoring, either setting but QUERY_MAJOR lets large batches of the first three be selected list-major
  *     in stages; ivfpq_resolve_strategy calls that query-major.)
  *   IVFPQ_SCAN_AUTO         the library chooses: list-major where it is available, when the
- *     batch has at least 16 384 (query, list) pairs (4096 to 9600, by the shape, with 8 probes and more, k <= 112
- *     and where the index's longest list fits the pass that ranks the nearest lists) and the index's mean
+ *     batch has at least 16 384 (query, list) pairs (4096 to 9600, by the shape, with 8 probes and more, k <= 100
+ *     and where the index's longest list fits the pass that ranks the nearest lists; with 16 subspaces also a
+ *     mean list of 16 k points, or 256 queries, 6144 pairs and k <= 64 where hits are counted) and the index's mean
  *     list length is at most 4096, or, with distance scoring and up to 64 subspaces, at most 16 384 and the batch
  *     large enough that its queries share their nearest lists (two a list, 16 million points in all); query-major
  *     otherwise.  On lists above 4096 points the workspace's candidate slots are bounded by 1 GiB or

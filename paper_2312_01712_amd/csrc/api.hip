@@ -253,13 +253,23 @@ static bool use_list_major(const ivfpq_index *ix, int64_t Q, int32_t nprobe, int
     //   48, without structure          153 / 160     182 / 196     229 / 216     296 / 238     382 / 275
     //   48, hit counts                 171 / 148     215 / 177     266 / 187     332 / 211     411 / 237
     //   16, clustered                    87 / 44       76 / 45       75 / 47       74 / 48       76 / 58
-    //   16, without structure           138 / 82      115 / 93     135 / 107     164 / 120     199 / 178
     //   100, clustered                   78 / 76      86 / 105      93 / 106     123 / 111     133 / 113
-    // The lines are where neither kind of data pays (16 subspaces: with a margin).  So it does from 8 probes on (16 subspaces, 1000 queries of 4: 51 / 55) and while the
-    // k nearest and a few more fit the head pass' 128 keys (64 subspaces, 300 queries, k = 128: 104 / 112, k = 100 104 / 66).
-    if (nprobe < 8 || k > 112) return false;
+    // So it does from 8 probes on (16 subspaces, 1000 queries of 4: 51 / 55) and while the k nearest and a few more fit the head
+    // pass' 128 keys: beyond, ties of the histogram's bins leave queries over, which are redone (64 subspaces, 300 queries, k = 128:
+    // 104 / 112, k = 100 104 / 66; of random calls with k = 112 and radii that hold nine tenths of the entries, half lose).
+    // With 16 subspaces the query-major scan is cheap, and calls whose bound lets many of a list's points through pay for their
+    // candidates (without structure, 128, 256 and 510 queries, lists of 976, k = 10 107 / 80, 125 / 91, 190 / 123; k = 100 122 / 136,
+    // 145 / 173, 216 / 218; lists of 390, k = 100 106 / 125, 121 / 162, 178 / 210; lists of 2000 gain), and so do hit counts of few
+    // queries, which the query-major scan splits over workgroups (162 queries, k = 100 286 / 617).
+    // Over 5600 random calls between the lines and LM_ALWAYS, query-major over list-major as a geometric mean, least, and how many of 100
+    // are below 0.95, radii that hold a tenth to half of the entries: 16 subspaces 1.38, 0.89, 1; its hit counts 1.47, 0.91, none; 48
+    // 1.64, 0.79, 1, hit counts 1.64, 0.92, 1; 64 1.61, 0.54 (lists of a few hundred points, k = 100), 3, hit counts 1.74, 0.87, 1; 73
+    // and more 1.96, 0.61 (clustered data, 64 probes), 2.  Radii that hold nine tenths: distances 1.3 to 1.6, 0.40, 2 to 11; hit counts
+    // 16 subspaces 1.16, 0.42, 27, 48 and 64 1.6, 0.82, 1.
+    if (nprobe < 8 || k > 100) return false;
     if (pairs < (ix->M == 16 ? 4096 : byte_table_shape(ix) ? 6144 : 9600)) return false;
     if (mode == IVFPQ_SCORE_DISTANCE && !head_pass_holds_all(ix)) return false;
+    if (ix->M == 16 && !(mode == IVFPQ_SCORE_DISTANCE ? ix->N >= (int64_t)16 * k * ix->nlist : (k <= 64 && Q >= 256 && pairs >= 6144))) return false;
     return ix->N <= (int64_t)4096 * ix->nlist;
   }
   // (73 subspaces and more: no byte tables for the head pass on long lists, and lists that it does not hold pay where they are

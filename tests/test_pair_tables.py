@@ -158,3 +158,26 @@ def test_small_batches_that_go_list_major(D, M, line):
         for kk in (100, 112):
             _same(gi.search(dq, nprobe, kk, radii), oracle.search(q, idx, nprobe, kk, radii, threads=8), (longest, kk))
         gi.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("D,M,mean,longest,Q,nprobe,k,mode,list_major", [
+    (64, 16, 400, 500, 256, 32, 25, 0, True), (64, 16, 400, 500, 256, 32, 26, 0, False),       # mean lists of 16 k points
+    (64, 16, 400, 500, 512, 32, 26, 0, True),                                                  # (16 384 pairs: always)
+    (64, 16, 400, 500, 256, 24, 64, 1, True), (64, 16, 400, 500, 255, 32, 64, 1, False),       # hit counts: queries ...
+    (64, 16, 400, 500, 256, 23, 64, 2, False), (64, 16, 400, 500, 256, 32, 65, 1, False),      # ... pairs and neighbours
+    (96, 48, 400, 500, 256, 32, 100, 0, True), (96, 48, 400, 500, 256, 32, 101, 0, False),
+    (160, 80, 1100, 4000, 512, 32, 10, 0, True)])
+def test_lines_of_auto(D, M, mean, longest, Q, nprobe, k, mode, list_major):
+    """Either side of what AUTO asks of 16 subspaces, and of neighbours."""
+    from paper_2312_01712_amd import binding as b
+    rng = np.random.default_rng(M)
+    sizes = np.full(70, mean)
+    sizes[7] += longest - mean
+    sizes[8:68] -= (longest - mean) // 60 + 1
+    sizes[9] += 70 * mean - sizes.sum()   # (the mean is what it says)
+    gi = b.IvfPqIndex.from_index(_index(rng, D, M, sizes))
+    try:
+        assert gi.resolve_strategy(Q, nprobe, k, mode=mode) == (b.SCAN_LIST_MAJOR if list_major else b.SCAN_QUERY_MAJOR)
+    finally:
+        gi.close()

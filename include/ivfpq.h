@@ -224,7 +224,9 @@ typedef enum {
  *     cluster structure.
  *     Needs the L2 metric, k <= 128 and an (M, dsub) of (48, 2), (64, 2) or (16, 4), or, with distance scoring,
  *     73 to 128 subspaces of up to three dimensions, 256 in all; any other call is served query-major.  Takes a larger
- *     workspace (with 73 subspaces and more, a call with less than that is served query-major).  (For 128 < k <= 1024 with distance
+ *     workspace: 2 KiB a query and probe for candidates, 32 KiB at least and 128 KiB at most.  (With 73 subspaces and more 2 GiB
+ *     for them or what 4096 queries want, whichever is more, larger batches go through them in pieces; and a call with less than
+ *     that is served query-major.)  (For 128 < k <= 1024 with distance
  *     scoring, either setting but QUERY_MAJOR lets large batches of the first three be selected list-major
  *     in stages; ivfpq_resolve_strategy calls that query-major.)
  *   IVFPQ_SCAN_AUTO         the library chooses: list-major where it is available, when the

@@ -218,12 +218,14 @@ static int check_workspace(const Workspace &w, const void *ws, size_t bytes, con
   return IVFPQ_OK;
 }
 
-// Queries that go through the list-major scan together.  Where AUTO takes it on long lists, calls that the query-major
-// scan serves with a few KiB of workspace a query, the candidates' slots (up to 128 KiB a query) take 1 GiB at most, or
+// Queries that go through the list-major scan together.  Where AUTO takes it on long lists, and on shapes without byte tables
+// whichever way it is asked for, it serves calls that the query-major scan serves with a few KiB of workspace a query: there
+// the candidates' slots (up to 128 KiB a query) take 1 GiB at most, 2 GiB on those shapes (16 384 queries of 64 probes), or
 // what 4096 queries want of them; larger batches go through them in pieces.  Anywhere else all queries of the call.
 static int64_t lm_together(const ivfpq_index *ix, int64_t Q, int32_t nprobe, int32_t requested) {
-  if (requested == IVFPQ_SCAN_LIST_MAJOR || ix->N <= (int64_t)4096 * ix->nlist) return Q;
-  int64_t fit = ((int64_t)1 << 30) / ((int64_t)plan_list_major(ix, 1, nprobe).cap * 8) & ~(int64_t)63;
+  if (byte_table_shape(ix) && (requested == IVFPQ_SCAN_LIST_MAJOR || ix->N <= (int64_t)4096 * ix->nlist)) return Q;
+  const int64_t room = (int64_t)1 << (byte_table_shape(ix) ? 30 : 31);
+  int64_t fit = room / ((int64_t)plan_list_major(ix, 1, nprobe).cap * 8) & ~(int64_t)63;
   if (fit < 4096) fit = 4096;
   return Q < fit ? Q : fit;
 }

@@ -181,3 +181,41 @@ def test_lines_of_auto(D, M, mean, longest, Q, nprobe, k, mode, list_major):
         assert gi.resolve_strategy(Q, nprobe, k, mode=mode) == (b.SCAN_LIST_MAJOR if list_major else b.SCAN_QUERY_MAJOR)
     finally:
         gi.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("D,M", [(200, 100), (160, 80)])
+def test_large_batches_go_in_pieces(D, M):
+    """Shapes without byte tables for everything: what a workspace holds for candidates stops growing at 2 GiB (or what 4096
+    queries want), however the scan is asked for; batches of two pieces, the last one short, return what the oracle does."""
+    import torch
+    from paper_2312_01712_amd import binding as b
+    rng = np.random.default_rng(M)
+    nprobe, k, distinct, reps = 8, 10, 60, 75
+    idx = _index(rng, D, M, rng.integers(40, 400, size=70))
+    q = (idx.centroids[rng.integers(0, 70, distinct)] + 0.3 * rng.normal(size=(distinct, D))).astype(np.float32)
+    radii = np.full(M, 0.6 * np.sqrt(2), dtype=np.float32)
+    gi = b.IvfPqIndex.from_index(idx)
+
+    def slots(Q, nprobe, strategy):
+        return gi.workspace_bytes(Q, nprobe, k, strategy=strategy) - gi.workspace_bytes(Q, nprobe, k, strategy=b.SCAN_QUERY_MAJOR)
+
+    try:
+        for strategy in (b.SCAN_AUTO, b.SCAN_LIST_MAJOR):
+            assert gi.resolve_strategy(1_000_000, 64, k, strategy=strategy) == b.SCAN_LIST_MAJOR
+            assert slots(1_000_000, 64, strategy) == slots(16_384, 64, strategy) < (2 << 30) + (64 << 20), strategy
+        b.set_option("lm_cap", 65536)   # 4096 queries a piece
+        assert slots(distinct * reps, nprobe, b.SCAN_AUTO) == slots(4096, nprobe, b.SCAN_AUTO) > slots(4000, nprobe, b.SCAN_AUTO)
+        dq = torch.from_numpy(q).cuda().repeat(reps, 1)
+        own = np.tile(radii, (distinct, 1)) * rng.uniform(0.7, 1.3, (distinct, M)).astype(np.float32)
+        for per_query in (None, own):
+            want = oracle.search(q, idx, nprobe, k, radii if per_query is None else per_query, threads=8)
+            want = (np.tile(want[0], (reps, 1)), np.tile(want[1], (reps, 1)))
+            rq = None if per_query is None else torch.from_numpy(per_query).cuda().repeat(reps, 1)
+            shared = radii if per_query is None else None
+            for strategy in (b.SCAN_AUTO, b.SCAN_LIST_MAJOR):
+                _same(gi.search(dq, nprobe, k, shared, query_radii=rq, strategy=strategy), want, ("search", strategy))
+            _same(gi.scan_topk(dq, gi.coarse(dq, nprobe)[0], k, shared, query_radii=rq), want, "scan_topk")
+    finally:
+        b.set_option("lm_cap", 0)
+        gi.close()

@@ -517,12 +517,13 @@ def test_stages_above_128_neighbours_in_two_chunks(D, M):
         gi.close()
 
 
-@pytest.mark.parametrize("D,M", [(96, 48), (128, 64), (64, 16)])
+@pytest.mark.parametrize("D,M", [(96, 48), (128, 64), (64, 16), (200, 100), (160, 80)])
 @pytest.mark.parametrize("lm_cap", [0, 64])
 def test_candidates_settled_together(D, M, lm_cap):
     """Byte tables in batches of one query, of fewer and of more than one per workgroup, of 4097 (queries to be redone are
     listed) and of more than 64 per workgroup (a wavefront a query); queries without candidates, with a few and with
-    thousands, in one main pass and in two, and buffers of 64 slots that overflow."""
+    thousands, in one main pass and in two, and buffers of 64 slots that overflow; 80 subspaces (fp32
+    tables) hand over by a map instead of a list."""
     b = _binding()
     rng = np.random.default_rng(M + lm_cap)
     nlist, distinct = 72, 41

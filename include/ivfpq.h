@@ -232,8 +232,9 @@ typedef enum {
  *   IVFPQ_SCAN_AUTO         the library chooses: list-major where it is available, when the
  *     batch has at least 16 384 (query, list) pairs (4096 to 9600, by the shape, with 8 probes and more, k <= 100
  *     and where the index's longest list fits the pass that ranks the nearest lists; with 16 subspaces also a
- *     mean list of 16 k points, or 256 queries, 6144 pairs and k <= 64 where hits are counted) and the index's mean
- *     list length is at most 4096, or, with distance scoring and up to 64 subspaces, at most 16 384 and the batch
+ *     mean list of 16 k points, or 256 queries, 6144 pairs and k <= 64 where hits are counted, with 48 and 64 a mean list of
+ *     8 k points for distances) and the index's mean list length is at most 4096 (with 73 subspaces and more also k <= 112 and,
+ *     unless that pass holds every list, 4096 queries, or 1024 on mean lists of 1024 points at most), or, with distance scoring and up to 64 subspaces, at most 16 384 and the batch
  *     large enough that its queries share their nearest lists (two a list, 16 million points in all); query-major
  *     otherwise.  On lists above 4096 points the workspace's candidate slots are bounded by 1 GiB or
  *     4096 queries, whichever is more, larger batches go through them in pieces.  There, and below 16 384

@@ -263,21 +263,34 @@ static bool use_list_major(const ivfpq_index *ix, int64_t Q, int32_t nprobe, int
     // candidates (without structure, 128, 256 and 510 queries, lists of 976, k = 10 107 / 80, 125 / 91, 190 / 123; k = 100 122 / 136,
     // 145 / 173, 216 / 218; lists of 390, k = 100 106 / 125, 121 / 162, 178 / 210; lists of 2000 gain), and so do hit counts of few
     // queries, which the query-major scan splits over workgroups (162 queries, k = 100 286 / 617).
+    // With 48 and 64 subspaces lists of 8 k points are asked for: on shorter ones the k-th distance over the nearest list rules
+    // out little (64 subspaces, k = 100, 166 queries of 57 probes, lists of 330 without structure 234 / 486, 473 of 16, clustered lists
+    // of 688 97 / 144; 48, 470 of 16, lists of 510 223 / 296; of 30 random calls on such lists with 64 subspaces a quarter lose).
     // Over 5600 random calls between the lines and LM_ALWAYS, query-major over list-major as a geometric mean, least, and how many of 100
     // are below 0.95, radii that hold a tenth to half of the entries: 16 subspaces 1.38, 0.89, 1; its hit counts 1.47, 0.91, none; 48
     // 1.64, 0.79, 1, hit counts 1.64, 0.92, 1; 64 1.61, 0.54 (lists of a few hundred points, k = 100), 3, hit counts 1.74, 0.87, 1; 73
     // and more 1.96, 0.61 (clustered data, 64 probes), 2.  Radii that hold nine tenths: distances 1.3 to 1.6, 0.40, 2 to 11; hit counts
-    // 16 subspaces 1.16, 0.42, 27, 48 and 64 1.6, 0.82, 1.
+    // 16 subspaces 1.16, 0.42, 27, 48 and 64 1.6, 0.82, 1.  (Taken before 8 k was asked for.)
     if (nprobe < 8 || k > 100) return false;
     if (pairs < (ix->M == 16 ? 4096 : byte_table_shape(ix) ? 6144 : 9600)) return false;
     if (mode == IVFPQ_SCORE_DISTANCE && !head_pass_holds_all(ix)) return false;
     if (ix->M == 16 && !(mode == IVFPQ_SCORE_DISTANCE ? ix->N >= (int64_t)16 * k * ix->nlist : (k <= 64 && Q >= 256 && pairs >= 6144))) return false;
+    if (ix->M != 16 && byte_table_shape(ix) && mode == IVFPQ_SCORE_DISTANCE && ix->N < (int64_t)8 * k * ix->nlist) return false;
     return ix->N <= (int64_t)4096 * ix->nlist;
   }
-  // (73 subspaces and more: no byte tables for the head pass on long lists, and lists that it does not hold pay where they are
-  // short on average or the queries many.  100 subspaces, two components a list: 617 queries, lists of 2113 2674 us / 3527 list-major,
-  // 1000, 977 5022 / 4114, 4000, 977 19 661 / 10 471.)
-  if (!byte_table_shape(ix)) return ix->N <= (int64_t)4096 * ix->nlist && (head_pass_holds_all(ix) || ix->N <= (int64_t)1024 * ix->nlist || Q >= 4096);
+  // 73 subspaces and more: no byte tables for the head pass on long lists, and lists that it does not hold pay where they are
+  // short on average and the queries many, or the queries very many.  100 subspaces, two components a list, query-major / list-major: 617
+  // queries, lists of 2113 2674 / 3527 us, 1000, 977 5022 / 4114, 4000, 977 19 661 / 10 471; such lists of 1024 points on average at
+  // most, random calls of fewer than 1024 queries: 0.94 times as fast, two thirds of them lose (75 x 3, 800 queries of 43
+  // probes 1799 / 2268; 121 x 2, 392 of 80 629 / 1152), 1024 to 4096 1.3 times, one in 40.  k <= 112: the head pass ranks 128 keys, and beyond 112
+  // the ties of the histogram's bins leave queries over on any kind of data, which are redone (k = 128, 69 random calls: 0.89 times as
+  // fast, two thirds lose, 100 subspaces, 205 queries of 82 probes 107 / 218; k = 112, 76 calls: 1.62 times, one in nine loses; up
+  // to 100 1.8 times, 4 of 100).  Of 760 random calls that these lines let through 4 of 100 lose, the least 0.68, nearly all of them where
+  // the radii hold nine tenths of the entries; 1.8 times as fast as a geometric mean.
+  if (!byte_table_shape(ix)) {
+    if (k > 112) return false;
+    return ix->N <= (int64_t)4096 * ix->nlist && (head_pass_holds_all(ix) || Q >= (ix->N <= (int64_t)1024 * ix->nlist ? 1024 : 4096));
+  }
   if (ix->N <= (int64_t)4096 * ix->nlist) return true;
   // Longer lists: the query-major scan prunes block by block, the list-major one shares each pass over a list among the
   // queries that probe it.  Distances only (the hit counts' first lists are ranked query-major either way).  Query-major /

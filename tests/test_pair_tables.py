@@ -166,10 +166,15 @@ def test_small_batches_that_go_list_major(D, M, line):
     (64, 16, 400, 500, 512, 32, 26, 0, True),                                                  # (16 384 pairs: always)
     (64, 16, 400, 500, 256, 24, 64, 1, True), (64, 16, 400, 500, 255, 32, 64, 1, False),       # hit counts: queries ...
     (64, 16, 400, 500, 256, 23, 64, 2, False), (64, 16, 400, 500, 256, 32, 65, 1, False),      # ... pairs and neighbours
-    (96, 48, 400, 500, 256, 32, 100, 0, True), (96, 48, 400, 500, 256, 32, 101, 0, False),
-    (160, 80, 1100, 4000, 512, 32, 10, 0, True)])
+    (96, 48, 800, 900, 256, 32, 100, 0, True), (96, 48, 900, 999, 256, 32, 101, 0, False),
+    (128, 64, 400, 500, 256, 32, 50, 0, True), (128, 64, 400, 500, 256, 32, 51, 0, False),     # mean lists of 8 k points
+    (128, 64, 400, 500, 256, 32, 51, 1, True), (128, 64, 400, 500, 512, 32, 51, 0, True),      # (not hit counts, nor larger batches)
+    (160, 80, 1100, 4000, 512, 32, 10, 0, True),
+    (200, 100, 400, 500, 512, 32, 112, 0, True), (200, 100, 400, 500, 512, 32, 113, 0, False),
+    (160, 80, 1000, 5000, 1024, 32, 10, 0, True), (160, 80, 1000, 5000, 1023, 32, 10, 0, False),   # a list that the head pass does not hold
+    (160, 80, 1100, 5000, 4096, 32, 10, 0, True), (160, 80, 1100, 5000, 4095, 32, 10, 0, False)])
 def test_lines_of_auto(D, M, mean, longest, Q, nprobe, k, mode, list_major):
-    """Either side of what AUTO asks of 16 subspaces, and of neighbours."""
+    """Either side of what AUTO asks of the lists, the batch and the neighbours."""
     from paper_2312_01712_amd import binding as b
     rng = np.random.default_rng(M)
     sizes = np.full(70, mean)

@@ -2192,7 +2192,13 @@ static LmArgs lm_args(const ivfpq_index *ix, const float *d_queries, int64_t Q, 
   // tables / in parts, 64 probes (48 subspaces, 10 000 queries, without structure), 32 probes (64, 8192, without structure), k = 100,
   // by the mean list: 48: 500 2421 / 2105, 977 3439 / 3073, 1515 3982 / 3895, 1953 3573 / 3690, 2500 3994 / 4349, 3906 5212 / 5996;
   // 64: 977 2203 / 1996, 1515 2308 / 2040, 1953 2498 / 2184, 2941 2812 / 2907, 3906 3090 / 3146.  The line is where both gain.
-  a.parts = ix->d_cb_split && ix->N <= (int64_t)1536 * ix->nlist ? 1 : 0;
+  // Lists of very different lengths: the long ones are probed the most, and the mean says nothing about them (48 subspaces, lists of
+  // 1108, the longest of 95 742, 2567 queries of 12 probes 1484 / 1841; random calls with a list above 8192 points 1.00 times as fast, one
+  // in seven loses a twentieth and more; with shorter ones and 512 queries 1.12 times, one in 60).  Small batches have a task or
+  // two for a workgroup, which then waits for every part's rows (a search: 64 subspaces, clustered, 185 queries of 100 probes 88 / 104,
+  // 296 of 72 99 / 115, 300 of 32, radii per query 82 / 90, 451 of 64 118 / 123; 48, 217 of 83 238 / 254; without structure 450 of 64
+  // 281 / 249, 511 of 32 140 / 131, 300 of 32 137 / 138): whole below 512 queries.
+  a.parts = ix->d_cb_split && ix->N <= (int64_t)1536 * ix->nlist && ix->max_list_len <= 4 * LMP_SEG && Q >= 512 ? 1 : 0;
   return a;
 }
 

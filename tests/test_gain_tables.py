@@ -207,7 +207,7 @@ def test_points_on_their_query_behind_the_first_list(D, M, kind):
                 for radius in (0.6, 1e-3):
                     radii = np.full(M, 0.3 * radius, dtype=np.float32)
                     want = oracle.search(qs, idx, nprobe, k, radii, threads=8)
-                    for reps in (1, 4):   # (the head pass with whole tables, and in parts)
+                    for reps in (1, 4):   # (whole tables, but with 100 subspaces; tables in parts)
                         got = [x.cpu().numpy() for x in gi.search(torch.from_numpy(qs).cuda().repeat(reps, 1), nprobe, k, radii, strategy=b.SCAN_LIST_MAJOR)]
                         wrong = int((got[0] != np.tile(want[0], (reps, 1))).any(1).sum())
                         assert wrong == 0, (off, k, radius, reps, f"{wrong} of {len(qs) * reps} queries")

@@ -206,14 +206,17 @@ def run_workload(args, name: str, steps: int, warmup: int, cpu_seconds: float, p
     default_traffic = measured_traffic(w.name, args.keep, "default") if (args.score_mode == 0 and not args.dynamic_radii and k == w.k and not metric and not plain_only) else None
     resolved = gi_strategy
     pruned = {"strategy": "list-major" if resolved == binding.SCAN_LIST_MAJOR else "query-major",
-              "kernel": ("probe_bound_kernel + lm_pairs / lm_offsets + lm_scan_kernel (head pass: every query's nearest list, "
-                         "ranked list-major, two queries per fp32 table) + lm_byte_kernel (main pass: the other lists that the "
-                         "list-level bound does not rule out, eight queries per byte table, fp32 distances for what passes; "
-                         "lm_scan_kernel where lists are short against k) + lm_settle_kernel or lm_merge_kernel, as shipped") if resolved == binding.SCAN_LIST_MAJOR else
+              "kernel": ("lm_pair_kernel or lm_scan_kernel (head pass: every query's nearest list, ranked list-major, two queries "
+                         "per fp32 table, in parts or whole) + lm_bound_kernel (list-level bounds against its k-th distances; "
+                         "probe_bound_kernel up front where subspaces have another number of dimensions than two) + lm_pairs / "
+                         "lm_offsets + lm_part_kernel or lm_byte_kernel (main pass: the other lists that the bounds do not rule out, "
+                         "eight queries per byte table, in parts or whole; fp32 tables where lists are short against k) + "
+                         "lm_settle_kernel (fp32 distances for what passes) or lm_merge_kernel, as shipped") if resolved == binding.SCAN_LIST_MAJOR else
                         "probe_bound_kernel + scan_kernel as shipped (list-level bound, early exit of the sums, chunked loads: "
                         "bytes that cannot change the result are not read)",
-              "bound": ("lds + per-task phases: one workgroup per CU alternates between building the table of a group of "
-                        "queries (vector ALU, matrix units), 8-byte LDS gathers and the settling of candidates") if resolved == binding.SCAN_LIST_MAJOR else
+              "bound": ("clustered data: the head pass, whose two workgroups per CU share the building of tables (vector ALU), 8-byte LDS "
+                        "gathers, the selection and the way of codebook rows and codes from the L2; elsewhere the LDS gathers and "
+                        "tables (matrix units) of the main pass and the settling of candidates") if resolved == binding.SCAN_LIST_MAJOR else
                        "alu where most lists are ruled out (the tables of the lists that remain), lds gathers where nothing is",
               "avg_launch_ms": launch_ms, "algorithmic_rate": algo_bytes / (launch_ms * 1e-3) / 1e9, "unit": "GB/s",
               "note": "algorithmic bytes over time: exceeds the HBM peak when exact pruning skips bytes; not an efficiency",
@@ -221,7 +224,7 @@ def run_workload(args, name: str, steps: int, warmup: int, cpu_seconds: float, p
               "hbm_rate_from_traffic": (default_traffic / (launch_ms * 1e-3) / 1e9) if default_traffic else None}
     if plain is not None:
         achieved = algo_bytes / (plain * 1e-3) / 1e9
-        res["roofline"] = {"bound": "hbm", "kernel": ("list-major scan (probe_bound_kernel, bucketing, lm_scan_kernel head and main pass, lm_merge_kernel), plain: "
+        res["roofline"] = {"bound": "hbm", "kernel": ("list-major scan (probe_bound_kernel, bucketing, head pass and main pass with fp32 tables of two queries, lm_merge_kernel), plain: "
                                                       "scan_ablate 8|16|64, scan_loads 1: every (query, list) pair scanned in full; results equal to the default scan's") if plain_lm else
                                                      "scan_kernel, plain scan (table + ADC scan + top-k; scan_ablate 8|16|64, scan_loads 1; results equal to the default scan's)",
                            "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS,

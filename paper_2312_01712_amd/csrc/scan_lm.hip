@@ -146,8 +146,8 @@ __device__ __forceinline__ float xor_f32(float v) { return __uint_as_float(xor_u
 // a time, ended where they pass the query's k-th distance so far: the terms are not negative, so what is summed by then is
 // a lower bound too.  A list that is too far is so by half of its subspaces or a few more, and what the bounds cost is their
 // way from the L2 (24 bytes per pair and subspace).  Queries that are left to the query-major scan get theirs in full.
-// 10 000 queries, clustered data, bounds up front and count / so: 64 subspaces of 32 probes 64 + 5 / 39 us, 100 of 64 184 + 5 / 109;
-// 48 of 64 without structure, where none ends early, 117 + 118 / 245.
+// 10 000 queries, clustered data, bounds up front and count / so: 64 subspaces of 32 probes 64 + 5 / 38 us, 100 of 64 184 + 5 / 102;
+// 48 of 64 without structure, where none ends early, 117 + 118 / 155.
 // The pairs of a workgroup are counted by one instruction: atomics on a line are served one after the other, those of an
 // instruction together (four lanes at a time, 30 000 pairs on few lists took 70 us, the whole of probe_bound_kernel and lm_pairs_kernel 37).
 constexpr int LM_BOUND_SETS = 2;   // pairs of a quarter of a wavefront, whose loads are issued together
